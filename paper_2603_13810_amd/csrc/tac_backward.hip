@@ -58,8 +58,9 @@ __device__ __forceinline__ float grad_out_at(const BackwardParams& p, size_t n, 
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-// VEC consecutive neurons of one row as one load or store (VEC = 4: 16 bytes per lane)
+// VEC consecutive neurons of one row as one load or store (VEC = 4: 16 bytes per lane, 2: 8 bytes)
 template <int VEC>
 struct Lanes {
   float v[VEC];
@@ -71,6 +72,10 @@ __device__ __forceinline__ Lanes<VEC> load_lanes(const float* src) {
     const f32x4 t = *reinterpret_cast<const f32x4*>(src);
 #pragma unroll
     for (int e = 0; e < 4; ++e) r.v[e] = t[e];
+  } else if constexpr (VEC == 2) {
+    const f32x2 t = *reinterpret_cast<const f32x2*>(src);
+    r.v[0] = t[0];
+    r.v[1] = t[1];
   } else {
     r.v[0] = *src;
   }
@@ -80,6 +85,8 @@ template <int VEC>
 __device__ __forceinline__ void store_lanes(float* dst, const Lanes<VEC>& a) {
   if constexpr (VEC == 4)
     *reinterpret_cast<f32x4*>(dst) = f32x4{a.v[0], a.v[1], a.v[2], a.v[3]};
+  else if constexpr (VEC == 2)
+    *reinterpret_cast<f32x2*>(dst) = f32x2{a.v[0], a.v[1]};
   else
     *dst = a.v[0];
 }
@@ -106,26 +113,49 @@ __device__ __forceinline__ Lanes<VEC> grad_out_lanes(const BackwardParams& p, si
   }
 }
 
+// The sums dW and dbias start from: cleared by the LIF recurrence, which comes first, or by clear_kernel where dW has
+// held something else in between.
+__device__ __forceinline__ void clear_sums(const BackwardParams& p, size_t first, size_t threads) {
+  const size_t n_w = (size_t)p.Cout * p.Cin * 9;
+  for (size_t i = first; i < n_w; i += threads) p.grad_w[i] = 0.0f;
+  if (p.grad_bias)
+    for (size_t i = first; i < (size_t)p.Cout; i += threads) p.grad_bias[i] = 0.0f;
+}
+
+__global__ __launch_bounds__(kThreads) void clear_kernel(const BackwardParams p) {
+  clear_sums(p, (size_t)blockIdx.x * kThreads + threadIdx.x, (size_t)gridDim.x * kThreads);
+}
+
+// Where a LIF step stands in its group, walking backwards.
+struct StepCursor {
+  int k, j;                                     // group, LIF step within it
+  float decay;
+  bool first;                                   // first step of the group (in this order)
+  __device__ __forceinline__ void enter(const BackwardParams& p, int group) {
+    k = group;
+    first = true;
+    if (k < 0) return;
+    j = (p.mode == TAC_PRESERVE ? group_frames(p, k) : 1) - 1;
+    decay = p.mode == TAC_COLLAPSE ? (group_frames(p, k) == p.K ? p.decay_full : p.decay_last) : p.beta;
+  }
+};
+
 // One thread per VEC output neurons; the LIF steps backwards, c = dL/dV' carried.  The loads of U steps are issued
 // together, only the chain through c is serial.  dL/dY_k is the sum of dL/dV over the LIF steps of group k (one step,
 // or the group's frames with TAC-TP).
 template <int VEC, int U>
-__global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardParams p) {
+__global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardParams p, int clear) {
   const size_t n_out = (size_t)p.B * p.Cout * p.Ho * p.Wo;
-  const size_t i = ((size_t)blockIdx.x * kThreads + threadIdx.x) * VEC;
+  const size_t thread = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (clear) clear_sums(p, thread, (size_t)gridDim.x * kThreads);
+  const size_t i = thread * VEC;
   if (i >= n_out) return;
   float c[VEC], acc[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) c[e] = acc[e] = 0.0f;
   int n = p.n_steps;
-  int k = p.G - 1;
-  auto lif_steps = [&](int kk) { return p.mode == TAC_PRESERVE ? group_frames(p, kk) : 1; };
-  auto decay_of = [&](int kk) {
-    return p.mode == TAC_COLLAPSE ? (group_frames(p, kk) == p.K ? p.decay_full : p.decay_last) : p.beta;
-  };
-  int j = lif_steps(k) - 1;                     // LIF step within the group
-  float decay = decay_of(k);
-  bool first = true;                            // first step of the group (in this order)
+  StepCursor at;
+  at.enter(p, p.G - 1);
   while (n > 0) {
     const int m = min(U, n);
     Lanes<VEC> v[U], g[U];
@@ -143,23 +173,18 @@ __global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardPa
         for (int e = 0; e < VEC; ++e) {
           const float sg = surrogate(p.surrogate, p.alpha, v[u].v[e] - p.theta);
           const float gv = g[u].v[e] * sg + c[e] * (p.detach_reset ? 1.0f : 1.0f - p.theta * sg);
-          acc[e] = first ? gv : acc[e] + gv;
-          c[e] = decay * gv;
+          acc[e] = at.first ? gv : acc[e] + gv;
+          c[e] = at.decay * gv;
         }
-        first = false;
-        if (j == 0) {
+        at.first = false;
+        if (at.j == 0) {
           Lanes<VEC> out;
 #pragma unroll
           for (int e = 0; e < VEC; ++e) out.v[e] = acc[e];
-          store_lanes<VEC>(p.grad_y + (size_t)k * n_out + i, out);
-          --k;
-          if (k >= 0) {
-            j = lif_steps(k) - 1;
-            decay = decay_of(k);
-          }
-          first = true;
+          store_lanes<VEC>(p.grad_y + (size_t)at.k * n_out + i, out);
+          at.enter(p, at.k - 1);
         } else {
-          --j;
+          --at.j;
         }
       }
     }
@@ -167,9 +192,87 @@ __global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardPa
   }
 }
 
-__global__ __launch_bounds__(kThreads) void zero_kernel(float* __restrict__ a, size_t n) {
-  const size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) a[i] = 0.0f;
+// The same where the layer stored the 2 x 2 max pool of its spikes.  A thread owns the two rows and VEC columns of
+// VEC / 2 windows, so that a membrane is read once (one neuron per thread reads its window's four membranes, five loads
+// for one gradient), the window's route is decided in registers and the pooled gradient is read once.  Bound by HBM on large layers, by the chain of
+// loads over the steps on small ones: 128 channels, B = 16, 16 steps at 64 x 64 / 32 x 32 / 16 x 16 take 161 / 37 / 18 us
+// (one neuron per thread: 540 / 141 / 46 us).
+template <int VEC, int U>
+__global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const BackwardParams p, int clear) {
+  constexpr int WIN = VEC / 2;
+  const size_t n_out = (size_t)p.B * p.Cout * p.Ho * p.Wo;
+  const size_t thread = (size_t)blockIdx.x * kThreads + threadIdx.x;
+  if (clear) clear_sums(p, thread, (size_t)gridDim.x * kThreads);
+  if (thread >= n_out / (2 * VEC)) return;
+  const uint32_t per_row = (uint32_t)p.Wo / VEC;
+  const size_t row2 = thread / per_row;                                   // row pair over all channels and samples
+  const size_t i = row2 * 2 * p.Wo + (thread - row2 * per_row) * VEC;     // upper left neuron
+  const size_t ip = thread * WIN;                                         // its window in the pooled tensor
+  float c[2][VEC], acc[2][VEC];
+#pragma unroll
+  for (int y = 0; y < 2; ++y)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) c[y][e] = acc[y][e] = 0.0f;
+  int n = p.n_steps;
+  StepCursor at;
+  at.enter(p, p.G - 1);
+  while (n > 0) {
+    const int m = min(U, n);
+    Lanes<VEC> v[U][2];
+    Lanes<WIN> g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u < m) {
+        const size_t step = (size_t)(n - 1 - u);
+        v[u][0] = load_lanes<VEC>(p.v_trace + step * n_out + i);
+        v[u][1] = load_lanes<VEC>(p.v_trace + step * n_out + i + p.Wo);
+        size_t gstep = step;
+        float f = 1.0f;
+        if (p.go_K > 1) {
+          const int kc = (int)step / p.go_K, j = (int)step - kc * p.go_K;
+          f = (p.go_last && kc == p.go_G - 1) ? p.go_w_last[j] : p.go_w[j];
+          gstep = (size_t)kc;
+        }
+        g[u] = load_lanes<WIN>(p.grad_out + gstep * (n_out >> 2) + ip);
+#pragma unroll
+        for (int w = 0; w < WIN; ++w) g[u].v[w] = f * g[u].v[w];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (u < m) {
+#pragma unroll
+        for (int w = 0; w < WIN; ++w) {
+          // the first maximal spike of the window in row-major order: the first set bit, else the first neuron
+          const float v0 = v[u][0].v[2 * w], v1 = v[u][0].v[2 * w + 1], v2 = v[u][1].v[2 * w], v3 = v[u][1].v[2 * w + 1];
+          const bool s0 = v0 >= p.theta, s1 = v1 >= p.theta, s2 = v2 >= p.theta, s3 = v3 >= p.theta;
+          const bool to[4] = {s0 || !(s1 || s2 || s3), !s0 && s1, !s0 && !s1 && s2, !s0 && !s1 && !s2 && s3};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int y = q >> 1, e = 2 * w + (q & 1);
+            const float sg = surrogate(p.surrogate, p.alpha, v[u][y].v[e] - p.theta);
+            const float gv = (to[q] ? g[u].v[w] : 0.0f) * sg + c[y][e] * (p.detach_reset ? 1.0f : 1.0f - p.theta * sg);
+            acc[y][e] = at.first ? gv : acc[y][e] + gv;
+            c[y][e] = at.decay * gv;
+          }
+        }
+        at.first = false;
+        if (at.j == 0) {
+#pragma unroll
+          for (int y = 0; y < 2; ++y) {
+            Lanes<VEC> out;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) out.v[e] = acc[y][e];
+            store_lanes<VEC>(p.grad_y + (size_t)at.k * n_out + i + (size_t)y * p.Wo, out);
+          }
+          at.enter(p, at.k - 1);
+        } else {
+          --at.j;
+        }
+      }
+    }
+    n -= m;
+  }
 }
 
 // A_k at (frame group k, sample b, channel ci, iy, ix), zero outside the image (Eq. 2)
@@ -207,7 +310,7 @@ __device__ __forceinline__ float aggregate_at(const BackwardParams& p, int k, in
 // row strip) list).  Per strip the aggregate rows it touches are rebuilt in LDS (with the zero
 // border), then every thread takes output pixels of the strip: 9 aggregates x kCoTile gradients.
 // Partial sums are reduced over the workgroup and added to dW (and to dbias by the ci = 0
-// workgroups) with float atomics; both arrays are cleared by zero_kernel before.
+// workgroups) with float atomics; both arrays have been cleared before.
 __global__ __launch_bounds__(kThreads) void wgrad_kernel(const BackwardParams p, int n_strips, int n_split) {
   extern __shared__ float a_strip[];             // [(kStripRows - 1) * stride + 3][W + 2]
   __shared__ float red[kThreads / 64][kCoTile * 9 + kCoTile];
@@ -356,29 +459,32 @@ size_t backward_wgrad_lds_bytes(int W, int stride) { return (size_t)((kStripRows
 
 hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
   const size_t n_out = (size_t)p.B * p.Cout * p.Ho * p.Wo;
-  // four neurons per thread where rows allow 16-byte accesses (the route through a pooled output is per neuron); with
-  // 16 bytes per lane one step in flight per thread keeps the memory busy, the scalar form asks for four steps at once
-  const bool vec4 = !p.out_pool && n_out % 4 == 0 &&
-                    (((uintptr_t)p.v_trace | (uintptr_t)p.grad_out | (uintptr_t)p.grad_y) & 15) == 0;
-  if (vec4)
-    hipLaunchKernelGGL((lif_backward_kernel<4, 1>), dim3((unsigned)((n_out / 4 + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, p);
-  else
-    hipLaunchKernelGGL((lif_backward_kernel<1, 4>), dim3((unsigned)((n_out + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, p);
+  // the wide-tile input gradient uses grad_w as scratch for its prepared weights: it runs before grad_w is cleared
+  const bool dgrad_tile = p.grad_in && backward_dgrad_tile_supported(p);
+  const int clear = dgrad_tile ? 0 : 1;
+  const uintptr_t bases = (uintptr_t)p.v_trace | (uintptr_t)p.grad_out | (uintptr_t)p.grad_y;
+  auto blocks = [](size_t threads) { return dim3((unsigned)((threads + kThreads - 1) / kThreads)); };
+  if (p.out_pool && p.Wo % 4 == 0 && (bases & 15) == 0 && n_out >= ((size_t)1 << 20)) {
+    // two windows per thread: 16-byte membrane accesses, enough threads to fill the chip from 2^20 neurons on
+    hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 2>), blocks(n_out / 8), dim3(kThreads), 0, s, p, clear);
+  } else if (p.out_pool && (bases & 7) == 0) {
+    // small layers wait for memory, step after step: one window per thread, four steps asked for together
+    hipLaunchKernelGGL((lif_backward_pooled_kernel<2, 4>), blocks(n_out / 4), dim3(kThreads), 0, s, p, clear);
+  } else if (!p.out_pool && n_out % 4 == 0 && (bases & 15) == 0) {
+    // four neurons per thread where rows allow 16-byte accesses; with 16 bytes per lane one step in flight per thread
+    // keeps the memory busy, the scalar form asks for four steps at once
+    hipLaunchKernelGGL((lif_backward_kernel<4, 1>), blocks(n_out / 4), dim3(kThreads), 0, s, p, clear);
+  } else {
+    hipLaunchKernelGGL((lif_backward_kernel<1, 4>), blocks(n_out), dim3(kThreads), 0, s, p, clear);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  // the wide-tile input gradient uses grad_w as scratch for its prepared weights: it runs before grad_w is cleared
-  const bool dgrad_tile = p.grad_in && backward_dgrad_tile_supported(p);
   if (dgrad_tile) {
     e = backward_dgrad_tile_launch(p, s);
     if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(clear_kernel, blocks((size_t)p.Cout * p.Cin * 9), dim3(kThreads), 0, s, p);
   }
-
-  const size_t n_w = (size_t)p.Cout * p.Cin * 9;
-  hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((n_w + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, p.grad_w, n_w);
-  if (p.grad_bias)
-    hipLaunchKernelGGL(zero_kernel, dim3((unsigned)((p.Cout + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, p.grad_bias,
-                       (size_t)p.Cout);
   if (p.bf16 && !p.dense && p.pool2 != 1 && backward_wgrad_mfma_supported(p)) {
     e = backward_wgrad_mfma_launch(p, s);
     if (e != hipSuccess) return e;
