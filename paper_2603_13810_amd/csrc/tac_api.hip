@@ -179,13 +179,23 @@ int tac_conv_lif(const tac_layer_desc_t* d, const void* input, const void* w_pre
   double pw = 1.0;
   for (int j = p.K - 1; j >= 0; --j) { p.wj[j] = (float)pw; p.wjd[j] = pw; pw *= beta; }   // wj[j] = beta^(K-1-j)
   p.decay = desc->mode == TAC_COLLAPSE ? (float)pw /* beta^K */ : desc->beta;
+  // kernels that take the shorter last group along do it in the same launch
+  const bool tail_inside = K_last && p.mfma_kind == 3;
+  if (tail_inside) {
+    p.K_last = K_last;
+    p.n_lif_last = desc->mode == TAC_PRESERVE ? K_last : 1;
+    p.decay_last = desc->mode == TAC_COLLAPSE ? (float)p.wjd[p.K - 1 - K_last] /* beta^K_last */ : desc->beta;
+  }
 
   hipError_t e = kern == TAC_KERNEL_MFMA ? tac::mfma_launch(p, (hipStream_t)stream)
                                          : tac::direct_launch(p, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(e, "tac_conv_lif");
   g_conv_stages += (uint64_t)p.G;
   g_lif_steps += (uint64_t)p.G * (uint64_t)p.n_lif;
-  if (K_last) {
+  if (tail_inside) {
+    g_conv_stages += 1;
+    g_lif_steps += (uint64_t)p.n_lif_last;
+  } else if (K_last) {
     // The K_last frames left over are one more group with K_last in the place of K: weights
     // beta^(K_last-1-j), decay beta^K_last, K_last LIF steps in TAC-TP.  It runs as a second
     // launch of the same kernel on the last K frames of the sequence with the weights of the

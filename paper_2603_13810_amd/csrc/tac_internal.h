@@ -31,6 +31,10 @@ struct LayerParams {
   float theta;
   float wj[TAC_MAX_K];      // aggregation weights beta^(K-1-j), Eq. 2
   double wjd[TAC_MAX_K];    // the same before the rounding to fp32 (used with real-valued input frames)
+  // a shorter last group behind the G whole ones, where the kernel takes it in the same launch (0 frames: none): its
+  // weights are the last K_last of a whole group's
+  int K_last, n_lif_last;
+  float decay_last;
 };
 
 // direct (vector-FMA) kernel family: any shape
@@ -65,7 +69,7 @@ hipError_t mfma_probe_launch(int iterations, float* sums, hipStream_t s);
 bool mfma_mid_supported(const tac_layer_desc_t& d);
 size_t mfma_mid_weight_bytes(const tac_layer_desc_t& d);
 hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);
-hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s);
+hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s);      // takes a shorter last group along
 // which member takes a layer: 0 none, 1 large, 2 short contraction, 3 in between
 int mfma_kind(const tac_layer_desc_t& d);
 // its member for short contractions (Cin * 9 <= 32)

@@ -210,28 +210,6 @@ __device__ __forceinline__ void stage_load(uint32_t (&wd)[NG][KM * (MP ? 4 : 1)]
     }
 }
 
-// (a & m) | (b & ~m): one v_bfi_b32
-__device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
-
-// K frame words -> K class words, in place (K a power of two up to 8).  Recursion: the two
-// halves of the frames give class words with K/2-bit fields; class c of the result takes the
-// even fields of both (low half of the new field from the first half of the frames), class
-// c + K/2 the odd ones.
-template <int K>
-__device__ __forceinline__ void frames_to_fields(uint32_t* w) {
-  if constexpr (K >= 2) {
-    frames_to_fields<K / 2>(w);
-    frames_to_fields<K / 2>(w + K / 2);
-    constexpr uint32_t m = K == 2 ? 0x55555555u : (K == 4 ? 0x33333333u : 0x0f0f0f0fu);
-#pragma unroll
-    for (int c = 0; c < K / 2; ++c) {
-      const uint32_t lo = w[c], hi = w[c + K / 2];
-      w[c] = bfi(m, lo, hi << (K / 2));
-      w[c + K / 2] = bfi(m, lo >> (K / 2), hi);
-    }
-  }
-}
-
 template <int KT, int KM, int NG, bool MP>
 __device__ __forceinline__ void stage_store(const uint32_t (&wd)[NG][KM * (MP ? 4 : 1)], const StagePlan<NG>& sp,
                                             uint8_t* words_buf, int K) {

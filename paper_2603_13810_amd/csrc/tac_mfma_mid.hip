@@ -1,283 +1,27 @@
-// MFMA kernel for the layers in between: input channels a multiple of 8 up to 128, any width up
-// to 128 with at most 64 output pixels per row, any input format made of bits (as they are, or
-// through the 2 x 2 mean or max pool on load), output channels in tiles of 32 or 64.  It takes the
-// shapes the large kernel does not (widths other than 32 / 64, fewer than 128 output channels,
-// the mean pool), e.g. the second convolution of the rate-coded network (32 -> 64 at 14 x 14
-// after Pool(2), Sec. 5.1).
-//
-// Same GEMM orientation and LIF epilogue as the other two MFMA kernels.  One workgroup = 4
-// wavefronts = 4 output rows of one sample x one tile of output channels; a wave owns one output
-// row of up to 64 pixels (NMC x 2 MFMA tiles), membrane in registers for the whole call.  The
-// tile's weights (all 9 taps, all input channels) are copied to LDS once.  Per group of K frames:
-//   1. every thread forms its share of the aggregate A_k (Eq. 2) from the packed words in global
-//      memory (8 input channels of one pixel at a time), in the same 24-bit fixed point as the
-//      other kernels (mean pool: quarter counts), rounds once to bf16 and writes the tile
-//      [row][x + 1][cin] to LDS (columns 0 and W + 1 stay zero: the padding);
-//   2. the contraction runs over slots kk = tap * Cin + cin in steps of 16: a lane's B fragment is
-//      8 consecutive input channels of one pixel of the window, one 16-byte LDS read;
-//   3. bias, LIF steps (1, or K for TAC-TP), ballot, packed stores.
-// F32: the fp32 layers of these shapes (the second convolution of the rate-coded network in fp32) on the same
-// structure with v_mfma_f32_32x32x2_f32: aggregate tile and weights in LDS as float32, two contraction slots per
-// MFMA (a lane supplies one weight and one aggregate value), products and sums in fp32.
-#include "tac_mfma_common.h"
+// Host side of the MFMA kernel for the layers in between (tac_mfma_mid_kernel.h has the kernel): which layers it takes,
+// their prepared weights, and the tile a launch uses.
+#include <algorithm>
+#include <cmath>
+#include "tac_mfma_mid_kernel.h"
 
 namespace tac {
 
 namespace {
 
-constexpr int kMidThreads = 256;
-constexpr int kMidRows = 4;                    // output rows per workgroup = waves
 constexpr int kMidMaxW = 128, kMidMaxWo = 64, kMidMaxCin = 128;
-constexpr int kMidLdsLimit = 150 * 1024;
+constexpr int kMidLds = 160 * 1024;
 
-struct MidLayout {
-  int rows_in, WP, nks, a_bytes, w_bytes, tab_bytes, total;
-};
+// Which layers the kernel takes, and in tiles of how many 32-channel blocks their weights are laid out: four output rows
+// of aggregates and the weights of a tile of output channels have to fit this much LDS together.
+constexpr int kMidRows = 4;
+constexpr int kMidLdsRule = 150 * 1024;
 
-// f32: float32 operands, k-steps of 2 contraction slots (one per lane half) instead of 16 (8 per lane half)
-__host__ __device__ inline MidLayout mid_layout(int Cin, int S, int W, int nmc, bool f32 = false) {
-  MidLayout m;
-  m.rows_in = (kMidRows - 1) * S + 3;
-  m.WP = W + 2;
-  m.nks = f32 ? (9 * Cin + 1) / 2 : (9 * Cin + 15) / 16;
-  m.a_bytes = ((m.rows_in * m.WP * Cin + 8) * (f32 ? 4 : 2) + 15) & ~15;       // + 8 zero elements for empty slots
-  m.w_bytes = m.nks * nmc * 64 * (f32 ? 4 : 16);
-  m.tab_bytes = (m.nks * 2 * 4 + 15) & ~15;
-  m.total = m.a_bytes + m.w_bytes + m.tab_bytes + nmc * 32 * 4;
-  return m;
-}
+int mid_k_steps(int Cin, bool f32) { return f32 ? (9 * Cin + 1) / 2 : (9 * Cin + 15) / 16; }
 
-template <int S, int NMC, bool TRACE, bool F32 = false>
-__global__ __launch_bounds__(kMidThreads, TRACE ? 1 : 2) void mid_kernel(const MfmaParams p) {
-  constexpr int kEl = F32 ? 4 : 2;             // bytes of an operand element
-  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n = lane & 31, h = lane >> 5;
-  const int Cin = p.Cin, K = p.K;
-  const MidLayout m = mid_layout(Cin, S, p.W, NMC, F32);
-  const int row_tiles = (p.Ho + kMidRows - 1) / kMidRows;
-  const int co_tiles = (p.Cout + NMC * 32 - 1) / (NMC * 32);
-  int t = blockIdx.x;
-  const int y0 = (t % row_tiles) * kMidRows; t /= row_tiles;
-  const int co_tile = t % co_tiles;
-  const int b = t / co_tiles;
-  const int co0 = co_tile * (NMC * 32);
-  const int oy = y0 + wave;
-  const int iy0 = y0 * S - 1;
-  const int Wwo = (p.Wo + 31) >> 5;
-  const int pool = p.pool;                     // 0 none, 1 mean, 2 max (stored image 2H x 2W)
-  const int Hs = pool ? 2 * p.H : p.H;
-  const int WWs = ((pool ? 2 * p.W : p.W) + 31) >> 5;
-
-  uint8_t* const a_tile = lds;
-  uint8_t* const w_lds = lds + m.a_bytes;
-  int32_t* const tab = reinterpret_cast<int32_t*>(w_lds + m.w_bytes);
-  float* const bias_lds = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(tab) + m.tab_bytes);
-  uint32_t* const pool_ex = reinterpret_cast<uint32_t*>(lds + m.total);        // only there when the output is pooled
-  const int n_a = m.rows_in * m.WP * Cin;
-
-  for (int i = tid; i < (n_a + 8) * kEl / 4; i += kMidThreads) reinterpret_cast<uint32_t*>(a_tile)[i] = 0u;   // padding columns, empty-slot zeros
-  {
-    // the tile's weights: [k-step][mc][lane][8] bf16 in global memory, copied as they are
-    const u32x4* src = reinterpret_cast<const u32x4*>(p.w + (size_t)co_tile * m.w_bytes);
-    for (int i = tid; i < m.w_bytes / 16; i += kMidThreads) reinterpret_cast<u32x4*>(w_lds)[i] = src[i];
-  }
-  // slot table: k-step ks, lane half hh -> byte offset of the 8 channels (tap, cin0) relative to the
-  // window's first element, or the zero elements behind the tile for slots beyond 9 Cin
-  for (int i = tid; i < m.nks * 2; i += kMidThreads) {
-    const int kk0 = F32 ? i : 16 * (i >> 1) + 8 * (i & 1);         // fp32: k-step i / 2, lane half i % 2 -> slot i
-    const int tap = kk0 / Cin, cin0 = kk0 - tap * Cin;
-    const int ky = tap / 3, kx = tap - ky * 3;
-    tab[i] = tap < 9 ? ((ky * m.WP + kx) * Cin + cin0) * kEl : -1;
-  }
-  if (tid < NMC * 32) bias_lds[tid] = (p.bias && co0 + tid < p.Cout) ? p.bias[co0 + tid] : 0.f;
-
-  LaneGeom lg;
-  uint32_t pix_base[2];
-  const size_t plane = (size_t)p.Ho * p.Wo;
-#pragma unroll
-  for (int np = 0; np < 2; ++np) {
-    const int ox = 32 * np + n;
-    lg.ok[np] = oy < p.Ho && ox < p.Wo;
-    lg.theta[np] = lg.ok[np] ? p.theta : __builtin_inff();
-    lg.v_off[np] = (uint32_t)((4 * h * plane + ox) * 4);
-    pix_base[np] = (uint32_t)((((wave * S) * m.WP + (lg.ok[np] ? ox : 0) * S) * Cin) * kEl);
-  }
-  lg.co_lim = p.Cout - co0 - 4 * h;
-  const size_t v_wave = ((size_t)b * p.Cout + co0) * plane + (size_t)oy * p.Wo;
-
-  float V[NMC][2][16];
-#pragma unroll
-  for (int mc = 0; mc < NMC; ++mc)
-#pragma unroll
-    for (int np = 0; np < 2; ++np)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
-        V[mc][np][r] = (p.v_inout && lg.ok[np] && c < lg.co_lim)
-                           ? *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.v_inout + v_wave) +
-                                                             (size_t)c * plane * 4 + lg.v_off[np])
-                           : 0.f;
-      }
-
-  const int st_r = lane >> 2, st_hi = (lane >> 1) & 1, st_np = lane & 1;
-  const int st_co = 8 * (st_r >> 2) + 4 * st_hi + (st_r & 3);
-  const size_t out_plane = (size_t)p.Ho * Wwo;
-  const size_t out_lane = ((size_t)b * p.Cout + co0 + st_co) * out_plane + (size_t)oy * Wwo + st_np;
-  const bool out_ok = oy < p.Ho && st_np < Wwo;
-  const size_t out_step = (size_t)p.B * p.Cout * out_plane;
-  // pooled output (2 x 2 max pool in the writer): [step][b][cout][Ho / 2][one word]
-  const size_t plane_p = (size_t)(p.Ho >> 1);
-  const size_t out_step_p = (size_t)p.B * p.Cout * plane_p;
-  uint32_t* const out_tile_p = p.out + ((size_t)b * p.Cout + co0) * plane_p + (y0 >> 1);
-
-  const size_t in_chan = (size_t)Hs * WWs;                         // stored words per (t, b, cin)
-  const size_t t_stride = (size_t)p.B * Cin * in_chan;
-  const int n_el = m.rows_in * p.W * (Cin >> 3);                   // (row, x, group of 8 channels)
-
-  for (int g = 0; g < p.G; ++g) {
-    __syncthreads();                           // the previous group's fragment reads are done
-    // ---- 1. aggregate (Eq. 2), fixed point, one rounding to bf16
-    const uint32_t* gbase = p.spikes + (((size_t)g * K) * p.B + b) * Cin * in_chan;
-    for (int e = tid; e < n_el; e += kMidThreads) {
-      const int c8 = e % (Cin >> 3);
-      const int rx = e / (Cin >> 3);
-      const int row = rx / p.W, x = rx - row * p.W;
-      const int iy = iy0 + row;
-      uint32_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (iy >= 0 && iy < p.H) {
-        const uint32_t* src = gbase + (size_t)(c8 * 8) * in_chan;
-        if (!pool) {
-          const size_t off = (size_t)iy * WWs + (x >> 5);
-          for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-              acc[c] = __umul24(__builtin_amdgcn_ubfe(src[j * t_stride + c * in_chan + off], x & 31, 1), p.wq[j]) + acc[c];
-        } else {
-          const int xs = 2 * x;                // both stored columns of the block sit in one word
-          const size_t off = (size_t)(2 * iy) * WWs + (xs >> 5);
-          for (int j = 0; j < K; ++j)
-#pragma unroll
-            for (int c = 0; c < 8; ++c) {
-              const uint32_t w0 = src[j * t_stride + c * in_chan + off], w1 = src[j * t_stride + c * in_chan + off + WWs];
-              // mean: quarter counts (the factor 1/4 is applied with the scale below); max: OR
-              const uint32_t cnt = pool == 2 ? ((((w0 | w1) >> (xs & 31)) & 3u) ? 4u : 0u)
-                                             : (uint32_t)(__popc((w0 >> (xs & 31)) & 3u) + __popc((w1 >> (xs & 31)) & 3u));
-              acc[c] = __umul24(cnt, p.wq[j]) + acc[c];
-            }
-        }
-      }
-      const float sc = pool ? 0.25f / (float)(1u << kFixShift) : 1.0f / (float)(1u << kFixShift);
-      uint8_t* const dst = a_tile + (size_t)((row * m.WP + x + 1) * Cin + c8 * 8) * kEl;
-      if constexpr (F32) {
-        // the fixed-point sum is exact; one rounding to fp32
-        f32x4v lo = {(float)acc[0] * sc, (float)acc[1] * sc, (float)acc[2] * sc, (float)acc[3] * sc};
-        f32x4v hi = {(float)acc[4] * sc, (float)acc[5] * sc, (float)acc[6] * sc, (float)acc[7] * sc};
-        reinterpret_cast<f32x4v*>(dst)[0] = lo;
-        reinterpret_cast<f32x4v*>(dst)[1] = hi;
-      } else {
-        u32x4 pk;
-#pragma unroll
-        for (int c2 = 0; c2 < 4; ++c2) pk[c2] = pack_bf16((float)acc[2 * c2] * sc, (float)acc[2 * c2 + 1] * sc);
-        *reinterpret_cast<u32x4*>(dst) = pk;
-      }
-    }
-    __syncthreads();
-    // ---- 2. contraction
-    f32x16 acc[NMC][2];
-#pragma unroll
-    for (int mc = 0; mc < NMC; ++mc)
-#pragma unroll
-      for (int np = 0; np < 2; ++np)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mc][np][r] = bias_lds[mc * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
-    if constexpr (F32) {
-      // Four partial sums per output (k-steps ks % 4), added at the end: the rounding error of a long fp32 sum grows
-      // with its length, and a quarter of the length keeps the membrane within the fp32 bar where one chain of
-      // 9 Cin terms does not.  Rows of at most 32 pixels leave the wave's second pixel block empty: its MFMAs are
-      // skipped (wave-uniform).
-      static_assert(NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
-      const int nblk = p.Wo > 32 ? 2 : 1;
-      f32x16 part[3][2];
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
-#pragma unroll
-        for (int np = 0; np < 2; ++np)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) part[i][np][r] = 0.f;
-      auto step = [&](int ks, f32x16 (&dst)[2]) {
-        const int off = tab[ks * 2 + h];
-        const float wf = *reinterpret_cast<const float*>(w_lds + (ks * 64 + lane) * 4);
-        const float a0 = *reinterpret_cast<const float*>(a_tile + (off < 0 ? (uint32_t)(n_a * 4) : pix_base[0] + (uint32_t)off));
-        dst[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, a0, dst[0], 0, 0, 0);
-        if (nblk == 2) {
-          const float a1 = *reinterpret_cast<const float*>(a_tile + (off < 0 ? (uint32_t)(n_a * 4) : pix_base[1] + (uint32_t)off));
-          dst[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(wf, a1, dst[1], 0, 0, 0);
-        }
-      };
-      int ks = 0;
-      for (; ks + 3 < m.nks; ks += 4) {
-        step(ks, acc[0]);
-        step(ks + 1, part[0]);
-        step(ks + 2, part[1]);
-        step(ks + 3, part[2]);
-      }
-      for (; ks < m.nks; ++ks) step(ks, acc[0]);
-#pragma unroll
-      for (int np = 0; np < 2; ++np)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][np][r] = (acc[0][np][r] + part[0][np][r]) + (part[1][np][r] + part[2][np][r]);
-    } else {
-    for (int ks = 0; ks < m.nks; ++ks) {
-      const int off = tab[ks * 2 + h];
-      bf16x8 af[2], wf[NMC];
-#pragma unroll
-      for (int np = 0; np < 2; ++np)
-        af[np] = *reinterpret_cast<const bf16x8*>(reinterpret_cast<const uint8_t*>(a_tile) +
-                                                  (off < 0 ? (uint32_t)(n_a * 2) : pix_base[np] + (uint32_t)off));
-#pragma unroll
-      for (int mc = 0; mc < NMC; ++mc)
-        wf[mc] = *reinterpret_cast<const bf16x8*>(w_lds + ((ks * NMC + mc) * 64 + lane) * 16);
-#pragma unroll
-      for (int mc = 0; mc < NMC; ++mc)
-#pragma unroll
-        for (int np = 0; np < 2; ++np)
-          acc[mc][np] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[mc], af[np], acc[mc][np], 0, 0, 0);
-    }
-    }
-    // ---- 3. LIF steps on Y_k = acc (bias included)
-    for (int j = 0; j < p.n_lif; ++j) {
-      const size_t step = (size_t)g * p.n_lif + j;
-      uint32_t word[NMC][2];
-#pragma unroll
-      for (int mc = 0; mc < NMC; ++mc) word[mc][0] = word[mc][1] = 0u;
-      float* tl = TRACE ? p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_wave : nullptr;
-      lif_step<NMC, 64, TRACE>(V, acc, p.decay, p.theta, lg, word, tl, plane);
-      if (p.out_pool) {
-        pooled_store<NMC>(word, pool_ex + (step & 1) * (kMidRows * NMC * 32), tid, kMidThreads, kMidRows, 1, false, wave, 0,
-                          out_tile_p + step * out_step_p, plane_p, 1, min(kMidRows >> 1, (p.Ho - y0) >> 1), p.Cout - co0);
-      } else if (out_ok) {
-#pragma unroll
-        for (int mc = 0; mc < NMC; ++mc)
-          if (co0 + mc * 32 + st_co < p.Cout) p.out[step * out_step + out_lane + (size_t)mc * 32 * out_plane] = word[mc][0];
-      }
-    }
-  }
-
-  if (p.v_inout) {
-#pragma unroll
-    for (int mc = 0; mc < NMC; ++mc)
-#pragma unroll
-      for (int np = 0; np < 2; ++np)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
-          if (lg.ok[np] && c < lg.co_lim)
-            *reinterpret_cast<float*>(reinterpret_cast<char*>(p.v_inout + v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) =
-                V[mc][np][r];
-        }
-  }
+int mid_rule_bytes(int Cin, int S, int W, int nmc, bool f32) {
+  const int rows_in = (kMidRows - 1) * S + 3, nks = mid_k_steps(Cin, f32);
+  const int a_bytes = ((rows_in * (W + 2) * Cin + 8) * (f32 ? 4 : 2) + 15) & ~15;
+  return a_bytes + nks * nmc * 64 * (f32 ? 4 : 16) + ((nks * 2 * 4 + 15) & ~15) + nmc * 32 * 4;
 }
 
 // OIHW fp32 -> [cout tile][k-step][mc][lane][8] bf16: lane l of block mc holds cout
@@ -322,23 +66,103 @@ __global__ void mid_prepare_f32_kernel(const float* __restrict__ w, float* __res
 
 // 64-channel tiles when the tile's weights and the aggregate tile fit the LDS together, else 32
 int mid_nmc(int Cin, int S, int W, int Cout, bool f32) {
-  return (!f32 && Cout > 32 && mid_layout(Cin, S, W, 2, f32).total <= kMidLdsLimit) ? 2 : 1;
+  return (!f32 && Cout > 32 && mid_rule_bytes(Cin, S, W, 2, f32) <= kMidLdsRule) ? 2 : 1;
 }
 
-template <int S, int NMC, bool F32>
-hipError_t mid_launch_t(const MfmaParams& mp, hipStream_t s) {
-  const MidLayout m = mid_layout(mp.Cin, S, mp.W, NMC, F32);
-  const int co_tiles = (mp.Cout + NMC * 32 - 1) / (NMC * 32);
-  const dim3 grid(((mp.Ho + kMidRows - 1) / kMidRows) * co_tiles * mp.B);
-  auto kern = mp.v_trace ? &mid_kernel<S, NMC, true, F32> : &mid_kernel<S, NMC, false, F32>;
-  const int lds = m.total + (mp.out_pool ? pool_exchange_bytes(kMidRows, NMC * 32, 1) : 0);
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kMidLdsLimit + pool_exchange_bytes(kMidRows, 64, 1));
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, grid, dim3(kMidThreads), lds, s, mp);
-  return hipGetLastError();
+size_t mid_tile_bytes(const tac_layer_desc_t& d, int nmc, bool f32) { return (size_t)mid_k_steps(d.Cin, f32) * nmc * 64 * (f32 ? 4 : 16); }
+
+// The plan of one tile shape, or false when it does not fit the LDS.  pw_shift: lanes per row of a block (their log2),
+// trg: row groups per tile.
+bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w) {
+  const bool f32 = !p.bf16;
+  const int S = p.stride, C8 = p.Cin / 8;
+  q.pw_shift = pw_shift;
+  q.rpb = 32 >> q.pw_shift;
+  q.wb = (p.Wo + 31) / 32;
+  q.trg = trg;
+  q.tr = trg * q.rpb;
+  q.flatten = flatten;
+  const long long rows = flatten ? (long long)p.B * p.Ho : p.Ho;
+  q.tr = (int)std::min<long long>(q.tr, p.out_pool ? (rows + 1) / 2 * 2 : rows);
+  const int samples = flatten ? std::min((q.tr + p.Ho - 2) / p.Ho + 1, p.B) : 1;        // a tile may touch
+  q.lr = (q.tr - 1) * S + 3 + (samples - 1) * (3 - S);
+  q.row_tiles = (int)((rows + q.tr - 1) / q.tr);
+  q.co_tiles = (p.Cout + nmc * 32 - 1) / (nmc * 32);
+  q.srows = p.pool2 ? 2 : 1;
+  q.wws = p.Wwi;
+  q.hs = p.Hs;
+  q.nb = (p.K + kp - 1) / kp;
+  q.rws = q.nb * kp * 8 + 4;                   // four unused dwords spread consecutive pairs over the LDS banks
+  q.wpx = p.W + 2;
+  q.xh = (q.wpx + 1) / 2;
+  q.plane = q.lr * q.wpx * 16;
+  q.plane += (128 - q.plane % 256 + 256) % 256;       // consecutive planes start half the banks apart (the two lane halves)
+  q.nks = mid_k_steps(p.Cin, f32);
+  q.nmc_w = nmc_w;
+  auto up = [](int x) { return (x + 15) & ~15; };
+  const int w_bytes = q.nks * nmc * (f32 ? 256 : 1024);
+  const int ahead = (2 * mid_depth(nmc, nnp) - 1) * nmc * 1024;       // the fetches ahead read past the weights
+  const bool sums = f32 || q.nb > 1 || p.pool2 == 1;
+  const int lut_entries = sums ? q.nb << kp : (kp == 8 ? 256 : 1 << (2 * kp));
+  q.off_w = q.plane * C8 * (f32 ? 2 : 1);
+  q.off_tab = q.off_w + w_bytes;
+  q.off_bias = up(q.off_tab + (q.nks * 2 + kMidTabPad) * 4);
+  q.off_wq = q.off_bias + nmc * 32 * 4;
+  q.off_lut = q.off_wq + TAC_MAX_K * 4;
+  q.off_unit = up(q.off_lut + lut_entries * 4);
+  // Four waves form aggregates, each in as few jobs as the LDS has room to stage; fewer waves only where even the smallest
+  // jobs of four do not fit (rows of 100 and more pixels in groups of 16 and more frames).
+  bool found = false;
+  double best = 0.0;
+  MidPlan c = q;
+  for (c.loaders = 4; c.loaders >= 1 && !found; c.loaders >>= 1)
+    for (c.parts_shift = 0; c.parts_shift <= 6; ++c.parts_shift) {
+      c.parts = 1 << c.parts_shift;
+      c.lrp = (c.lr + c.parts - 1) / c.parts;
+      if (c.parts > 1 && (c.lr + c.parts / 2 - 1) / (c.parts / 2) == 1) break;  // a row each already
+      for (c.cg = C8; c.cg >= 1; --c.cg) {
+        if (C8 % c.cg) continue;
+        c.n_jobs = C8 / c.cg * c.parts;
+        c.rw = c.lrp * c.srows * c.wws;
+        const int n_units = 8 * c.cg * c.rw, n_px = c.cg * c.lrp * p.W;
+        c.chunks = c.nb * ((n_units + 64 * mid_units(kp) - 1) / (64 * mid_units(kp)));
+        c.batches = (c.chunks + kMidBatch - 1) / kMidBatch;
+        c.off_px = up(c.off_unit + c.parts * n_units * 8);
+        c.off_stage = up(c.off_px + c.parts * n_px * 8);
+        c.stage_wave = up(c.cg * c.rw * c.rws * 4);
+        c.total = std::max(c.off_stage + c.loaders * c.stage_wave, c.off_w + w_bytes + ahead);
+        if (c.total > kMidLds || c.stage_wave >= 1 << 24) continue;
+        // a wave's instructions per group, roughly: a batch, a pass over 256 pixels
+        const double cost = (double)((c.n_jobs + c.loaders - 1) / c.loaders) * (300.0 + 350.0 * c.batches + 130.0 * ((n_px + 255) / 256));
+        // a second workgroup per compute unit is worth more than a job less
+        const double scaled = cost * (c.total > kMidLds / 2 && c.off_px < kMidLds / 2 ? 1.3 : 1.0);
+        if (found && scaled >= best) continue;
+        found = true;
+        best = scaled;
+        q = c;
+      }
+    }
+  return found;
+}
+
+// Estimated time of a launch in cycles: rounds of resident workgroups, each the sum of its phases (instructions of the
+// loader; MFMAs, 32 cycles per 32x32x16 and 64 per fp32 32x32x2, or the LDS reads that feed them at 128 bytes per cycle;
+// LIF steps).  Two resident workgroups fill each other's gaps, but share the LDS and the matrix cores.
+double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
+  const bool f32 = !p.bf16;
+  const int n_px = q.cg * q.lrp * p.W;
+  const bool sums = q.nb > 1 || p.pool2 || f32;
+  const double jobs = (q.n_jobs + q.loaders - 1) / q.loaders;
+  const double build = jobs * (1000.0 + 1400.0 * q.batches + ((n_px + 255) / 256) * (sums ? 1200.0 * q.nb * (p.pool2 ? 4 : 1) : 700.0));
+  const double mfma = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
+  const double lif = p.n_lif * (nmc * nnp * 500.0 + 400.0 + 60.0 * q.rpb);
+  const double wgs = (double)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
+  const double per_cu = std::ceil(wgs / 256.0);
+  const int resident = q.total <= kMidLds / 2 ? 2 : 1;
+  const double alone = 9000.0 + p.G * (build + mfma + lif + 500.0);
+  const double shared = p.G * mfma;                                     // what a second workgroup cannot hide
+  if (resident == 1 || per_cu <= 1) return per_cu * alone;
+  return std::ceil(per_cu / 2) * std::max(alone * 1.15, 2.0 * shared);
 }
 
 }  // namespace
@@ -348,14 +172,14 @@ bool mfma_mid_supported(const tac_layer_desc_t& d) {
   const bool f32 = d.precision == TAC_FP32;
   if (d.Cin % 8 != 0 || d.Cin > kMidMaxCin) return false;
   if (d.W > kMidMaxW || (d.W + 2 - 3) / d.stride + 1 > kMidMaxWo) return false;
-  return mid_layout(d.Cin, d.stride, d.W, mid_nmc(d.Cin, d.stride, d.W, d.Cout, f32), f32).total <= kMidLdsLimit;
+  return mid_rule_bytes(d.Cin, d.stride, d.W, mid_nmc(d.Cin, d.stride, d.W, d.Cout, f32), f32) <= kMidLdsRule;
 }
 
 size_t mfma_mid_weight_bytes(const tac_layer_desc_t& d) {
   const bool f32 = d.precision == TAC_FP32;
   const int nmc = mid_nmc(d.Cin, d.stride, d.W, d.Cout, f32);
   const int tiles = (d.Cout + nmc * 32 - 1) / (nmc * 32);
-  return (size_t)tiles * mid_layout(d.Cin, d.stride, d.W, nmc, f32).w_bytes;
+  return (size_t)tiles * mid_tile_bytes(d, nmc, f32);
 }
 
 hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s) {
@@ -376,8 +200,42 @@ hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void
   return hipGetLastError();
 }
 
+static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, int& nnp) {
+  const bool f32 = !p.bf16;
+  kp = p.K <= 2 ? 2 : p.K <= 4 ? 4 : 8;
+  const int nmc_w = mid_nmc(p.Cin, p.stride, p.W, p.Cout, f32);
+  const int wb = (p.Wo + 31) / 32;
+  // a tile that straddles samples offsets its membranes by 32 bits and counts rows in fp32
+  const bool may_flatten = (long long)p.B * p.Cout * p.Ho * p.Wo < (1ll << 30) && (long long)p.B * p.Ho < (1ll << 20) - 1024;
+  double best = 0.0;
+  bool found = false;
+  // as many rows per block as its lanes hold; fewer only where such a tile does not fit the LDS
+  for (int pw = p.Wo > 16 ? 5 : p.Wo > 8 ? 4 : p.Wo > 4 ? 3 : p.Wo > 2 ? 2 : 1; pw <= 5 && !found; ++pw)
+    for (int c = 1; c <= (f32 || p.Cout <= 32 ? 1 : 2); ++c)
+      for (int x = 2; x >= 1; --x)
+        for (int trg = 4 * x / wb; trg >= 1; trg >>= 1) {
+          // pooled output, one row per block: the wave's two blocks are the two rows of a pooled row
+          const bool pairs = p.out_pool && pw == 5;
+          if (pairs && (x == 1 || trg < 2)) continue;
+          if (f32 && x == 2 && !pairs) continue;              // two blocks with four partial sums each: one wave per SIMD
+          for (int fl = may_flatten ? 1 : 0; fl >= 0; --fl) {
+            MidPlan q;
+            if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w)) continue;
+            const double cost = mid_cost(q, p, c, x);
+            if (found && cost >= best) continue;
+            found = true;
+            best = cost;
+            out.q = q;
+            nmc = c;
+            nnp = x;
+          }
+        }
+  return found;
+}
+
 hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
-  MfmaParams mp;
+  MidParams a;
+  MfmaParams& mp = a.m;
   mp.spikes = p.spikes; mp.w = static_cast<const uint8_t*>(p.w); mp.bias = p.bias; mp.v_inout = p.v_inout;
   mp.out = p.out; mp.v_trace = p.v_trace;
   mp.B = p.B; mp.Cin = p.Cin; mp.H = p.H; mp.W = p.W; mp.Ho = p.Ho; mp.Wo = p.Wo; mp.Cout = p.Cout; mp.stride = p.stride;
@@ -388,10 +246,11 @@ hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
     mp.wq[j] = j < p.K ? (uint32_t)(q + 0.5) : 0u;
     mp.wjd[j] = p.wjd[j];
   }
-  const int nmc = mid_nmc(p.Cin, p.stride, p.W, p.Cout, !p.bf16);
-  if (!p.bf16) return p.stride == 1 ? mid_launch_t<1, 1, true>(mp, s) : mid_launch_t<2, 1, true>(mp, s);
-  if (p.stride == 1) return nmc == 1 ? mid_launch_t<1, 1, false>(mp, s) : mid_launch_t<1, 2, false>(mp, s);
-  return nmc == 1 ? mid_launch_t<2, 1, false>(mp, s) : mid_launch_t<2, 2, false>(mp, s);
+  a.K_last = p.K_last; a.n_lif_last = p.n_lif_last; a.decay_last = p.decay_last;
+  int kp, nmc, nnp;
+  if (!mid_choose(p, a, kp, nmc, nnp)) return hipErrorInvalidValue;
+  if (!p.bf16) return p.v_trace ? mid_launch_f32_trace(a, kp, nnp, s) : mid_launch_f32(a, kp, nnp, s);
+  return p.v_trace ? mid_launch_bf16_trace(a, kp, nmc, nnp, s) : mid_launch_bf16(a, kp, nmc, nnp, s);
 }
 
 }  // namespace tac

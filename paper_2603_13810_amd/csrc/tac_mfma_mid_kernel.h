@@ -1,0 +1,674 @@
+// MFMA kernel for the layers in between: input channels a multiple of 8 up to 128, any width up to 128 with at most 64
+// output pixels per row, any input format made of bits (as they are, or through the 2 x 2 mean or max pool on load),
+// any number of output channels.  It takes the shapes the large kernel does not (widths other than 32 / 64, fewer than
+// 128 output channels, the mean pool), e.g. the second convolution of the rate-coded network (32 -> 64 at 14 x 14 after
+// Pool(2), Sec. 5.1) and the deep 16 x 16 .. 2 x 2 blocks of the event-data network.
+//
+// Same GEMM orientation and LIF epilogue as the other MFMA kernels.  A pixel block is 32 lanes: a word of an output row,
+// or, where rows have at most 16 pixels, several rows of 16, 8, 4 or 2 lanes each, counted over the rows of all samples,
+// so that small images fill the lanes (a block per row of 14, 8 or 4 pixels would leave 56, 75 or 88 % of the matrix
+// cores' columns empty).  Workgroup = 4 waves = up to 4 NNP pixel blocks x NMC blocks of 32 output channels, membrane in
+// registers and the tile's weights (all taps, all input channels) in LDS for the whole call.  Per group of K frames:
+//   1. aggregate tile A_k (Eq. 2) in LDS as [8 channels][row][column][8], so that neighbouring pixels are neighbouring
+//      16-byte reads.  A wave forms its share of the tile (some 8-channel groups, some rows) without meeting the others:
+//      it loads the packed words, each word once (consecutive lanes take consecutive words of a channel), turns the K
+//      frame words of 32 pixels into per-pixel K-bit fields in registers (frames_to_fields), stages them in its own
+//      corner of the LDS, and then, a pixel per lane, looks the aggregates of 8 channels up in a table.  The next words
+//      are requested before that, through the end of a group into the next one.  On the small layers this kernel serves
+//      a wave has a SIMD nearly to itself and what counts is the number of instructions and of LDS round trips, so a
+//      wave does its share in one piece where the LDS allows (`job`), with what it needs to know about its words and
+//      pixels in tables made once.
+//   2. contraction over slots kk = tap * Cin + cin in steps of 16 (two 8-channel groups, one per lane half)
+//   3. bias, LIF steps (1, or K for TAC-TP), ballot, packed stores
+// F32: the fp32 layers of these shapes on the same structure with v_mfma_f32_32x32x2_f32: aggregate tile and weights in
+// LDS as float32, two contraction slots per MFMA, products and sums in fp32.
+//
+// A shorter last group (T mod K frames) is one more turn of the loop with tables of its own, the membrane still in
+// registers.
+//
+// Measured against one row per wave, every thread gathering the bits of its own 8 values from global memory and the
+// shorter last group a launch of its own: 48 -> 80 at 45 x 45, B = 24, 25 frames in groups of 4: 541 -> 112 us; blocks of
+// 128 -> 128 at 16 x 16 / 8 x 8 / 4 x 4, B = 16, TAC-TP K = 4, 16 frames: 141 / 86 / 63 -> 33 / 31 / 31 us; fp32 32 -> 64 at
+// 14 x 14 behind the mean pool, B = 128, K = 8, 25 frames: 125 -> 26 us.  What is left on the small ones (31 us for
+// 4 groups) is one wave's instruction stream: 14 % tables, 40 % aggregates, 22 % MFMAs (61 cycles a step: 2 KiB of
+// fragments for one MFMA, the LDS delivers 128 bytes a cycle), 23 % LIF steps.
+#pragma once
+#include "tac_mfma_common.h"
+
+namespace tac {
+
+constexpr int kMidThreads = 256;
+constexpr int kMidTabPad = 24;  // entries of the slot table behind the last k-step (fetched ahead)
+// Sets of operand fragments in flight: with few MFMAs per step (32 cycles each) a step is shorter than an LDS read
+__host__ __device__ constexpr int mid_depth(int nmc, int nnp) { return nmc * nnp == 1 ? 4 : nmc * nnp == 2 ? 3 : 2; }
+
+// Geometry of one launch, resolved on the host (mid_plan).  Byte offsets are from the start of the LDS.
+struct MidPlan {
+  int pw_shift, rpb, wb;        // lanes of a row within a block = 1 << pw_shift, rows per block, blocks per row
+  int trg, tr;                  // row groups (of rpb rows) and output rows per tile
+  int lr;                       // LDS rows of the largest tile
+  int flatten;                  // output rows are counted through all samples (a tile may straddle two)
+  int row_tiles, co_tiles;      // tiles over the rows (per sample, or over all of them), over the output channels
+  int cg, parts_shift, parts, lrp;      // a job = cg groups of 8 channels x lrp LDS rows; parts: jobs over the rows, a power of two
+  int loaders;                  // waves that form aggregates: all four unless their staging areas do not fit the LDS
+  int srows, wws, hs;           // stored rows per LDS row (2: pool on load), words per stored row, stored rows per channel
+  int rw, rws;                  // (stored row, word) pairs per job and channel; staged dwords per pair and 8 channels
+  int n_jobs, chunks, batches;  // jobs per tile; (chunk of frames, 64 U units) pairs per job, the same in batches of kMidBatch
+  int nb;                       // table chunks of 8 frames
+  int wpx, xh, plane;           // columns of the aggregate tile, of its even half (stride 2), bytes per channel group
+  int nks, nmc_w;               // k-steps; 32-channel blocks per tile of the prepared weights
+  int off_w, off_tab, off_bias, off_wq, off_unit, off_px, off_lut, off_stage, stage_wave, total;
+};
+
+struct MidParams {
+  MfmaParams m;
+  MidPlan q;
+  int K_last, n_lif_last;       // frames and LIF steps of a shorter last group (0: none)
+  float decay_last;
+};
+
+hipError_t mid_launch_bf16(const MidParams& p, int kp, int nmc, int nnp, hipStream_t s);
+hipError_t mid_launch_bf16_trace(const MidParams& p, int kp, int nmc, int nnp, hipStream_t s);
+hipError_t mid_launch_f32(const MidParams& p, int kp, int nnp, hipStream_t s);
+hipError_t mid_launch_f32_trace(const MidParams& p, int kp, int nnp, hipStream_t s);
+
+namespace {
+
+constexpr int kMidBatch = 4;    // chunks of words a wave loads at a time
+// units a lane takes per chunk
+__host__ __device__ constexpr int mid_units(int kp) { return kp == 2 ? 2 : 1; }
+
+// i / d for a wave-uniform divisor and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
+// the rounding of the reciprocal and the product moves it
+struct SmallDiv {
+  int d;
+  float r;
+  __device__ __forceinline__ explicit SmallDiv(int divisor) : d(divisor), r(1.0f / (float)divisor) {}
+  __device__ __forceinline__ int quot(int i) const { return (int)(((float)i + 0.5f) * r); }
+};
+
+// KP: frames per table index (2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
+// per wave.
+template <int KP, int NMC, int NNP, bool TRACE, bool F32>
+__global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) void mid_kernel(const MidParams mp) {
+  static_assert(!F32 || NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
+  constexpr uint32_t kNone = 0xffffffffu;
+  const MfmaParams& p = mp.m;
+  const MidPlan& q = mp.q;
+  extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, h = lane >> 5;
+  const int Cin = p.Cin, S = p.stride, C8 = Cin >> 3;
+
+  const uint32_t row_tile = blockIdx.x / (uint32_t)q.co_tiles;
+  const int co_tile = (int)(blockIdx.x - row_tile * (uint32_t)q.co_tiles);
+  // output rows are counted through all samples (fewer than 2^20), or the grid's z is the sample
+  const SmallDiv by_ho(p.Ho);
+  const int first_row = (int)row_tile * q.tr;
+  const int b0 = q.flatten ? by_ho.quot(first_row) : (int)blockIdx.z;
+  const int oy0 = q.flatten ? first_row - b0 * p.Ho : first_row;
+  const int rows_valid = min(q.tr, (q.flatten ? p.B * p.Ho : p.Ho) - first_row);
+  auto sample_of = [&](int rr) { return q.flatten ? by_ho.quot(oy0 + rr) : 0; };     // tile row -> sample - b0
+  const int co0 = co_tile * (NMC * 32);
+  const size_t plane = (size_t)p.Ho * p.Wo;
+  const size_t in_chan = (size_t)q.hs * q.wws;
+  const size_t t_stride = (size_t)p.B * Cin * in_chan;
+
+  uint8_t* const w_lds = lds + q.off_w;
+  int32_t* const tab = reinterpret_cast<int32_t*>(lds + q.off_tab);
+  float* const bias_lds = reinterpret_cast<float*>(lds + q.off_bias);
+  u32x2* const unit = reinterpret_cast<u32x2*>(lds + q.off_unit);
+  u32x2* const pxt = reinterpret_cast<u32x2*>(lds + q.off_px);
+  uint32_t* const lut = reinterpret_cast<uint32_t*>(lds + q.off_lut);
+  uint8_t* const stage = lds + q.off_stage + wave * q.stage_wave;
+
+  // ---- the tile's weights: [k-step][block] fragments of 1 KiB (fp32: 256 bytes), on their way while the tables are made
+  {
+    if constexpr (F32) {
+      const uint8_t* const src = p.w + (size_t)co_tile * q.nks * 256 + lane * 16;
+      for (int f = wave; f < q.nks / 4; f += 4) lds_dma16<1, 0>(src + (size_t)f * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + f * 1024));
+    } else {
+#pragma unroll
+      for (int mc = 0; mc < NMC; ++mc) {
+        const int blk = co_tile * NMC + mc, tile = blk / q.nmc_w;
+        // (a block beyond the channels is multiplied but never stored)
+        const uint8_t* const src =
+            p.w + (blk * 32 < p.Cout ? ((size_t)tile * q.nks * q.nmc_w + (blk - tile * q.nmc_w)) * 1024 : (size_t)0) + lane * 16;
+        for (int ks = wave; ks < q.nks; ks += 4)
+          lds_dma16<1, 0>(src + (size_t)ks * q.nmc_w * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + (ks * NMC + mc) * 1024));
+      }
+    }
+  }
+  // ---- tables
+  const int n0 = min(p.Ho - oy0, q.tr) * S + (3 - S);                  // LDS rows of the tile's first sample
+  const int per_sample = p.Ho * S + (3 - S);
+  const int lr_used = (rows_valid - 1) * S + sample_of(rows_valid - 1) * (3 - S) + 3;
+  const int n_units = 8 * q.cg * q.rw;                                 // per job
+  const int stage_cg = q.rw * q.rws * 4;
+  // which words a job loads: unit (channel, stored row, word) -> dword offset from (frame, first sample, first channel
+  // of the job), top bit: outside the image; byte offset in the staging area
+  const SmallDiv by_rw(q.rw), by_wws(q.wws), by_ch(8 * q.cg);
+#pragma clang loop unroll(disable)
+  for (int i = tid; i < q.parts * n_units; i += kMidThreads) {
+    const int pc = by_rw.quot(i), rw = i - pc * q.rw;
+    const int part = by_ch.quot(pc), ch = pc - part * 8 * q.cg;
+    const int srow = by_wws.quot(rw), word = rw - srow * q.wws;
+    const int row = part * q.lrp + (srow >> (q.srows - 1));
+    int bsel = 0, iy = oy0 * S - 1 + row;
+    if (row >= n0) {
+      const int over = SmallDiv(per_sample).quot(row - n0);
+      bsel = 1 + over;
+      iy = row - n0 - over * per_sample - 1;
+    }
+    const bool inside = row < lr_used && iy >= 0 && iy < p.H;
+    const int sy = p.pool ? 2 * iy + (srow & (q.srows - 1)) : iy;
+    u32x2 u;
+    u[0] = inside ? (uint32_t)((size_t)(bsel * Cin + ch) * in_chan + (size_t)sy * q.wws + word) : 0x80000000u;
+    u[1] = row < lr_used ? (uint32_t)((ch >> 3) * stage_cg + (rw * q.rws + (ch & 7)) * 4) : kNone;
+    unit[i] = u;
+  }
+  __syncthreads();
+
+  // ---- the loader: a wave's jobs are wave, wave + loaders, ..  A job's words come in batches of kMidBatch chunks, a
+  // chunk being 64 U units of up to KP frames; the registers of a batch are requested again as soon as it has been staged.
+  // Every load is issued, from an address inside the tensor, whatever the lane's word is for (a load under a condition
+  // makes the compiler wait for it at once); words outside the image and frames beyond the group become zero when they
+  // are staged.
+  constexpr int U = mid_units(KP);
+  const int n_groups = p.G + (mp.K_last ? 1 : 0);
+  auto frames_of = [&](int g) { return g == p.G ? mp.K_last : p.K; };
+  const int n_uc = q.nb == 1 ? q.chunks : q.chunks / q.nb;
+  uint32_t wd[kMidBatch][U][KP];
+  auto chunk_of = [&](int c, int& nb, int& uc) {
+    nb = 0;
+    uc = c;
+    while (uc >= n_uc) { uc -= n_uc; ++nb; }
+  };
+  auto load_batch = [&](int g, int job, int batch) {
+    const int Kg = frames_of(g), part = job & (q.parts - 1);
+    const u32x2* const units = unit + part * n_units;
+    const uint32_t* const base =
+        p.spikes + (((size_t)g * p.K) * p.B + b0) * Cin * in_chan + (size_t)(job >> q.parts_shift) * q.cg * 8 * in_chan;
+    uint32_t off[kMidBatch][U];
+    int f0[kMidBatch];
+#pragma unroll
+    for (int c = 0; c < kMidBatch; ++c) {
+      int nb, uc;
+      chunk_of(min(batch * kMidBatch + c, q.chunks - 1), nb, uc);
+      f0[c] = nb * KP;
+#pragma unroll
+      for (int u = 0; u < U; ++u) off[c][u] = units[min((uc * U + u) * 64 + lane, n_units - 1)][0] & 0x7fffffffu;
+    }
+#pragma unroll
+    for (int c = 0; c < kMidBatch; ++c)
+#pragma unroll
+      for (int j = 0; j < KP; ++j) {
+        const uint32_t* const frame = base + (size_t)min(f0[c] + j, Kg - 1) * t_stride;
+#pragma unroll
+        for (int u = 0; u < U; ++u) wd[c][u][j] = frame[off[c][u]];
+      }
+  };
+  auto store_batch = [&](int Kg, int job, int batch) {
+    const u32x2* const units = unit + (job & (q.parts - 1)) * n_units;
+    u32x2 un[kMidBatch][U];
+    int f0[kMidBatch];
+#pragma unroll
+    for (int c = 0; c < kMidBatch; ++c) {
+      int nb, uc;
+      const int chunk = batch * kMidBatch + c;
+      chunk_of(min(chunk, q.chunks - 1), nb, uc);
+      f0[c] = nb * KP;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int e = (uc * U + u) * 64 + lane;
+        un[c][u] = units[min(e, n_units - 1)];
+        if (chunk >= q.chunks || e >= n_units) un[c][u][1] = kNone;
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < kMidBatch; ++c)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const uint32_t keep = un[c][u][0] >> 31 ? 0u : 0xffffffffu;
+#pragma unroll
+        for (int j = 0; j < KP; ++j) wd[c][u][j] &= f0[c] + j < Kg ? keep : 0u;
+        frames_to_fields<KP>(wd[c][u]);
+        if (un[c][u][1] != kNone) {
+          uint32_t* dst = reinterpret_cast<uint32_t*>(stage + un[c][u][1]) + f0[c] * 8;
+#pragma unroll
+          for (int j = 0; j < KP; ++j) dst[j * 8] = wd[c][u][j];
+        }
+      }
+  };
+  const int job0 = min(wave, q.n_jobs - 1);
+  load_batch(0, job0, 0);
+
+  // which pixels a job forms: byte offset of the pixel's class words, shift of its field (top byte); byte offset in LDS
+  // from the job's first plane
+  const SmallDiv by_w(p.W), by_lrp(q.lrp), by_cg(q.cg);
+  const int n_px = q.cg * q.lrp * p.W;                                 // per job
+#pragma clang loop unroll(disable)
+  for (int i = tid; i < q.parts * n_px; i += kMidThreads) {
+    const int line = by_w.quot(i), x = i - line * p.W;                 // (part, channel group, row)
+    const int pcg = by_lrp.quot(line), rl = line - pcg * q.lrp;
+    const int part = by_cg.quot(pcg), cg = pcg - part * q.cg, row = part * q.lrp + rl;
+    const int xs = p.pool ? 2 * x : x;
+    const int c = xs & (KP - 1), xp = x + 1;
+    u32x2 u;
+    u[0] = (uint32_t)(cg * stage_cg + ((rl * q.srows * q.wws + (xs >> 5)) * q.rws + c * 8) * 4) | ((uint32_t)((xs & 31) - c) << 24);
+    u[1] = row < lr_used ? (uint32_t)(cg * (F32 ? 2 : 1) * q.plane + (row * q.wpx + (S == 1 ? xp : (xp & 1) * q.xh + (xp >> 1))) * 16) : kNone;
+    pxt[i] = u;
+  }
+  // the padding columns x = -1 and x = W stay zero
+  const SmallDiv by_lr(q.lr), by_cin(Cin);
+#pragma clang loop unroll(disable)
+  for (int i = tid; i < C8 * (F32 ? 2 : 1) * q.lr * 2; i += kMidThreads) {
+    const int side = i & 1, pl = by_lr.quot(i >> 1), r = (i >> 1) - pl * q.lr;
+    const int xp = side ? p.W + 1 : 0;
+    *reinterpret_cast<u32x4*>(lds + pl * q.plane + (r * q.wpx + (S == 1 ? xp : (xp & 1) * q.xh + (xp >> 1))) * 16) = u32x4{0, 0, 0, 0};
+  }
+  // slot table: k-step ks, lane half hh -> byte offset of its channels (tap, cin) from the window's first pixel.  Slots
+  // beyond 9 Cin meet zero weights; entries behind the last step are only ever fetched ahead.
+#pragma clang loop unroll(disable)
+  for (int i = tid; i < q.nks * 2 + kMidTabPad; i += kMidThreads) {
+    const int kk0 = F32 ? i : 8 * i;                                   // fp32: k-step i / 2, lane half i % 2 -> slot i
+    const int tap = by_cin.quot(kk0), cin = kk0 - tap * Cin;
+    const int ky = (tap * 11) >> 5, kx = tap - ky * 3;                 // tap / 3 for the nine taps
+    const int col = S == 1 ? kx : (kx & 1) * q.xh + (kx >> 1);
+    const int ch = F32 ? (cin >> 2) * q.plane + (cin & 3) * 4 : (cin >> 3) * q.plane;
+    tab[i] = tap < 9 ? ch + (ky * q.wpx + col) * 16 : 0;
+  }
+  uint32_t* const wq = reinterpret_cast<uint32_t*>(lds + q.off_wq);    // read with lane-dependent indices below
+  if (tid < TAC_MAX_K) wq[tid] = p.wq[tid];
+  if (tid < NMC * 32) bias_lds[tid] = (p.bias && co0 + tid < p.Cout) ? p.bias[co0 + tid] : 0.f;
+  // aggregates by frame bits: pairs of channels as two bf16 (groups of up to four frames), one bf16 (up to eight), or
+  // 2^-23 fixed-point sums per chunk of eight frames (more frames, the mean pool's counts, fp32)
+  const bool sums = F32 || q.nb > 1 || p.pool == 1;
+  const float scale = p.pool == 1 ? 0.25f / (float)(1u << kFixShift) : 1.0f / (float)(1u << kFixShift);
+  auto make_lut = [&](int first) {                                     // first: weight index of the group's first frame
+    const int n_lut = sums ? q.nb << KP : KP == 8 ? 256 : 1 << (2 * KP);
+#pragma clang loop unroll(disable)
+    for (int i = tid; i < n_lut; i += kMidThreads) {
+      // low KP bits: a channel's frames; the bits above: the pair's second channel, or the chunk of frames
+      uint32_t a[2] = {0, 0};
+      const int second = sums || KP == 8 ? 0 : i >> KP, j0 = first + (sums ? (i >> KP) * KP : 0);
+#pragma unroll
+      for (int j = 0; j < KP; ++j) {
+        const uint32_t w = wq[min(j0 + j, TAC_MAX_K - 1)];
+        a[0] += (i >> j) & 1 ? w : 0u;
+        a[1] += (second >> j) & 1 ? w : 0u;
+      }
+      lut[i] = sums ? a[0] : pack_bf16((float)a[0] * scale, (float)a[1] * scale);
+    }
+  };
+
+  // ---- the lane's pixels
+  LaneGeom lg;
+  uint32_t pix_base[NNP];
+  const int word_w = q.wb == 1 ? 0 : wave & 1;
+  const int rg_w = (q.wb == 1 ? wave : wave >> 1) * NNP;               // the wave's first row group; block np: row group + np
+#pragma unroll
+  for (int np = 0; np < 2; ++np) { lg.ok[np] = false; lg.theta[np] = __builtin_inff(); lg.v_off[np] = 0; }
+#pragma unroll
+  for (int np = 0; np < NNP; ++np) {
+    const int rr0 = (rg_w + np) * q.rpb + (n >> q.pw_shift), ox = word_w * 32 + (n & ((1 << q.pw_shift) - 1));
+    const bool ok = rg_w + np < q.trg && rr0 < rows_valid && ox < p.Wo;
+    const int rr = ok ? rr0 : 0;
+    const int bsel = sample_of(rr), oy = oy0 + rr - bsel * p.Ho;
+    lg.ok[np] = ok;
+    lg.theta[np] = ok ? p.theta : __builtin_inff();
+    lg.v_off[np] = (uint32_t)((((size_t)bsel * p.Cout + 4 * h) * plane + (size_t)oy * p.Wo + (ok ? ox : 0)) * 4);
+    pix_base[np] = (uint32_t)(((rr * S + bsel * (3 - S)) * q.wpx + (ok ? ox : 0)) * 16);
+  }
+  lg.co_lim = p.Cout - co0 - 4 * h;
+  const size_t v_wave = ((size_t)b0 * p.Cout + co0) * plane;
+  const bool wave_active = rg_w < q.trg && rg_w * q.rpb < rows_valid;  // wave-uniform
+
+  float V[NMC][NNP][16];
+#pragma unroll
+  for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+    for (int np = 0; np < NNP; ++np)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) V[mc][np][r] = 0.f;
+  if (p.v_inout) {
+#pragma unroll
+    for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+      for (int np = 0; np < NNP; ++np)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
+          if (lg.ok[np] && c < lg.co_lim)
+            V[mc][np][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.v_inout + v_wave) +
+                                                           (size_t)c * plane * 4 + lg.v_off[np]);
+        }
+  }
+
+  // ---- output words: lane (r << 2) | (hi << 1) | np holds channel 8 (r / 4) + 4 hi + r % 4, pixel block np
+  const int st_r = lane >> 2, st_hi = (lane >> 1) & 1, st_np = lane & 1;
+  const int st_co = co0 + 8 * (st_r >> 2) + 4 * st_hi + (st_r & 3);
+  const int Wwo = (p.Wo + 31) >> 5;
+  const int st_rr = (rg_w + st_np) * q.rpb;                            // the block's first tile row
+  const bool st_ok = st_np < NNP && rg_w + st_np < q.trg;
+  const int st_bsel = sample_of(st_rr), st_b = b0 + st_bsel, st_oy = oy0 + st_rr - st_bsel * p.Ho;
+  const int out_rows = p.out_pool ? p.Ho >> 1 : p.Ho;                  // stored rows and words per channel
+  const int out_words = p.out_pool ? 1 : Wwo;
+  const size_t out_step = (size_t)p.B * p.Cout * out_rows * out_words;
+  const int st_row = p.out_pool ? st_oy >> 1 : st_oy;
+  // word offset of the block's first row within a step, and what the row behind a sample's last one adds to the next row
+  const uint32_t st_off = (uint32_t)((((size_t)st_b * p.Cout + st_co) * out_rows + st_row) * out_words);
+  const uint32_t next_sample = (uint32_t)((p.Cout - 1) * out_rows * out_words);
+  const int st_rows = st_ok ? min(q.rpb, rows_valid - st_rr) : 0;      // rows of the block
+  const uint32_t field = q.rpb > 1 ? (1u << (32 / q.rpb)) - 1u : 0xffffffffu;
+  auto store_words = [&](size_t step, const uint32_t (&word)[NMC][2]) {
+    uint32_t* const out = p.out + step * out_step;
+#pragma unroll
+    for (int mc = 0; mc < NMC; ++mc) {
+      const bool ok = st_co + mc * 32 < p.Cout;
+      const uint32_t wd = word[mc][0];
+      uint32_t at = st_off + (uint32_t)(mc * 32 * out_rows * out_words);
+      if (!p.out_pool) {
+        at += word_w;
+        if (q.rpb == 1) {
+          if (ok && st_rows > 0) out[at] = wd;
+          continue;
+        }
+        for (int s = 0, row = st_row; s < q.rpb; ++s, ++at) {
+          if (ok && s < st_rows) out[at] = (wd >> (s << q.pw_shift)) & field;
+          if (++row == out_rows) { row = 0; at += next_sample; }
+        }
+      } else if (q.rpb > 1) {
+        // 2 x 2 max pool: both rows of a window are in the lane's word (rows per sample are even)
+        for (int s = 0, row = st_row; s < q.rpb; s += 2, ++at) {
+          const uint32_t two = (wd >> (s << q.pw_shift)) | (wd >> ((s + 1) << q.pw_shift));
+          if (ok && s < st_rows) out[at] = pool_pairs(two & field);
+          if (++row == out_rows) { row = 0; at += next_sample; }
+        }
+      } else {
+        // the wave's two blocks are the two rows of a pooled row (NNP = 2): neighbouring lanes; 16 pooled pixels per
+        // word of the unpooled row
+        const uint32_t pooled = pool_pairs(wd | (uint32_t)__shfl_xor((int)wd, 1, 64));
+        if (ok && st_np == 0 && st_rows > 0) {
+          if (q.wb == 1) out[at] = pooled;
+          else reinterpret_cast<uint16_t*>(out + at)[word_w] = (uint16_t)pooled;
+        }
+      }
+    }
+  };
+
+  // max pool on load: the other three pixels of the block are OR-ed to the first one's class words (their fields stand at
+  // the same bit, the right-hand neighbour's in the next class word)
+  auto or_corners = [&]<int PX>(const u32x2 (&px)[PX], int nb, u32x4 (&c0)[PX], u32x4 (&c1)[PX]) {
+    for (int corner = 1; corner < 4; ++corner)
+#pragma unroll
+      for (int k = 0; k < PX; ++k) {
+        const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + (corner & 1) * 8) * 4;
+        c0[k] |= *reinterpret_cast<const u32x4*>(sk);
+        c1[k] |= *reinterpret_cast<const u32x4*>(sk + 16);
+      }
+  };
+  // the pixels of a job, PX per lane at a time: all reads of a stage before the next (table address, class words, table,
+  // tile), so that PX chains of LDS latencies overlap
+  auto build_job = [&](int job) {
+    uint8_t* const pl = lds + (job >> q.parts_shift) * q.cg * (F32 ? 2 : 1) * q.plane;
+    const u32x2* const px_part = pxt + (job & (q.parts - 1)) * n_px;
+    if (!sums) {
+      constexpr int PX = 4;
+      for (int e0 = lane; e0 < n_px; e0 += 64 * PX) {
+        u32x2 px[PX];
+        u32x4 c0[PX], c1[PX], v[PX];
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+          px[k] = px_part[min(e0 + 64 * k, n_px - 1)];
+          if (e0 + 64 * k >= n_px) px[k][1] = kNone;
+        }
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+          const uint8_t* src = stage + (px[k][0] & 0xffffffu);
+          c0[k] = *reinterpret_cast<const u32x4*>(src);
+          c1[k] = *reinterpret_cast<const u32x4*>(src + 16);
+        }
+        if (p.pool == 2) or_corners(px, 0, c0, c1);
+#pragma unroll
+        for (int k = 0; k < PX; ++k) {
+          const uint32_t sh = px[k][0] >> 24;
+#pragma unroll
+          for (int c2 = 0; c2 < 4; ++c2) {
+            const uint32_t lo = __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2] : c1[k][2 * c2 - 4], sh, KP);
+            const uint32_t hi = __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2 + 1] : c1[k][2 * c2 - 3], sh, KP);
+            if constexpr (KP == 8) v[k][c2] = lut[lo] | (lut[hi] << 16);
+            else v[k][c2] = lut[lo | (hi << KP)];
+          }
+        }
+#pragma unroll
+        for (int k = 0; k < PX; ++k)
+          if (px[k][1] != kNone) *reinterpret_cast<u32x4*>(pl + px[k][1]) = v[k];
+      }
+      return;
+    }
+    constexpr int PX = 2;
+    for (int e0 = lane; e0 < n_px; e0 += 64 * PX) {
+      u32x2 px[PX];
+      uint32_t a[PX][8];
+#pragma unroll
+      for (int k = 0; k < PX; ++k) {
+        px[k] = px_part[min(e0 + 64 * k, n_px - 1)];
+        if (e0 + 64 * k >= n_px) px[k][1] = kNone;
+#pragma unroll
+        for (int c = 0; c < 8; ++c) a[k][c] = 0;
+      }
+      const int corners = p.pool == 1 ? 4 : 1;                         // mean pool: the sum over the block's four pixels
+      for (int nb = 0; nb < q.nb; ++nb)
+        for (int corner = 0; corner < corners; ++corner) {
+          const uint32_t* const tb = lut + (nb << KP);
+          u32x4 c0[PX], c1[PX];
+#pragma unroll
+          for (int k = 0; k < PX; ++k) {
+            const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + (corner & 1) * 8) * 4;
+            c0[k] = *reinterpret_cast<const u32x4*>(sk);
+            c1[k] = *reinterpret_cast<const u32x4*>(sk + 16);
+          }
+          if (p.pool == 2) or_corners(px, nb, c0, c1);
+#pragma unroll
+          for (int k = 0; k < PX; ++k)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) a[k][c] += tb[__builtin_amdgcn_ubfe(c < 4 ? c0[k][c] : c1[k][c - 4], px[k][0] >> 24, KP)];
+        }
+#pragma unroll
+      for (int k = 0; k < PX; ++k) {
+        if (px[k][1] == kNone) continue;
+        uint8_t* const dst = pl + px[k][1];
+        if constexpr (F32) {
+          // the fixed-point sum is exact; one rounding to fp32
+          *reinterpret_cast<f32x4v*>(dst) = f32x4v{(float)a[k][0] * scale, (float)a[k][1] * scale, (float)a[k][2] * scale, (float)a[k][3] * scale};
+          *reinterpret_cast<f32x4v*>(dst + q.plane) = f32x4v{(float)a[k][4] * scale, (float)a[k][5] * scale, (float)a[k][6] * scale, (float)a[k][7] * scale};
+        } else {
+          u32x4 v;
+#pragma unroll
+          for (int c2 = 0; c2 < 4; ++c2) v[c2] = pack_bf16((float)a[k][2 * c2] * scale, (float)a[k][2 * c2 + 1] * scale);
+          *reinterpret_cast<u32x4*>(dst) = v;
+        }
+      }
+    }
+  };
+
+  size_t step = 0;
+  for (int g = 0; g < n_groups; ++g) {
+    const bool last = g == p.G;                // the shorter last group
+    const int Kg = frames_of(g), n_lif = last ? mp.n_lif_last : p.n_lif;
+    const float decay = last ? mp.decay_last : p.decay;
+    __syncthreads();                           // the previous group's fragment reads are done (first group: the tables are made)
+    if (g == 0 || last) {
+      make_lut(last ? p.K - mp.K_last : 0);    // a shorter last group's weights are the last of a whole group's
+      __syncthreads();
+    }
+    // ---- 1. aggregate
+    for (int job = wave; job < q.n_jobs && wave < q.loaders; job += q.loaders) {
+      for (int batch = 0; batch < q.batches; ++batch) {
+        store_batch(Kg, job, batch);
+        const bool more = batch + 1 < q.batches, next_job = job + q.loaders < q.n_jobs;
+        // what to request next; behind the last batch of the call any batch will do
+        load_batch(more || next_job ? g : min(g + 1, n_groups - 1), more ? job : next_job ? job + q.loaders : job0, more ? batch + 1 : 0);
+      }
+      asm volatile("" ::: "memory");           // the wave's own LDS accesses execute in order; keep the compiler to it too
+      build_job(job);
+      asm volatile("" ::: "memory");
+    }
+    if (g == 0) lds_dma_wait();                // the weights
+    __syncthreads();
+    if (!wave_active) { step += n_lif; continue; }
+    // ---- 2. contraction
+    f32x16 acc[NMC][NNP];
+#pragma unroll
+    for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+      for (int np = 0; np < NNP; ++np)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[mc][np][r] = bias_lds[mc * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
+    const int32_t* const tabh = tab + h;
+    if constexpr (F32) {
+      // Four partial sums per output (k-steps ks % 4), added at the end: the rounding error of a long fp32 sum grows
+      // with its length, and a quarter of the length keeps the membrane within the fp32 bar where one chain of
+      // 9 Cin terms does not.
+      f32x16 part[3][NNP];
+#pragma unroll
+      for (int i = 0; i < 3; ++i)
+#pragma unroll
+        for (int np = 0; np < NNP; ++np)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) part[i][np][r] = 0.f;
+      // nks is a multiple of 4 (9 Cin / 2, Cin a multiple of 8); operands of four steps are fetched ahead
+      float wf[2][4], af[2][4][NNP];
+      int32_t off[4];
+      auto fetch = [&](int ks, float (&w)[4], float (&a)[4][NNP]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          w[i] = *reinterpret_cast<const float*>(w_lds + ((ks + i) * 64 + lane) * 4);
+#pragma unroll
+          for (int np = 0; np < NNP; ++np) a[i][np] = *reinterpret_cast<const float*>(lds + pix_base[np] + (uint32_t)off[i]);
+        }
+      };
+      auto offsets = [&](int ks) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) off[i] = tabh[2 * (ks + i)];
+      };
+      auto multiply = [&](const float (&w)[4], const float (&a)[4][NNP]) {
+#pragma unroll
+        for (int np = 0; np < NNP; ++np) {
+          acc[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[0], a[0][np], acc[0][np], 0, 0, 0);
+          part[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[1], a[1][np], part[0][np], 0, 0, 0);
+          part[1][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[2], a[2][np], part[1][np], 0, 0, 0);
+          part[2][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[3], a[3][np], part[2][np], 0, 0, 0);
+        }
+      };
+      offsets(0);
+      fetch(0, wf[0], af[0]);
+      offsets(min(4, q.nks - 4));
+      for (int ks = 0; ks < q.nks; ks += 8) {
+        if (ks + 4 < q.nks) {
+          fetch(ks + 4, wf[1], af[1]);
+          offsets(min(ks + 8, q.nks - 4));
+        }
+        multiply(wf[0], af[0]);
+        if (ks + 4 >= q.nks) break;
+        if (ks + 8 < q.nks) {
+          fetch(ks + 8, wf[0], af[0]);
+          offsets(min(ks + 12, q.nks - 4));
+        }
+        multiply(wf[1], af[1]);
+      }
+#pragma unroll
+      for (int np = 0; np < NNP; ++np)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][np][r] = (acc[0][np][r] + part[0][np][r]) + (part[1][np][r] + part[2][np][r]);
+    } else {
+      // fragments are requested F - 1 steps ahead, table offsets F steps before that; beyond the last step the fetches read
+      // what lies behind the weights (inside the LDS) and nobody uses it
+      constexpr int F = mid_depth(NMC, NNP);
+      bf16x8 af[F][NNP], wf[F][NMC];
+      int32_t off[F];
+      const uint8_t* const w_lane = w_lds + lane * 16;
+      auto fetch = [&](int ks, int set) {
+#pragma unroll
+        for (int mc = 0; mc < NMC; ++mc) wf[set][mc] = *reinterpret_cast<const bf16x8*>(w_lane + (ks * NMC + mc) * 1024);
+#pragma unroll
+        for (int np = 0; np < NNP; ++np) af[set][np] = *reinterpret_cast<const bf16x8*>(lds + pix_base[np] + (uint32_t)off[set]);
+        off[set] = tabh[2 * (ks + F)];
+      };
+#pragma unroll
+      for (int d = 0; d < F; ++d) off[d] = tabh[2 * d];
+#pragma unroll
+      for (int d = 0; d < F - 1; ++d) fetch(d, d);
+      auto multiply = [&](int set) {
+#pragma unroll
+        for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+          for (int np = 0; np < NNP; ++np)
+            acc[mc][np] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][mc], af[set][np], acc[mc][np], 0, 0, 0);
+      };
+      int ks = 0;
+      for (; ks + F <= q.nks; ks += F) {
+#pragma unroll
+        for (int d = 0; d < F; ++d) {
+          fetch(ks + d + F - 1, (d + F - 1) % F);
+          multiply(d);
+        }
+      }
+#pragma unroll
+      for (int d = 0; d < F - 1; ++d)
+        if (ks + d < q.nks) multiply(d);
+    }
+    // ---- 3. LIF steps on Y_k = acc (bias included)
+    for (int j = 0; j < n_lif; ++j, ++step) {
+      uint32_t word[NMC][2];
+#pragma unroll
+      for (int mc = 0; mc < NMC; ++mc) word[mc][0] = word[mc][1] = 0u;
+      float* tl = TRACE ? p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_wave : nullptr;
+      lif_step<NMC, 64, TRACE, NNP>(V, acc, decay, p.theta, lg, word, tl, plane);
+      store_words(step, word);
+    }
+  }
+
+  if (p.v_inout) {
+#pragma unroll
+    for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+      for (int np = 0; np < NNP; ++np)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
+          if (lg.ok[np] && c < lg.co_lim)
+            *reinterpret_cast<float*>(reinterpret_cast<char*>(p.v_inout + v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) =
+                V[mc][np][r];
+        }
+  }
+}
+
+template <int KP, int NMC, int NNP, bool TRACE, bool F32>
+hipError_t mid_launch_t(const MidParams& p, hipStream_t s) {
+  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32>;
+  if (p.q.total > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid((unsigned)p.q.row_tiles * (unsigned)p.q.co_tiles, 1, p.q.flatten ? 1 : p.m.B);
+  hipLaunchKernelGGL(kern, grid, dim3(kMidThreads), p.q.total, s, p);
+  return hipGetLastError();
+}
+
+template <int KP, bool TRACE>
+hipError_t mid_launch_bf16_kp(const MidParams& p, int nmc, int nnp, hipStream_t s) {
+  if (nmc == 1) return nnp == 1 ? mid_launch_t<KP, 1, 1, TRACE, false>(p, s) : mid_launch_t<KP, 1, 2, TRACE, false>(p, s);
+  return nnp == 1 ? mid_launch_t<KP, 2, 1, TRACE, false>(p, s) : mid_launch_t<KP, 2, 2, TRACE, false>(p, s);
+}
+
+template <int KP, bool TRACE>
+hipError_t mid_launch_f32_kp(const MidParams& p, int nnp, hipStream_t s) {
+  return nnp == 1 ? mid_launch_t<KP, 1, 1, TRACE, true>(p, s) : mid_launch_t<KP, 1, 2, TRACE, true>(p, s);
+}
+
+}  // namespace
+
+}  // namespace tac

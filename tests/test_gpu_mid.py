@@ -1,0 +1,50 @@
+"""The in-between matrix-core kernel at the edges of its tiles: pixel blocks of 1 to 16 rows, tiles that straddle samples,
+partial tiles in rows and channels, groups of up to 32 frames, every way to load, and a shorter last group inside the
+launch; against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_13810_amd import api, synth
+from gpu_util import check_layer
+
+pytestmark = pytest.mark.gpu
+B16, F32 = api.TAC_BF16, api.TAC_FP32
+TAC, TP, STEP = api.TAC_COLLAPSE, api.TAC_PRESERVE, api.TAC_PER_STEP
+
+# (B, Cin, Cout, H, W, stride, pool on load, pool in the writer, precision, mode, K, T)
+CASES = [
+    (3, 8, 5, 1, 1, 1, False, False, B16, TAC, 2, 5),                 # one pixel, sixteen rows of two lanes per block
+    (5, 8, 33, 3, 2, 1, False, False, B16, TP, 3, 7),                 # tiles straddle the samples; a second channel block of one
+    (7, 128, 40, 4, 4, 1, False, True, B16, TP, 4, 8),                # the deep blocks of the event-data network
+    (5, 128, 128, 2, 2, 1, False, True, B16, TAC, 2, 4),
+    (3, 40, 70, 9, 13, 1, False, False, B16, TAC, 4, 11),             # 16 lanes a row, parts of rows per wave
+    (2, 48, 80, 11, 45, 1, False, False, B16, TAC, 4, 9),             # two words a row
+    (2, 24, 36, 6, 20, 1, False, True, B16, TP, 2, 5),                # pooled rows across a wave's two blocks
+    (2, 24, 36, 6, 40, 1, False, True, B16, TAC, 8, 17),              # the same with two words a row
+    (1, 56, 20, 7, 61, 2, False, False, B16, TAC, 16, 33),            # stride 2, two chunks of frames, one frame left over
+    (1, 16, 40, 5, 100, 2, True, False, B16, TP, 5, 12),              # stride 2 behind the mean pool, 200 stored pixels
+    (2, 32, 64, 14, 14, 1, True, False, B16, TAC, 17, 35),            # mean pool, three chunks of frames
+    (2, 24, 17, 8, 10, 1, "max", False, B16, TAC, 3, 8),
+    (1, 16, 33, 6, 36, 1, "max", False, B16, TP, 32, 40),             # max pool, four chunks of frames
+    (3, 64, 48, 7, 7, 1, False, False, F32, TAC, 4, 10),
+    (2, 32, 64, 14, 14, 1, True, False, F32, TAC, 8, 25),             # the rate-coded network's second layer, 25 frames
+    (2, 16, 40, 9, 33, 2, "max", False, F32, STEP, 1, 3),
+    (2, 8, 24, 6, 40, 1, False, True, F32, TAC, 2, 4),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["%dx%d_to_%d_%dx%d_K%d" % (c[0], c[1], c[2], c[3], c[4], c[10]) for c in CASES])
+def test_edges_of_the_tiles(case):
+    B, Cin, Cout, H, W, stride, pool, out_pool, precision, mode, K, T = case
+    r = np.random.Generator(np.random.PCG64(6000 + Cin + Cout + H + W + K))
+    f = 2 if pool else 1
+    s = (r.random((T, B, Cin, f * H, f * W)) < 0.12).astype(np.uint8)
+    w = synth.kaiming_normal(61, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    v0 = (r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32)
+    par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, pool2=pool, precision=precision, bias=bias,
+                              v0=v0, expect_kernel=api.TAC_KERNEL_MFMA, **(dict(out_pool=True) if out_pool else {}))
+    assert ref[0].any()
+    print(case, par)
