@@ -104,7 +104,7 @@ struct BackwardParams {
   float go_w[TAC_MAX_K], go_w_last[TAC_MAX_K];   // the next layer's beta^(Kg-1-j)
 };
 hipError_t backward_launch(const BackwardParams& p, hipStream_t s);
-size_t backward_wgrad_lds_bytes(int W, int stride);
+hipError_t backward_wgrad_f32_launch(const BackwardParams& p, hipStream_t s);    // any layer, fp32 operands; adds to grad_w, grad_bias
 bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_tile_supported(const BackwardParams& p);     // wide tiles (128 input channels), grad_w as scratch

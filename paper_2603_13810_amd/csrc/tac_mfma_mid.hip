@@ -202,7 +202,7 @@ hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void
 
 static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, int& nnp) {
   const bool f32 = !p.bf16;
-  kp = p.K <= 2 ? 2 : p.K <= 4 ? 4 : 8;
+  kp = p.K <= 2 ? p.K : p.K <= 4 ? 4 : 8;
   const int nmc_w = mid_nmc(p.Cin, p.stride, p.W, p.Cout, f32);
   const int wb = (p.Wo + 31) / 32;
   // a tile that straddles samples offsets its membranes by 32 bits and counts rows in fp32

@@ -4,6 +4,7 @@
 namespace tac {
 
 hipError_t mid_launch_f32_trace(const MidParams& p, int kp, int nnp, hipStream_t s) {
+  if (kp == 1) return mid_launch_f32_kp<1, true>(p, nnp, s);
   if (kp == 2) return mid_launch_f32_kp<2, true>(p, nnp, s);
   if (kp == 4) return mid_launch_f32_kp<4, true>(p, nnp, s);
   return mid_launch_f32_kp<8, true>(p, nnp, s);

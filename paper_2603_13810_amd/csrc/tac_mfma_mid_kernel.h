@@ -76,7 +76,7 @@ namespace {
 
 constexpr int kMidBatch = 4;    // chunks of words a wave loads at a time
 // units a lane takes per chunk
-__host__ __device__ constexpr int mid_units(int kp) { return kp == 2 ? 2 : 1; }
+__host__ __device__ constexpr int mid_units(int kp) { return kp <= 2 ? 2 : 1; }
 
 // i / d for a wave-uniform divisor and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
 // the rounding of the reciprocal and the product moves it
@@ -87,7 +87,7 @@ struct SmallDiv {
   __device__ __forceinline__ int quot(int i) const { return (int)(((float)i + 0.5f) * r); }
 };
 
-// KP: frames per table index (2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
+// KP: frames per table index (1, 2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
 // per wave.
 template <int KP, int NMC, int NNP, bool TRACE, bool F32>
 __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) void mid_kernel(const MidParams mp) {
@@ -172,8 +172,8 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
 
   // ---- the loader: a wave's jobs are wave, wave + loaders, ..  A job's words come in batches of kMidBatch chunks, a
   // chunk being 64 U units of up to KP frames; the registers of a batch are requested again as soon as it has been staged.
-  // Every load is issued, from an address inside the tensor, whatever the lane's word is for (a load under a condition
-  // makes the compiler wait for it at once); words outside the image and frames beyond the group become zero when they
+  // Every load of a chunk is issued, from an address inside the tensor, whatever the lane's word is for (a load under a
+  // lane's condition makes the compiler wait for it at once); words outside the image and frames beyond the group become zero when they
   // are staged.
   constexpr int U = mid_units(KP);
   const int n_groups = p.G + (mp.K_last ? 1 : 0);
@@ -194,20 +194,23 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
     int f0[kMidBatch];
 #pragma unroll
     for (int c = 0; c < kMidBatch; ++c) {
+      if (c > 0 && batch * kMidBatch + c >= q.chunks) break;           // (wave-uniform: small jobs have one or two chunks)
       int nb, uc;
-      chunk_of(min(batch * kMidBatch + c, q.chunks - 1), nb, uc);
+      chunk_of(batch * kMidBatch + c, nb, uc);
       f0[c] = nb * KP;
 #pragma unroll
       for (int u = 0; u < U; ++u) off[c][u] = units[min((uc * U + u) * 64 + lane, n_units - 1)][0] & 0x7fffffffu;
     }
 #pragma unroll
-    for (int c = 0; c < kMidBatch; ++c)
+    for (int c = 0; c < kMidBatch; ++c) {
+      if (c > 0 && batch * kMidBatch + c >= q.chunks) break;
 #pragma unroll
       for (int j = 0; j < KP; ++j) {
         const uint32_t* const frame = base + (size_t)min(f0[c] + j, Kg - 1) * t_stride;
 #pragma unroll
         for (int u = 0; u < U; ++u) wd[c][u][j] = frame[off[c][u]];
       }
+    }
   };
   auto store_batch = [&](int Kg, int job, int batch) {
     const u32x2* const units = unit + (job & (q.parts - 1)) * n_units;
@@ -217,17 +220,19 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
     for (int c = 0; c < kMidBatch; ++c) {
       int nb, uc;
       const int chunk = batch * kMidBatch + c;
-      chunk_of(min(chunk, q.chunks - 1), nb, uc);
+      if (c > 0 && chunk >= q.chunks) break;
+      chunk_of(chunk, nb, uc);
       f0[c] = nb * KP;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int e = (uc * U + u) * 64 + lane;
         un[c][u] = units[min(e, n_units - 1)];
-        if (chunk >= q.chunks || e >= n_units) un[c][u][1] = kNone;
+        if (e >= n_units) un[c][u][1] = kNone;
       }
     }
 #pragma unroll
-    for (int c = 0; c < kMidBatch; ++c)
+    for (int c = 0; c < kMidBatch; ++c) {
+      if (c > 0 && batch * kMidBatch + c >= q.chunks) break;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const uint32_t keep = un[c][u][0] >> 31 ? 0u : 0xffffffffu;
@@ -240,6 +245,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
           for (int j = 0; j < KP; ++j) dst[j * 8] = wd[c][u][j];
         }
       }
+    }
   };
   const int job0 = min(wave, q.n_jobs - 1);
   load_batch(0, job0, 0);
@@ -398,15 +404,16 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
     }
   };
 
-  // max pool on load: the other three pixels of the block are OR-ed to the first one's class words (their fields stand at
-  // the same bit, the right-hand neighbour's in the next class word)
+  // the right-hand neighbour's field stands at the same bit of the next class word (single frames: at the next bit)
+  auto right = [](int corner) { return KP == 1 ? 0 : (corner & 1) * 8; };
+  // max pool on load: the other three pixels of the block are OR-ed to the first one's class words
   auto or_corners = [&]<int PX>(const u32x2 (&px)[PX], int nb, u32x4 (&c0)[PX], u32x4 (&c1)[PX]) {
     for (int corner = 1; corner < 4; ++corner)
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
-        const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + (corner & 1) * 8) * 4;
-        c0[k] |= *reinterpret_cast<const u32x4*>(sk);
-        c1[k] |= *reinterpret_cast<const u32x4*>(sk + 16);
+        const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + right(corner)) * 4;
+        c0[k] |= *reinterpret_cast<const u32x4*>(sk) >> (KP == 1 ? corner & 1 : 0);
+        c1[k] |= *reinterpret_cast<const u32x4*>(sk + 16) >> (KP == 1 ? corner & 1 : 0);
       }
   };
   // the pixels of a job, PX per lane at a time: all reads of a stage before the next (table address, class words, table,
@@ -415,8 +422,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
     uint8_t* const pl = lds + (job >> q.parts_shift) * q.cg * (F32 ? 2 : 1) * q.plane;
     const u32x2* const px_part = pxt + (job & (q.parts - 1)) * n_px;
     if (!sums) {
-      constexpr int PX = 4;
-      for (int e0 = lane; e0 < n_px; e0 += 64 * PX) {
+      auto pass = [&]<int PX>(std::integral_constant<int, PX>, int e0) {
         u32x2 px[PX];
         u32x4 c0[PX], c1[PX], v[PX];
 #pragma unroll
@@ -445,7 +451,10 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
 #pragma unroll
         for (int k = 0; k < PX; ++k)
           if (px[k][1] != kNone) *reinterpret_cast<u32x4*>(pl + px[k][1]) = v[k];
-      }
+      };
+      int e0 = lane;
+      for (; e0 - lane + 64 < n_px; e0 += 256) pass(std::integral_constant<int, 4>{}, e0);
+      if (e0 - lane < n_px) pass(std::integral_constant<int, 1>{}, e0);                  // 64 or fewer are left
       return;
     }
     constexpr int PX = 2;
@@ -466,7 +475,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
           u32x4 c0[PX], c1[PX];
 #pragma unroll
           for (int k = 0; k < PX; ++k) {
-            const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + (corner & 1) * 8) * 4;
+            const uint8_t* sk = stage + (px[k][0] & 0xffffffu) + ((corner >> 1) * q.wws * q.rws + nb * KP * 8 + right(corner)) * 4;
             c0[k] = *reinterpret_cast<const u32x4*>(sk);
             c1[k] = *reinterpret_cast<const u32x4*>(sk + 16);
           }
@@ -474,7 +483,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) 
 #pragma unroll
           for (int k = 0; k < PX; ++k)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) a[k][c] += tb[__builtin_amdgcn_ubfe(c < 4 ? c0[k][c] : c1[k][c - 4], px[k][0] >> 24, KP)];
+            for (int c = 0; c < 8; ++c) a[k][c] += tb[__builtin_amdgcn_ubfe(c < 4 ? c0[k][c] : c1[k][c - 4], (px[k][0] >> 24) + (KP == 1 ? corner & 1 : 0), KP)];
         }
 #pragma unroll
       for (int k = 0; k < PX; ++k) {

@@ -31,6 +31,10 @@ CASES = [
     (2, 32, 64, 14, 14, 1, True, False, F32, TAC, 8, 25),             # the rate-coded network's second layer, 25 frames
     (2, 16, 40, 9, 33, 2, "max", False, F32, STEP, 1, 3),
     (2, 8, 24, 6, 40, 1, False, True, F32, TAC, 2, 4),
+    (3, 8, 80, 17, 16, 1, False, False, B16, STEP, 1, 5),             # single frames: bits as they are, mean pool, max pool
+    (2, 24, 40, 9, 21, 1, True, False, B16, STEP, 1, 4),
+    (2, 40, 24, 6, 18, 1, "max", True, B16, STEP, 1, 3),
+    (1, 32, 40, 7, 9, 2, True, False, F32, STEP, 1, 3),
 ]
 
 
