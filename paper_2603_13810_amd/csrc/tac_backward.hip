@@ -4,7 +4,7 @@
 // per-step layer).
 //
 //   lif_backward_kernel  dL/dY_k from dL/ds and the membranes the forward pass recorded
-//   dgrad_kernel         dL/dS_{kK+j} = beta^(Kg-1-j) * (dY_k convolved back through W): fp32 vector arithmetic, any shape
+//   dgrad_kernel         dL/dS_{kK+j} = beta^(Kg-1-j) * (dY_k convolved back through W): fp32 vector arithmetic, any shape (stride 2)
 // and the choice among the matrix-core kernels of the other files.
 #include "tac_internal.h"
 
@@ -389,6 +389,8 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
     // done above
   } else if (p.grad_in && p.bf16 && p.pool2 != 1 && backward_dgrad_mfma_supported(p)) {
     e = backward_dgrad_mfma_launch(p, s);
+  } else if (p.grad_in && backward_dgrad_f32_supported(p)) {
+    e = backward_dgrad_f32_launch(p, s);
   } else if (p.grad_in) {
     const dim3 grid((p.H * p.W + kThreads - 1) / kThreads, (p.Cin + kCiTile - 1) / kCiTile, p.G * p.B);
     hipLaunchKernelGGL(dgrad_kernel, grid, dim3(kThreads), 0, s, p);

@@ -109,6 +109,8 @@ bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_tile_supported(const BackwardParams& p);     // wide tiles (128 input channels), grad_w as scratch
 hipError_t backward_dgrad_tile_launch(const BackwardParams& p, hipStream_t s);
+bool backward_dgrad_f32_supported(const BackwardParams& p);      // stride 1, fp32 operands
+hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_dgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
 

@@ -1,0 +1,68 @@
+"""The fp32 matrix-core input gradient at the edges of its tiles: several samples per tile, rows and segments with a
+remainder, channel counts that fill no block, the three ways it is written; against the gradient that automatic
+differentiation of a double-precision convolution gives for the same dL/dY."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_13810_amd import api
+from parity_util import np_pack
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+BITS, MEAN, MAX = api.TAC_IN_BITS, api.TAC_IN_BITS_POOL2, api.TAC_IN_BITS_MAXPOOL2
+
+# (B, Cin, Cout, H, W, format, per group, K, T)
+CASES = [
+    (5, 128, 128, 4, 4, BITS, True, 4, 8),      # several samples per tile, the last tile partly filled
+    (3, 5, 3, 1, 1, BITS, False, 2, 5),
+    (2, 37, 21, 9, 11, BITS, False, 3, 7),      # weights not readable 16 bytes at a time, two channel blocks
+    (1, 130, 9, 6, 70, BITS, True, 2, 3),       # two row segments, two channel groups, rounds of eight with a rest of one
+    (2, 72, 40, 16, 16, BITS, True, 4, 6),
+    (3, 32, 64, 14, 14, MEAN, False, 4, 7),     # the rate-coded network's second layer
+    (2, 20, 16, 5, 40, MAX, False, 2, 3),
+    (2, 64, 8, 33, 20, BITS, False, 1, 2),      # strips with a remainder
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["%d_to_%d_%dx%d_f%d" % c[1:6] for c in CASES])
+def test_input_gradient(case):
+    B, Cin, Cout, H, W, fmt, per_group, K, T = case
+    r = np.random.Generator(np.random.PCG64(7500 + Cin + Cout + H + W))
+    f = 1 if fmt == BITS else 2
+    x = (r.random((T, B, Cin, f * H, f * W)) < 0.3).astype(np.uint8)
+    desc = api.make_desc(T, B, Cin, H, W, Cout, K=K, beta=0.9, theta=1.0, mode=api.TAC_COLLAPSE, in_format=fmt)
+    T_out = api.tac_out_shape(desc)[0]
+    v = (0.6 * r.standard_normal((T_out, B, Cout, H, W)) + 0.3).astype(np.float32)
+    g = r.standard_normal(v.shape).astype(np.float32)
+    w = (r.standard_normal((Cout, Cin, 3, 3)) * 0.1).astype(np.float32)
+    got = api.tac_conv_lif_backward(desc, torch.from_numpy(np_pack(x)).to(DEV), torch.from_numpy(w).to(DEV), torch.from_numpy(v).to(DEV),
+                                    torch.from_numpy(g).to(DEV), grad_in_per_group=per_group)
+    torch.cuda.synchronize()
+    gy = got["grad_y"].cpu().double()
+
+    def back(weights, grads):
+        a = torch.zeros((T_out * B, Cin, H, W), dtype=torch.float64, requires_grad=True)
+        torch.nn.functional.conv2d(a, weights, None, 1, 1).backward(grads.flatten(0, 1))
+        return a.grad.view(T_out, B, Cin, H, W).numpy()
+    wd = torch.from_numpy(w).double()
+    dA, size = back(wd, gy), back(wd.abs(), gy.abs())
+    if not per_group:
+        beta = float(np.float32(0.9))
+        k = np.arange(T) // K
+        factor = np.array([beta ** (min(K, T - i // K * K) - 1 - i % K) for i in range(T)])[:, None, None, None, None]
+        dA, size = dA[k] * factor, size[k] * factor
+        if fmt == MEAN:
+            dA, size = (0.25 * a.repeat(2, 3).repeat(2, 4) for a in (dA, size))
+        elif fmt == MAX:
+            win = x.reshape(T, B, Cin, H, 2, W, 2).transpose(0, 1, 2, 3, 5, 4, 6).reshape(T, B, Cin, H, W, 4)
+            first = np.where(win.any(-1), win.argmax(-1), 0)
+
+            def route(a):
+                out = np.zeros(win.shape)
+                np.put_along_axis(out, first[..., None], a[..., None], -1)
+                return out.reshape(T, B, Cin, H, W, 2, 2).transpose(0, 1, 2, 3, 5, 4, 6).reshape(T, B, Cin, 2 * H, 2 * W)
+            dA, size = route(dA), route(size)
+    # sums of n = 9 Cout fp32 terms in any order and two factors: 2^-24 (sqrt(n) + 3) of the sum of the magnitudes, times four
+    tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
+    assert (np.abs(got["grad_in"].cpu().numpy() - dA) <= tol * size + 1e-12).all()
