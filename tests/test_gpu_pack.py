@@ -1,0 +1,22 @@
+"""Packing of dense bytes: rows of every remainder, tensors that end inside a dword, addresses of every alignment, any
+non-zero byte; against numpy."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_13810_amd import api
+from parity_util import np_pack
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("W", [1, 3, 15, 16, 31, 32, 33, 48, 64, 80, 105, 128, 131])
+@pytest.mark.parametrize("offset", [0, 1, 4, 8, 16])
+def test_pack_bytes(W, offset):
+    r = np.random.Generator(np.random.PCG64(W + offset))
+    rows = 37
+    x = np.where(r.random((rows, W)) < 0.4, r.integers(1, 256, (rows, W)), 0).astype(np.uint8)
+    buf = torch.full((offset + rows * W,), 255, dtype=torch.uint8, device="cuda:0")
+    buf[offset:].copy_(torch.from_numpy(x.reshape(-1)))
+    got = api.tac_pack_spikes(buf[offset:].view(rows, W)).cpu().numpy().view(np.uint32)
+    assert np.array_equal(got, np_pack((x != 0).astype(np.uint8)).view(np.uint32))
