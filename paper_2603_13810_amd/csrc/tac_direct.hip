@@ -1,4 +1,6 @@
-// DIRECT kernel family: the conv-LIF layer for any shape with fp32 vector FMAs.
+// DIRECT kernel family: the conv-LIF layer for any shape with fp32 vector FMAs.  With few input channels it is bound by
+// instructions around the FMAs and by the loader's trips to memory: 1 -> 32 at 28 x 28, B = 128, 25 frames in groups of 8
+// 49 us (a store per channel and step, frames one by one, the shorter last group a launch of its own: 56 + 21 us).
 //
 // One workgroup (4 wavefronts) owns 8 consecutive packed output words of one sample
 // (32 output pixels each, so 1 to 8 output rows) for a block of CB output channels, and
@@ -13,7 +15,7 @@
 //   3. LIF:     V <- decay V + Y_k, spike iff V >= theta, subtractive reset; once for TAC
 //               and per-step, K times with the same Y_k for TAC-TP; each step's spikes
 //               leave as one wave ballot = two packed words.
-#include "tac_internal.h"
+#include "tac_mfma_common.h"
 
 namespace tac {
 
@@ -21,6 +23,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWordsPerBlock = 8;   // 4 waves x 2 words
+constexpr int kAhead = 4;           // frames whose words a thread asks for together (one by one a group of 8 waits 8 times)
 
 __device__ __forceinline__ float round_bf16(float x) {
   // nearest-even rounding of the fp32 bit pattern to its upper 16 bits (finite inputs)
@@ -44,6 +47,7 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
   const int rows_in = (oy1 - oy0) * p.stride + 3;
   const int iy0 = oy0 * p.stride - 1;
   const int Wp = p.W + 2;
+  const float inv_wp = 1.0f / (float)Wp, inv_rows = 1.0f / (float)rows_in;
 
   int oy = q / p.Wwo;
   int ox = (q - oy * p.Wwo) * 32 + (lane & 31);
@@ -66,7 +70,15 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
   const int lds_base = ((oy - oy0) * p.stride) * Wp + ox * p.stride;
   const size_t in_chan = (size_t)p.Hs * p.Wwi;            // words per (t, b, ci)
 
-  for (int g = 0; g < p.G; ++g) {
+  // the whole groups, then a shorter last one (its weights are the last K_last of a whole group's)
+  const int n_groups = p.G + (p.K_last ? 1 : 0);
+  size_t step = 0;
+  for (int g = 0; g < n_groups; ++g) {
+    const bool last = g == p.G;
+    const int Kg = last ? p.K_last : p.K, n_lif = last ? p.n_lif_last : p.n_lif;
+    const float decay = last ? p.decay_last : p.decay;
+    const float* const wj = p.wj + (p.K - Kg);
+    const double* const wjd = p.wjd + (p.K - Kg);
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
       const int co = min(co0 + c, p.Cout - 1);
@@ -78,11 +90,9 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
       // ---- 1. loader: packed bits -> A_k in LDS
       const int n_el = cc * rows_in * Wp;
       for (int i = tid; i < n_el; i += kThreads) {
-        const int ci = i / (rows_in * Wp);
-        const int r = i - ci * rows_in * Wp;
-        const int row = r / Wp;
-        const int x = r - row * Wp - 1;
-        const int iy = iy0 + row;
+        // (fewer than 2^20 elements: the quotients (i + 1/2) / d stay clear of integers by more than fp32 rounds)
+        const int line = (int)(((float)i + 0.5f) * inv_wp), x = i - line * Wp - 1;
+        const int ci = (int)(((float)line + 0.5f) * inv_rows), iy = iy0 + line - ci * rows_in;
         float a = 0.0f;
         if (x >= 0 && x < p.W && iy >= 0 && iy < p.H) {
           const uint32_t* src = p.spikes + ((size_t)(g * p.K) * p.B + b) * p.Cin * in_chan +
@@ -95,7 +105,14 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
                               (((size_t)(g * p.K) * p.B + b) * p.Cin + (c0 + ci)) * ((size_t)p.H * p.W) + (size_t)iy * p.W + x;
             const size_t ts = (size_t)p.B * p.Cin * p.H * p.W;
             double ad = 0.0;
-            for (int j = 0; j < p.K; ++j) ad = __dadd_rn(ad, __dmul_rn(p.wjd[j], (double)xs[j * ts]));
+            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
+              float f[kAhead];
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u) f[u] = xs[(size_t)min(j0 + u, Kg - 1) * ts];
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u)
+                if (j0 + u < Kg) ad = __dadd_rn(ad, __dmul_rn(wjd[j0 + u], (double)f[u]));
+            }
             a = (float)ad;
           } else if (p.bf16) {
             // bf16 operands: the sum over the frames is formed exactly, in the 2^-23 fixed point of the matrix-core
@@ -105,34 +122,40 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
             const int xs = p.pool2 ? 2 * x : x;       // pooled: both stored columns sit in one word
             const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
             uint32_t q = 0u;
-            for (int j = 0; j < p.K; ++j) {
-              const uint32_t wq = (uint32_t)(p.wj[j] * 8388608.0f + 0.5f);
-              const uint32_t w0 = src[j * t_stride + off];
-              if (!p.pool2) {
-                q += ((w0 >> (xs & 31)) & 1u) ? 4u * wq : 0u;
-              } else {
-                const uint32_t w1 = src[j * t_stride + off + p.Wwi];
-                if (p.pool2 == 2) q += (((w0 | w1) >> (xs & 31)) & 3u) ? 4u * wq : 0u;      // max pool of bits = OR
-                else q += (uint32_t)(__popc((w0 >> (xs & 31)) & 3u) + __popc((w1 >> (xs & 31)) & 3u)) * wq;
+            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
+              uint32_t w0[kAhead], w1[kAhead];
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u) {
+                const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
+                w0[u] = f[0];
+                w1[u] = p.pool2 ? f[p.Wwi] : 0u;
+              }
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u) {
+                const uint32_t wq = j0 + u < Kg ? (uint32_t)(wj[min(j0 + u, Kg - 1)] * 8388608.0f + 0.5f) : 0u;
+                if (!p.pool2) q += ((w0[u] >> (xs & 31)) & 1u) ? 4u * wq : 0u;
+                else if (p.pool2 == 2) q += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? 4u * wq : 0u;      // max pool of bits = OR
+                else q += (uint32_t)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u)) * wq;
               }
             }
             a = round_bf16((float)q * (1.0f / 33554432.0f));        // quarter units of 2^-23
-          } else if (!p.pool2) {
-            const size_t off = (size_t)iy * p.Wwi + (x >> 5);
-            for (int j = 0; j < p.K; ++j) {
-              const uint32_t wd = src[j * t_stride + off];
-              a += ((wd >> (x & 31)) & 1u) ? p.wj[j] : 0.0f;
-            }
           } else {
-            const int xs = 2 * x;                     // both pooled columns sit in one word
-            const size_t off = (size_t)(2 * iy) * p.Wwi + (xs >> 5);
-            for (int j = 0; j < p.K; ++j) {
-              const uint32_t w0 = src[j * t_stride + off], w1 = src[j * t_stride + off + p.Wwi];
-              if (p.pool2 == 2) {                     // max pool of bits = OR
-                a += (((w0 | w1) >> (xs & 31)) & 3u) ? p.wj[j] : 0.0f;
-              } else {
-                const int cnt = __popc((w0 >> (xs & 31)) & 3u) + __popc((w1 >> (xs & 31)) & 3u);
-                a += (0.25f * (float)cnt) * p.wj[j];
+            const int xs = p.pool2 ? 2 * x : x;
+            const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
+            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
+              uint32_t w0[kAhead], w1[kAhead];
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u) {
+                const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
+                w0[u] = f[0];
+                w1[u] = p.pool2 ? f[p.Wwi] : 0u;
+              }
+#pragma unroll
+              for (int u = 0; u < kAhead; ++u) {
+                const float wt = j0 + u < Kg ? wj[min(j0 + u, Kg - 1)] : 0.0f;
+                if (!p.pool2) a += ((w0[u] >> (xs & 31)) & 1u) ? wt : 0.0f;
+                else if (p.pool2 == 2) a += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? wt : 0.0f;         // max pool of bits = OR
+                else a += (0.25f * (float)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u))) * wt;
               }
             }
           }
@@ -164,23 +187,35 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
 #pragma unroll
       for (int c = 0; c < CB; ++c) acc[c] += part[c];
     }
-    // ---- 3. LIF steps, ballot, packed store
-    for (int j = 0; j < p.n_lif; ++j) {
-      const size_t step = (size_t)g * p.n_lif + j;
+    // ---- 3. LIF steps, ballots; the words of a step are gathered one per lane (lane c: channel c of the wave's first
+    //      word, lane 32 + c: of its second) and stored together, where a store per channel costs more than its LIF step
+    for (int j = 0; j < n_lif; ++j, ++step) {
+      uint32_t word = 0;
+      static_for<0, CB / 4>([&](auto c4_) {
+        constexpr int c4 = decltype(c4_)::value * 4;
+        float v[4];
+        uint64_t m[4];
+        uint32_t x[4][2];
 #pragma unroll
-      for (int c = 0; c < CB; ++c) {
-        const int co = co0 + c;
-        const float v = fmaf(p.decay, V[c], acc[c]);
-        const bool fire = valid && v >= p.theta;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(fire);
-        if (co < p.Cout) {
-          if ((lane & 31) == 0 && q < nq)
-            p.out[(step * p.B + b) * p.Cout * nq + (size_t)co * nq + q] = (uint32_t)(m >> (lane & 32));
-          if (p.v_trace && valid)
-            p.v_trace[step * out_slab + ((size_t)b * p.Cout + co) * plane + (size_t)oy * p.Wo + ox] = v;
+        for (int i = 0; i < 4; ++i) v[i] = fmaf(decay, V[c4 + i], acc[c4 + i]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          m[i] = __builtin_amdgcn_ballot_w64(valid && v[i] >= p.theta);
+          x[i][0] = (uint32_t)m[i];
+          x[i][1] = (uint32_t)(m[i] >> 32);
         }
-        V[c] = fire ? v - p.theta : v;
-      }
+        word = write_lanes<c4, 1, 32>(word, x);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) V[c4 + i] = __builtin_amdgcn_inverse_ballot_w64(m[i]) ? v[i] - p.theta : v[i];
+        if (p.v_trace && valid) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (co0 + c4 + i < p.Cout)
+              p.v_trace[step * out_slab + ((size_t)b * p.Cout + co0 + c4 + i) * plane + (size_t)oy * p.Wo + ox] = v[i];
+        }
+      });
+      if ((lane & 31) < CB && co0 + (lane & 31) < p.Cout && q < nq)
+        p.out[((step * p.B + b) * p.Cout + co0 + (lane & 31)) * nq + q] = word;
     }
   }
   if (p.v_inout && valid) {
