@@ -90,7 +90,7 @@ struct SmallDiv {
 // KP: frames per table index (1, 2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
 // per wave.
 template <int KP, int NMC, int NNP, bool TRACE, bool F32>
-__global__ __launch_bounds__(kMidThreads, (TRACE || (F32 && NNP == 2)) ? 1 : 2) void mid_kernel(const MidParams mp) {
+__global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && NNP == 2) ? 1 : 2) void mid_kernel(const MidParams mp) {
   static_assert(!F32 || NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
   constexpr uint32_t kNone = 0xffffffffu;
   const MfmaParams& p = mp.m;
