@@ -535,18 +535,23 @@ bool backward_wgrad_mfma_supported(const BackwardParams& p) {
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s) {
   const int R = 256 / p.W;                               // output rows per strip (16 MFMA steps); two workgroups per compute unit fit the LDS
   const int n_strips = (p.Ho + R - 1) / R;
-  // two blocks of input channels per workgroup (eight waves) where the channel count and the LDS allow it
-  const int ncb = (p.Cin % 64 == 0 && p.W <= 64) ? 2 : 1;
+  const long long items = (long long)p.G * p.B * n_strips;
+  // two blocks of input channels per workgroup (eight waves) where the channel count and the LDS allow it and there is
+  // work for them: every slice of the items adds a whole dW with atomics (some 200 a nanosecond over the chip, 0.7 us for
+  // 128 x 128 x 9), and workgroups of one block fill the chip with half the slices (128 -> 128, B = 16, 4 groups at
+  // 32 x 32, 256 items: 96 -> 69 us; at 16 x 16, 64 items: 49 -> 37 us)
+  const bool few = items < 512;
+  const int ncb = (p.Cin % 64 == 0 && p.W <= 64 && !few) ? 2 : 1;
   // aggregates, then the staging area of the frame words: [pass][4 frames][thread]
   const int n_threads = kThreads * ncb, wwi = p.W >= 32 ? p.W / 32 : 1;
   const int passes = (32 * ncb * (R + 2) * wwi + n_threads - 1) / n_threads;
   size_t lds = (size_t)ncb * 3 * (R + 2) * (p.W / 8) * 512 + (size_t)passes * 4 * n_threads * 4;
   lds = std::max(lds, (size_t)4 * ncb * 8 * 288 * sizeof(float));        // the sums on their way to dW
   const int ci_blocks = p.Cin / (32 * ncb), co_blocks = p.Cout / 128;
-  const long long items = (long long)p.G * p.B * n_strips;
-  const int resident = ncb == 2 ? 256 : 512;             // eight waves per compute unit either way
+  const int resident = ncb == 2 || few ? 256 : 512;      // eight waves per compute unit (four with few items)
   long long split = (resident + ci_blocks * co_blocks - 1) / (ci_blocks * co_blocks);
   split = (split + 7) / 8 * 8;                           // a multiple of the XCD count
+  if (few) split = std::min(split, items / 2);
   if (split > items) split = items;
   if (split < 1) split = 1;
   auto launch = [&](auto kern) -> hipError_t {
