@@ -194,30 +194,32 @@ def tac_conv_lif(desc, spikes_packed, w_prepared, bias=None, v_inout=None, out_s
     description here because the C side only sees raw pointers.  Returns out_spikes_packed
     (int32 tensor [T_out,B,Cout,Ho,ceil(Wo/32)], allocated if not given)."""
     import torch
+    # small layers are called in a few microseconds: the sizes are worked out here from the one shape that the library
+    # is asked for (it rejects an invalid description), the tensors' bytes once each
     T_out, Ho, Wo = tac_out_shape(desc)
-    f = 2 if desc.in_format in (TAC_IN_BITS_POOL2, TAC_IN_BITS_MAXPOOL2) else 1
-    if desc.in_format == TAC_IN_F32:
-        need_in = desc.T * desc.B * desc.Cin * desc.H * desc.W * 4
+    B, Cout, fmt = desc.B, desc.Cout, desc.in_format
+    if fmt == TAC_IN_F32:
+        need_in = desc.T * B * desc.Cin * desc.H * desc.W * 4
         if spikes_packed.dtype != torch.float32:
             raise ValueError("TAC_IN_F32 needs a float32 input tensor")
     else:
-        need_in = tac_packed_bytes(desc.T, desc.B, desc.Cin, desc.H * f, desc.W * f)
-    if spikes_packed.numel() * spikes_packed.element_size() != need_in:
-        raise ValueError("spikes_packed has %d bytes, the description needs %d" %
-                         (spikes_packed.numel() * spikes_packed.element_size(), need_in))
+        f = 1 if fmt == TAC_IN_BITS else 2
+        need_in = desc.T * B * desc.Cin * desc.H * f * ((desc.W * f + 31) // 32) * 4
+    have_in = spikes_packed.numel() * spikes_packed.element_size()
+    if have_in != need_in:
+        raise ValueError("spikes_packed has %d bytes, the description needs %d" % (have_in, need_in))
     if w_prepared.numel() * w_prepared.element_size() < tac_prepared_weight_bytes(desc):
         raise ValueError("prepared-weight buffer too small for this description")
-    _, Hs, Ws = stored_out_shape(desc)
+    Hs, Ws = (Ho // 2, Wo // 2) if desc.out_format == TAC_OUT_BITS_MAXPOOL2 else (Ho, Wo)
     if out_spikes_packed is None:
-        out_spikes_packed = torch.empty((T_out, desc.B, desc.Cout, Hs, (Ws + 31) // 32), dtype=torch.int32,
-                                        device=spikes_packed.device)
-    elif out_spikes_packed.numel() * out_spikes_packed.element_size() != tac_packed_bytes(T_out, desc.B, desc.Cout, Hs, Ws):
+        out_spikes_packed = torch.empty((T_out, B, Cout, Hs, (Ws + 31) // 32), dtype=torch.int32, device=spikes_packed.device)
+    elif out_spikes_packed.numel() * out_spikes_packed.element_size() != T_out * B * Cout * Hs * ((Ws + 31) // 32) * 4:
         raise ValueError("out_spikes_packed has the wrong size")
-    if bias is not None and tuple(bias.shape) != (desc.Cout,):
+    if bias is not None and tuple(bias.shape) != (Cout,):
         raise ValueError("bias must be [Cout]")
-    if v_inout is not None and tuple(v_inout.shape) != (desc.B, desc.Cout, Ho, Wo):
+    if v_inout is not None and tuple(v_inout.shape) != (B, Cout, Ho, Wo):
         raise ValueError("v_inout must be [B,Cout,Ho,Wo]")
-    if v_trace is not None and tuple(v_trace.shape) != (T_out, desc.B, desc.Cout, Ho, Wo):
+    if v_trace is not None and tuple(v_trace.shape) != (T_out, B, Cout, Ho, Wo):
         raise ValueError("v_trace must be [T_out,B,Cout,Ho,Wo]")
     _check(lib().tac_conv_lif(ctypes.byref(desc), _dev_ptr(spikes_packed, None, "spikes_packed"),
                               _dev_ptr(w_prepared, None, "w_prepared"), _dev_ptr(bias, torch.float32, "bias"),
