@@ -23,7 +23,9 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWordsPerBlock = 8;   // 4 waves x 2 words
-constexpr int kAhead = 4;           // frames whose words a thread asks for together (one by one a group of 8 waits 8 times)
+// frames whose words a thread asks for together (one by one a group of 8 waits 8 times); groups of one or two frames ask
+// for no more than they have (2 -> 8 at 34 x 23, B = 6, 17 single frames: 72 us a call asking for four, 60 so)
+constexpr int kAhead = 4;
 
 __device__ __forceinline__ float round_bf16(float x) {
   // nearest-even rounding of the fp32 bit pattern to its upper 16 bits (finite inputs)
@@ -89,80 +91,85 @@ __global__ __launch_bounds__(kThreads) void direct_kernel(const LayerParams p, c
       __syncthreads();                                // previous chunk fully consumed
       // ---- 1. loader: packed bits -> A_k in LDS
       const int n_el = cc * rows_in * Wp;
-      for (int i = tid; i < n_el; i += kThreads) {
-        // (fewer than 2^20 elements: the quotients (i + 1/2) / d stay clear of integers by more than fp32 rounds)
-        const int line = (int)(((float)i + 0.5f) * inv_wp), x = i - line * Wp - 1;
-        const int ci = (int)(((float)line + 0.5f) * inv_rows), iy = iy0 + line - ci * rows_in;
-        float a = 0.0f;
-        if (x >= 0 && x < p.W && iy >= 0 && iy < p.H) {
-          const uint32_t* src = p.spikes + ((size_t)(g * p.K) * p.B + b) * p.Cin * in_chan +
-                                (size_t)(c0 + ci) * in_chan;
-          const size_t t_stride = (size_t)p.B * p.Cin * in_chan;
-          if (p.dense) {
-            // real-valued frames: the weighted sum in double, products and sums rounded one by one,
-            // then once to fp32 (and to bf16 below when asked)
-            const float* xs = reinterpret_cast<const float*>(p.spikes) +
-                              (((size_t)(g * p.K) * p.B + b) * p.Cin + (c0 + ci)) * ((size_t)p.H * p.W) + (size_t)iy * p.W + x;
-            const size_t ts = (size_t)p.B * p.Cin * p.H * p.W;
-            double ad = 0.0;
-            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
-              float f[kAhead];
+      auto load = [&]<int kN>(std::integral_constant<int, kN>) {
+        for (int i = tid; i < n_el; i += kThreads) {
+          // (fewer than 2^20 elements: the quotients (i + 1/2) / d stay clear of integers by more than fp32 rounds)
+          const int line = (int)(((float)i + 0.5f) * inv_wp), x = i - line * Wp - 1;
+          const int ci = (int)(((float)line + 0.5f) * inv_rows), iy = iy0 + line - ci * rows_in;
+          float a = 0.0f;
+          if (x >= 0 && x < p.W && iy >= 0 && iy < p.H) {
+            const uint32_t* src = p.spikes + ((size_t)(g * p.K) * p.B + b) * p.Cin * in_chan +
+                                  (size_t)(c0 + ci) * in_chan;
+            const size_t t_stride = (size_t)p.B * p.Cin * in_chan;
+            if (p.dense) {
+              // real-valued frames: the weighted sum in double, products and sums rounded one by one,
+              // then once to fp32 (and to bf16 below when asked)
+              const float* xs = reinterpret_cast<const float*>(p.spikes) +
+                                (((size_t)(g * p.K) * p.B + b) * p.Cin + (c0 + ci)) * ((size_t)p.H * p.W) + (size_t)iy * p.W + x;
+              const size_t ts = (size_t)p.B * p.Cin * p.H * p.W;
+              double ad = 0.0;
+              for (int j0 = 0; j0 < Kg; j0 += kN) {
+                float f[kN];
 #pragma unroll
-              for (int u = 0; u < kAhead; ++u) f[u] = xs[(size_t)min(j0 + u, Kg - 1) * ts];
+                for (int u = 0; u < kN; ++u) f[u] = xs[(size_t)min(j0 + u, Kg - 1) * ts];
 #pragma unroll
-              for (int u = 0; u < kAhead; ++u)
-                if (j0 + u < Kg) ad = __dadd_rn(ad, __dmul_rn(wjd[j0 + u], (double)f[u]));
+                for (int u = 0; u < kN; ++u)
+                  if (j0 + u < Kg) ad = __dadd_rn(ad, __dmul_rn(wjd[j0 + u], (double)f[u]));
+              }
+              a = (float)ad;
+            } else if (p.bf16) {
+              // bf16 operands: the sum over the frames is formed exactly, in the 2^-23 fixed point of the matrix-core
+              // kernels (weights rounded to it once, quarter counts with the mean pool), and rounded once: all bf16
+              // kernels then hand the same A_k to the convolution, and a sum of up to 16 terms does not drift across a
+              // bf16 rounding boundary the way a chain of fp32 additions can
+              const int xs = p.pool2 ? 2 * x : x;       // pooled: both stored columns sit in one word
+              const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
+              uint32_t q = 0u;
+              for (int j0 = 0; j0 < Kg; j0 += kN) {
+                uint32_t w0[kN], w1[kN];
+#pragma unroll
+                for (int u = 0; u < kN; ++u) {
+                  const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
+                  w0[u] = f[0];
+                  w1[u] = p.pool2 ? f[p.Wwi] : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < kN; ++u) {
+                  const uint32_t wq = j0 + u < Kg ? (uint32_t)(wj[min(j0 + u, Kg - 1)] * 8388608.0f + 0.5f) : 0u;
+                  if (!p.pool2) q += ((w0[u] >> (xs & 31)) & 1u) ? 4u * wq : 0u;
+                  else if (p.pool2 == 2) q += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? 4u * wq : 0u;      // max pool of bits = OR
+                  else q += (uint32_t)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u)) * wq;
+                }
+              }
+              a = round_bf16((float)q * (1.0f / 33554432.0f));        // quarter units of 2^-23
+            } else {
+              const int xs = p.pool2 ? 2 * x : x;
+              const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
+              for (int j0 = 0; j0 < Kg; j0 += kN) {
+                uint32_t w0[kN], w1[kN];
+#pragma unroll
+                for (int u = 0; u < kN; ++u) {
+                  const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
+                  w0[u] = f[0];
+                  w1[u] = p.pool2 ? f[p.Wwi] : 0u;
+                }
+#pragma unroll
+                for (int u = 0; u < kN; ++u) {
+                  const float wt = j0 + u < Kg ? wj[min(j0 + u, Kg - 1)] : 0.0f;
+                  if (!p.pool2) a += ((w0[u] >> (xs & 31)) & 1u) ? wt : 0.0f;
+                  else if (p.pool2 == 2) a += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? wt : 0.0f;         // max pool of bits = OR
+                  else a += (0.25f * (float)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u))) * wt;
+                }
+              }
             }
-            a = (float)ad;
-          } else if (p.bf16) {
-            // bf16 operands: the sum over the frames is formed exactly, in the 2^-23 fixed point of the matrix-core
-            // kernels (weights rounded to it once, quarter counts with the mean pool), and rounded once: all bf16
-            // kernels then hand the same A_k to the convolution, and a sum of up to 16 terms does not drift across a
-            // bf16 rounding boundary the way a chain of fp32 additions can
-            const int xs = p.pool2 ? 2 * x : x;       // pooled: both stored columns sit in one word
-            const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
-            uint32_t q = 0u;
-            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
-              uint32_t w0[kAhead], w1[kAhead];
-#pragma unroll
-              for (int u = 0; u < kAhead; ++u) {
-                const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
-                w0[u] = f[0];
-                w1[u] = p.pool2 ? f[p.Wwi] : 0u;
-              }
-#pragma unroll
-              for (int u = 0; u < kAhead; ++u) {
-                const uint32_t wq = j0 + u < Kg ? (uint32_t)(wj[min(j0 + u, Kg - 1)] * 8388608.0f + 0.5f) : 0u;
-                if (!p.pool2) q += ((w0[u] >> (xs & 31)) & 1u) ? 4u * wq : 0u;
-                else if (p.pool2 == 2) q += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? 4u * wq : 0u;      // max pool of bits = OR
-                else q += (uint32_t)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u)) * wq;
-              }
-            }
-            a = round_bf16((float)q * (1.0f / 33554432.0f));        // quarter units of 2^-23
-          } else {
-            const int xs = p.pool2 ? 2 * x : x;
-            const size_t off = (size_t)(p.pool2 ? 2 * iy : iy) * p.Wwi + (xs >> 5);
-            for (int j0 = 0; j0 < Kg; j0 += kAhead) {
-              uint32_t w0[kAhead], w1[kAhead];
-#pragma unroll
-              for (int u = 0; u < kAhead; ++u) {
-                const uint32_t* const f = src + (size_t)min(j0 + u, Kg - 1) * t_stride + off;
-                w0[u] = f[0];
-                w1[u] = p.pool2 ? f[p.Wwi] : 0u;
-              }
-#pragma unroll
-              for (int u = 0; u < kAhead; ++u) {
-                const float wt = j0 + u < Kg ? wj[min(j0 + u, Kg - 1)] : 0.0f;
-                if (!p.pool2) a += ((w0[u] >> (xs & 31)) & 1u) ? wt : 0.0f;
-                else if (p.pool2 == 2) a += (((w0[u] | w1[u]) >> (xs & 31)) & 3u) ? wt : 0.0f;         // max pool of bits = OR
-                else a += (0.25f * (float)(__popc((w0[u] >> (xs & 31)) & 3u) + __popc((w1[u] >> (xs & 31)) & 3u))) * wt;
-              }
-            }
+            if (p.bf16 && p.dense) a = round_bf16(a);
           }
-          if (p.bf16 && p.dense) a = round_bf16(a);
+          a_lds[i] = a;
         }
-        a_lds[i] = a;
-      }
+      };
+      if (Kg == 1) load(std::integral_constant<int, 1>{});
+      else if (Kg == 2) load(std::integral_constant<int, 2>{});
+      else load(std::integral_constant<int, kAhead>{});
       __syncthreads();
       // ---- 2. conv: 9 taps x cc channels, CB output channels per lane.  The chunk's terms are summed on their own and
       //      added to the sum of the chunks before: with hundreds of input channels one chain of fp32 additions

@@ -418,6 +418,9 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   };
   // the pixels of a job, PX per lane at a time: all reads of a stage before the next (table address, class words, table,
   // tile), so that PX chains of LDS latencies overlap
+  // (Single frames have two aggregates, 0 and the weight: a mask and the weight take the place of the table:
+  // 8 -> 32 at 59 x 39, B = 17, 18 frames one by one 50.6 -> 48.0 us, two layers at 26 x 26 in fp32 160 -> 149 us.)
+  const uint32_t one = KP != 1 ? 0u : sums ? p.wq[0] : pack_bf16((float)p.wq[0] * scale, (float)p.wq[0] * scale);
   auto build_job = [&](int job) {
     uint8_t* const pl = lds + (job >> q.parts_shift) * q.cg * (F32 ? 2 : 1) * q.plane;
     const u32x2* const px_part = pxt + (job & (q.parts - 1)) * n_px;
@@ -442,6 +445,12 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
           const uint32_t sh = px[k][0] >> 24;
 #pragma unroll
           for (int c2 = 0; c2 < 4; ++c2) {
+            if constexpr (KP == 1) {
+              const uint32_t m0 = 0u - __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2] : c1[k][2 * c2 - 4], sh, 1);
+              const uint32_t m1 = 0u - __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2 + 1] : c1[k][2 * c2 - 3], sh, 1);
+              v[k][c2] = one & ((m0 & 0xffffu) | (m1 << 16));
+              continue;
+            }
             const uint32_t lo = __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2] : c1[k][2 * c2 - 4], sh, KP);
             const uint32_t hi = __builtin_amdgcn_ubfe(c2 < 2 ? c0[k][2 * c2 + 1] : c1[k][2 * c2 - 3], sh, KP);
             if constexpr (KP == 8) v[k][c2] = lut[lo] | (lut[hi] << 16);
@@ -453,11 +462,15 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
           if (px[k][1] != kNone) *reinterpret_cast<u32x4*>(pl + px[k][1]) = v[k];
       };
       int e0 = lane;
-      for (; e0 - lane + 64 < n_px; e0 += 256) pass(std::integral_constant<int, 4>{}, e0);
+      if constexpr (KP == 1) {
+        for (; e0 - lane + 64 < n_px; e0 += 128) pass(std::integral_constant<int, 2>{}, e0);
+      } else {
+        for (; e0 - lane + 64 < n_px; e0 += 256) pass(std::integral_constant<int, 4>{}, e0);
+      }
       if (e0 - lane < n_px) pass(std::integral_constant<int, 1>{}, e0);                  // 64 or fewer are left
       return;
     }
-    constexpr int PX = 2;
+    constexpr int PX = KP == 1 ? 1 : 2;        // (without lookups there is little to overlap)
     for (int e0 = lane; e0 < n_px; e0 += 64 * PX) {
       u32x2 px[PX];
       uint32_t a[PX][8];
@@ -471,7 +484,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       const int corners = p.pool == 1 ? 4 : 1;                         // mean pool: the sum over the block's four pixels
       for (int nb = 0; nb < q.nb; ++nb)
         for (int corner = 0; corner < corners; ++corner) {
-          const uint32_t* const tb = lut + (nb << KP);
+          [[maybe_unused]] const uint32_t* const tb = lut + (nb << KP);
           u32x4 c0[PX], c1[PX];
 #pragma unroll
           for (int k = 0; k < PX; ++k) {
@@ -483,7 +496,11 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
 #pragma unroll
           for (int k = 0; k < PX; ++k)
 #pragma unroll
-            for (int c = 0; c < 8; ++c) a[k][c] += tb[__builtin_amdgcn_ubfe(c < 4 ? c0[k][c] : c1[k][c - 4], (px[k][0] >> 24) + (KP == 1 ? corner & 1 : 0), KP)];
+            for (int c = 0; c < 8; ++c) {
+              const uint32_t bits = __builtin_amdgcn_ubfe(c < 4 ? c0[k][c] : c1[k][c - 4], (px[k][0] >> 24) + (KP == 1 ? corner & 1 : 0), KP);
+              if constexpr (KP == 1) a[k][c] += one & (0u - bits);
+              else a[k][c] += tb[bits];
+            }
         }
 #pragma unroll
       for (int k = 0; k < PX; ++k) {
