@@ -65,7 +65,7 @@ hipError_t mfma_aggregate_launch(const LayerParams& p, uint64_t* tile_sums, hipS
 // the matrix cores alone (measurement aid): 4 workgroups per compute unit, `iterations` x 8 MFMAs per wave
 size_t mfma_probe_workgroups();
 hipError_t mfma_probe_launch(int iterations, float* sums, hipStream_t s);
-// its member for the shapes in between (Cin a multiple of 8 up to 64, widths up to 128, any pool on load)
+// its member for the shapes in between (Cin a multiple of 8 up to 128, widths up to 128, any pool on load)
 bool mfma_mid_supported(const tac_layer_desc_t& d);
 size_t mfma_mid_weight_bytes(const tac_layer_desc_t& d);
 hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);
