@@ -154,7 +154,11 @@ double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
   const int n_px = q.cg * q.lrp * p.W;
   const bool sums = q.nb > 1 || p.pool2 || f32;
   const double jobs = (q.n_jobs + q.loaders - 1) / q.loaders;
-  const double build = jobs * (1000.0 + 1400.0 * q.batches + ((n_px + 255) / 256) * (sums ? 1200.0 * q.nb * (p.pool2 ? 4 : 1) : 700.0));
+  // the passes over the job's pixels: 256 at a time; single frames, which need no table, in narrower ones
+  const double passes = p.K > 1 ? ((n_px + 255) / 256) * (sums ? 1200.0 * q.nb * (p.pool2 ? 4 : 1) : 700.0)
+                        : sums  ? ((n_px + 63) / 64) * (300.0 + 400.0 * (p.pool2 ? 4 : 1))
+                                : n_px <= 64 ? 300.0 : ((n_px + 127) / 128) * 450.0;
+  const double build = jobs * (1000.0 + 1400.0 * q.batches + passes);
   const double mfma = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
   const double lif = p.n_lif * (nmc * nnp * 500.0 + 400.0 + 60.0 * q.rpb);
   const double wgs = (double)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
