@@ -80,3 +80,28 @@ def test_an_infinite_frame_value_stays_where_it_is():
     assert torch.isfinite(gw[:, 0]).all()
     # column kx = 0 sees input pixels 0 .. 3 of a row (x = 1 .. 4), never the last one
     assert torch.isfinite(gw[:, 1, :, 0]).all() and torch.isinf(gw[:, 1, :, 1:]).all()
+
+
+@pytest.mark.parametrize("B,Cin,Cout,hw,T,rate", [(16, 256, 256, 40, 4, 0.12), (100, 256, 128, 32, 2, 1.0)])
+def test_long_sums_of_one_sign(B, Cin, Cout, hw, T, rate):
+    # 1e5 pixels and more per element, all terms positive: a sum that is one long chain of additions loses digits here.
+    # dL/dY is the same everywhere within a step, so that dW is that value times the number of spikes under the tap.
+    r = np.random.Generator(np.random.PCG64(7100 + hw))
+    x = (r.random((T, B, Cin, hw, hw)) < rate).astype(np.uint8)
+    desc = api.make_desc(T, B, Cin, hw, hw, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    v = torch.full((T, B, Cout, hw, hw), 0.4, device=DEV)
+    got = api.tac_conv_lif_backward(desc, torch.from_numpy(np_pack(x)).to(DEV), torch.zeros((Cout, Cin, 3, 3), device=DEV), v,
+                                    torch.full_like(v, 0.37), want_input_grad=False, detach_reset=True)
+    gy = got["grad_y"].flatten(1)
+    assert (gy > 0).all() and torch.equal(gy, gy[:, :1].expand_as(gy))
+    per_step = gy[:, 0].double().cpu().numpy()
+    padded = np.pad(x, ((0, 0), (0, 0), (0, 0), (1, 1), (1, 1)))
+    count = np.stack([padded[:, :, :, ky:ky + hw, kx:kx + hw].sum((1, 3, 4), dtype=np.int64) for ky in range(3) for kx in range(3)], -1)
+    dW = np.broadcast_to((per_step[:, None, None] * count).sum(0), (Cout, Cin, 9))
+    db = per_step.sum() * B * hw * hw
+    # Chains of at most some 64 MFMAs, 64 sums of chains, 8 waves and 48 slices follow one another; n additions, each
+    # rounded by up to 2^-24 of the sum so far, leave about 2^-24 sqrt(n) of it: n < 256
+    tol = 16 * 2.0 ** -24
+    err = got["grad_w"].double().cpu().numpy().reshape(dW.shape) - dW
+    assert np.linalg.norm(err) <= tol * np.linalg.norm(dW)
+    assert np.abs(got["grad_bias"].double().cpu().numpy() - db).max() <= tol * db
