@@ -72,6 +72,22 @@ int mid_nmc(int Cin, int S, int W, int Cout, bool f32) {
 
 size_t mid_tile_bytes(const tac_layer_desc_t& d, int nmc, bool f32) { return (size_t)mid_k_steps(d.Cin, f32) * nmc * 64 * (f32 ? 4 : 16); }
 
+// Cycles of a wave's job: its chunks of words, then the passes over its pixels as build_job makes them (a last pass of 64 or
+// fewer is a narrow one; sums take two at a time, single frames one; the mean pool goes over the four pixels of a block, the
+// max pool reads all four first).
+double mid_job_cycles(const MidPlan& q, const LayerParams& p) {
+  const int n_px = q.cg * q.lrp * p.W;
+  const bool sums = q.nb > 1 || p.pool2 == 1 || !p.bf16;
+  const double corners = p.pool2 == 1 ? 4.0 : 1.0, reads = p.pool2 == 2 ? 300.0 : 0.0;
+  double passes;
+  if (sums && p.K == 1) passes = ((n_px + 63) / 64) * (300.0 + 400.0 * corners + reads);
+  else if (sums) passes = ((n_px + 127) / 128) * q.nb * (600.0 * corners + reads);
+  else if (p.K == 1) passes = n_px <= 64 ? 300.0 + reads : ((n_px + 127) / 128) * (450.0 + reads);
+  else passes = (n_px / 256 + (n_px % 256 > 64)) * (700.0 + 2.0 * reads) + (n_px % 256 && n_px % 256 <= 64 ? 350.0 + reads : 0.0);
+  // (a second batch of words is asked for when the first has been staged, and waited for)
+  return 1000.0 + 500.0 * q.chunks + 600.0 * (q.batches - 1) + passes;
+}
+
 // The plan of one tile shape, or false when it does not fit the LDS.  pw_shift: lanes per row of a block (their log2),
 // trg: row groups per tile.
 bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w) {
@@ -111,6 +127,20 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   q.off_wq = q.off_bias + nmc * 32 * 4;
   q.off_lut = q.off_wq + TAC_MAX_K * 4;
   q.off_unit = up(q.off_lut + lut_entries * 4);
+  // groups of one or two frames on few channels: see the kernel's build_direct
+  q.direct = kp <= 2 && (kp == 1 || !p.pool2) && C8 * q.lr * p.W <= kMidDirect * kMidThreads;
+  if (q.direct) {
+    q.n_jobs = 0;
+    q.loaders = 4;
+    q.parts = 1;
+    q.parts_shift = 0;
+    q.lrp = q.lr;
+    q.cg = C8;
+    q.chunks = q.batches = q.rw = q.stage_wave = 0;
+    q.off_px = q.off_stage = q.off_unit;
+    q.total = std::max(q.off_unit, q.off_w + w_bytes + ahead);
+    return q.total <= kMidLds;
+  }
   // Four waves form aggregates, each in as few jobs as the LDS has room to stage; fewer waves only where even the smallest
   // jobs of four do not fit (rows of 100 and more pixels in groups of 16 and more frames).
   bool found = false;
@@ -133,8 +163,7 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
         c.stage_wave = up(c.cg * c.rw * c.rws * 4);
         c.total = std::max(c.off_stage + c.loaders * c.stage_wave, c.off_w + w_bytes + ahead);
         if (c.total > kMidLds || c.stage_wave >= 1 << 24) continue;
-        // a wave's instructions per group, roughly: a batch, a pass over 256 pixels
-        const double cost = (double)((c.n_jobs + c.loaders - 1) / c.loaders) * (300.0 + 350.0 * c.batches + 130.0 * ((n_px + 255) / 256));
+        const double cost = (double)((c.n_jobs + c.loaders - 1) / c.loaders) * mid_job_cycles(c, p);
         // a second workgroup per compute unit is worth more than a job less
         const double scaled = cost * (c.total > kMidLds / 2 && c.off_px < kMidLds / 2 ? 1.3 : 1.0);
         if (found && scaled >= best) continue;
@@ -148,26 +177,29 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
 
 // Estimated time of a launch in cycles: rounds of resident workgroups, each the sum of its phases (instructions of the
 // loader; MFMAs, 32 cycles per 32x32x16 and 64 per fp32 32x32x2, or the LDS reads that feed them at 128 bytes per cycle;
-// LIF steps).  Two resident workgroups fill each other's gaps, but share the LDS and the matrix cores.
+// LIF steps).  Resident workgroups fill each other's gaps, but share the LDS and the matrix cores.  The figures are fitted to
+// what the tiles of some hundred layers take; over 440 layers of all kinds the chosen tiles are 1.11 times as fast as with
+// a coarser estimate (passes of 256 pixels whatever the job, two residents at most), which put single frames of few channels
+// on one workgroup per compute unit.
 double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
   const bool f32 = !p.bf16;
-  const int n_px = q.cg * q.lrp * p.W;
-  const bool sums = q.nb > 1 || p.pool2 || f32;
-  const double jobs = (q.n_jobs + q.loaders - 1) / q.loaders;
-  // the passes over the job's pixels: 256 at a time; single frames, which need no table, in narrower ones
-  const double passes = p.K > 1 ? ((n_px + 255) / 256) * (sums ? 1200.0 * q.nb * (p.pool2 ? 4 : 1) : 700.0)
-                        : sums  ? ((n_px + 63) / 64) * (300.0 + 400.0 * (p.pool2 ? 4 : 1))
-                                : n_px <= 64 ? 300.0 : ((n_px + 127) / 128) * 450.0;
-  const double build = jobs * (1000.0 + 1400.0 * q.batches + passes);
-  const double mfma = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
-  const double lif = p.n_lif * (nmc * nnp * 500.0 + 400.0 + 60.0 * q.rpb);
+  const double build = q.direct ? 500.0 + 400.0 * ((p.Cin / 8 * q.lr * p.W + kMidThreads - 1) / kMidThreads) * (p.K == 2 || p.pool2 ? 2 : 1)
+                                : (q.n_jobs + q.loaders - 1) / q.loaders * mid_job_cycles(q, p);
+  // (an fp32 step waits for its operands: a wave alone takes about 170 cycles for one block)
+  const double busy = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
+  const double mfma = f32 ? q.nks * 170.0 * nnp + 300.0 : busy;
+  const double lif = p.n_lif * (nmc * nnp * (p.v_trace ? 1200.0 : 500.0) + 400.0 + 60.0 * q.rpb);
   const double wgs = (double)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
   const double per_cu = std::ceil(wgs / 256.0);
-  const int resident = q.total <= kMidLds / 2 ? 2 : 1;
+  // workgroups that share a compute unit: as the LDS allows, and the registers (words of the threads' own and single frames leave
+  // room for more than two with one or two accumulator blocks); 1003 workgroups of 8 -> 32 at 59 x 39, four a unit, take as
+  // long as 502, two a unit
+  const int blocks = nmc * nnp, by_registers = f32 || blocks > 2 || !(q.direct || p.K == 1) ? 2 : blocks == 1 ? 4 : 3;
+  const int resident = std::min(by_registers, kMidLds / q.total);
+  const double together = std::min<double>(resident, per_cu);
   const double alone = 9000.0 + p.G * (build + mfma + lif + 500.0);
-  const double shared = p.G * mfma;                                     // what a second workgroup cannot hide
-  if (resident == 1 || per_cu <= 1) return per_cu * alone;
-  return std::ceil(per_cu / 2) * std::max(alone * 1.15, 2.0 * shared);
+  const double shared = p.G * busy;                                     // what other workgroups cannot hide
+  return std::ceil(per_cu / resident) * std::max(alone * (together > 1 ? 1.1 + 0.025 * together : 1.0), together * shared);
 }
 
 }  // namespace
@@ -227,7 +259,10 @@ static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, 
             MidPlan q;
             if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w)) continue;
             const double cost = mid_cost(q, p, c, x);
-            if (found && cost >= best) continue;
+            // of equals the one that does not straddle samples, and of tiles that all have a compute unit to themselves the
+            // smaller one, both of which are tried later
+            const long long wgs = (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
+            if (found && (cost > best || (cost == best && wgs > 256 && q.flatten))) continue;
             found = true;
             best = cost;
             out.q = q;
@@ -254,7 +289,7 @@ hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
   a.K_last = p.K_last; a.n_lif_last = p.n_lif_last; a.decay_last = p.decay_last;
   // The choice looks at some hundred tiles (about 15 us); the geometry a thread has asked for lately is remembered.
   struct Key {
-    int v[13];
+    int v[14];
     bool operator==(const Key& o) const { return std::memcmp(v, o.v, sizeof(v)) == 0; }
   };
   struct Entry {
@@ -264,7 +299,7 @@ hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
     bool used;
   };
   static thread_local Entry known[64];
-  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.n_lif, p.pool2, p.out_pool, p.bf16, p.Wwi}};
+  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.n_lif, p.pool2, p.out_pool, p.bf16, p.Wwi, p.v_trace != nullptr}};
   uint32_t hash = 2166136261u;
   for (int v : key.v) hash = (hash ^ (uint32_t)v) * 16777619u;
   Entry& e = known[(hash >> 16) & 63];

@@ -23,6 +23,8 @@
 // F32: the fp32 layers of these shapes on the same structure with v_mfma_f32_32x32x2_f32: aggregate tile and weights in
 // LDS as float32, two contraction slots per MFMA, products and sums in fp32.
 //
+// DIRECT: groups of one or two frames where a thread has at most kMidDirect pixels of 8 channels; no staging, no tables.
+//
 // A shorter last group (T mod K frames) is one more turn of the loop with tables of its own, the membrane still in
 // registers.
 //
@@ -51,6 +53,7 @@ struct MidPlan {
   int row_tiles, co_tiles;      // tiles over the rows (per sample, or over all of them), over the output channels
   int cg, parts_shift, parts, lrp;      // a job = cg groups of 8 channels x lrp LDS rows; parts: jobs over the rows, a power of two
   int loaders;                  // waves that form aggregates: all four unless their staging areas do not fit the LDS
+  int direct;                   // no jobs: every thread forms up to kMidDirect pixels of 8 channels from words of its own
   int srows, wws, hs;           // stored rows per LDS row (2: pool on load), words per stored row, stored rows per channel
   int rw, rws;                  // (stored row, word) pairs per job and channel; staged dwords per pair and 8 channels
   int n_jobs, chunks, batches;  // jobs per tile; (chunk of frames, 64 U units) pairs per job, the same in batches of kMidBatch
@@ -75,6 +78,7 @@ hipError_t mid_launch_f32_trace(const MidParams& p, int kp, int nnp, hipStream_t
 namespace {
 
 constexpr int kMidBatch = 4;    // chunks of words a wave loads at a time
+constexpr int kMidDirect = 2;   // pixels of 8 channels per thread that go without staging
 // units a lane takes per chunk
 __host__ __device__ constexpr int mid_units(int kp) { return kp <= 2 ? 2 : 1; }
 
@@ -88,8 +92,8 @@ struct SmallDiv {
 };
 
 // KP: frames per table index (1, 2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
-// per wave.
-template <int KP, int NMC, int NNP, bool TRACE, bool F32>
+// per wave.  DIRECT: the plan's direct.
+template <int KP, int NMC, int NNP, bool TRACE, bool F32, bool DIRECT>
 __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && NNP == 2) ? 1 : 2) void mid_kernel(const MidParams mp) {
   static_assert(!F32 || NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
   constexpr uint32_t kNone = 0xffffffffu;
@@ -144,23 +148,28 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   const int n0 = min(p.Ho - oy0, q.tr) * S + (3 - S);                  // LDS rows of the tile's first sample
   const int per_sample = p.Ho * S + (3 - S);
   const int lr_used = (rows_valid - 1) * S + sample_of(rows_valid - 1) * (3 - S) + 3;
+  auto input_row = [&](int row, int& bsel, int& iy) {                  // LDS row -> sample - b0, row of its image
+    bsel = 0;
+    iy = oy0 * S - 1 + row;
+    if (row >= n0) {
+      const int over = SmallDiv(per_sample).quot(row - n0);
+      bsel = 1 + over;
+      iy = row - n0 - over * per_sample - 1;
+    }
+  };
   const int n_units = 8 * q.cg * q.rw;                                 // per job
   const int stage_cg = q.rw * q.rws * 4;
   // which words a job loads: unit (channel, stored row, word) -> dword offset from (frame, first sample, first channel
   // of the job), top bit: outside the image; byte offset in the staging area
   const SmallDiv by_rw(q.rw), by_wws(q.wws), by_ch(8 * q.cg);
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < q.parts * n_units; i += kMidThreads) {
+  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_units); i += kMidThreads) {
     const int pc = by_rw.quot(i), rw = i - pc * q.rw;
     const int part = by_ch.quot(pc), ch = pc - part * 8 * q.cg;
     const int srow = by_wws.quot(rw), word = rw - srow * q.wws;
     const int row = part * q.lrp + (srow >> (q.srows - 1));
-    int bsel = 0, iy = oy0 * S - 1 + row;
-    if (row >= n0) {
-      const int over = SmallDiv(per_sample).quot(row - n0);
-      bsel = 1 + over;
-      iy = row - n0 - over * per_sample - 1;
-    }
+    int bsel, iy;
+    input_row(row, bsel, iy);
     const bool inside = row < lr_used && iy >= 0 && iy < p.H;
     const int sy = p.pool ? 2 * iy + (srow & (q.srows - 1)) : iy;
     u32x2 u;
@@ -248,14 +257,56 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     }
   };
   const int job0 = min(wave, q.n_jobs - 1);
-  load_batch(0, job0, 0);
+
+  // Groups of one or two frames on few channels: the words are few, and what the staging takes is its chain of LDS round trips
+  // (8 -> 32 at 59 x 39, B = 17, 18 frames one by one: 52 us a call, of which staging 14, requests 8 and the passes over the
+  // pixels 10; 33 us so.  16 -> 16 at 64 x 41, B = 37, TAC-TP K = 2, 12 frames: 57 -> 39 us).  A thread asks for the 8 words (times
+  // two frames, or two rows with a pool on load) of each of its pixels one group ahead and keeps what it needs to know
+  // about them in registers.
+  static_assert(!DIRECT || KP <= 2, "groups of one or two frames");
+  uint32_t dw[kMidDirect][2][8], d_off[kMidDirect], d_dst[kMidDirect];  // dw: two frames, or two rows of the pool
+  auto load_direct = [&](int g) {
+    if constexpr (DIRECT) {
+      const uint32_t* const base = p.spikes + (((size_t)g * p.K) * p.B + b0) * Cin * in_chan;
+      const size_t second = KP == 2 ? (frames_of(g) > 1 ? t_stride : 0) : p.pool ? (size_t)q.wws : 0;
+#pragma unroll
+      for (int i = 0; i < kMidDirect; ++i) {
+        if (i > 0 && i * kMidThreads >= C8 * q.lr * p.W) break;        // (uniform)
+        const uint32_t* const src = base + (d_off[i] & 0x7fffffffu);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) dw[i][0][c] = src[c * in_chan];
+        if (KP == 2 || p.pool) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) dw[i][1][c] = src[second + c * in_chan];
+        }
+      }
+    }
+  };
+  if constexpr (DIRECT) {
+    const SmallDiv by_w(p.W), by_lr(q.lr);
+#pragma unroll
+    for (int i = 0; i < kMidDirect; ++i) {
+      const int e = tid + i * kMidThreads, line = by_w.quot(min(e, C8 * q.lr * p.W - 1));
+      const int x = min(e, C8 * q.lr * p.W - 1) - line * p.W, cg = by_lr.quot(line), row = line - cg * q.lr;
+      int bsel, iy;
+      input_row(row, bsel, iy);
+      const bool used = e < C8 * q.lr * p.W && row < lr_used, inside = used && iy >= 0 && iy < p.H;
+      const int xs = p.pool ? 2 * x : x, xp = x + 1;
+      d_off[i] = inside ? (uint32_t)((size_t)(bsel * Cin + cg * 8) * in_chan + (size_t)(p.pool ? 2 * iy : iy) * q.wws + (xs >> 5)) : 0x80000000u;
+      d_dst[i] = used ? (uint32_t)(cg * (F32 ? 2 : 1) * q.plane + (row * q.wpx + (S == 1 ? xp : (xp & 1) * q.xh + (xp >> 1))) * 16) | (uint32_t)(xs & 31) << 24
+                      : kNone;
+    }
+    load_direct(0);
+  } else {
+    load_batch(0, job0, 0);
+  }
 
   // which pixels a job forms: byte offset of the pixel's class words, shift of its field (top byte); byte offset in LDS
   // from the job's first plane
   const SmallDiv by_w(p.W), by_lrp(q.lrp), by_cg(q.cg);
   const int n_px = q.cg * q.lrp * p.W;                                 // per job
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < q.parts * n_px; i += kMidThreads) {
+  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_px); i += kMidThreads) {
     const int line = by_w.quot(i), x = i - line * p.W;                 // (part, channel group, row)
     const int pcg = by_lrp.quot(line), rl = line - pcg * q.lrp;
     const int part = by_cg.quot(pcg), cg = pcg - part * q.cg, row = part * q.lrp + rl;
@@ -418,8 +469,8 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   };
   // the pixels of a job, PX per lane at a time: all reads of a stage before the next (table address, class words, table,
   // tile), so that PX chains of LDS latencies overlap
-  // (Single frames have two aggregates, 0 and the weight: a mask and the weight take the place of the table:
-  // 8 -> 32 at 59 x 39, B = 17, 18 frames one by one 50.6 -> 48.0 us, two layers at 26 x 26 in fp32 160 -> 149 us.)
+  // (Single frames have two aggregates, 0 and the weight: a mask and the weight take the place of the table: two layers at
+  // 26 x 26 in fp32 160 -> 149 us.)
   const uint32_t one = KP != 1 ? 0u : sums ? p.wq[0] : pack_bf16((float)p.wq[0] * scale, (float)p.wq[0] * scale);
   auto build_job = [&](int job) {
     uint8_t* const pl = lds + (job >> q.parts_shift) * q.cg * (F32 ? 2 : 1) * q.plane;
@@ -520,18 +571,57 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     }
   };
 
+  auto build_direct = [&](int Kg) {
+    if constexpr (DIRECT) {
+      const uint32_t w0 = p.wq[p.K - Kg], w1 = KP == 2 && Kg == 2 ? p.wq[1] : 0u;
+#pragma unroll
+      for (int i = 0; i < kMidDirect; ++i) {
+        if (i > 0 && i * kMidThreads >= C8 * q.lr * p.W) break;
+        const uint32_t keep = d_off[i] >> 31 ? 0u : 0xffffffffu, sh = d_dst[i] >> 24 & 31;
+        uint32_t a[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+          const uint32_t f0 = dw[i][0][c] & keep, f1 = dw[i][1][c] & keep;
+          if (KP == 2) {
+            a[c] = ((0u - __builtin_amdgcn_ubfe(f0, sh, 1)) & w0) + ((0u - __builtin_amdgcn_ubfe(f1, sh, 1)) & w1);
+          } else if (!p.pool) {
+            a[c] = (0u - __builtin_amdgcn_ubfe(f0, sh, 1)) & w0;
+          } else {
+            const uint32_t top = __builtin_amdgcn_ubfe(f0, sh, 2), bottom = __builtin_amdgcn_ubfe(f1, sh, 2);
+            a[c] = p.pool == 1 ? __umul24(__popc(top | bottom << 2), w0) : (top | bottom) ? w0 : 0u;
+          }
+        }
+        if (d_dst[i] == kNone) continue;
+        uint8_t* const dst = lds + (d_dst[i] & 0xffffffu);
+        if constexpr (F32) {
+          *reinterpret_cast<f32x4v*>(dst) = f32x4v{(float)a[0] * scale, (float)a[1] * scale, (float)a[2] * scale, (float)a[3] * scale};
+          *reinterpret_cast<f32x4v*>(dst + q.plane) = f32x4v{(float)a[4] * scale, (float)a[5] * scale, (float)a[6] * scale, (float)a[7] * scale};
+        } else {
+          u32x4 v;
+#pragma unroll
+          for (int c2 = 0; c2 < 4; ++c2) v[c2] = pack_bf16((float)a[2 * c2] * scale, (float)a[2 * c2 + 1] * scale);
+          *reinterpret_cast<u32x4*>(dst) = v;
+        }
+      }
+    }
+  };
+
   size_t step = 0;
   for (int g = 0; g < n_groups; ++g) {
     const bool last = g == p.G;                // the shorter last group
     const int Kg = frames_of(g), n_lif = last ? mp.n_lif_last : p.n_lif;
     const float decay = last ? mp.decay_last : p.decay;
     __syncthreads();                           // the previous group's fragment reads are done (first group: the tables are made)
-    if (g == 0 || last) {
+    if ((g == 0 || last) && !DIRECT) {
       make_lut(last ? p.K - mp.K_last : 0);    // a shorter last group's weights are the last of a whole group's
       __syncthreads();
     }
     // ---- 1. aggregate
-    for (int job = wave; job < q.n_jobs && wave < q.loaders; job += q.loaders) {
+    if constexpr (DIRECT) {
+      build_direct(Kg);
+      load_direct(min(g + 1, n_groups - 1));     // behind the last group it is asked for again
+    }
+    for (int job = wave; !DIRECT && job < q.n_jobs && wave < q.loaders; job += q.loaders) {
       for (int batch = 0; batch < q.batches; ++batch) {
         store_batch(Kg, job, batch);
         const bool more = batch + 1 < q.batches, next_job = job + q.loaders < q.n_jobs;
@@ -674,7 +764,10 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
 
 template <int KP, int NMC, int NNP, bool TRACE, bool F32>
 hipError_t mid_launch_t(const MidParams& p, hipStream_t s) {
-  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32>;
+  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, false>;
+  if constexpr (KP <= 2) {
+    if (p.q.direct) kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, true>;
+  }
   if (p.q.total > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;

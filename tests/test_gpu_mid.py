@@ -37,9 +37,32 @@ CASES = [
     (1, 32, 40, 7, 9, 2, True, False, F32, STEP, 1, 3),
 ]
 
+# The tile is chosen by its estimated time, and layers as small as those above take the smallest one.  These take the other
+# variants: the launch's plan has the values named here, without the membrane trace and with it (where only the first is
+# named the second differs).  test_mid_plan.py holds the choice to them on the CPU.
+VARIANTS = {
+    "two channel blocks": ((1, 80, 40, 3, 37, 2, True, False, B16, TAC, 2, 4), dict(nmc=2, nnp=1, direct=0)),
+    "two by two blocks, one with the trace": ((16, 8, 200, 19, 19, 1, "max", False, B16, TAC, 4, 6), dict(nmc=2, nnp=2, direct=0), dict(nmc=2, nnp=1)),
+    "two by two blocks": ((40, 8, 200, 30, 33, 1, False, False, B16, TP, 4, 5), dict(nmc=2, nnp=2, direct=0)),
+    "two by two blocks, direct": ((40, 8, 200, 11, 34, 1, False, False, B16, STEP, 1, 3), dict(nmc=2, nnp=2, direct=1)),
+    "eight jobs": ((1, 96, 40, 7, 3, 1, "max", False, B16, TAC, 2, 3), dict(jobs=8, batches=1)),
+    "two batches": ((1, 112, 96, 7, 2, 1, True, False, B16, TAC, 2, 5), dict(jobs=4, batches=2)),
+    "eight jobs of two batches": ((1, 120, 96, 20, 2, 2, "max", False, B16, STEP, 1, 2), dict(jobs=8, batches=2)),
+    "two loaders, fp32": ((1, 112, 70, 10, 2, 2, "max", False, F32, TAC, 8, 17), dict(loaders=2)),
+    "two loaders of two batches": ((1, 48, 70, 3, 119, 2, True, True, B16, TAC, 32, 33), dict(loaders=2, batches=2)),
+    "two channel blocks, direct": ((16, 8, 200, 19, 33, 1, False, False, B16, STEP, 1, 3), dict(nmc=2, nnp=1, direct=1)),
+    "direct, tiles that straddle samples": ((24, 8, 200, 3, 20, 1, False, False, B16, STEP, 1, 3), dict(direct=1, flatten=1, rpb=1)),
+    "direct, blocks that straddle samples": ((32, 8, 130, 3, 9, 1, False, False, B16, STEP, 1, 3), dict(direct=1, flatten=1, rpb=2)),
+    "direct, two rows a block, a last group of one": ((3, 16, 70, 9, 14, 1, False, False, B16, TP, 2, 5), dict(direct=1, rpb=2)),
+    "direct, fp32, stride 2": ((2, 24, 33, 6, 30, 2, False, False, F32, TAC, 2, 7), dict(direct=1)),
+    "direct, max pool, pooled output": ((2, 8, 33, 12, 20, 1, "max", True, B16, STEP, 1, 3), dict(direct=1, nnp=2)),
+    "direct, two pixels a thread": ((3, 24, 20, 17, 30, 1, False, False, B16, TAC, 2, 3), dict(direct=1, flatten=0)),
+    "direct, mean pool, fp32": ((3, 16, 24, 18, 40, 1, True, False, F32, STEP, 1, 2), dict(direct=1)),
+    "direct, eight rows a block, fp32, stride 2": ((3, 32, 48, 7, 7, 2, "max", False, F32, STEP, 1, 2), dict(direct=1, rpb=8)),
+}
 
-@pytest.mark.parametrize("case", CASES, ids=["%dx%d_to_%d_%dx%d_K%d" % (c[0], c[1], c[2], c[3], c[4], c[10]) for c in CASES])
-def test_edges_of_the_tiles(case):
+
+def _check(case):
     B, Cin, Cout, H, W, stride, pool, out_pool, precision, mode, K, T = case
     r = np.random.Generator(np.random.PCG64(6000 + Cin + Cout + H + W + K))
     f = 2 if pool else 1
@@ -48,7 +71,18 @@ def test_edges_of_the_tiles(case):
     bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
     Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
     v0 = (r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32)
+    samples = dict(oracle_samples=[0, 1, B // 2, B - 1]) if B > 8 else {}
     par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, pool2=pool, precision=precision, bias=bias,
-                              v0=v0, expect_kernel=api.TAC_KERNEL_MFMA, **(dict(out_pool=True) if out_pool else {}))
+                              v0=v0, expect_kernel=api.TAC_KERNEL_MFMA, **(dict(out_pool=True) if out_pool else {}), **samples)
     assert ref[0].any()
     print(case, par)
+
+
+@pytest.mark.parametrize("case", CASES, ids=["%dx%d_to_%d_%dx%d_K%d" % (c[0], c[1], c[2], c[3], c[4], c[10]) for c in CASES])
+def test_edges_of_the_tiles(case):
+    _check(case)
+
+
+@pytest.mark.parametrize("name", VARIANTS)
+def test_variants_of_the_tile(name):
+    _check(VARIANTS[name][0])

@@ -1,0 +1,63 @@
+"""Which tile the in-between matrix-core kernel takes for a layer: the cases of test_gpu_mid.py that are there for a variant
+of the kernel take it, and no layer it accepts is left without a tile.  The choice is host code: it is compiled into a
+small library of its own (mid_plan_shim.cpp)."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2603_13810_amd import api, build
+from test_gpu_mid import VARIANTS
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+FIELDS = ("kp", "nmc", "nnp", "direct", "jobs", "loaders", "batches", "flatten", "rpb", "workgroups", "lds")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("plan") / "mid_plan.so")
+    subprocess.check_call([build.hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++20", "-fPIC", "-shared", "-x", "hip", "-I", build.INCLUDE,
+                           "-I", build.CSRC, os.path.join(HERE, "mid_plan_shim.cpp"), "-o", lib])
+    shim = ctypes.CDLL(lib)
+
+    def of(B, Cin, Cout, H, W, stride, pool, out_pool, precision, mode, K, T, trace=False):
+        desc = api.make_desc(T, B, Cin, H, W, Cout, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, precision=precision,
+                             in_format={False: api.TAC_IN_BITS, True: api.TAC_IN_BITS_POOL2, "max": api.TAC_IN_BITS_MAXPOOL2}[pool],
+                             out_format=api.TAC_OUT_BITS_MAXPOOL2 if out_pool else api.TAC_OUT_BITS)
+        out = (ctypes.c_int * len(FIELDS))()
+        rc = shim.mid_plan_of(ctypes.byref(desc), int(trace), out)
+        return dict(zip(FIELDS, out)) if rc == 1 else rc
+    return of
+
+
+@pytest.mark.parametrize("name", VARIANTS)
+def test_case_takes_the_variant_it_is_there_for(plan, name):
+    case, plain = VARIANTS[name][:2]
+    with_trace = VARIANTS[name][2] if len(VARIANTS[name]) > 2 else plain
+    for want, got in ((plain, plan(*case)), (with_trace, plan(*case, trace=True))):
+        assert {k: got[k] for k in want} == want
+    if "two pixels a thread" in name:
+        assert case[1] // 8 * 4 * case[4] > 256                # at least four rows of aggregates
+
+
+def test_single_frames_of_few_channels_share_the_compute_units(plan):
+    # one workgroup of two pixel blocks per compute unit, 251 of them, takes 52 us a call; twice as many smaller ones without
+    # staging 33 us
+    got = plan(17, 8, 32, 59, 39, 1, False, False, api.TAC_BF16, api.TAC_PER_STEP, 1, 18)
+    assert got["direct"] == 1 and got["nnp"] == 1 and got["workgroups"] >= 2 * 251
+
+
+def test_every_layer_it_accepts_has_a_tile(plan):
+    r = random.Random(3)
+    seen = 0
+    for _ in range(4000):
+        stride, K = r.choice([1, 2]), r.choice([1, 2, 3, 4, 7, 8, 15, 16, 24, 32])
+        got = plan(r.choice([1, 3, 20]), 8 * r.randint(1, 16), r.choice([5, 32, 64, 130]), r.choice([1, 2, 9, 30]), r.randint(1, 128), stride,
+                   r.choice([False, True, "max"]), False, r.choice([api.TAC_FP32, api.TAC_BF16]), api.TAC_COLLAPSE, K, K, r.random() < 0.5)
+        assert got != -1
+        if got:
+            seen += 1
+            assert got["lds"] <= 160 * 1024 and got["loaders"] in (1, 2, 4)
+    assert seen > 1500
