@@ -360,7 +360,9 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     }
   };
 
-  // ---- the lane's pixels
+  // ---- the lane's pixels.  Their membranes are 32-bit byte offsets from the wave's; without a second sample in the tile they are
+  // counted from the tile's first row, which keeps planes of up to 2^28 neurons in reach.
+  const int v_row = q.flatten ? 0 : oy0;
   LaneGeom lg;
   uint32_t pix_base[NNP];
   const int word_w = q.wb == 1 ? 0 : wave & 1;
@@ -375,11 +377,11 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     const int bsel = sample_of(rr), oy = oy0 + rr - bsel * p.Ho;
     lg.ok[np] = ok;
     lg.theta[np] = ok ? p.theta : __builtin_inff();
-    lg.v_off[np] = (uint32_t)((((size_t)bsel * p.Cout + 4 * h) * plane + (size_t)oy * p.Wo + (ok ? ox : 0)) * 4);
+    lg.v_off[np] = (uint32_t)((((size_t)bsel * p.Cout + 4 * h) * plane + (size_t)(oy - v_row) * p.Wo + (ok ? ox : 0)) * 4);
     pix_base[np] = (uint32_t)(((rr * S + bsel * (3 - S)) * q.wpx + (ok ? ox : 0)) * 16);
   }
   lg.co_lim = p.Cout - co0 - 4 * h;
-  const size_t v_wave = ((size_t)b0 * p.Cout + co0) * plane;
+  const size_t v_wave = ((size_t)b0 * p.Cout + co0) * plane + (size_t)v_row * p.Wo;
   const bool wave_active = rg_w < q.trg && rg_w * q.rpb < rows_valid;  // wave-uniform
 
   float V[NMC][NNP][16];

@@ -86,3 +86,27 @@ def test_edges_of_the_tiles(case):
 @pytest.mark.parametrize("name", VARIANTS)
 def test_variants_of_the_tile(name):
     _check(VARIANTS[name][0])
+
+
+def test_last_rows_of_a_very_tall_image():
+    # 217 million neurons a channel: byte offsets of the fifth channel's last rows do not fit 32 bits.  What the layer leaves in its
+    # first and last rows is what it leaves for an image of those rows alone.
+    H, W, C, part = 3_400_000, 64, 8, 80
+    dev = "cuda:0"
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(11)
+    frames = torch.randint(-2 ** 31, 2 ** 31 - 1, (1, 1, C, H, W // 32), dtype=torch.int32, device=dev, generator=gen)
+    frames &= torch.randint(-2 ** 31, 2 ** 31 - 1, frames.shape, dtype=torch.int32, device=dev, generator=gen)
+    w = torch.from_numpy(synth.kaiming_normal(67, C, C)).to(dev)
+
+    def run(x):
+        desc = api.make_desc(1, 1, C, x.shape[3], W, C, K=1, beta=0.9, theta=0.5, mode=STEP, precision=B16)
+        assert api.tac_select_kernel(desc) == api.TAC_KERNEL_MFMA
+        v = torch.zeros((1, C, x.shape[3], W), dtype=torch.float32, device=dev)
+        return api.tac_conv_lif(desc, x, api.tac_prepare_weights(desc, w), None, v), v
+    spikes, v = run(frames)
+    for rows, inner in ((slice(0, part), slice(0, part - 1)), (slice(H - part, H), slice(1, part))):
+        spikes_part, v_part = run(frames[:, :, :, rows].contiguous())
+        assert spikes_part.any()
+        assert torch.equal(spikes[:, :, :, rows][:, :, :, inner], spikes_part[:, :, :, inner])
+        assert torch.equal(v[:, :, rows][:, :, inner], v_part[:, :, inner])
