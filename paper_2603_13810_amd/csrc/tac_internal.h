@@ -104,10 +104,6 @@ struct BackwardParams {
   float go_w[TAC_MAX_K], go_w_last[TAC_MAX_K];   // the next layer's beta^(Kg-1-j)
 };
 hipError_t backward_launch(const BackwardParams& p, hipStream_t s);
-// Whether the LIF recurrence clears dW on the side: up to four floats a thread.  Deep small layers have few neurons and a large
-// dW, and the chip would wait for a handful of workgroups (backward calls in us, in the recurrence / by a launch of its own:
-// @CLEAR@).
-inline bool backward_clear_in_recurrence(size_t threads, size_t floats) { return floats <= 4 * threads; }
 hipError_t backward_wgrad_f32_launch(const BackwardParams& p, hipStream_t s);    // any layer, fp32 operands; adds to grad_w, grad_bias
 bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
