@@ -110,8 +110,8 @@ __device__ __forceinline__ Lanes<VEC> grad_out_lanes(const BackwardParams& p, si
   }
 }
 
-// The sums dW and dbias start from: cleared by the LIF recurrence, which comes first, or by clear_kernel where dW has
-// held something else in between.
+// The sums dW and dbias start from: cleared by the LIF recurrence, which comes first, or by clear_kernel where that has too few
+// threads for it (backward_launch) or dW has held something else in between.
 __device__ __forceinline__ void clear_sums(const BackwardParams& p, size_t first, size_t threads) {
   const size_t n_w = (size_t)p.Cout * p.Cin * 9;
   for (size_t i = first; i < n_w; i += threads) p.grad_w[i] = 0.0f;
@@ -353,30 +353,29 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
   const size_t n_out = (size_t)p.B * p.Cout * p.Ho * p.Wo;
   // the wide-tile input gradient uses grad_w as scratch for its prepared weights: it runs before grad_w is cleared
   const bool dgrad_tile = p.grad_in && backward_dgrad_tile_supported(p);
-  const int clear = dgrad_tile ? 0 : 1;
   const uintptr_t bases = (uintptr_t)p.v_trace | (uintptr_t)p.grad_out | (uintptr_t)p.grad_y;
   auto blocks = [](size_t threads) { return dim3((unsigned)((threads + kThreads - 1) / kThreads)); };
-  if (p.out_pool && p.Wo % 4 == 0 && (bases & 15) == 0 && n_out >= ((size_t)1 << 20)) {
-    // two windows per thread: 16-byte membrane accesses, enough threads to fill the chip from 2^20 neurons on
-    hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 2>), blocks(n_out / 8), dim3(kThreads), 0, s, p, clear);
-  } else if (p.out_pool && (bases & 7) == 0) {
-    // small layers wait for memory, step after step: one window per thread, four steps asked for together
-    hipLaunchKernelGGL((lif_backward_pooled_kernel<2, 4>), blocks(n_out / 4), dim3(kThreads), 0, s, p, clear);
-  } else if (!p.out_pool && n_out % 4 == 0 && (bases & 15) == 0) {
-    // four neurons per thread where rows allow 16-byte accesses; with 16 bytes per lane one step in flight per thread
-    // keeps the memory busy, the scalar form asks for four steps at once
-    hipLaunchKernelGGL((lif_backward_kernel<4, 1>), blocks(n_out / 4), dim3(kThreads), 0, s, p, clear);
-  } else {
-    hipLaunchKernelGGL((lif_backward_kernel<1, 4>), blocks(n_out), dim3(kThreads), 0, s, p, clear);
-  }
+  // Two windows per thread: 16-byte membrane accesses, enough threads to fill the chip from 2^20 neurons on.  Small layers wait
+  // for memory, step after step: one window per thread, four steps asked for together.  Without a pool four neurons per thread
+  // where rows allow 16-byte accesses; with 16 bytes per lane one step in flight per thread keeps the memory busy, the scalar
+  // form asks for four steps at once.
+  const bool windows2 = p.out_pool && p.Wo % 4 == 0 && (bases & 15) == 0 && n_out >= ((size_t)1 << 20);
+  const bool windows1 = p.out_pool && !windows2 && (bases & 7) == 0;
+  const bool neurons4 = !p.out_pool && n_out % 4 == 0 && (bases & 15) == 0;
+  const size_t threads = windows2 ? n_out / 8 : windows1 || neurons4 ? n_out / 4 : n_out;
+  const int clear = !dgrad_tile && backward_clear_in_recurrence(threads, (size_t)p.Cout * p.Cin * 9);
+  if (windows2) hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 2>), blocks(threads), dim3(kThreads), 0, s, p, clear);
+  else if (windows1) hipLaunchKernelGGL((lif_backward_pooled_kernel<2, 4>), blocks(threads), dim3(kThreads), 0, s, p, clear);
+  else if (neurons4) hipLaunchKernelGGL((lif_backward_kernel<4, 1>), blocks(threads), dim3(kThreads), 0, s, p, clear);
+  else hipLaunchKernelGGL((lif_backward_kernel<1, 4>), blocks(threads), dim3(kThreads), 0, s, p, clear);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
   if (dgrad_tile) {
     e = backward_dgrad_tile_launch(p, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(clear_kernel, blocks((size_t)p.Cout * p.Cin * 9), dim3(kThreads), 0, s, p);
   }
+  if (!clear) hipLaunchKernelGGL(clear_kernel, blocks((size_t)p.Cout * p.Cin * 9), dim3(kThreads), 0, s, p);
   if (p.bf16 && !p.dense && p.pool2 != 1 && backward_wgrad_mfma_supported(p)) {
     e = backward_wgrad_mfma_launch(p, s);
     if (e != hipSuccess) return e;

@@ -104,6 +104,11 @@ struct BackwardParams {
   float go_w[TAC_MAX_K], go_w_last[TAC_MAX_K];   // the next layer's beta^(Kg-1-j)
 };
 hipError_t backward_launch(const BackwardParams& p, hipStream_t s);
+// Whether the LIF recurrence clears dW on the side: up to 256 floats a thread.  Deep small layers have few neurons and a large dW,
+// and the chip would wait for a handful of workgroups; below that the launch saved counts for more.  Backward calls without
+// input gradient, in the recurrence / by a launch of its own: 512 -> 512 at 2 x 2, B = 1 (4608 floats a thread) 143 / 29 us; at
+// 4 x 4, B = 4 (288) 47 / 43 us; 128 -> 128 at 4 x 4, B = 16 (18) 21.5 / 23.9 us.
+inline bool backward_clear_in_recurrence(size_t threads, size_t floats) { return floats <= 256 * threads; }
 hipError_t backward_wgrad_f32_launch(const BackwardParams& p, hipStream_t s);    // any layer, fp32 operands; adds to grad_w, grad_bias
 bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);

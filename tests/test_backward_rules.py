@@ -1,0 +1,26 @@
+"""Which kernels a backward call launches: host rules, compiled into a small library of their own (backward_rules_shim.cpp)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2603_13810_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("rules") / "backward_rules.so")
+    subprocess.check_call([build.hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++20", "-fPIC", "-shared", "-x", "hip", "-I", build.INCLUDE,
+                           "-I", build.CSRC, os.path.join(HERE, "backward_rules_shim.cpp"), "-o", lib])
+    return ctypes.CDLL(lib)
+
+
+@pytest.mark.parametrize("neurons,channels,aside", [(512 * 4, 512, False), (1024 * 16, 1024, False), (128 * 2 * 4, 128, False),
+                                                    (128 * 16 * 16, 128, True), (64 * 8 * 64, 64, True)])
+def test_a_large_weight_gradient_is_not_cleared_by_a_handful_of_threads(rules, neurons, channels, aside):
+    # four neurons a thread in the recurrence; dW of channels x channels x 9 floats
+    threads, floats = ctypes.c_longlong(neurons // 4), ctypes.c_longlong(9 * channels * channels)
+    assert bool(rules.clear_in_recurrence(threads, floats)) == aside

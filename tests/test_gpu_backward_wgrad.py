@@ -23,6 +23,7 @@ CASES = [
     (2, 37, 130, 5, 5, 1, BITS, 8, 11),       # column groups that start inside a channel, a channel block of two
     (1, 72, 96, 3, 2, 1, BITS, 16, 17),
     (2, 32, 64, 14, 14, 1, MEAN, 4, 7),
+    (1, 512, 512, 2, 2, 1, BITS, 2, 4),       # few neurons: dW is cleared by a launch of its own
 ]
 
 
@@ -40,6 +41,8 @@ def test_weight_and_bias_gradient(case):
     v = (0.6 * r.standard_normal((T_out, B, Cout, Ho, Wo)) + 0.3).astype(np.float32)
     g = r.standard_normal(v.shape).astype(np.float32)
     w = (r.standard_normal((Cout, Cin, 3, 3)) * 0.1).astype(np.float32)
+    stale = torch.full((Cout, Cin, 3, 3), float("nan"), device=DEV)       # what the allocator hands out next
+    del stale
     got = api.tac_conv_lif_backward(desc, xd, torch.from_numpy(w).to(DEV), torch.from_numpy(v).to(DEV), torch.from_numpy(g).to(DEV),
                                     want_input_grad=False)
     torch.cuda.synchronize()
