@@ -114,8 +114,9 @@ __global__ __launch_bounds__(kThreads, WI > 1 && NP == 4 ? 1 : 2) void dgrad_f32
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       const int e = tid + i * kThreads;
-      // channels beyond Cout meet dY = 0 (their weights are the last channel's); input channels beyond Cin are not stored
-      if (e < kCo * kRow / 4) *reinterpret_cast<f32x4*>(wl + 4 * e) = wr[i];
+      // channels beyond Cout are zeros against zeros (the last channel's weights, read in their place, may be infinite); input
+      // channels beyond Cin are not stored
+      if (e < kCo * kRow / 4) *reinterpret_cast<f32x4*>(wl + 4 * e) = co + e / (kRow / 4) < p.Cout ? wr[i] : f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int m = 0; m < kM; ++m)

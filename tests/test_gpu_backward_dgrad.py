@@ -66,3 +66,17 @@ def test_input_gradient(case):
     # sums of n = 9 Cout fp32 terms in any order and two factors: 2^-24 (sqrt(n) + 3) of the sum of the magnitudes, times four
     tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
     assert (np.abs(got["grad_in"].cpu().numpy() - dA) <= tol * size + 1e-12).all()
+
+
+def test_an_infinite_weight_of_the_last_channel_is_multiplied_once():
+    # five output channels in rounds of eight: the three that fill the round must not multiply the last channel's weights by zero
+    B, Cin, Cout, H, W = 1, 6, 5, 6, 6
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    w = torch.full((Cout, Cin, 3, 3), 0.1, device=DEV)
+    w[4, 2, 1, 1] = float("inf")
+    v = torch.zeros((1, B, Cout, H, W), device=DEV)
+    x = torch.zeros((1, B, Cin, H, 1), dtype=torch.int32, device=DEV)
+    got = api.tac_conv_lif_backward(desc, x, w, v, torch.ones_like(v))["grad_in"][0, 0]
+    assert (got[2] == float("inf")).all()             # the centre tap meets every pixel's own dL/dY, which is positive
+    others = [0, 1, 3, 4, 5]
+    assert torch.isfinite(got[others]).all() and (got[others] > 0).all()
