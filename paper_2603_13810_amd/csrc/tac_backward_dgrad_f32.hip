@@ -217,8 +217,6 @@ bool dgrad_f32_tile(const BackwardParams& p, int wi, int np, DgradPlan& q) {
 
 }  // namespace
 
-bool backward_dgrad_f32_supported(const BackwardParams& p) { return p.stride == 1; }
-
 hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
   const int wi = p.Cin > 64 ? 4 : p.Cin > 32 ? 2 : 1;
   DgradPlan q{};

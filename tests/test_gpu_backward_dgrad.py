@@ -22,6 +22,9 @@ CASES = [
     (3, 32, 64, 14, 14, MEAN, False, 4, 7),     # the rate-coded network's second layer
     (2, 20, 16, 5, 40, MAX, False, 2, 3),
     (2, 64, 8, 33, 20, BITS, False, 1, 2),      # strips with a remainder
+    (9, 1, 6, 50, 60, BITS, True, 2, 6),        # few input channels over many pixels: the vector kernel, stride 1
+    (40, 3, 5, 30, 40, MAX, False, 2, 5),
+    (30, 7, 3, 66, 80, MEAN, False, 1, 2),
 ]
 
 
