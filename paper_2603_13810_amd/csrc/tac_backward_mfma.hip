@@ -15,6 +15,7 @@
 // 144 accumulator registers) per 16 pixels.  Sums over the slices are combined with float atomics
 // into the cleared dW.
 #include <algorithm>
+#include <cmath>
 #include "tac_mfma_common.h"
 
 namespace tac {
@@ -536,22 +537,30 @@ hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s) {
   const int R = 256 / p.W;                               // output rows per strip (16 MFMA steps); two workgroups per compute unit fit the LDS
   const int n_strips = (p.Ho + R - 1) / R;
   const long long items = (long long)p.G * p.B * n_strips;
-  // two blocks of input channels per workgroup (eight waves) where the channel count and the LDS allow it and there is
-  // work for them: every slice of the items adds a whole dW with atomics (some 200 a nanosecond over the chip, 0.7 us for
-  // 128 x 128 x 9), and workgroups of one block fill the chip with half the slices (128 -> 128, B = 16, 4 groups at
-  // 32 x 32, 256 items: 96 -> 69 us; at 16 x 16, 64 items: 49 -> 37 us)
-  const bool few = items < 512;
-  const int ncb = (p.Cin % 64 == 0 && p.W <= 64 && !few) ? 2 : 1;
+  // Two blocks of input channels per workgroup (eight waves, which share the dY they read) where the channel count and the LDS
+  // allow it and there is work for them: 64 -> 128 at 64 x 64 with the best number of slices of either, 1024 items 175 us two
+  // blocks, 160 one; 2048 items 300 and 299; 4096 items 536 and 561.
+  const int ncb = (p.Cin % 64 == 0 && p.W <= 64 && items >= 2048) ? 2 : 1;
   // aggregates, then the staging area of the frame words: [pass][4 frames][thread]
   const int n_threads = kThreads * ncb, wwi = p.W >= 32 ? p.W / 32 : 1;
   const int passes = (32 * ncb * (R + 2) * wwi + n_threads - 1) / n_threads;
   size_t lds = (size_t)ncb * 3 * (R + 2) * (p.W / 8) * 512 + (size_t)passes * 4 * n_threads * 4;
   lds = std::max(lds, (size_t)4 * ncb * 8 * 288 * sizeof(float));        // the sums on their way to dW
   const int ci_blocks = p.Cin / (32 * ncb), co_blocks = p.Cout / 128;
-  const int resident = ncb == 2 || few ? 256 : 512;      // eight waves per compute unit (four with few items)
+  const int resident = ncb == 2 ? 256 : 512;             // eight waves per compute unit either way
   long long split = (resident + ci_blocks * co_blocks - 1) / (ci_blocks * co_blocks);
   split = (split + 7) / 8 * 8;                           // a multiple of the XCD count
-  if (few) split = std::min(split, items / 2);
+  if (items < 2048) {
+    // Every slice adds a whole dW with atomics, some 200 a nanosecond over the chip, and an item takes about 7 us: n items a slice
+    // are the fastest where n * 7 us and the additions of items / n slices are equal.  Backward calls without input gradient by
+    // 256 / (blocks of channels) slices and by these: 32 -> 128 at 16 x 16, 450 items 87 / 76 us, at 32 x 32, 512 items 137 / 83 us;
+    // 128 -> 128 at 16 x 16, 64 items 39 / 39 us; 256 -> 256, 450 items 284 / 237 us; 96 -> 384, 64 items 71 / 60 us.
+    const double sum_us = 9.0 * p.Cin * p.Cout / 200e3;
+    const long long n = std::max(1ll, (long long)std::sqrt((double)items * sum_us / 7.0));
+    auto us = [&](long long k) { return (double)k * 7.0 + (double)((items + k - 1) / k) * sum_us; };
+    const long long slices = us(n) <= us(n + 1) ? (items + n - 1) / n : (items + n) / (n + 1);
+    split = std::min(split, (slices + 7) / 8 * 8);
+  }
   if (split > items) split = items;
   if (split < 1) split = 1;
   auto launch = [&](auto kern) -> hipError_t {
