@@ -10,17 +10,19 @@ __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) {
 }
 
 // A thread per packed word.  ALIGNED: rows are multiples of 16 bytes from a 16-byte aligned address, a word is one or two
-// 16-byte loads; otherwise the row may start anywhere in a dword and its up to nine dwords are shifted into place.
-// (n_bytes: of the tensor; a dword that reaches beyond it is read byte by byte.)
-// One wave per 64 pixels with a ballot reads 64 bytes a load instruction: 16.8 MB of 128-pixel rows 24.5 us, now 5.4 us.
+// 16-byte loads; otherwise the tensor and its rows may start anywhere in a dword and the word's up to nine dwords are shifted
+// into place.  (`dense` is then the dword that holds the tensor's first byte, `skip` that byte's place in it; n_bytes: from there to
+// the tensor's end; a dword that reaches beyond the tensor is read byte by byte.)
+// One wave per 64 pixels with a ballot reads 64 bytes a load instruction: 16.8 MB of 128-pixel rows 24.5 us, now 5.4 us; from an
+// address that is one byte off a call takes 9.8 us (21.7 with the ballot, 29.4 byte by byte).
 template <bool ALIGNED>
 __global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ dense, uint32_t* __restrict__ packed, int64_t words,
-                                                   int64_t n_bytes, int W, int Ww) {
+                                                   int64_t n_bytes, int W, int Ww, int skip) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) {
     const int64_t row = i / Ww;
     const int word = (int)(i - row * Ww);
-    const int64_t first = row * W + 32 * word;
+    const int64_t first = row * W + 32 * word + (ALIGNED ? 0 : skip);
     const int n = min(32, W - 32 * word);
     uint32_t bits = 0;
     if constexpr (ALIGNED) {
@@ -38,10 +40,11 @@ __global__ __launch_bounds__(256) void pack_kernel(const uint8_t* __restrict__ d
         if (4 * d >= lead + n) break;
         const int64_t at = base + 4 * d;
         uint32_t v = 0;
-        if (at + 4 <= n_bytes) {
+        if (at >= skip && at + 4 <= n_bytes) {
           v = *reinterpret_cast<const uint32_t*>(dense + at);
         } else {
-          for (int k = 0; k < 4 && at + k < n_bytes; ++k) v |= (uint32_t)dense[at + k] << (8 * k);
+          for (int k = 0; k < 4; ++k)
+            if (at + k >= skip && at + k < n_bytes) v |= (uint32_t)dense[at + k] << (8 * k);
         }
         all |= (uint64_t)nonzero_bytes(v) << (4 * d);
       }
@@ -71,30 +74,15 @@ static int grid_for(int64_t work_per_block_units) {
   return (int)g;
 }
 
-// Addresses that are not a multiple of four bytes: one byte at a time.
-__global__ __launch_bounds__(256) void pack_bytes_kernel(const uint8_t* __restrict__ dense, uint32_t* __restrict__ packed, int64_t words,
-                                                         int W, int Ww) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < words; i += stride) {
-    const int64_t row = i / Ww;
-    const int word = (int)(i - row * Ww);
-    const uint8_t* const src = dense + row * W + 32 * word;
-    uint32_t bits = 0;
-    for (int x = 0; x < min(32, W - 32 * word); ++x) bits |= src[x] ? 1u << x : 0u;
-    packed[i] = bits;
-  }
-}
-
 hipError_t pack_launch(const uint8_t* dense, uint32_t* packed, int64_t rows, int W, hipStream_t s) {
   const int Ww = (W + 31) / 32;
   const int64_t words = rows * Ww;
   const dim3 grid(grid_for((words + 255) / 256));
+  const int skip = (int)((uintptr_t)dense & 3u);
   if (W % 16 == 0 && ((uintptr_t)dense & 15u) == 0)
-    hipLaunchKernelGGL(pack_kernel<true>, grid, dim3(256), 0, s, dense, packed, words, rows * W, W, Ww);
-  else if (((uintptr_t)dense & 3u) == 0)
-    hipLaunchKernelGGL(pack_kernel<false>, grid, dim3(256), 0, s, dense, packed, words, rows * W, W, Ww);
+    hipLaunchKernelGGL(pack_kernel<true>, grid, dim3(256), 0, s, dense, packed, words, rows * W, W, Ww, 0);
   else
-    hipLaunchKernelGGL(pack_bytes_kernel, grid, dim3(256), 0, s, dense, packed, words, W, Ww);
+    hipLaunchKernelGGL(pack_kernel<false>, grid, dim3(256), 0, s, dense - skip, packed, words, rows * W + skip, W, Ww, skip);
   return hipGetLastError();
 }
 
