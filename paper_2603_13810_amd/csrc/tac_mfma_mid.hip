@@ -287,7 +287,8 @@ hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
     mp.wjd[j] = p.wjd[j];
   }
   a.K_last = p.K_last; a.n_lif_last = p.n_lif_last; a.decay_last = p.decay_last;
-  // The choice looks at some hundred tiles (about 15 us); the geometry a thread has asked for lately is remembered.
+  // The choice looks at some hundred tiles (up to 18 us); the geometries a thread has asked for lately are remembered, in sets of
+  // four so that the layers of a network do not turn each other out (two of them in one place: 18 us each, every pass).
   struct Key {
     int v[14];
     bool operator==(const Key& o) const { return std::memcmp(v, o.v, sizeof(v)) == 0; }
@@ -298,20 +299,28 @@ hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
     int kp, nmc, nnp;
     bool used;
   };
-  static thread_local Entry known[64];
+  struct Set {
+    Entry entry[4];
+    unsigned oldest;
+  };
+  static thread_local Set known[16];
   const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.n_lif, p.pool2, p.out_pool, p.bf16, p.Wwi, p.v_trace != nullptr}};
   uint32_t hash = 2166136261u;
   for (int v : key.v) hash = (hash ^ (uint32_t)v) * 16777619u;
-  Entry& e = known[(hash >> 16) & 63];
-  if (!e.used || !(e.key == key)) {
-    e.used = false;
-    if (!mid_choose(p, a, e.kp, e.nmc, e.nnp)) return hipErrorInvalidValue;
-    e.key = key;
-    e.q = a.q;
-    e.used = true;
+  Set& set = known[(hash >> 16) & 15];
+  Entry* e = nullptr;
+  for (Entry& x : set.entry)
+    if (x.used && x.key == key) e = &x;
+  if (!e) {
+    e = &set.entry[set.oldest++ & 3];
+    e->used = false;
+    if (!mid_choose(p, a, e->kp, e->nmc, e->nnp)) return hipErrorInvalidValue;
+    e->key = key;
+    e->q = a.q;
+    e->used = true;
   }
-  a.q = e.q;
-  const int kp = e.kp, nmc = e.nmc, nnp = e.nnp;
+  a.q = e->q;
+  const int kp = e->kp, nmc = e->nmc, nnp = e->nnp;
   if (!p.bf16) return p.v_trace ? mid_launch_f32_trace(a, kp, nnp, s) : mid_launch_f32(a, kp, nnp, s);
   return p.v_trace ? mid_launch_bf16_trace(a, kp, nmc, nnp, s) : mid_launch_bf16(a, kp, nmc, nnp, s);
 }

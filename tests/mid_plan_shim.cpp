@@ -9,14 +9,12 @@ hipError_t mid_launch_f32(const MidParams&, int, int, hipStream_t) { return hipS
 hipError_t mid_launch_f32_trace(const MidParams&, int, int, hipStream_t) { return hipSuccess; }
 }  // namespace tac
 
-// out: kp, nmc, nnp, direct, jobs, loaders, batches, flatten, rows per block, workgroups, bytes of LDS.  0: the kernel does not
+// out (mid_plan_of): kp, nmc, nnp, direct, jobs, loaders, batches, flatten, rows per block, workgroups, bytes of LDS.  0: the kernel does not
 // take the layer, -1: no tile fits.
-extern "C" int mid_plan_of(const tac_layer_desc_t* d, int with_trace, int* out) {
-  if (!tac::mfma_mid_supported(*d)) return 0;
+static tac::LayerParams params_of(const tac_layer_desc_t* d, float* trace) {
   tac::LayerParams p;
   std::memset(&p, 0, sizeof(p));
-  float trace;
-  p.v_trace = with_trace ? &trace : nullptr;
+  p.v_trace = trace;
   p.B = d->B; p.Cin = d->Cin; p.H = d->H; p.W = d->W; p.Cout = d->Cout; p.stride = d->stride;
   p.Ho = (d->H - 1) / d->stride + 1;
   p.Wo = (d->W - 1) / d->stride + 1;
@@ -29,6 +27,13 @@ extern "C" int mid_plan_of(const tac_layer_desc_t* d, int with_trace, int* out) 
   p.G = d->T / p.K;
   p.n_lif = d->mode == TAC_PRESERVE ? p.K : 1;
   p.bf16 = d->precision == TAC_BF16;
+  return p;
+}
+
+extern "C" int mid_plan_of(const tac_layer_desc_t* d, int with_trace, int* out) {
+  if (!tac::mfma_mid_supported(*d)) return 0;
+  float trace;
+  const tac::LayerParams p = params_of(d, with_trace ? &trace : nullptr);
   tac::MidParams a;
   int kp, nmc, nnp;
   if (!tac::mid_choose(p, a, kp, nmc, nnp)) return -1;
@@ -38,3 +43,6 @@ extern "C" int mid_plan_of(const tac_layer_desc_t* d, int with_trace, int* out) 
   std::copy(std::begin(v), std::end(v), out);
   return 1;
 }
+
+// Everything a launch does on the host, for timing it.
+extern "C" int mid_launch_of(const tac_layer_desc_t* d) { return tac::mfma_mid_launch(params_of(d, nullptr), nullptr); }
