@@ -185,9 +185,9 @@ double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
   const bool f32 = !p.bf16;
   const double build = q.direct ? 500.0 + 400.0 * ((p.Cin / 8 * q.lr * p.W + kMidThreads - 1) / kMidThreads) * (p.K == 2 || p.pool2 ? 2 : 1)
                                 : (q.n_jobs + q.loaders - 1) / q.loaders * mid_job_cycles(q, p);
-  // (an fp32 step waits for its operands: a wave alone takes about 170 cycles for one block)
+  // (an fp32 step waits for its operands: a wave alone takes about 90 cycles for one block)
   const double busy = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
-  const double mfma = f32 ? q.nks * 170.0 * nnp + 300.0 : busy;
+  const double mfma = f32 ? q.nks * 90.0 * nnp + 300.0 : busy;
   const double lif = p.n_lif * (nmc * nnp * (p.v_trace ? 1200.0 : 500.0) + 400.0 + 60.0 * q.rpb);
   const double wgs = (double)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
   const double per_cu = std::ceil(wgs / 256.0);

@@ -681,22 +681,25 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
           part[2][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[3], a[3][np], part[2][np], 0, 0, 0);
         }
       };
+      // eight steps a turn and no way out of its middle (the accumulators would change registers on every turn); behind the last
+      // step the last four are fetched again
       offsets(0);
       fetch(0, wf[0], af[0]);
       offsets(min(4, q.nks - 4));
-      for (int ks = 0; ks < q.nks; ks += 8) {
-        if (ks + 4 < q.nks) {
-          fetch(ks + 4, wf[1], af[1]);
-          offsets(min(ks + 8, q.nks - 4));
-        }
+      int ks = 0;
+      for (; ks + 8 <= q.nks; ks += 8) {
+        fetch(ks + 4, wf[1], af[1]);
+        offsets(min(ks + 8, q.nks - 4));
+        __builtin_amdgcn_sched_barrier(0);               // in front of the MFMAs: else they wait for reads just issued
         multiply(wf[0], af[0]);
-        if (ks + 4 >= q.nks) break;
-        if (ks + 8 < q.nks) {
-          fetch(ks + 8, wf[0], af[0]);
-          offsets(min(ks + 12, q.nks - 4));
-        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(min(ks + 8, q.nks - 4), wf[0], af[0]);
+        offsets(min(ks + 12, q.nks - 4));
+        __builtin_amdgcn_sched_barrier(0);
         multiply(wf[1], af[1]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      if (ks < q.nks) multiply(wf[0], af[0]);
 #pragma unroll
       for (int np = 0; np < NNP; ++np)
 #pragma unroll
