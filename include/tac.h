@@ -58,7 +58,7 @@ enum { TAC_IN_BITS = 0, TAC_IN_BITS_POOL2 = 1, TAC_IN_BITS_MAXPOOL2 = 2, TAC_IN_
  * next layer reads as plain TAC_IN_BITS of size Ho/2 x Wo/2.  Ho and Wo must be even.  The membrane (v_inout,
  * v_trace) keeps the size Ho x Wo.  Supported by the MFMA kernels (tac_select_kernel: the large-shape member
  * takes it with stride 1 only, other shapes go to the in-between member where it takes them);
- * TAC_ERR_UNSUPPORTED otherwise (fp32 layers, the vector kernel).  The backward pass takes the gradient of the pooled
+ * TAC_ERR_UNSUPPORTED otherwise (layers of the vector kernel).  The backward pass takes the gradient of the pooled
  * spikes and routes it to the first maximal spike of each window (see tac_conv_lif_backward). */
 enum { TAC_OUT_BITS = 0, TAC_OUT_BITS_MAXPOOL2 = 1 };
 /* Kernel family.  AUTO picks MFMA when the shape qualifies (see
@@ -139,9 +139,9 @@ int tac_prepare_weights(const tac_layer_desc_t* desc, const float* w_oihw, void*
  * (K = 1).  A_k and Y_k never leave the chip.
  * K need not divide T (App. A assumes it does; Sec. 5 uses T = 25 with K = 4, 8, 16): the
  * K' = T mod K frames left over form a last group treated like every other with K' in the place
- * of K (weights beta^(K'-1-j), decay beta^K', K' LIF steps in TAC-TP).  That group is a second
- * launch and the membrane passes from the first to it through v_inout, which must then be
- * given: TAC_ERR_NEED_STATE otherwise.
+ * of K (weights beta^(K'-1-j), decay beta^K', K' LIF steps in TAC-TP).  In some kernels that group is
+ * a second launch, to which the membrane passes through v_inout, so v_inout must be given whenever K
+ * does not divide T, whichever kernel runs: TAC_ERR_NEED_STATE otherwise.
  *   input              DEVICE, read-only, packed uint32 [T][B][Cin][H][ceil(W/32)]
  *                      (or [T][B][Cin][2H][ceil(2W/32)] with TAC_IN_BITS_[MAX]POOL2, or float32
  *                      [T][B][Cin][H][W] with TAC_IN_F32)

@@ -471,7 +471,7 @@ const char* tac_status_string(int status) {
     case TAC_ERR_NULL: return "a required pointer is NULL";
     case TAC_ERR_BAD_SHAPE: return "bad shape (dimension <= 0, kernel not 3x3, stride not 1/2, pad not 1, or tensor too large)";
     case TAC_ERR_BAD_K: return "bad group size K (K < 1 or K > 32)";
-    case TAC_ERR_NEED_STATE: return "T is not a multiple of K: the shorter last group is a launch of its own and needs v_inout to carry the membrane";
+    case TAC_ERR_NEED_STATE: return "T is not a multiple of K: the shorter last group needs v_inout, whichever kernel runs (in some it is a launch of its own)";
     case TAC_ERR_BAD_PARAM: return "bad parameter (beta outside [0,1], theta <= 0 or not finite, or unknown enum value)";
     case TAC_ERR_UNSUPPORTED: return "the requested kernel family does not support this layer";
     case TAC_ERR_HIP: return "a HIP call failed (see tac_last_error)";

@@ -192,8 +192,8 @@ __global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardPa
 // The same where the layer stored the 2 x 2 max pool of its spikes.  A thread owns the two rows and VEC columns of
 // VEC / 2 windows, so that a membrane is read once (one neuron per thread reads its window's four membranes, five loads
 // for one gradient), the window's route is decided in registers and the pooled gradient is read once.  Bound by HBM on
-// large layers, by the chain of loads over the steps on small ones: 128 channels, B = 16, 16 steps at 64 x 64 / 32 x 32 / 16 x 16 take 161 / 37 / 18 us
-// (one neuron per thread: 540 / 141 / 46 us).
+// large layers, by the chain of loads over the steps on small ones: 128 channels, B = 16, 16 steps at 64 x 64 / 32 x 32 /
+// 16 x 16 take 161 / 37 / 18 us (one neuron per thread: 540 / 141 / 46 us).
 template <int VEC, int U>
 __global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const BackwardParams p, int clear) {
   constexpr int WIN = VEC / 2;

@@ -454,12 +454,12 @@ bool wgrad_f32_tile(const BackwardParams& p, int nt, WgradPlan& q) {
 //   for one, two and three tiles, 8.4 us one of 256 for five.)
 // Backward calls without input gradient in us, and the error of dW against 64-bit sums for dY of both signs: the vector kernel;
 // larger tiles in four waves with one chain per slice; this:
-//   128 -> 128, 8 groups at 64 x 64, B = 64     41200 5.4e-7;  11700 11e-7;  9380 2.3e-7
-//   32 -> 64, 7 groups at 14 x 14, B = 128       1290 1.6e-7;    161 4.1e-7;  170 1.5e-7
+//   128 -> 128, 8 groups at 64 x 64, B = 64     41200 5.4e-7;  11700 11e-7;  9060 2.1e-7
+//   32 -> 64, 7 groups at 14 x 14, B = 128       1290 1.6e-7;    161 4.1e-7;  169 1.4e-7
 //   1 -> 32, 7 groups at 28 x 28, B = 128         192 5.4e-7;    118 3.8e-7;  101 3.0e-7
-//   128 -> 128, 4 groups at 8 x 8, B = 16         375 1.0e-7;     55 1.5e-7;   39 0.9e-7
-//   8 -> 32, 18 groups at 59 x 59, B = 17         460 2.0e-7;    184 4.0e-7;  234 2.0e-7
-//   16 -> 16, 10 groups at 100 x 100, B = 16      512 2.0e-7;    343 4.2e-7;  405 2.2e-7
+//   128 -> 128, 4 groups at 8 x 8, B = 16         375 1.0e-7;     55 1.5e-7;   40 1.0e-7
+//   8 -> 32, 18 groups at 59 x 59, B = 17         460 2.0e-7;    184 4.0e-7;  198 2.5e-7
+//   16 -> 16, 10 groups at 100 x 100, B = 16      512 2.0e-7;    343 4.2e-7;  400 2.4e-7
 hipError_t backward_wgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
   WgradPlan q{};
   int nt = 0;

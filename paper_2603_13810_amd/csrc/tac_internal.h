@@ -93,7 +93,7 @@ struct BackwardParams {
   int n_steps;              // LIF steps = output steps of the forward pass
   int mode, surrogate, detach_reset;
   int bf16;                 // bf16 operands on the matrix cores where the shape allows
-  int dense;                // `spikes` points to float32 frames [T][B][Cin][H][W] (weight gradient by the vector kernel)
+  int dense;                // `spikes` points to float32 frames [T][B][Cin][H][W] (weight gradient in fp32)
   int pool2;                // the stored frames are unpooled [2H][2W] (Wwi = their words per row): 1 mean pool, 2 max pool
   float beta, theta, alpha;
   float decay_full, decay_last;          // beta^K, beta^K_last (TAC)
