@@ -29,11 +29,11 @@
 // registers.
 //
 // Measured against one row per wave, every thread gathering the bits of its own 8 values from global memory and the
-// shorter last group a launch of its own: 48 -> 80 at 45 x 45, B = 24, 25 frames in groups of 4: 541 -> 112 us; blocks of
-// 128 -> 128 at 16 x 16 / 8 x 8 / 4 x 4, B = 16, TAC-TP K = 4, 16 frames: 141 / 86 / 63 -> 33 / 31 / 31 us; fp32 32 -> 64 at
-// 14 x 14 behind the mean pool, B = 128, K = 8, 25 frames: 125 -> 26 us.  What is left on the small ones (31 us for
-// 4 groups) is one wave's instruction stream: 14 % tables, 40 % aggregates, 22 % MFMAs (61 cycles a step: 2 KiB of
-// fragments for one MFMA, the LDS delivers 128 bytes a cycle), 23 % LIF steps.
+// shorter last group a launch of its own, calls in us: 48 -> 80 at 45 x 45, B = 24, 25 frames in groups of 4: 531 -> 107; blocks
+// of 128 -> 128 at 16 x 16 / 8 x 8 / 4 x 4, B = 16, TAC-TP K = 4, 16 frames: 136 / 85 / 62 -> 34 / 32 / 33; fp32 32 -> 64 at
+// 14 x 14 behind the mean pool, B = 128, 25 frames in groups of 8: 423 -> 84.  The small ones have 64 to 256 workgroups and are
+// bound by one wave's instruction stream and LDS trips (a step reads 2 KiB of fragments for one MFMA; the LDS delivers 128
+// bytes a cycle): tables, aggregates, MFMAs and LIF steps of a group follow each other.
 #pragma once
 #include "tac_mfma_common.h"
 
