@@ -180,7 +180,7 @@ int tac_conv_lif(const tac_layer_desc_t* d, const void* input, const void* w_pre
   for (int j = p.K - 1; j >= 0; --j) { p.wj[j] = (float)pw; p.wjd[j] = pw; pw *= beta; }   // wj[j] = beta^(K-1-j)
   p.decay = desc->mode == TAC_COLLAPSE ? (float)pw /* beta^K */ : desc->beta;
   // kernels that take the shorter last group along do it in the same launch
-  const bool tail_inside = K_last && (p.mfma_kind == 3 || kern == TAC_KERNEL_DIRECT);
+  const bool tail_inside = K_last && (p.mfma_kind != 1 || kern == TAC_KERNEL_DIRECT);
   if (tail_inside) {
     p.K_last = K_last;
     p.n_lif_last = desc->mode == TAC_PRESERVE ? K_last : 1;

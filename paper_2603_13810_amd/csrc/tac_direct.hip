@@ -1,6 +1,6 @@
-// DIRECT kernel family: the conv-LIF layer for any shape with fp32 vector FMAs.  With few input channels it is bound by
-// instructions around the FMAs and by the loader's trips to memory: 1 -> 32 at 28 x 28, B = 128, 25 frames in groups of 8
-// 49 us (a store per channel and step, frames one by one, the shorter last group a launch of its own: 56 + 21 us).
+// DIRECT kernel family: the conv-LIF layer for any shape with fp32 vector FMAs.  fp32 layers with one or two input channels go to
+// the matrix-core kernel of the first layers on the same prepared weights (first_f32_launch: 1 -> 32 at 28 x 28, B = 128, 25 frames
+// in groups of 8 18 us, 49 here, where the instructions around the FMAs and the loader's trips to memory are the bound).
 //
 // One workgroup (4 wavefronts) owns 8 consecutive packed output words of one sample
 // (32 output pixels each, so 1 to 8 output rows) for a block of CB output channels, and
@@ -261,6 +261,7 @@ hipError_t direct_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* 
 }
 
 hipError_t direct_launch(const LayerParams& p, hipStream_t s) {
+  if (first_f32_supported(p)) return first_f32_launch(p, s);
   const int nq = p.Ho * p.Wwo;
   // worst-case input rows behind 8 output words
   const int rows_out_max = (kWordsPerBlock + p.Wwo - 1) / p.Wwo + (p.Wwo > 1 && kWordsPerBlock % p.Wwo ? 1 : 0);

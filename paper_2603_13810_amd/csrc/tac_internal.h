@@ -76,7 +76,10 @@ int mfma_kind(const tac_layer_desc_t& d);
 bool mfma_small_supported(const tac_layer_desc_t& d);
 size_t mfma_small_weight_bytes(const tac_layer_desc_t& d);
 hipError_t mfma_small_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);
-hipError_t mfma_small_launch(const LayerParams& p, hipStream_t s);
+hipError_t mfma_small_launch(const LayerParams& p, hipStream_t s);   // takes a shorter last group along
+// the same kernel for fp32 layers, on the direct family's prepared weights
+bool first_f32_supported(const LayerParams& p);
+hipError_t first_f32_launch(const LayerParams& p, hipStream_t s);
 
 // The backward pass (surrogate-gradient BPTT of one layer), resolved on the host.
 struct BackwardParams {

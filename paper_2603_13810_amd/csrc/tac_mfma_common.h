@@ -196,11 +196,14 @@ __device__ __forceinline__ void lif_step(float (&V)[NMC][NP][16], const f32x16 (
           }
         }
         __builtin_amdgcn_sched_barrier(0);
+        [[maybe_unused]] int co_lim = lg.co_lim;
+        // (compared again in every step: the conditions of all registers together do not fit the scalar registers)
+        if constexpr (TRACE) asm volatile("" : "+v"(co_lim));
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           V[mc][np][r0 + i] = __builtin_amdgcn_inverse_ballot_w64(m[i]) ? v[i] - theta : v[i];
           if constexpr (TRACE) {
-            if (lg.ok[np] && mc * 32 + 8 * ((r0 + i) >> 2) + ((r0 + i) & 3) < lg.co_lim)
+            if (lg.ok[np] && mc * 32 + 8 * ((r0 + i) >> 2) + ((r0 + i) & 3) < co_lim)
               *reinterpret_cast<float*>(reinterpret_cast<char*>(trace_wave) +
                                         (size_t)(mc * 32 + 8 * ((r0 + i) >> 2) + ((r0 + i) & 3)) * plane * 4 +
                                         lg.v_off[np]) = v[i];
@@ -214,6 +217,55 @@ __device__ __forceinline__ void lif_step(float (&V)[NMC][NP][16], const f32x16 (
       });
     });
   });
+}
+
+// One LIF step with a channel per lane: the operands of the MFMAs swapped (pixels as rows, channels as columns), register r of a
+// block on lane (n, h) is pixel 8 (r / 4) + 4 h + r % 4 of channel n.  A ballot costs two v_writelane per register on the way to a
+// store, and select and subtraction two more instructions; here the lanes that spike are what EXEC holds while the threshold is
+// subtracted and the pixel's bit set, four vector instructions per register instead of 6.25, and one scalar move that other
+// waves' vector instructions run beside.  Measured, ns per register and step on a SIMD, against compare, subtract, select and
+// a v_addc that shifts the mask into the bits (five): 6.8 / 8.9 with four waves on the SIMD, 8.2 / 9.3 with two, 12.5 / 10.9 with one.
+// The membranes v are formed outside: they read MFMA results, whose wait states the compiler knows.
+template <int R0>
+__device__ __forceinline__ void spike_reset4(float (&v)[4], float theta, uint32_t& bits) {
+  uint64_t m[4], all;
+  asm("v_cmp_ge_f32_e64 %5, %1, %10\n\tv_cmp_ge_f32_e64 %6, %2, %10\n\tv_cmp_ge_f32_e64 %7, %3, %10\n\tv_cmp_ge_f32_e64 %8, %4, %10\n\t"
+      "s_mov_b64 %9, exec\n\t"
+      "s_mov_b64 exec, %5\n\tv_subrev_f32_e32 %1, %10, %1\n\tv_or_b32_e32 %0, %11, %0\n\t"
+      "s_mov_b64 exec, %6\n\tv_subrev_f32_e32 %2, %10, %2\n\tv_or_b32_e32 %0, %12, %0\n\t"
+      "s_mov_b64 exec, %7\n\tv_subrev_f32_e32 %3, %10, %3\n\tv_or_b32_e32 %0, %13, %0\n\t"
+      "s_mov_b64 exec, %8\n\tv_subrev_f32_e32 %4, %10, %4\n\tv_or_b32_e32 %0, %14, %0\n\t"
+      "s_mov_b64 exec, %9"
+      : "+v"(bits), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]), "=&s"(all)
+      : "s"(theta), "n"(1 << (2 * R0)), "n"(2 << (2 * R0)), "n"(4 << (2 * R0)), "n"(8 << (2 * R0)));
+}
+
+// bits[np]: the spikes of the lane's 16 pixels at their places in the packed word, the upper lane half's four bits too low
+template <int NP>
+__device__ __forceinline__ void lif_step_cols(float (&V)[NP][16], const f32x16 (&y)[NP], float decay, float theta, uint32_t (&bits)[NP]) {
+  static_for<0, NP * 4>([&](auto q_) {
+    constexpr int q = decltype(q_)::value, np = q >> 2, r0 = (q & 3) * 4;
+    float v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = fmaf(decay, V[np][r0 + i], y[np][r0 + i]);
+    if (r0 == 0) bits[np] = 0;
+    spike_reset4<r0>(v, theta, bits[np]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) V[np][r0 + i] = v[i];
+  });
+}
+
+// The packed words of two blocks: lane n gets block 0's word of channel n, lane 32 + n block 1's.
+__device__ __forceinline__ uint32_t words_of_cols(const uint32_t (&bits)[2]) {
+  const auto w = __builtin_amdgcn_permlane32_swap(bits[0], bits[1], false, false);
+  return w[0] | (w[1] << 4);
+}
+
+// The same for two blocks that are the two rows of a 2 x 2 max pool: 16 pooled pixels of channel n in either half.
+__device__ __forceinline__ uint32_t pooled_of_cols(const uint32_t (&bits)[2]) {
+  const uint32_t rows = bits[0] | bits[1];
+  const auto w = __builtin_amdgcn_permlane32_swap(rows, rows, false, false);
+  return pool_pairs(w[0] | (w[1] << 4));
 }
 
 // MaxPool(2) of the output spikes in the layer that writes them (the Conv -> BN -> LIF -> MaxPool(2) blocks of

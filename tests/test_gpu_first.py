@@ -1,0 +1,72 @@
+"""First layers on the matrix cores (1 or 2 input channels, bf16 and fp32): the edges of their tiles against the oracle.  A tile is some
+pairs of packed words x some blocks of 32 output channels, chosen by the number of words, channels and samples; groups ask for up to
+8 frames together (4 with two input channels); with rows of 65 to 96 pixels a tile starts in the middle of a row."""
+import numpy as np
+import pytest
+
+from paper_2603_13810_amd import api, synth
+
+from gpu_util import check_layer
+
+pytestmark = pytest.mark.gpu
+B16, F32 = api.TAC_BF16, api.TAC_FP32
+STEP, TAC, TP = api.TAC_PER_STEP, api.TAC_COLLAPSE, api.TAC_PRESERVE
+
+# (Cin, Cout, H, W, stride, B, T, K, mode, what)
+CASES = [
+    (1, 8, 28, 28, 1, 4, 4, 2, TAC, "one wave per workgroup"),
+    (1, 32, 1, 1, 1, 1, 3, 2, TP, "one pixel, a shorter last group"),
+    (2, 33, 7, 33, 1, 2, 9, 4, TAC, "a second word of one pixel, a second block of one channel"),
+    (2, 96, 9, 90, 1, 2, 6, 3, TP, "three words a row, three blocks"),
+    (1, 160, 5, 65, 1, 3, 8, 8, TAC, "three words a row, five blocks in two tiles, eight frames together"),
+    (2, 128, 6, 128, 1, 1, 10, 5, TP, "four words a row, four blocks, five frames in two batches"),
+    (2, 16, 70, 128, 2, 2, 11, 4, TAC, "more words than threads, stride 2"),
+    (1, 40, 33, 63, 2, 2, 25, 16, TAC, "two batches, a shorter last group of nine"),
+    (2, 64, 20, 31, 1, 40, 4, 1, STEP, "single frames, many samples"),
+    (1, 32, 28, 28, 1, 128, 8, 4, TAC, "tiles of an even number of words that do not divide the sample"),
+    (2, 12, 3, 2, 2, 5, 7, 32, TP, "a group longer than the sequence"),
+]
+
+
+@pytest.mark.parametrize("dense", [False, True], ids=["bits", "values"])
+@pytest.mark.parametrize("precision", [B16, F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("case", CASES, ids=[c[-1] for c in CASES])
+def test_tiles_of_first_layers(case, precision, dense):
+    Cin, Cout, H, W, stride, B, T, K, mode, _ = case
+    if dense and precision == F32 and B > 8:
+        B = 8
+    r = np.random.Generator(np.random.PCG64(9100 + 7 * Cin + Cout + H + W + T + K))
+    s = (r.random((T, B, Cin, H, W)) < 0.3).astype(np.uint8)
+    if dense:
+        s = (s * r.random(s.shape)).astype(np.float32)
+    w = synth.kaiming_normal(61, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    v0 = (r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32)
+    par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, precision=precision, bias=bias, v0=v0,
+                              expect_kernel=api.TAC_KERNEL_MFMA if precision == B16 else api.TAC_KERNEL_DIRECT,
+                              oracle_samples=None if B <= 8 else [0, B // 2, B - 1])
+    assert H * W == 1 or ref[0].sum() > 0
+    print("first layer", par)
+
+
+@pytest.mark.parametrize("precision", [B16, F32], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("Cin", [1, 2])
+def test_values_beyond_a_window_do_not_reach_it(Cin, precision):
+    """Infinite input values: the outputs whose windows hold none are what they are without (no slot of another pixel, and no frame
+    beyond a shorter last group, is multiplied by zero)."""
+    T, H, W = 3, 8, 70
+    r = np.random.Generator(np.random.PCG64(9200 + Cin))
+    x = (r.random((T, 1, Cin, H, W)) * (r.random((T, 1, Cin, H, W)) < 0.3)).astype(np.float32)
+    w = synth.kaiming_normal(62, 40, Cin)
+    kw = dict(K=2, beta=0.9, theta=1.0, mode=api.TAC_PRESERVE, precision=precision)
+    from gpu_util import run_gpu
+    clean = run_gpu(x, w, **kw)
+    bad = x.copy()
+    bad[:, 0, :, 3, 31] = np.inf
+    dirty = run_gpu(bad, w, **kw)
+    clear = np.ones((H, W), bool)
+    clear[2:5, 30:33] = False
+    assert np.array_equal(clean["v_trace"][..., clear], dirty["v_trace"][..., clear])
+    assert np.array_equal(clean["spikes"][..., clear], dirty["spikes"][..., clear])
+    assert not np.isfinite(dirty["v_trace"][..., ~clear]).all()
