@@ -240,19 +240,58 @@ __device__ __forceinline__ void spike_reset4(float (&v)[4], float theta, uint32_
       : "s"(theta), "n"(1 << (2 * R0)), "n"(2 << (2 * R0)), "n"(4 << (2 * R0)), "n"(8 << (2 * R0)));
 }
 
-// bits[np]: the spikes of the lane's 16 pixels at their places in the packed word, the upper lane half's four bits too low
-template <int NP>
-__device__ __forceinline__ void lif_step_cols(float (&V)[NP][16], const f32x16 (&y)[NP], float decay, float theta, uint32_t (&bits)[NP]) {
+// The same with compare, subtraction, select and a v_addc that shifts the mask into the bits (v[0] first): for kernels with one wave
+// on a SIMD, where nothing runs beside the moves of EXEC.
+__device__ __forceinline__ void spike_reset4_shift(float (&v)[4], float theta, uint32_t& bits) {
+  uint64_t m[4];
+  float t[4];
+  asm("v_cmp_ge_f32_e64 %5, %1, %13\n\tv_cmp_ge_f32_e64 %6, %2, %13\n\tv_cmp_ge_f32_e64 %7, %3, %13\n\tv_cmp_ge_f32_e64 %8, %4, %13\n\t"
+      "v_subrev_f32_e32 %9, %13, %1\n\tv_subrev_f32_e32 %10, %13, %2\n\tv_subrev_f32_e32 %11, %13, %3\n\tv_subrev_f32_e32 %12, %13, %4\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %5\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %6\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %7\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %8\n\t"
+      "v_cndmask_b32_e64 %1, %1, %9, %5\n\tv_cndmask_b32_e64 %2, %2, %10, %6\n\t"
+      "v_cndmask_b32_e64 %3, %3, %11, %7\n\tv_cndmask_b32_e64 %4, %4, %12, %8"
+      : "+v"(bits), "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "=&s"(m[0]), "=&s"(m[1]), "=&s"(m[2]), "=&s"(m[3]),
+        "=&v"(t[0]), "=&v"(t[1]), "=&v"(t[2]), "=&v"(t[3])
+      : "s"(theta)
+      : "vcc");
+}
+
+// bits[np]: the spikes of the lane's 16 pixels at their places in the packed word, the upper lane half's four bits too low.
+// ALONE: one wave on the SIMD.
+template <int NP, bool ALONE = false>
+__device__ __forceinline__ void lif_step_cols(float (&V)[NP][16], const f32x16 (&y)[NP], float decay, float theta, uint32_t (&bits)[2]) {
+  bits[0] = bits[1] = 0;
+  [[maybe_unused]] uint32_t all = 0;             // ALONE: bit 16 np + r, the last register first
   static_for<0, NP * 4>([&](auto q_) {
-    constexpr int q = decltype(q_)::value, np = q >> 2, r0 = (q & 3) * 4;
+    constexpr int q = ALONE ? NP * 4 - 1 - decltype(q_)::value : decltype(q_)::value, np = q >> 2, r0 = (q & 3) * 4;
     float v[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = fmaf(decay, V[np][r0 + i], y[np][r0 + i]);
-    if (r0 == 0) bits[np] = 0;
-    spike_reset4<r0>(v, theta, bits[np]);
+    for (int i = 0; i < 4; ++i) v[i] = fmaf(decay, V[np][r0 + (ALONE ? 3 - i : i)], y[np][r0 + (ALONE ? 3 - i : i)]);
+    if constexpr (ALONE) spike_reset4_shift(v, theta, all);
+    else spike_reset4<r0>(v, theta, bits[np]);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) V[np][r0 + i] = v[i];
+    for (int i = 0; i < 4; ++i) V[np][r0 + (ALONE ? 3 - i : i)] = v[i];
   });
+  if constexpr (ALONE) {                       // nibble i of a block -> byte i
+    const uint32_t even = all & 0x0f0f0f0fu, odd = (all >> 4) & 0x0f0f0f0fu;
+    bits[0] = __builtin_amdgcn_perm(odd, even, 0x05010400u);
+    if (NP == 2) bits[1] = __builtin_amdgcn_perm(odd, even, 0x07030602u);
+  }
+}
+
+// A 32 x 32 block between its two layouts, through 33 floats per channel of LDS that belong to the wave: register r on lane (n, h)
+// is channel 8 (r / 4) + 4 h + r % 4 of pixel n, or that pixel of channel n.
+constexpr int kTurnFloats = 32 * 33;
+__device__ __forceinline__ void turn_block(float (&v)[16], float* t, int n, int h) {
+  // the wave's own LDS accesses execute in order; keep the compiler to it too
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < 16; ++r) t[(8 * (r >> 2) + 4 * h + (r & 3)) * 33 + n] = v[r];
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int r = 0; r < 16; ++r) v[r] = t[n * 33 + 8 * (r >> 2) + 4 * h + (r & 3)];
+  asm volatile("" ::: "memory");
 }
 
 // The packed words of two blocks: lane n gets block 0's word of channel n, lane 32 + n block 1's.
@@ -283,14 +322,15 @@ __device__ __forceinline__ uint32_t pooled_of_cols(const uint32_t (&bits)[2]) {
 //   plane_p    words per channel of the pooled tensor, Wwp words per pooled row
 //   rows_p     pooled rows of the tile inside the image,  c_valid: channels of the tile that exist
 // Called by all threads of the workgroup (it contains a barrier); consecutive steps alternate between two areas.
-template <int NMC>
+// COLS: the words as words_of_cols leaves them (lane 32 np + n: channel n).
+template <int NMC, bool COLS>
 __device__ __forceinline__ void pooled_store(const uint32_t (&word)[NMC][2], uint32_t* ex, int tid, int nthreads, int rows,
                                              int nseg, bool two_rows, int row0, int seg, uint32_t* out_tile, size_t plane_p,
                                              int Wwp, int rows_p, int c_valid) {
   constexpr int ctile = NMC * 32;
   const int lane = tid & 63;
-  const int r = lane >> 2, hi = (lane >> 1) & 1, np = lane & 1;
-  const int c_lane = 8 * (r >> 2) + 4 * hi + (r & 3);
+  const int r = lane >> 2, hi = (lane >> 1) & 1, np = COLS ? lane >> 5 : lane & 1;
+  const int c_lane = COLS ? lane & 31 : 8 * (r >> 2) + 4 * hi + (r & 3);
 #pragma unroll
   for (int mc = 0; mc < NMC; ++mc) {
     const uint32_t hp = pool_pairs(word[mc][0]);

@@ -421,7 +421,8 @@ __device__ __forceinline__ void lds_barrier() {
 // The 64-channel tiles ask for two waves per SIMD (256 registers each, which they fit without scratch): where
 // their LDS allows it two workgroups share a compute unit, and with the wave priorities below (high while a wave
 // feeds the matrix cores, low during its LIF steps) one workgroup's LIF steps run under the other's MFMAs.
-template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP, bool AGG = false>
+// COLS: the LIF steps run with a channel per lane (lif_step_cols); the MFMA operands are swapped and a register is a pixel.
+template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP, bool AGG = false, bool COLS = false>
 __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_kernel(const MfmaParams p) {
   using G = Geo<WIN, S, NP>;
   // MC = 32-channel blocks per workgroup and wave: 4 (128 output channels), or 2 (64) for layers
@@ -484,6 +485,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   const size_t v_wave = ((size_t)b * p.Cout + co_wave) * plane + (size_t)oy_wave * G::kWo;
 
   // membrane, MFMA result layout: register r of tile (mc, np), lane -> cout = 32 mc + 8 (r/4) + 4 h + r%4
+  static_assert(!COLS || (!TRACE && !AGG), "recorded membranes are stored with pixels along the lanes");
   float V[MC][NP][16];
   f32x16 acc[MC][NP];
   uint64_t agg_sum = 0;
@@ -506,6 +508,11 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         }); });
       }
     });
+    if constexpr (COLS) {
+      float* const t = reinterpret_cast<float*>(lds + G::kLdsW) + wave * kTurnFloats;
+      static_for<0, MC>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
+      __syncthreads();                         // before the first weights arrive there
+    }
   }
 
   // Position in the sequence of chunks (group-major), with the addresses that go with it: the
@@ -741,7 +748,8 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         for (int mc = 0; mc < MC; ++mc)
 #pragma unroll
           for (int np = 0; np < NP; ++np)
-            acc[mc][np] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][mc], af[slot][np], acc[mc][np], 0, 0, 0);
+            acc[mc][np] = COLS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[slot][np], wf[slot][mc], acc[mc][np], 0, 0, 0)
+                                : __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[slot][mc], af[slot][np], acc[mc][np], 0, 0, 0);
       }
       // the tile built during the last chunk repeats that chunk (nothing follows it) and is not counted
       uint64_t* const agg_s = (AGG && s + 1 < total) ? agg : nullptr;
@@ -781,16 +789,20 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     advance(cur);
   };
 
-  // Packed stores (lane order: see lif_step).  The lane's word of 32-channel block mc sits at
+  // Packed stores (lane order: see lif_step and words_of_cols).  The lane's word of 32-channel block mc sits at
   // out_wave + mc * 32 * out_plane + out_off, with out_wave wave-uniform and out_off a small
   // per-lane offset, the only part kept in a vector register across the time loop.
   constexpr int kStoreRegs = G::kWo >= 32 ? 1 : 2;
   const uint32_t out_plane = (uint32_t)(Ho * G::kOutWords);           // words per (step, b, cout)
   const size_t out_step = (size_t)p.B * p.Cout * out_plane;
   uint32_t* const out_wave = p.out + ((size_t)b * p.Cout + co_wave) * out_plane + (size_t)oy_wave * G::kOutWords;
-  uint32_t out_off;                                                   // in words; store register 1: + 16 out_plane
+  uint32_t out_off;                            // in words; store register 1: + 16 out_plane (a channel per lane: the next row)
   int out_row;                                                        // the lane's row within the wave
-  if constexpr (G::kWo >= 32) {
+  if constexpr (COLS) {
+    // channel n; block h, or with one block its row h (rows of 16 pixels: block np is rows 2 np and 2 np + 1)
+    out_row = G::kWo == 64 ? 0 : G::kWo == 32 ? h : NP == 2 ? 2 * h : h;
+    out_off = (uint32_t)n * out_plane + (G::kWo == 64 ? h : out_row);
+  } else if constexpr (G::kWo >= 32) {
     const int r = lane >> 2, hi = (lane >> 1) & 1;
     out_row = G::kWo == 64 ? 0 : (lane & 1);
     out_off = (uint32_t)(8 * (r >> 2) + 4 * hi + (r & 3)) * out_plane + (G::kWo == 64 ? (lane & 1) : out_row);
@@ -827,13 +839,13 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
       for (int mc = 0; mc < MC; ++mc)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const float bv = bias_lds[mc * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
+          const float bv = bias_lds[mc * 32 + (COLS ? n : 8 * (r >> 2) + 4 * h + (r & 3))];
 #pragma unroll
           for (int np = 0; np < NP; ++np) acc[mc][np][r] += bv;
         }
     }
     // epilogue geometry, recomputed per group: nothing of it lives across the MFMA loop
-    const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane, p.theta);
+    [[maybe_unused]] const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane, p.theta);
     for (int j = 0; j < p.n_lif; ++j) {
       const size_t step = (size_t)g * p.n_lif + j;
       uint32_t word[MC][2];
@@ -844,23 +856,38 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         size_t plane_l = plane;
         asm volatile("" : "+s"(plane_l));       // keep the trace addresses out of the loop preheader
         lif_step<MC, G::kWo, true, NP>(V, acc, p.decay, p.theta, lg, word, tl, plane_l);
-      } else {
+      } else if constexpr (!COLS) {
         lif_step<MC, G::kWo, false, NP>(V, acc, p.decay, p.theta, lg, word, nullptr, plane);
+      } else {
+        static_for<0, MC>([&](auto mc_) {
+          constexpr int mc = decltype(mc_)::value;
+          uint32_t bits[2];
+          lif_step_cols<NP, NP == 1>(V[mc], acc[mc], p.decay, p.theta, bits);
+          if (NP == 1 && G::kWo == 16) bits[1] = bits[0];      // both lane halves get the one block's word, and store a row each
+          word[mc][0] = words_of_cols(bits);
+          if constexpr (G::kWo == 16) {        // two rows of 16 pixels
+            word[mc][1] = word[mc][0] >> 16;
+            word[mc][0] = NP == 2 ? word[mc][0] & 0xffffu : (h ? word[mc][1] : word[mc][0] & 0xffffu);
+          }
+        });
       }
       if (G::kCanPoolOut && p.out_pool) {
         if constexpr (G::kCanPoolOut) {
           const uint32_t plane_p = (uint32_t)(Ho >> 1);                      // one word per pooled row
           uint32_t* ex = reinterpret_cast<uint32_t*>(lds + G::lds_bytes(K, MC)) + (step & 1) * (G::kTileRows * kCT);
-          pooled_store<MC>(word, ex, tid, kThreads, G::kTileRows, 1, G::kWaveRows == 2, wave * G::kWaveRows, 0,
+          pooled_store<MC, COLS>(word, ex, tid, kThreads, G::kTileRows, 1, G::kWaveRows == 2, wave * G::kWaveRows, 0,
                            p.out + (step * p.B * p.Cout + (size_t)b * p.Cout + co_wave) * plane_p + (y0 >> 1), plane_p, 1,
                            min(G::kTileRows >> 1, (Ho - y0) >> 1), kCT);
         }
       } else if (out_ok) {
         uint32_t* const o = out_wave + step * out_step;
 #pragma unroll
-        for (int sr = 0; sr < kStoreRegs; ++sr)
+        for (int sr = 0; sr < kStoreRegs; ++sr) {
+          if (COLS && sr == 1 && (NP == 1 || oy_wave + out_row + 1 >= Ho)) break;
 #pragma unroll
-          for (int mc = 0; mc < MC; ++mc) o[(uint32_t)(mc * 32 + sr * 16) * out_plane + out_off] = word[mc][sr];
+          for (int mc = 0; mc < MC; ++mc)
+            o[(uint32_t)(mc * 32 + (COLS ? 0 : sr * 16)) * out_plane + out_off + (COLS ? sr : 0)] = word[mc][sr];
+        }
       }
     }
   }
@@ -882,6 +909,10 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     asm volatile("" : "+s"(plane_l));         // not before the time loop (they would not fit in registers)
     const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane_l, p.theta);
     char* vb = reinterpret_cast<char*>(p.v_inout + v_wave);
+    if constexpr (COLS) {
+      float* const t = reinterpret_cast<float*>(lds + G::kLdsW) + wave * kTurnFloats;
+      static_for<0, MC>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
+    }
     static_for<0, NP>([&](auto np_) {
       constexpr int np = decltype(np_)::value;
       if (lg.ok[np]) {
@@ -894,30 +925,6 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   }
 }
 
-template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP = 2>
-hipError_t launch_tile(const MfmaParams& mp, hipStream_t s) {
-  using G = Geo<WIN, S, NP>;
-  constexpr int lds_layer = G::lds_bytes(KT > 0 ? KT : TAC_MAX_K, MC);
-  constexpr int lds_max = lds_layer + G::pool_bytes(MC);
-  static_assert(lds_max <= kLdsLimit, "tile does not fit the LDS");
-  static std::once_flag once;               // one attribute call per kernel, also with several host threads
-  static hipError_t attr = hipSuccess;
-  std::call_once(once, [] {
-    attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-  });
-  if (attr != hipSuccess) return attr;
-  if (mp.out_pool && !G::kCanPoolOut) return hipErrorInvalidValue;
-  const int lds = mp.out_pool ? lds_max : lds_layer;
-  MfmaParams q = mp;
-  q.row_tiles = (mp.Ho + G::kTileRows - 1) / G::kTileRows;
-  const dim3 grid(q.row_tiles * (mp.Cout / (MC * 32)) * mp.B);
-  hipLaunchKernelGGL((mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP>), grid, dim3(kThreads), lds, s, q);
-  return hipGetLastError();
-}
-
-// 64-channel tiles when 128-channel tiles would give fewer workgroups than the chip has compute
-// units (small batches, deep layers); not combined with the max pool on load.
 // Compute units of the current device, asked once (256 on an MI355X; that figure also where the query fails).
 inline int compute_units() {
   static std::once_flag once;
@@ -930,6 +937,52 @@ inline int compute_units() {
   });
   return n;
 }
+
+template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP = 2, bool COLS = false>
+hipError_t launch_tile(const MfmaParams& mp, hipStream_t s) {
+  using G = Geo<WIN, S, NP>;
+  constexpr int lds_layer = G::lds_bytes(KT > 0 ? KT : TAC_MAX_K, MC);
+  constexpr int lds_max = lds_layer + G::pool_bytes(MC);
+  static_assert(lds_max <= kLdsLimit, "tile does not fit the LDS");
+  static std::once_flag once;               // one attribute call per kernel, also with several host threads
+  static hipError_t attr = hipSuccess;
+  std::call_once(once, [] {
+    attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP, false, COLS>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+  });
+  if (attr != hipSuccess) return attr;
+  if (mp.out_pool && !G::kCanPoolOut) return hipErrorInvalidValue;
+  const int lds = mp.out_pool ? lds_max : lds_layer;
+  MfmaParams q = mp;
+  q.row_tiles = (mp.Ho + G::kTileRows - 1) / G::kTileRows;
+  const dim3 grid(q.row_tiles * (mp.Cout / (MC * 32)) * mp.B);
+  hipLaunchKernelGGL((mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP, false, COLS>), grid, dim3(kThreads), lds, s, q);
+  return hipGetLastError();
+}
+
+// 64-channel tiles when 128-channel tiles would give fewer workgroups than the chip has compute
+// units (small batches, deep layers); not combined with the max pool on load.
+// Tiles of 64 channels, NP blocks of 32 pixels per wave.  Which way round the LIF steps run: with a channel per lane they have fewer
+// vector instructions (four or five a neuron in the place of 6.25).  Half tiles take it always (128 -> 256 stride 2 at 32 x 32, TAC-TP
+// K = 2, B = 16 133 -> 129 us; the pooled 128 -> 128 at 32 x 32, K = 4 38.2 -> 36.5); two blocks where two workgroups share a compute unit, so
+// that the moves of EXEC cost nothing (K = 2, one workgroup per compute unit: 77 -> 82 us), and the steps weigh enough that
+// the swapped MFMAs, 1 % slower for reasons not found, do not show: TAC-TP on 128 channels at 64 x 64 K = 4 / 8 / 16
+// 556 / 362 / 318 -> 547 / 356 / 292 us, 64 -> 128 K = 2, B = 16 72 -> 69; 128 -> 128 K = 2 919 -> 931.
+template <int KT, int WIN, int S, bool TRACE, bool MP, int NP>
+hipError_t launch_tile64(const MfmaParams& mp, hipStream_t s) {
+  if constexpr (TRACE || MP || KT == 1) {
+    return launch_tile<KT, WIN, S, TRACE, MP, 2, NP>(mp, s);
+  } else if constexpr (NP == 1) {
+    return launch_tile<KT, WIN, S, TRACE, MP, 2, 1, true>(mp, s);
+  } else {
+    const int row_tiles = (mp.Ho + Geo<WIN, S, NP>::kTileRows - 1) / Geo<WIN, S, NP>::kTileRows;
+    const bool shared = 2 * Geo<WIN, S, NP>::lds_bytes(KT > 0 ? KT : TAC_MAX_K, 2) <= kLdsLimit &&
+                        (long long)row_tiles * (mp.Cout / 64) * mp.B > compute_units();
+    if (shared && (KT > 2 || mp.n_lif * 32 >= mp.Cin)) return launch_tile<KT, WIN, S, TRACE, MP, 2, 2, true>(mp, s);
+    return launch_tile<KT, WIN, S, TRACE, MP, 2, 2>(mp, s);
+  }
+}
+
 template <int KT, int WIN, int S, bool TRACE, bool MP>
 hipError_t launch_traced(const MfmaParams& mp, hipStream_t s) {
   const int kComputeUnits = compute_units();
@@ -942,16 +995,16 @@ hipError_t launch_traced(const MfmaParams& mp, hipStream_t s) {
   // two frames, per two chunks with larger groups (TAC-TP with groups of 4, 8 or 16 on 128 channels).
   if constexpr (!MP && KT >= 1 && 2 * Geo<WIN, S>::lds_bytes(KT, 2) <= kLdsLimit) {
     const int kChannelsPerStep = KT == 1 ? 128 : (KT == 2 ? (mp.n_lif == 1 ? 128 : 64) : 32);
-    if (mp.n_lif * kChannelsPerStep >= mp.Cin && !mp.out_pool) return launch_tile<KT, WIN, S, TRACE, MP, 2>(mp, s);
+    if (mp.n_lif * kChannelsPerStep >= mp.Cin && !mp.out_pool) return launch_tile64<KT, WIN, S, TRACE, MP, 2>(mp, s);
   }
   if constexpr (!MP) {
     const int row_tiles = (mp.Ho + Geo<WIN, S>::kTileRows - 1) / Geo<WIN, S>::kTileRows;
     if ((long long)row_tiles * (mp.Cout / kCoutTile) * mp.B < kComputeUnits) {
       // still fewer workgroups than compute units with 64-channel tiles: half as high a tile as well
       if constexpr (Geo<WIN, S>::kWo <= 32) {
-        if ((long long)row_tiles * (mp.Cout / 64) * mp.B < kComputeUnits) return launch_tile<KT, WIN, S, TRACE, MP, 2, 1>(mp, s);
+        if ((long long)row_tiles * (mp.Cout / 64) * mp.B < kComputeUnits) return launch_tile64<KT, WIN, S, TRACE, MP, 1>(mp, s);
       }
-      return launch_tile<KT, WIN, S, TRACE, MP, 2>(mp, s);
+      return launch_tile64<KT, WIN, S, TRACE, MP, 2>(mp, s);
     }
   }
   return launch_tile<KT, WIN, S, TRACE, MP, 4>(mp, s);

@@ -28,7 +28,6 @@ namespace {
 
 constexpr int kFirstWaves = 8;                 // per workgroup at most
 constexpr int kFirstMaxW = 128;                // input width limit (4 words per row)
-constexpr int kFirstVStride = 33;              // floats per channel of a block on its way between membrane layouts
 
 // x / d by multiplication: the product is the quotient or one less
 struct Div {
@@ -214,42 +213,23 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
   // ---- membranes
   float V[1][2][16];
   float* const v_wave = p.v_inout + ((size_t)b * p.Cout + co0) * plane + (size_t)row0 * p.Wo;     // of the tile's first row
-  float* const turn = reinterpret_cast<float*>(tiles + 2 * p.tile_words) + wave * 32 * kFirstVStride;   // only there where it is used
+  float* const turn = reinterpret_cast<float*>(tiles + 2 * p.tile_words) + wave * kTurnFloats;   // only there where it is used
 #pragma unroll
   for (int np = 0; np < 2; ++np)
 #pragma unroll
     for (int r = 0; r < 16; ++r) V[0][np][r] = 0.f;
-  // (channel per lane:) the lane's pixel, and the block's last channel
-  float* v_lane[2];
-#pragma unroll
-  for (int np = 0; np < 2; ++np) v_lane[np] = v_wave + (lg.ok[np] ? (size_t)(oy[np] - row0) * p.Wo + 32 * word_of[np] + n : 0);
-  const int v_lim = min(31, p.Cout - co0 - 1);
   if (p.v_inout && active) {
-    if constexpr (TRACE) {
 #pragma unroll
-      for (int np = 0; np < 2; ++np)
+    for (int np = 0; np < 2; ++np)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = 8 * (r >> 2) + (r & 3);
-          if (lg.ok[np] && c < lg.co_lim)
-            V[0][np][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(v_wave) + (size_t)c * plane * 4 + lg.v_off[np]);
-        }
-    } else {
-      // channels 2 i + h of pixel n, handed over through the LDS (lanes outside the image or the channels load one that is inside)
-      float v[2][16];
-#pragma unroll
-      for (int np = 0; np < 2; ++np)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[np][i] = v_lane[np][(size_t)min(2 * i + h, v_lim) * plane];
-#pragma unroll
-      for (int np = 0; np < 2; ++np) {
-#pragma unroll
-        for (int i = 0; i < 16; ++i) turn[(2 * i + h) * kFirstVStride + n] = v[np][i];
-        asm volatile("" ::: "memory");         // the wave's own LDS accesses execute in order; keep the compiler to it too
-#pragma unroll
-        for (int r = 0; r < 16; ++r) V[0][np][r] = turn[n * kFirstVStride + 8 * (r >> 2) + 4 * h + (r & 3)];
-        asm volatile("" ::: "memory");
+      for (int r = 0; r < 16; ++r) {
+        // (lanes outside the image or the channels load a membrane that is inside; nobody stores theirs)
+        const int c = min(8 * (r >> 2) + (r & 3), lg.co_lim - 1);
+        V[0][np][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(v_wave) + (c >= 0 ? (size_t)c * plane * 4 + lg.v_off[np] : 0));
       }
+    if constexpr (!TRACE) {
+#pragma unroll
+      for (int np = 0; np < 2; ++np) turn_block(V[0][np], turn, n, h);
     }
   }
 
@@ -442,23 +422,12 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
   if (p.v_inout && active) {
 #pragma unroll
     for (int np = 0; np < 2; ++np) {
-      if constexpr (TRACE) {
+      if constexpr (!TRACE) turn_block(V[0][np], turn, n, h);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = 8 * (r >> 2) + (r & 3);
-          if (lg.ok[np] && c < lg.co_lim)
-            *reinterpret_cast<float*>(reinterpret_cast<char*>(v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) = V[0][np][r];
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) turn[n * kFirstVStride + 8 * (r >> 2) + 4 * h + (r & 3)] = V[0][np][r];
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float v = turn[(2 * i + h) * kFirstVStride + n];
-          if (lg.ok[np] && 2 * i + h <= v_lim) v_lane[np][(size_t)(2 * i + h) * plane] = v;
-        }
-        asm volatile("" ::: "memory");
+      for (int r = 0; r < 16; ++r) {
+        const int c = 8 * (r >> 2) + (r & 3);
+        if (lg.ok[np] && c < lg.co_lim)
+          *reinterpret_cast<float*>(reinterpret_cast<char*>(v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) = V[0][np][r];
       }
     }
   }
@@ -516,7 +485,7 @@ hipError_t first_launch_c(const LayerParams& l, FirstParams& p, hipStream_t s) {
   const int rows = l.out_pool ? 2 * ((p.pairs + p.Wwo - 2) / p.Wwo + 1) : (2 * p.pairs + p.Wwo - 2) / p.Wwo + 1;
   p.tile_words = (F32 ? CIN : 1) * ((rows - 1) * p.S + 3) * first_row_words(p.W);
   const size_t lds = (size_t)2 * p.tile_words * 4 +
-                     (size_t)p.pairs * p.blocks * 32 * 4 * (p.v_trace ? 1 : p.v_inout ? kFirstVStride : 0);
+                     (size_t)p.pairs * p.blocks * 4 * (p.v_trace ? 32 : p.v_inout ? kTurnFloats : 0);
   return l.dense ? first_launch_k<CIN, F32, true>(p, lds, s) : first_launch_k<CIN, F32, false>(p, lds, s);
 }
 
