@@ -62,6 +62,18 @@ __device__ __forceinline__ uint32_t write_lanes(uint32_t old, const uint32_t (&x
   return r;
 }
 
+// the same for two pairs
+template <int L0, int STEP, int HALF>
+__device__ __forceinline__ uint32_t write_lanes(uint32_t old, const uint32_t (&x)[2][2]) {
+  uint32_t r;
+  asm volatile(
+      "s_nop 1\n\tv_writelane_b32 %0, %1, %5\n\tv_writelane_b32 %0, %2, %6\n\t"
+      "v_writelane_b32 %0, %3, %7\n\tv_writelane_b32 %0, %4, %8"
+      : "=v"(r)
+      : "s"(x[0][0]), "s"(x[0][1]), "s"(x[1][0]), "s"(x[1][1]), "n"(L0), "n"(L0 + HALF), "n"(L0 + STEP), "n"(L0 + STEP + HALF), "0"(old));
+  return r;
+}
+
 // (a & m) | (b & ~m): one v_bfi_b32
 __device__ __forceinline__ uint32_t bfi(uint32_t m, uint32_t a, uint32_t b) { return (a & m) | (b & ~m); }
 

@@ -90,8 +90,10 @@ double mid_job_cycles(const MidPlan& q, const LayerParams& p) {
 
 // The plan of one tile shape, or false when it does not fit the LDS.  pw_shift: lanes per row of a block (their log2),
 // trg: row groups per tile.
-bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w) {
+bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w, int split = 0) {
   const bool f32 = !p.bf16;
+  const int threads = split ? 512 : kMidThreads, four = split ? 2 : 1;         // loaders counts waves of every four
+  q.split = split;
   const int S = p.stride, C8 = p.Cin / 8;
   q.pw_shift = pw_shift;
   q.rpb = 32 >> q.pw_shift;
@@ -117,8 +119,9 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   q.nks = mid_k_steps(p.Cin, f32);
   q.nmc_w = nmc_w;
   auto up = [](int x) { return (x + 15) & ~15; };
-  const int w_bytes = q.nks * nmc * (f32 ? 256 : 1024);
-  const int ahead = (2 * mid_depth(nmc, nnp) - 1) * nmc * 1024;       // the fetches ahead read past the weights
+  const int w_bytes = split ? 0 : q.nks * nmc * (f32 ? 256 : 1024);
+  const int ahead = split ? 0 : (2 * mid_depth(nmc, nnp) - 1) * nmc * 1024;    // the fetches ahead read past the weights
+  const int parts_bytes = split ? 8 * 4096 : 0;                       // the waves' partial sums, behind everything else
   const bool sums = f32 || q.nb > 1 || p.pool2 == 1;
   const int lut_entries = sums ? q.nb << kp : (kp == 8 ? 256 : 1 << (2 * kp));
   q.off_w = q.plane * C8 * (f32 ? 2 : 1);
@@ -128,7 +131,7 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   q.off_lut = q.off_wq + TAC_MAX_K * 4;
   q.off_unit = up(q.off_lut + lut_entries * 4);
   // groups of one or two frames on few channels: see the kernel's build_direct
-  q.direct = kp <= 2 && (kp == 1 || !p.pool2) && C8 * q.lr * p.W <= kMidDirect * kMidThreads;
+  q.direct = kp <= 2 && (kp == 1 || !p.pool2) && C8 * q.lr * p.W <= kMidDirect * threads;
   if (q.direct) {
     q.n_jobs = 0;
     q.loaders = 4;
@@ -138,7 +141,8 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
     q.cg = C8;
     q.chunks = q.batches = q.rw = q.stage_wave = 0;
     q.off_px = q.off_stage = q.off_unit;
-    q.total = std::max(q.off_unit, q.off_w + w_bytes + ahead);
+    q.off_part = up(std::max(q.off_unit, q.off_w + w_bytes + ahead));
+    q.total = q.off_part + parts_bytes;
     return q.total <= kMidLds;
   }
   // Four waves form aggregates, each in as few jobs as the LDS has room to stage; fewer waves only where even the smallest
@@ -161,9 +165,10 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
         c.off_px = up(c.off_unit + c.parts * n_units * 8);
         c.off_stage = up(c.off_px + c.parts * n_px * 8);
         c.stage_wave = up(c.cg * c.rw * c.rws * 4);
-        c.total = std::max(c.off_stage + c.loaders * c.stage_wave, c.off_w + w_bytes + ahead);
+        c.off_part = up(std::max(c.off_stage + four * c.loaders * c.stage_wave, c.off_w + w_bytes + ahead));
+        c.total = c.off_part + parts_bytes;
         if (c.total > kMidLds || c.stage_wave >= 1 << 24) continue;
-        const double cost = (double)((c.n_jobs + c.loaders - 1) / c.loaders) * mid_job_cycles(c, p);
+        const double cost = (double)((c.n_jobs + four * c.loaders - 1) / (four * c.loaders)) * mid_job_cycles(c, p);
         // a second workgroup per compute unit is worth more than a job less
         const double scaled = cost * (c.total > kMidLds / 2 && c.off_px < kMidLds / 2 ? 1.3 : 1.0);
         if (found && scaled >= best) continue;
@@ -237,6 +242,28 @@ hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void
   return hipGetLastError();
 }
 
+// Small images on many channels: eight waves share the pixel blocks of a workgroup (the kernel's SPLIT), as long as there are few of them:
+// 512 blocks of 32 pixels x 32 channels.  Beyond that the four-wave tiles fill their waves and the exchange of partial sums costs more
+// than it gives (us, split / not: 128 -> 128 at 16 x 16, K = 4, B = 16 (512) 23.5 / 33; B = 64 92 / 72; 64 -> 64 at 10 x 10, B = 128 (1280) 47 / 29).
+static bool mid_split_rule(const LayerParams& p) {
+  if (!p.bf16 || p.pool2 || p.Cin < 64 || p.Wo > 16) return false;
+  const int rows = p.Wo > 8 ? 2 : p.Wo > 4 ? 4 : p.Wo > 2 ? 8 : 16;    // of a block
+  return ((long long)p.B * p.Ho + rows - 1) / rows * ((p.Cout + 31) / 32) <= 512;
+}
+
+// Estimated time of such a launch, as mid_cost
+static double mid_split_cost(const MidPlan& q, const LayerParams& p) {
+  const int own = kMidRanges / q.split, regs = 16 / q.split, loaders = 2 * q.loaders;
+  const double build = q.direct ? 500.0 + 400.0 * ((p.Cin / 8 * q.lr * p.W + 511) / 512) * (p.K == 2 ? 2 : 1)
+                                : (q.n_jobs + loaders - 1) / loaders * mid_job_cycles(q, p);
+  const double mfma = own * (400.0 + q.nks / 8.0 * 64.0) + 900.0;
+  const double lif = p.n_lif * (200.0 + 40.0 * regs + 60.0 * q.rpb + (p.v_trace ? 20.0 * regs : 0.0));
+  const double wgs = (double)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
+  const int resident = std::min(2, kMidLds / q.total);
+  const double per_cu = std::ceil(wgs / 256.0), together = std::min<double>(resident, per_cu);
+  return std::ceil(per_cu / resident) * (7000.0 + p.G * (build + mfma + lif + 300.0)) * (together > 1 ? 1.5 : 1.0);
+}
+
 static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, int& nnp) {
   const bool f32 = !p.bf16;
   kp = p.K <= 2 ? p.K : p.K <= 4 ? 4 : 8;
@@ -246,6 +273,21 @@ static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, 
   const bool may_flatten = (long long)p.B * p.Cout * p.Ho * p.Wo < (1ll << 30) && (long long)p.B * p.Ho < (1ll << 20) - 1024;
   double best = 0.0;
   bool found = false;
+  if (mid_split_rule(p)) {
+    const int pw = p.Wo > 8 ? 4 : p.Wo > 4 ? 3 : p.Wo > 2 ? 2 : 1;
+    for (int split = 8; split >= 4; split /= 2)
+      for (int fl = may_flatten ? 1 : 0; fl >= 0; --fl) {
+        MidPlan q;
+        if (!mid_plan(q, p, kp, 1, 1, pw, 8 / split, fl != 0, nmc_w, split)) continue;
+        const double cost = mid_split_cost(q, p);
+        if (found && cost >= best) continue;
+        found = true;
+        best = cost;
+        out.q = q;
+        nmc = nnp = 1;
+      }
+    if (found) return true;
+  }
   // as many rows per block as its lanes hold; fewer only where such a tile does not fit the LDS
   for (int pw = p.Wo > 16 ? 5 : p.Wo > 8 ? 4 : p.Wo > 4 ? 3 : p.Wo > 2 ? 2 : 1; pw <= 5 && !found; ++pw)
     for (int c = 1; c <= (f32 || p.Cout <= 32 ? 1 : 2); ++c)

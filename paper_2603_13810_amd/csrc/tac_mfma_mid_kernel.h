@@ -40,6 +40,8 @@
 namespace tac {
 
 constexpr int kMidThreads = 256;
+constexpr int kMidRanges = 8;   // partial sums of an output where waves share a pixel block, whatever their number
+constexpr int kMidRangeSteps = 9;        // k-steps of one at most (128 input channels)
 constexpr int kMidTabPad = 24;  // entries of the slot table behind the last k-step (fetched ahead)
 // Sets of operand fragments in flight: with few MFMAs per step (32 cycles each) a step is shorter than an LDS read
 __host__ __device__ constexpr int mid_depth(int nmc, int nnp) { return nmc * nnp == 1 ? 4 : nmc * nnp == 2 ? 3 : 2; }
@@ -52,7 +54,7 @@ struct MidPlan {
   int flatten;                  // output rows are counted through all samples (a tile may straddle two)
   int row_tiles, co_tiles;      // tiles over the rows (per sample, or over all of them), over the output channels
   int cg, parts_shift, parts, lrp;      // a job = cg groups of 8 channels x lrp LDS rows; parts: jobs over the rows, a power of two
-  int loaders;                  // waves that form aggregates: all four unless their staging areas do not fit the LDS
+  int loaders;                  // waves, of every four, that form aggregates: all four unless their staging areas do not fit the LDS
   int direct;                   // no jobs: every thread forms up to kMidDirect pixels of 8 channels from words of its own
   int srows, wws, hs;           // stored rows per LDS row (2: pool on load), words per stored row, stored rows per channel
   int rw, rws;                  // (stored row, word) pairs per job and channel; staged dwords per pair and 8 channels
@@ -61,6 +63,7 @@ struct MidPlan {
   int wpx, xh, plane;           // columns of the aggregate tile, of its even half (stride 2), bytes per channel group
   int nks, nmc_w;               // k-steps; 32-channel blocks per tile of the prepared weights
   int off_w, off_tab, off_bias, off_wq, off_unit, off_px, off_lut, off_stage, stage_wave, total;
+  int split, off_part;          // eight waves, `split` of which share a pixel block (0: four waves with blocks of their own); their partial sums
 };
 
 struct MidParams {
@@ -92,10 +95,21 @@ struct SmallDiv {
 };
 
 // KP: frames per table index (1, 2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
-// per wave.  DIRECT: the plan's direct.
-template <int KP, int NMC, int NNP, bool TRACE, bool F32, bool DIRECT>
-__global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && NNP == 2) ? 1 : 2) void mid_kernel(const MidParams mp) {
+// per wave.  DIRECT: the plan's direct.  SPLIT: the plan's split, see below.
+//
+// SPLIT.  Images of at most 16 x 16 pixels on many channels have few pixel blocks: a workgroup's waves stood idle while one or two of
+// them multiplied 72 k-steps and made the LIF steps.  There eight waves share 8 / SPLIT pixel blocks of 32 channels, SPLIT waves
+// each: a wave multiplies its part of the k-steps, whose weights it keeps in registers for the whole call, the partial sums
+// meet in LDS, and each wave adds up and steps 16 / SPLIT registers of the block.  The sum is that of eight ranges of k-steps in
+// a fixed tree whatever SPLIT is.  A wave that has one job in every group keeps its entries of the tables in registers, and up to
+// four steps leave in one store.  128 -> 128, B = 16, TAC-TP K = 4, 16 frames, pooled, us a call before and now: 16 x 16 33.3 / 23.5, 8 x 8
+// 29.8 / 19.5, 4 x 4 31.0 / 18.4 (with membranes 48 / 28, 43 / 22, 44 / 20).  Of the 18.4 the products are less than one: what
+// remains is forming the aggregates (two thirds) and the chain of barriers and LDS trips.
+template <int KP, int NMC, int NNP, bool TRACE, bool F32, bool DIRECT, int SPLIT = 0>
+__global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && NNP == 2) ? 1 : 2) void mid_kernel(const MidParams mp) {
   static_assert(!F32 || NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
+  static_assert(!SPLIT || (NMC * NNP == 1 && !F32), "waves that share a pixel block: one block of bf16 operands");
+  constexpr int NT = SPLIT ? 512 : kMidThreads, NW = NT / 64;
   constexpr uint32_t kNone = 0xffffffffu;
   const MfmaParams& p = mp.m;
   const MidPlan& q = mp.q;
@@ -128,7 +142,19 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   uint8_t* const stage = lds + q.off_stage + wave * q.stage_wave;
 
   // ---- the tile's weights: [k-step][block] fragments of 1 KiB (fp32: 256 bytes), on their way while the tables are made
-  {
+  constexpr int kShare = SPLIT ? SPLIT : 1, kOwn = SPLIT ? kMidRanges / kShare : 1;                 // SPLIT: ranges of k-steps per wave
+  [[maybe_unused]] const int k_part = SPLIT ? wave % kShare : 0, px_wave = SPLIT ? wave / kShare : 0;
+  auto range_start = [&](int i) { return (q.nks * (k_part * kOwn + i)) >> 3; };
+  bf16x8 w_own[kOwn][SPLIT ? kMidRangeSteps : 1];
+  if constexpr (SPLIT) {
+    const int tile = co_tile / q.nmc_w;
+    const uint8_t* const src = p.w + ((size_t)tile * q.nks * q.nmc_w + (co_tile - tile * q.nmc_w)) * 1024 + lane * 16;
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+      for (int k = 0; k < kMidRangeSteps; ++k)                         // (a step behind the range's last is loaded and not multiplied)
+        w_own[i][k] = *reinterpret_cast<const bf16x8*>(src + (size_t)min(range_start(i) + k, q.nks - 1) * q.nmc_w * 1024);
+  } else {
     if constexpr (F32) {
       const uint8_t* const src = p.w + (size_t)co_tile * q.nks * 256 + lane * 16;
       for (int f = wave; f < q.nks / 4; f += 4) lds_dma16<1, 0>(src + (size_t)f * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + f * 1024));
@@ -163,7 +189,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   // of the job), top bit: outside the image; byte offset in the staging area
   const SmallDiv by_rw(q.rw), by_wws(q.wws), by_ch(8 * q.cg);
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_units); i += kMidThreads) {
+  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_units); i += NT) {
     const int pc = by_rw.quot(i), rw = i - pc * q.rw;
     const int part = by_ch.quot(pc), ch = pc - part * 8 * q.cg;
     const int srow = by_wws.quot(rw), word = rw - srow * q.wws;
@@ -189,6 +215,21 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   auto frames_of = [&](int g) { return g == p.G ? mp.K_last : p.K; };
   const int n_uc = q.nb == 1 ? q.chunks : q.chunks / q.nb;
   uint32_t wd[kMidBatch][U][KP];
+  // SPLIT: a wave that has one job of one batch in every group keeps what the tables say about it in registers
+  const bool own_job = SPLIT && q.n_jobs <= 2 * q.loaders && q.batches == 1;
+  u32x2 own_un[SPLIT ? kMidBatch : 1][U];
+  if constexpr (SPLIT && !DIRECT) {
+    if (own_job) {
+#pragma unroll
+      for (int c = 0; c < kMidBatch; ++c)
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = ((c < n_uc ? c : c % n_uc) * U + u) * 64 + lane;
+          own_un[c][u] = unit[(wave & (q.parts - 1)) * n_units + min(e, n_units - 1)];
+          if (e >= n_units) own_un[c][u][1] = kNone;
+        }
+    }
+  }
   auto chunk_of = [&](int c, int& nb, int& uc) {
     nb = 0;
     uc = c;
@@ -208,7 +249,10 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       chunk_of(batch * kMidBatch + c, nb, uc);
       f0[c] = nb * KP;
 #pragma unroll
-      for (int u = 0; u < U; ++u) off[c][u] = units[min((uc * U + u) * 64 + lane, n_units - 1)][0] & 0x7fffffffu;
+      for (int u = 0; u < U; ++u) {
+        if (SPLIT && own_job) off[c][u] = own_un[c][u][0] & 0x7fffffffu;
+        else off[c][u] = units[min((uc * U + u) * 64 + lane, n_units - 1)][0] & 0x7fffffffu;
+      }
     }
 #pragma unroll
     for (int c = 0; c < kMidBatch; ++c) {
@@ -234,6 +278,10 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       f0[c] = nb * KP;
 #pragma unroll
       for (int u = 0; u < U; ++u) {
+        if (SPLIT && own_job) {
+          un[c][u] = own_un[c][u];
+          continue;
+        }
         const int e = (uc * U + u) * 64 + lane;
         un[c][u] = units[min(e, n_units - 1)];
         if (e >= n_units) un[c][u][1] = kNone;
@@ -271,7 +319,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       const size_t second = KP == 2 ? (frames_of(g) > 1 ? t_stride : 0) : p.pool ? (size_t)q.wws : 0;
 #pragma unroll
       for (int i = 0; i < kMidDirect; ++i) {
-        if (i > 0 && i * kMidThreads >= C8 * q.lr * p.W) break;        // (uniform)
+        if (i > 0 && i * NT >= C8 * q.lr * p.W) break;        // (uniform)
         const uint32_t* const src = base + (d_off[i] & 0x7fffffffu);
 #pragma unroll
         for (int c = 0; c < 8; ++c) dw[i][0][c] = src[c * in_chan];
@@ -286,7 +334,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     const SmallDiv by_w(p.W), by_lr(q.lr);
 #pragma unroll
     for (int i = 0; i < kMidDirect; ++i) {
-      const int e = tid + i * kMidThreads, line = by_w.quot(min(e, C8 * q.lr * p.W - 1));
+      const int e = tid + i * NT, line = by_w.quot(min(e, C8 * q.lr * p.W - 1));
       const int x = min(e, C8 * q.lr * p.W - 1) - line * p.W, cg = by_lr.quot(line), row = line - cg * q.lr;
       int bsel, iy;
       input_row(row, bsel, iy);
@@ -306,7 +354,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   const SmallDiv by_w(p.W), by_lrp(q.lrp), by_cg(q.cg);
   const int n_px = q.cg * q.lrp * p.W;                                 // per job
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_px); i += kMidThreads) {
+  for (int i = tid; i < (DIRECT ? 0 : q.parts * n_px); i += NT) {
     const int line = by_w.quot(i), x = i - line * p.W;                 // (part, channel group, row)
     const int pcg = by_lrp.quot(line), rl = line - pcg * q.lrp;
     const int part = by_cg.quot(pcg), cg = pcg - part * q.cg, row = part * q.lrp + rl;
@@ -320,7 +368,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   // the padding columns x = -1 and x = W stay zero
   const SmallDiv by_lr(q.lr), by_cin(Cin);
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < C8 * (F32 ? 2 : 1) * q.lr * 2; i += kMidThreads) {
+  for (int i = tid; i < C8 * (F32 ? 2 : 1) * q.lr * 2; i += NT) {
     const int side = i & 1, pl = by_lr.quot(i >> 1), r = (i >> 1) - pl * q.lr;
     const int xp = side ? p.W + 1 : 0;
     *reinterpret_cast<u32x4*>(lds + pl * q.plane + (r * q.wpx + (S == 1 ? xp : (xp & 1) * q.xh + (xp >> 1))) * 16) = u32x4{0, 0, 0, 0};
@@ -328,7 +376,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   // slot table: k-step ks, lane half hh -> byte offset of its channels (tap, cin) from the window's first pixel.  Slots
   // beyond 9 Cin meet zero weights; entries behind the last step are only ever fetched ahead.
 #pragma clang loop unroll(disable)
-  for (int i = tid; i < q.nks * 2 + kMidTabPad; i += kMidThreads) {
+  for (int i = tid; i < q.nks * 2 + kMidTabPad; i += NT) {
     const int kk0 = F32 ? i : 8 * i;                                   // fp32: k-step i / 2, lane half i % 2 -> slot i
     const int tap = by_cin.quot(kk0), cin = kk0 - tap * Cin;
     const int ky = (tap * 11) >> 5, kx = tap - ky * 3;                 // tap / 3 for the nine taps
@@ -346,7 +394,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   auto make_lut = [&](int first) {                                     // first: weight index of the group's first frame
     const int n_lut = sums ? q.nb << KP : KP == 8 ? 256 : 1 << (2 * KP);
 #pragma clang loop unroll(disable)
-    for (int i = tid; i < n_lut; i += kMidThreads) {
+    for (int i = tid; i < n_lut; i += NT) {
       // low KP bits: a channel's frames; the bits above: the pair's second channel, or the chunk of frames
       uint32_t a[2] = {0, 0};
       const int second = sums || KP == 8 ? 0 : i >> KP, j0 = first + (sums ? (i >> KP) * KP : 0);
@@ -365,8 +413,8 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   const int v_row = q.flatten ? 0 : oy0;
   LaneGeom lg;
   uint32_t pix_base[NNP];
-  const int word_w = q.wb == 1 ? 0 : wave & 1;
-  const int rg_w = (q.wb == 1 ? wave : wave >> 1) * NNP;               // the wave's first row group; block np: row group + np
+  const int word_w = SPLIT || q.wb == 1 ? 0 : wave & 1;
+  const int rg_w = SPLIT ? px_wave : (q.wb == 1 ? wave : wave >> 1) * NNP;      // the wave's first row group; block np: row group + np
 #pragma unroll
   for (int np = 0; np < 2; ++np) { lg.ok[np] = false; lg.theta[np] = __builtin_inff(); lg.v_off[np] = 0; }
 #pragma unroll
@@ -384,33 +432,36 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   const size_t v_wave = ((size_t)b0 * p.Cout + co0) * plane + (size_t)v_row * p.Wo;
   const bool wave_active = rg_w < q.trg && rg_w * q.rpb < rows_valid;  // wave-uniform
 
-  float V[NMC][NNP][16];
+  constexpr int kRegs = 16 / kShare;         // registers of a block that the wave steps, from r0 on
+  const int r0 = SPLIT ? k_part * kRegs : 0;
+  float V[NMC][NNP][kRegs];
 #pragma unroll
   for (int mc = 0; mc < NMC; ++mc)
 #pragma unroll
     for (int np = 0; np < NNP; ++np)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) V[mc][np][r] = 0.f;
+      for (int r = 0; r < kRegs; ++r) V[mc][np][r] = 0.f;
   if (p.v_inout) {
 #pragma unroll
     for (int mc = 0; mc < NMC; ++mc)
 #pragma unroll
       for (int np = 0; np < NNP; ++np)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
+        for (int r = 0; r < kRegs; ++r) {
+          const int c = mc * 32 + 8 * ((r0 + r) >> 2) + ((r0 + r) & 3);
           if (lg.ok[np] && c < lg.co_lim)
             V[mc][np][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p.v_inout + v_wave) +
                                                            (size_t)c * plane * 4 + lg.v_off[np]);
         }
   }
 
-  // ---- output words: lane (r << 2) | (hi << 1) | np holds channel 8 (r / 4) + 4 hi + r % 4, pixel block np
-  const int st_r = lane >> 2, st_hi = (lane >> 1) & 1, st_np = lane & 1;
+  // ---- output words: lane (r << 2) | (hi << 1) | np holds channel 8 (r / 4) + 4 hi + r % 4, pixel block np.  SPLIT: lane 2 kRegs j + 2 i + hi,
+  // register r0 + i of the j-th step in hand
+  const int st_r = SPLIT ? r0 + ((lane % (2 * kRegs)) >> 1) : lane >> 2, st_hi = SPLIT ? lane & 1 : (lane >> 1) & 1, st_np = SPLIT ? 0 : lane & 1;
   const int st_co = co0 + 8 * (st_r >> 2) + 4 * st_hi + (st_r & 3);
   const int Wwo = (p.Wo + 31) >> 5;
   const int st_rr = (rg_w + st_np) * q.rpb;                            // the block's first tile row
-  const bool st_ok = st_np < NNP && rg_w + st_np < q.trg;
+  const bool st_ok = st_np < NNP && rg_w + st_np < q.trg && (!SPLIT || lane < 8 * kRegs);
   const int st_bsel = sample_of(st_rr), st_b = b0 + st_bsel, st_oy = oy0 + st_rr - st_bsel * p.Ho;
   const int out_rows = p.out_pool ? p.Ho >> 1 : p.Ho;                  // stored rows and words per channel
   const int out_words = p.out_pool ? 1 : Wwo;
@@ -474,6 +525,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   // (Single frames have two aggregates, 0 and the weight: a mask and the weight take the place of the table: two layers at
   // 26 x 26 in fp32 160 -> 149 us.)
   const uint32_t one = KP != 1 ? 0u : sums ? p.wq[0] : pack_bf16((float)p.wq[0] * scale, (float)p.wq[0] * scale);
+  u32x2 own_px[2];
   auto build_job = [&](int job) {
     uint8_t* const pl = lds + (job >> q.parts_shift) * q.cg * (F32 ? 2 : 1) * q.plane;
     const u32x2* const px_part = pxt + (job & (q.parts - 1)) * n_px;
@@ -483,6 +535,10 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
         u32x4 c0[PX], c1[PX], v[PX];
 #pragma unroll
         for (int k = 0; k < PX; ++k) {
+          if (SPLIT && PX <= 2 && own_job && n_px <= 128) {
+            px[k] = own_px[k];
+            continue;
+          }
           px[k] = px_part[min(e0 + 64 * k, n_px - 1)];
           if (e0 + 64 * k >= n_px) px[k][1] = kNone;
         }
@@ -518,7 +574,12 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       if constexpr (KP == 1) {
         for (; e0 - lane + 64 < n_px; e0 += 128) pass(std::integral_constant<int, 2>{}, e0);
       } else {
-        for (; e0 - lane + 64 < n_px; e0 += 256) pass(std::integral_constant<int, 4>{}, e0);
+        // (128 pixels of a job are a pass of two)
+        for (; e0 - lane + 128 < n_px; e0 += 256) pass(std::integral_constant<int, 4>{}, e0);
+        if (e0 - lane + 64 < n_px) {
+          pass(std::integral_constant<int, 2>{}, e0);
+          e0 += 128;
+        }
       }
       if (e0 - lane < n_px) pass(std::integral_constant<int, 1>{}, e0);                  // 64 or fewer are left
       return;
@@ -578,7 +639,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       const uint32_t w0 = p.wq[p.K - Kg], w1 = KP == 2 && Kg == 2 ? p.wq[1] : 0u;
 #pragma unroll
       for (int i = 0; i < kMidDirect; ++i) {
-        if (i > 0 && i * kMidThreads >= C8 * q.lr * p.W) break;
+        if (i > 0 && i * NT >= C8 * q.lr * p.W) break;
         const uint32_t keep = d_off[i] >> 31 ? 0u : 0xffffffffu, sh = d_dst[i] >> 24 & 31;
         uint32_t a[8];
 #pragma unroll
@@ -608,12 +669,28 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
     }
   };
 
+  // SPLIT: where the wave's k-steps find their channels and taps
+  int32_t tab_own[kOwn][SPLIT ? kMidRangeSteps : 1];
+  if constexpr (SPLIT) {
+    __syncthreads();                           // the tables
+    if (!DIRECT && own_job) {
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        own_px[k] = pxt[(wave & (q.parts - 1)) * n_px + min(lane + 64 * k, n_px - 1)];
+        if (lane + 64 * k >= n_px) own_px[k][1] = kNone;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i)
+#pragma unroll
+      for (int k = 0; k < kMidRangeSteps; ++k) tab_own[i][k] = tab[2 * min(range_start(i) + k, q.nks - 1) + h];
+  }
   size_t step = 0;
   for (int g = 0; g < n_groups; ++g) {
     const bool last = g == p.G;                // the shorter last group
     const int Kg = frames_of(g), n_lif = last ? mp.n_lif_last : p.n_lif;
     const float decay = last ? mp.decay_last : p.decay;
-    __syncthreads();                           // the previous group's fragment reads are done (first group: the tables are made)
+    if (!SPLIT) __syncthreads();               // the previous group's fragment reads are done (first group: the tables are made)
     if ((g == 0 || last) && !DIRECT) {
       make_lut(last ? p.K - mp.K_last : 0);    // a shorter last group's weights are the last of a whole group's
       __syncthreads();
@@ -623,19 +700,101 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       build_direct(Kg);
       load_direct(min(g + 1, n_groups - 1));     // behind the last group it is asked for again
     }
-    for (int job = wave; !DIRECT && job < q.n_jobs && wave < q.loaders; job += q.loaders) {
+    const int loaders = SPLIT ? 2 * q.loaders : q.loaders;
+    for (int job = wave; !DIRECT && job < q.n_jobs && wave < loaders; job += loaders) {
       for (int batch = 0; batch < q.batches; ++batch) {
         store_batch(Kg, job, batch);
-        const bool more = batch + 1 < q.batches, next_job = job + q.loaders < q.n_jobs;
+        const bool more = batch + 1 < q.batches, next_job = job + loaders < q.n_jobs;
         // what to request next; behind the last batch of the call any batch will do
-        load_batch(more || next_job ? g : min(g + 1, n_groups - 1), more ? job : next_job ? job + q.loaders : job0, more ? batch + 1 : 0);
+        load_batch(more || next_job ? g : min(g + 1, n_groups - 1), more ? job : next_job ? job + loaders : job0, more ? batch + 1 : 0);
       }
       asm volatile("" ::: "memory");           // the wave's own LDS accesses execute in order; keep the compiler to it too
       build_job(job);
       asm volatile("" ::: "memory");
     }
-    if (g == 0) lds_dma_wait();                // the weights
+    if (!SPLIT && g == 0) lds_dma_wait();      // the weights
     __syncthreads();
+    if constexpr (SPLIT) {
+      // ---- 2. this wave's k-steps
+      if (wave_active) {
+        f32x16 sum[kOwn];
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+          const int k0 = range_start(i), n_k = range_start(i + 1) - k0;
+          bf16x8 af[kMidRangeSteps];
+#pragma unroll
+          for (int k = 0; k < kMidRangeSteps; ++k) af[k] = *reinterpret_cast<const bf16x8*>(lds + pix_base[0] + (uint32_t)tab_own[i][k]);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[i][r] = 0.f;
+#pragma unroll
+          for (int k = 0; k < kMidRangeSteps; ++k)
+            if (k < n_k) sum[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_own[i][k], af[k], sum[i], 0, 0, 0);
+        }
+#pragma unroll
+        for (int d = 1; d < kOwn; d *= 2)
+#pragma unroll
+          for (int i = 0; i + d < kOwn; i += 2 * d)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) sum[i][r] += sum[i + d][r];
+        f32x2* const part = reinterpret_cast<f32x2*>(lds + q.off_part) + wave * 512 + lane;        // [wave][register pair][lane]
+#pragma unroll
+        for (int r2 = 0; r2 < 8; ++r2) part[r2 * 64] = f32x2{sum[0][2 * r2], sum[0][2 * r2 + 1]};
+      }
+      __syncthreads();
+      if (!wave_active) { step += n_lif; continue; }
+      // ---- 3. the block's partial sums of the wave's registers, LIF steps
+      float y[kRegs];
+      {
+        f32x2 in[SPLIT][kRegs / 2];
+        const f32x2* const part = reinterpret_cast<const f32x2*>(lds + q.off_part) + px_wave * SPLIT * 512 + (r0 / 2) * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < SPLIT; ++k)
+#pragma unroll
+          for (int r2 = 0; r2 < kRegs / 2; ++r2) in[k][r2] = part[k * 512 + r2 * 64];
+#pragma unroll
+        for (int d = 1; d < SPLIT; d *= 2)
+#pragma unroll
+          for (int k = 0; k + d < SPLIT; k += 2 * d)
+#pragma unroll
+            for (int r2 = 0; r2 < kRegs / 2; ++r2) {
+              in[k][r2][0] += in[k + d][r2][0];
+              in[k][r2][1] += in[k + d][r2][1];
+            }
+#pragma unroll
+        for (int r = 0; r < kRegs; ++r) y[r] = in[0][r >> 1][r & 1] + bias_lds[8 * ((r0 + r) >> 2) + 4 * h + ((r0 + r) & 3)];
+      }
+      // up to four steps' words are gathered, 2 kRegs lanes each, and stored together: a step of two or four registers is shorter than
+      // what leads to its store
+      for (int j0 = 0; j0 < n_lif; j0 += 4) {
+        uint32_t word[1][2] = {{0u, 0u}};
+        static_for<0, 4>([&](auto j_) {
+          constexpr int j = decltype(j_)::value;
+          if (j > 0 && j0 + j >= n_lif) return;                        // (uniform)
+          [[maybe_unused]] char* const tl = reinterpret_cast<char*>(p.v_trace + (step + j) * ((size_t)p.B * p.Cout * plane) + v_wave);
+          static_for<0, kRegs / 2>([&](auto r2_) {
+            constexpr int r = decltype(r2_)::value * 2;
+            float v[2];
+            uint64_t m[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              v[i] = fmaf(decay, V[0][0][r + i], y[r + i]);
+              m[i] = __builtin_amdgcn_ballot_w64(v[i] >= lg.theta[0]);
+            }
+            const uint32_t x[2][2] = {{(uint32_t)m[0], (uint32_t)(m[0] >> 32)}, {(uint32_t)m[1], (uint32_t)(m[1] >> 32)}};
+            word[0][0] = write_lanes<j * 2 * kRegs + 2 * r, 2, 1>(word[0][0], x);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+              V[0][0][r + i] = __builtin_amdgcn_inverse_ballot_w64(m[i]) ? v[i] - p.theta : v[i];
+              const int c = 8 * ((r0 + r + i) >> 2) + ((r0 + r + i) & 3);
+              if (TRACE && lg.ok[0] && c < lg.co_lim) *reinterpret_cast<float*>(tl + (size_t)c * plane * 4 + lg.v_off[0]) = v[i];
+            }
+          });
+        });
+        if (lane < 2 * kRegs * (n_lif - j0)) store_words(step + lane / (2 * kRegs), word);
+        step += min(4, n_lif - j0);
+      }
+      continue;
+    } else {
     if (!wave_active) { step += n_lif; continue; }
     // ---- 2. contraction
     f32x16 acc[NMC][NNP];
@@ -750,6 +909,7 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
       lif_step<NMC, 64, TRACE, NNP>(V, acc, decay, p.theta, lg, word, tl, plane);
       store_words(step, word);
     }
+    }
   }
 
   if (p.v_inout) {
@@ -758,8 +918,8 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
 #pragma unroll
       for (int np = 0; np < NNP; ++np)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int c = mc * 32 + 8 * (r >> 2) + (r & 3);
+        for (int r = 0; r < kRegs; ++r) {
+          const int c = mc * 32 + 8 * ((r0 + r) >> 2) + ((r0 + r) & 3);
           if (lg.ok[np] && c < lg.co_lim)
             *reinterpret_cast<float*>(reinterpret_cast<char*>(p.v_inout + v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) =
                 V[mc][np][r];
@@ -767,23 +927,25 @@ __global__ __launch_bounds__(kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && N
   }
 }
 
-template <int KP, int NMC, int NNP, bool TRACE, bool F32>
+template <int KP, int NMC, int NNP, bool TRACE, bool F32, int SPLIT = 0>
 hipError_t mid_launch_t(const MidParams& p, hipStream_t s) {
-  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, false>;
+  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, false, SPLIT>;
   if constexpr (KP <= 2) {
-    if (p.q.direct) kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, true>;
+    if (p.q.direct) kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, true, SPLIT>;
   }
   if (p.q.total > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
   const dim3 grid((unsigned)p.q.row_tiles * (unsigned)p.q.co_tiles, 1, p.q.flatten ? 1 : p.m.B);
-  hipLaunchKernelGGL(kern, grid, dim3(kMidThreads), p.q.total, s, p);
+  hipLaunchKernelGGL(kern, grid, dim3(SPLIT ? 512 : kMidThreads), p.q.total, s, p);
   return hipGetLastError();
 }
 
 template <int KP, bool TRACE>
 hipError_t mid_launch_bf16_kp(const MidParams& p, int nmc, int nnp, hipStream_t s) {
+  if (p.q.split == 8) return mid_launch_t<KP, 1, 1, TRACE, false, 8>(p, s);
+  if (p.q.split == 4) return mid_launch_t<KP, 1, 1, TRACE, false, 4>(p, s);
   if (nmc == 1) return nnp == 1 ? mid_launch_t<KP, 1, 1, TRACE, false>(p, s) : mid_launch_t<KP, 1, 2, TRACE, false>(p, s);
   return nnp == 1 ? mid_launch_t<KP, 2, 1, TRACE, false>(p, s) : mid_launch_t<KP, 2, 2, TRACE, false>(p, s);
 }
