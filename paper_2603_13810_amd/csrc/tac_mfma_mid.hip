@@ -90,10 +90,11 @@ double mid_job_cycles(const MidPlan& q, const LayerParams& p) {
 
 // The plan of one tile shape, or false when it does not fit the LDS.  pw_shift: lanes per row of a block (their log2),
 // trg: row groups per tile.
-bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w, int split = 0) {
+bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw_shift, int trg, bool flatten, int nmc_w, int split = 0, int nco = 1) {
   const bool f32 = !p.bf16;
-  const int threads = split ? 512 : kMidThreads, four = split ? 2 : 1;         // loaders counts waves of every four
+  const int four = split ? 2 : nco, threads = four * kMidThreads;      // loaders counts waves of every four
   q.split = split;
+  q.nco = nco;
   const int S = p.stride, C8 = p.Cin / 8;
   q.pw_shift = pw_shift;
   q.rpb = 32 >> q.pw_shift;
@@ -106,7 +107,7 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   const int samples = flatten ? std::min((q.tr + p.Ho - 2) / p.Ho + 1, p.B) : 1;        // a tile may touch
   q.lr = (q.tr - 1) * S + 3 + (samples - 1) * (3 - S);
   q.row_tiles = (int)((rows + q.tr - 1) / q.tr);
-  q.co_tiles = (p.Cout + nmc * 32 - 1) / (nmc * 32);
+  q.co_tiles = (p.Cout + nco * nmc * 32 - 1) / (nco * nmc * 32);
   q.srows = p.pool2 ? 2 : 1;
   q.wws = p.Wwi;
   q.hs = p.Hs;
@@ -119,7 +120,7 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   q.nks = mid_k_steps(p.Cin, f32);
   q.nmc_w = nmc_w;
   auto up = [](int x) { return (x + 15) & ~15; };
-  const int w_bytes = split ? 0 : q.nks * nmc * (f32 ? 256 : 1024);
+  const int w_bytes = split ? 0 : q.nks * nco * nmc * (f32 ? 256 : 1024);
   const int ahead = split ? 0 : (2 * mid_depth(nmc, nnp) - 1) * nmc * 1024;    // the fetches ahead read past the weights
   const int parts_bytes = split ? 8 * 4096 : 0;                       // the waves' partial sums, behind everything else
   const bool sums = f32 || q.nb > 1 || p.pool2 == 1;
@@ -127,11 +128,11 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
   q.off_w = q.plane * C8 * (f32 ? 2 : 1);
   q.off_tab = q.off_w + w_bytes;
   q.off_bias = up(q.off_tab + (q.nks * 2 + kMidTabPad) * 4);
-  q.off_wq = q.off_bias + nmc * 32 * 4;
+  q.off_wq = q.off_bias + nco * nmc * 32 * 4;
   q.off_lut = q.off_wq + TAC_MAX_K * 4;
   q.off_unit = up(q.off_lut + lut_entries * 4);
   // groups of one or two frames on few channels: see the kernel's build_direct
-  q.direct = kp <= 2 && (kp == 1 || !p.pool2) && C8 * q.lr * p.W <= kMidDirect * threads;
+  q.direct = nco == 1 && kp <= 2 && (kp == 1 || !p.pool2) && C8 * q.lr * p.W <= kMidDirect * threads;
   if (q.direct) {
     q.n_jobs = 0;
     q.loaders = 4;
@@ -189,7 +190,7 @@ bool mid_plan(MidPlan& q, const LayerParams& p, int kp, int nmc, int nnp, int pw
 double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
   const bool f32 = !p.bf16;
   const double build = q.direct ? 500.0 + 400.0 * ((p.Cin / 8 * q.lr * p.W + kMidThreads - 1) / kMidThreads) * (p.K == 2 || p.pool2 ? 2 : 1)
-                                : (q.n_jobs + q.loaders - 1) / q.loaders * mid_job_cycles(q, p);
+                                : (q.n_jobs + q.nco * q.loaders - 1) / (q.nco * q.loaders) * mid_job_cycles(q, p);
   // (an fp32 step waits for its operands: a wave alone takes about 90 cycles for one block)
   const double busy = q.nks * (f32 ? 64.0 * nnp : std::max(32.0 * nmc * nnp, 32.0 * (nmc + nnp))) + 300.0;
   const double mfma = f32 ? q.nks * 90.0 * nnp + 300.0 : busy;
@@ -200,8 +201,8 @@ double mid_cost(const MidPlan& q, const LayerParams& p, int nmc, int nnp) {
   // room for more than two with one or two accumulator blocks); 1003 workgroups of 8 -> 32 at 59 x 39, four a unit, take as
   // long as 502, two a unit
   const int blocks = nmc * nnp, by_registers = f32 || blocks > 2 || !(q.direct || p.K == 1) ? 2 : blocks == 1 ? 4 : 3;
-  const int resident = std::min(by_registers, kMidLds / q.total);
-  const double together = std::min<double>(resident, per_cu);
+  const int resident = std::min(q.nco == 1 ? by_registers : 1, kMidLds / q.total);
+  const double together = std::min<double>(resident, per_cu) * q.nco;         // sets of four waves
   const double alone = 9000.0 + p.G * (build + mfma + lif + 500.0);
   const double shared = p.G * busy;                                     // what other workgroups cannot hide
   return std::ceil(per_cu / resident) * std::max(alone * (together > 1 ? 1.1 + 0.025 * together : 1.0), together * shared);
@@ -288,19 +289,21 @@ static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, 
       }
     if (found) return true;
   }
+  const int max_nco = f32 && kp > 1 && p.Cin >= 16 && p.Cout > 32 ? 2 : 1;
   // as many rows per block as its lanes hold; fewer only where such a tile does not fit the LDS
   for (int pw = p.Wo > 16 ? 5 : p.Wo > 8 ? 4 : p.Wo > 4 ? 3 : p.Wo > 2 ? 2 : 1; pw <= 5 && !found; ++pw)
-    for (int c = 1; c <= (f32 || p.Cout <= 32 ? 1 : 2); ++c)
+   for (int nco = 1; nco <= max_nco; ++nco)
+    for (int c = 1; c <= (f32 || p.Cout <= 32 || nco > 1 ? 1 : 2); ++c)
       for (int x = 2; x >= 1; --x)
         for (int trg = 4 * x / wb; trg >= 1; trg >>= 1) {
           // pooled output, one row per block: the wave's two blocks are the two rows of a pooled row
           const bool pairs = p.out_pool && pw == 5;
           if (pairs && (x == 1 || trg < 2)) continue;
-          if (f32 && x == 2 && !pairs) continue;              // two blocks with four partial sums each: one wave per SIMD
+          if (f32 && x == 2 && (!pairs || nco > 1)) continue; // two blocks with four partial sums each: one wave per SIMD
           for (int fl = may_flatten ? 1 : 0; fl >= 0; --fl) {
             MidPlan q;
-            if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w)) continue;
-            const double cost = mid_cost(q, p, c, x);
+            if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w, 0, nco)) continue;
+            const double cost = mid_cost(q, p, c, x) * (nco > 1 ? 1.05 : 1.0);     // (where the estimates are close it is not faster)
             // of equals the one that does not straddle samples, and of tiles that all have a compute unit to themselves the
             // smaller one, both of which are tried later
             const long long wgs = (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);

@@ -63,6 +63,7 @@ struct MidPlan {
   int wpx, xh, plane;           // columns of the aggregate tile, of its even half (stride 2), bytes per channel group
   int nks, nmc_w;               // k-steps; 32-channel blocks per tile of the prepared weights
   int off_w, off_tab, off_bias, off_wq, off_unit, off_px, off_lut, off_stage, stage_wave, total;
+  int nco;                      // tiles of output channels per workgroup, four waves each, over one aggregate tile
   int split, off_part;          // eight waves, `split` of which share a pixel block (0: four waves with blocks of their own); their partial sums
 };
 
@@ -105,11 +106,19 @@ struct SmallDiv {
 // four steps leave in one store.  128 -> 128, B = 16, TAC-TP K = 4, 16 frames, pooled, us a call before and now: 16 x 16 33.3 / 23.5, 8 x 8
 // 29.8 / 19.5, 4 x 4 31.0 / 18.4 (with membranes 48 / 28, 43 / 22, 44 / 20).  Of the 18.4 the products are less than one: what
 // remains is forming the aggregates (two thirds) and the chain of barriers and LDS trips.
-template <int KP, int NMC, int NNP, bool TRACE, bool F32, bool DIRECT, int SPLIT = 0>
-__global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4) || (F32 && NNP == 2) ? 1 : 2) void mid_kernel(const MidParams mp) {
+//
+// NCO (fp32).  Four waves per tile of output channels, NCO tiles over one aggregate tile, which is formed once for them instead of
+// once per 32 channels: 32 -> 64 at 14 x 14 behind the mean pool, B = 128, 25 frames, groups of 8 81 -> 69 us, groups of 4 with membranes
+// 124 -> 115.  (bf16 layers have their 64-channel tiles; two or three tiles of 32 over one aggregate tile were not faster: 48 -> 80 at
+// 45 x 45 99 us so or so, 32 -> 128 at 40 x 40 72 -> 80 and 100, one large workgroup in step with itself against two that fill each
+// other's gaps.)
+template <int KP, int NMC, int NNP, bool TRACE, bool F32, bool DIRECT, int SPLIT = 0, int NCO = 1>
+__global__ __launch_bounds__(SPLIT ? 512 : kMidThreads * NCO,
+                             NCO == 1 && ((TRACE && NMC * NNP == 4) || (F32 && NNP == 2)) ? 1 : 2) void mid_kernel(const MidParams mp) {
   static_assert(!F32 || NMC == 1, "fp32: 32-channel tiles (the partial sums take the registers of a second block)");
-  static_assert(!SPLIT || (NMC * NNP == 1 && !F32), "waves that share a pixel block: one block of bf16 operands");
-  constexpr int NT = SPLIT ? 512 : kMidThreads, NW = NT / 64;
+  static_assert(NCO == 1 || F32, "tiles of several channel blocks: fp32");
+  static_assert(!SPLIT || (NMC * NNP == 1 && !F32 && NCO == 1), "waves that share a pixel block: one block of bf16 operands");
+  constexpr int NT = SPLIT ? 512 : kMidThreads * NCO;
   constexpr uint32_t kNone = 0xffffffffu;
   const MfmaParams& p = mp.m;
   const MidPlan& q = mp.q;
@@ -128,14 +137,16 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
   const int oy0 = q.flatten ? first_row - b0 * p.Ho : first_row;
   const int rows_valid = min(q.tr, (q.flatten ? p.B * p.Ho : p.Ho) - first_row);
   auto sample_of = [&](int rr) { return q.flatten ? by_ho.quot(oy0 + rr) : 0; };     // tile row -> sample - b0
-  const int co0 = co_tile * (NMC * 32);
+  const int px4 = NCO == 1 || SPLIT ? wave : wave & 3, co_grp = NCO == 1 ? 0 : wave >> 2;      // the wave among the four of its channels
+  const int co_first = co_tile * (NCO * NMC * 32), co0 = co_first + co_grp * (NMC * 32);
   const size_t plane = (size_t)p.Ho * p.Wo;
   const size_t in_chan = (size_t)q.hs * q.wws;
   const size_t t_stride = (size_t)p.B * Cin * in_chan;
 
-  uint8_t* const w_lds = lds + q.off_w;
+  uint8_t* const w_lds = lds + q.off_w + co_grp * q.nks * NMC * (F32 ? 256 : 1024);
   int32_t* const tab = reinterpret_cast<int32_t*>(lds + q.off_tab);
-  float* const bias_lds = reinterpret_cast<float*>(lds + q.off_bias);
+  float* const bias_all = reinterpret_cast<float*>(lds + q.off_bias);
+  const float* const bias_lds = bias_all + co_grp * (NMC * 32);
   u32x2* const unit = reinterpret_cast<u32x2*>(lds + q.off_unit);
   u32x2* const pxt = reinterpret_cast<u32x2*>(lds + q.off_px);
   uint32_t* const lut = reinterpret_cast<uint32_t*>(lds + q.off_lut);
@@ -156,16 +167,16 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
         w_own[i][k] = *reinterpret_cast<const bf16x8*>(src + (size_t)min(range_start(i) + k, q.nks - 1) * q.nmc_w * 1024);
   } else {
     if constexpr (F32) {
-      const uint8_t* const src = p.w + (size_t)co_tile * q.nks * 256 + lane * 16;
-      for (int f = wave; f < q.nks / 4; f += 4) lds_dma16<1, 0>(src + (size_t)f * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + f * 1024));
+      const uint8_t* const src = p.w + (co0 < p.Cout ? (size_t)(co_tile * NCO + co_grp) * q.nks * 256 : (size_t)0) + lane * 16;
+      for (int f = px4; f < q.nks / 4; f += 4) lds_dma16<1, 0>(src + (size_t)f * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + f * 1024));
     } else {
 #pragma unroll
       for (int mc = 0; mc < NMC; ++mc) {
-        const int blk = co_tile * NMC + mc, tile = blk / q.nmc_w;
+        const int blk = (co_tile * NCO + co_grp) * NMC + mc, tile = blk / q.nmc_w;
         // (a block beyond the channels is multiplied but never stored)
         const uint8_t* const src =
             p.w + (blk * 32 < p.Cout ? ((size_t)tile * q.nks * q.nmc_w + (blk - tile * q.nmc_w)) * 1024 : (size_t)0) + lane * 16;
-        for (int ks = wave; ks < q.nks; ks += 4)
+        for (int ks = px4; ks < q.nks; ks += 4)
           lds_dma16<1, 0>(src + (size_t)ks * q.nmc_w * 1024, (uint32_t)(uintptr_t)(lds_void_ptr)(w_lds + (ks * NMC + mc) * 1024));
       }
     }
@@ -386,7 +397,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
   }
   uint32_t* const wq = reinterpret_cast<uint32_t*>(lds + q.off_wq);    // read with lane-dependent indices below
   if (tid < TAC_MAX_K) wq[tid] = p.wq[tid];
-  if (tid < NMC * 32) bias_lds[tid] = (p.bias && co0 + tid < p.Cout) ? p.bias[co0 + tid] : 0.f;
+  if (tid < NCO * NMC * 32) bias_all[tid] = (p.bias && co_first + tid < p.Cout) ? p.bias[co_first + tid] : 0.f;
   // aggregates by frame bits: pairs of channels as two bf16 (groups of up to four frames), one bf16 (up to eight), or
   // 2^-23 fixed-point sums per chunk of eight frames (more frames, the mean pool's counts, fp32)
   const bool sums = F32 || q.nb > 1 || p.pool == 1;
@@ -413,8 +424,8 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
   const int v_row = q.flatten ? 0 : oy0;
   LaneGeom lg;
   uint32_t pix_base[NNP];
-  const int word_w = SPLIT || q.wb == 1 ? 0 : wave & 1;
-  const int rg_w = SPLIT ? px_wave : (q.wb == 1 ? wave : wave >> 1) * NNP;      // the wave's first row group; block np: row group + np
+  const int word_w = SPLIT || q.wb == 1 ? 0 : px4 & 1;
+  const int rg_w = SPLIT ? px_wave : (q.wb == 1 ? px4 : px4 >> 1) * NNP;      // the wave's first row group; block np: row group + np
 #pragma unroll
   for (int np = 0; np < 2; ++np) { lg.ok[np] = false; lg.theta[np] = __builtin_inff(); lg.v_off[np] = 0; }
 #pragma unroll
@@ -430,7 +441,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
   }
   lg.co_lim = p.Cout - co0 - 4 * h;
   const size_t v_wave = ((size_t)b0 * p.Cout + co0) * plane + (size_t)v_row * p.Wo;
-  const bool wave_active = rg_w < q.trg && rg_w * q.rpb < rows_valid;  // wave-uniform
+  const bool wave_active = rg_w < q.trg && rg_w * q.rpb < rows_valid && (NCO == 1 || co0 < p.Cout);      // wave-uniform
 
   constexpr int kRegs = 16 / kShare;         // registers of a block that the wave steps, from r0 on
   const int r0 = SPLIT ? k_part * kRegs : 0;
@@ -700,7 +711,7 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
       build_direct(Kg);
       load_direct(min(g + 1, n_groups - 1));     // behind the last group it is asked for again
     }
-    const int loaders = SPLIT ? 2 * q.loaders : q.loaders;
+    const int loaders = NT / 256 * q.loaders;
     for (int job = wave; !DIRECT && job < q.n_jobs && wave < loaders; job += loaders) {
       for (int batch = 0; batch < q.batches; ++batch) {
         store_batch(Kg, job, batch);
@@ -927,10 +938,10 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads, (TRACE && NMC * NNP == 4
   }
 }
 
-template <int KP, int NMC, int NNP, bool TRACE, bool F32, int SPLIT = 0>
+template <int KP, int NMC, int NNP, bool TRACE, bool F32, int SPLIT = 0, int NCO = 1>
 hipError_t mid_launch_t(const MidParams& p, hipStream_t s) {
-  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, false, SPLIT>;
-  if constexpr (KP <= 2) {
+  auto kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, false, SPLIT, NCO>;
+  if constexpr (KP <= 2 && NCO == 1) {
     if (p.q.direct) kern = &mid_kernel<KP, NMC, NNP, TRACE, F32, true, SPLIT>;
   }
   if (p.q.total > 64 * 1024) {
@@ -938,7 +949,7 @@ hipError_t mid_launch_t(const MidParams& p, hipStream_t s) {
     if (e != hipSuccess) return e;
   }
   const dim3 grid((unsigned)p.q.row_tiles * (unsigned)p.q.co_tiles, 1, p.q.flatten ? 1 : p.m.B);
-  hipLaunchKernelGGL(kern, grid, dim3(SPLIT ? 512 : kMidThreads), p.q.total, s, p);
+  hipLaunchKernelGGL(kern, grid, dim3(SPLIT ? 512 : kMidThreads * NCO), p.q.total, s, p);
   return hipGetLastError();
 }
 
@@ -952,6 +963,9 @@ hipError_t mid_launch_bf16_kp(const MidParams& p, int nmc, int nnp, hipStream_t 
 
 template <int KP, bool TRACE>
 hipError_t mid_launch_f32_kp(const MidParams& p, int nnp, hipStream_t s) {
+  if constexpr (KP >= 2) {
+    if (p.q.nco == 2) return mid_launch_t<KP, 1, 1, TRACE, true, 0, 2>(p, s);
+  }
   return nnp == 1 ? mid_launch_t<KP, 1, 1, TRACE, true>(p, s) : mid_launch_t<KP, 1, 2, TRACE, true>(p, s);
 }
 

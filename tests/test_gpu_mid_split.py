@@ -39,3 +39,21 @@ def test_waves_that_share_a_pixel_block(case):
                               **(dict(oracle_samples=[0, 1, B - 1]) if B > 8 else {}))
     assert ref[0].any()
     print(case, par)
+
+
+# fp32 layers: two tiles of 32 output channels over one aggregate tile; a last workgroup with one of them, a tile of few channels
+@pytest.mark.parametrize("case", [(2, 32, 96, 9, 14, 1, True, TAC, 4, 9), (1, 16, 33, 7, 20, 2, False, TP, 3, 7), (3, 40, 130, 5, 6, 1, False, TAC, 16, 17)],
+                         ids=["three tiles", "a second tile of one channel", "five tiles, a last group of one"])
+def test_two_channel_tiles_over_one_aggregate_tile_fp32(case):
+    B, Cin, Cout, H, W, stride, pool, mode, K, T = case
+    r = np.random.Generator(np.random.PCG64(6700 + Cin + Cout + K))
+    f = 2 if pool else 1
+    s = (r.random((T, B, Cin, f * H, f * W)) < 0.12).astype(np.uint8)
+    w = synth.kaiming_normal(64, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    v0 = (r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32)
+    par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, pool2=pool, precision=api.TAC_FP32, bias=bias, v0=v0,
+                              expect_kernel=api.TAC_KERNEL_MFMA)
+    assert ref[0].any()
+    print(case, par)
