@@ -61,9 +61,18 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
     for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
   float bias_acc[2] = {0.0f, 0.0f};                      // of the channels lane / 4 and 16 + lane / 4 (loading order)
 
+  // A slice is a stretch of the list, so that a strip finds its first two rows in LDS, built for the strip above it: the rows are a ring,
+  // tile row r of the strip from image row y0 on in slot (y0 + r) % (R + 2), and only the R new ones are built, which is also one pass of
+  // the workgroup less.  16 pixels wide, an image is one strip as a rule and every n_split-th strip stays 1 to 2 % faster.  Backward calls without
+  // input gradient by rebuilt strips / by this (us): 256 -> 128 at 128 x 128, B = 32, one group 917 / 813; 256 -> 128 at 64 x 64, B = 8, two
+  // groups 110 / 100; max-pooled frames, 96 -> 128 at 128 x 128, three groups of four 3124 / 2647.
   const int items = p.G * p.B * n_strips;
-  for (int it = blockIdx.x; it < items; it += n_split) {
+  const int share = items / n_split, rest = items - share * n_split;
+  const int first = (int)blockIdx.x * share + min((int)blockIdx.x, rest), last = first + share + ((int)blockIdx.x < rest ? 1 : 0);
+  for (int it = XS == 1 ? (int)blockIdx.x : first; it < (XS == 1 ? items : last); it += XS == 1 ? n_split : 1) {
     const int strip = it % n_strips, kb = it / n_strips;
+    const int r_new = XS == 1 || it == first || strip == 0 ? 0 : 2;    // first tile row to be built
+    const int slot0 = XS == 1 ? 0 : (strip * R) % rows_in;
     const int b = kb % p.B, k = kb / p.B;
     const int Kg = group_frames(p, k);
     const float* wj = Kg == p.K ? p.wj : p.wj_last;
@@ -131,8 +140,8 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
     auto stage_request = [&](int pass, int j0) {
       const int e = tid + pass * NT;
       const int wi = e % WWI, cr = e / WWI;
-      const int ci = cr % (32 * NCB), iy = y0 - 1 + cr / (32 * NCB);
-      if (e < 32 * NCB * rows_in * WWI && iy >= 0 && iy < p.H) {
+      const int ci = cr % (32 * NCB), iy = y0 - 1 + r_new + cr / (32 * NCB);
+      if (e < 32 * NCB * (rows_in - r_new) * WWI && iy >= 0 && iy < p.H) {
         // wave-uniform address of the (frame, sample) block + the lane's byte offset in it (32 bits: one register)
         const uint32_t* sbase = p.spikes + ((size_t)k * p.K * p.B + b) * p.Cin * p.H * p.Wwi;
         const uint32_t voff = (uint32_t)((((ci0 + ci) * p.H + iy) * p.Wwi + wi) * 4);
@@ -153,10 +162,10 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
     //      written as blocks of eight for kx = 0, 1, 2
     for (int pass = 0; pass < kPasses; ++pass) {
       const int e = tid + pass * NT;
-      if (e >= 32 * NCB * rows_in * WWI) break;
+      if (e >= 32 * NCB * (rows_in - r_new) * WWI) break;
       const int wi = e % WWI, cr = e / WWI;
-      const int ci = cr % (32 * NCB), r = cr / (32 * NCB);            // channel within the workgroup's NCB blocks
-      const int iy = y0 - 1 + r;
+      const int ci = cr % (32 * NCB), r = r_new + cr / (32 * NCB);    // channel within the workgroup's NCB blocks
+      const int iy = y0 - 1 + r, slot = slot0 + r < rows_in ? slot0 + r : slot0 + r - rows_in;
       uint32_t q[34];
 #pragma unroll
       for (int i = 0; i < 34; ++i) q[i] = 0u;
@@ -222,7 +231,7 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
 #pragma unroll
           for (int t = 0; t < 4; ++t)
             v[t] = pack_bf16((float)q[8 * xl + kx + 2 * t] * (1.0f / 8388608.0f), (float)q[8 * xl + kx + 2 * t + 1] * (1.0f / 8388608.0f));
-          *reinterpret_cast<u32x4*>(lds + ((ci >> 5) * 3 + kx) * copy_bytes + ((r * XB + wi * XBW + xl) * 32 + (ci & 31)) * 16) = v;
+          *reinterpret_cast<u32x4*>(lds + ((ci >> 5) * 3 + kx) * copy_bytes + ((slot * XB + wi * XBW + xl) * 32 + (ci & 31)) * 16) = v;
         }
       }
     }
@@ -237,7 +246,7 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
     bf16x8 gf[NGF];
     bf16x8 af[3];
     // one address register per kx copy (opaque to the compiler, which would otherwise keep one per row whose offset
-    // does not fit the instruction's 16 bits); row and column are immediate offsets
+    // does not fit the instruction's 16 bits); the column is an immediate offset, the row's slot a scalar that is added
     uint32_t a_lane[3];
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) {
@@ -245,7 +254,10 @@ __global__ __launch_bounds__(kThreads * NCB, (NCB == 1 && XS <= 4) ? 2 : 1) void
       asm volatile("" : "+v"(a_lane[kx]));
     }
     auto fetch_af = [&](int r, int xs, int kx) {
-      af[kx] = *reinterpret_cast<const bf16x8*>(lds + a_lane[kx] + (r * XB + 2 * xs) * 512);
+      const int slot = slot0 + r < rows_in ? slot0 + r : slot0 + r - rows_in;
+      uint32_t row = (uint32_t)(slot * (XB * 512));
+      if constexpr (XS == 2) asm volatile("" : "+s"(row));              // (no register per row and copy over the columns)
+      af[kx] = *reinterpret_cast<const bf16x8*>(lds + (a_lane[kx] + row) + 2 * xs * 512);
     };
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) fetch_af(0, 0, kx);
