@@ -78,6 +78,11 @@ __device__ __forceinline__ Lanes<VEC> load_lanes(const float* src) {
   }
   return r;
 }
+// four floats that nobody reads again
+__device__ __forceinline__ Lanes<4> load_once(const float* src) {
+  const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src));
+  return Lanes<4>{{t[0], t[1], t[2], t[3]}};
+}
 template <int VEC>
 __device__ __forceinline__ void store_lanes(float* dst, const Lanes<VEC>& a) {
   if constexpr (VEC == 4)
@@ -193,8 +198,9 @@ __global__ __launch_bounds__(kThreads) void lif_backward_kernel(const BackwardPa
 // VEC / 2 windows, so that a membrane is read once (one neuron per thread reads its window's four membranes, five loads
 // for one gradient), the window's route is decided in registers and the pooled gradient is read once.  Bound by HBM on
 // large layers, by the chain of loads over the steps on small ones: 128 channels, B = 16, 16 steps at 64 x 64 / 32 x 32 /
-// 16 x 16 take 161 / 37 / 18 us (one neuron per thread: 540 / 141 / 46 us).
-template <int VEC, int U>
+// 16 x 16 take 140 / 37 / 18 us (one neuron per thread: 540 / 141 / 46 us).
+// ONCE: the membranes are read past the caches (backward_launch).
+template <int VEC, int U, bool ONCE = false>
 __global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const BackwardParams p, int clear) {
   constexpr int WIN = VEC / 2;
   const size_t n_out = (size_t)p.B * p.Cout * p.Ho * p.Wo;
@@ -221,8 +227,14 @@ __global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const Bac
     for (int u = 0; u < U; ++u) {
       if (u < m) {
         const size_t step = (size_t)(n - 1 - u);
-        v[u][0] = load_lanes<VEC>(p.v_trace + step * n_out + i);
-        v[u][1] = load_lanes<VEC>(p.v_trace + step * n_out + i + p.Wo);
+        const float* const src = p.v_trace + step * n_out + i;
+        if constexpr (ONCE) {
+          v[u][0] = load_once(src);
+          v[u][1] = load_once(src + p.Wo);
+        } else {
+          v[u][0] = load_lanes<VEC>(src);
+          v[u][1] = load_lanes<VEC>(src + p.Wo);
+        }
         size_t gstep = step;
         float f = 1.0f;
         if (p.go_K > 1) {
@@ -364,7 +376,12 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
   const bool neurons4 = !p.out_pool && n_out % 4 == 0 && (bases & 15) == 0;
   const size_t threads = windows2 ? n_out / 8 : windows1 || neurons4 ? n_out / 4 : n_out;
   const int clear = !dgrad_tile && backward_clear_in_recurrence(threads, (size_t)p.Cout * p.Cin * 9);
-  if (windows2) hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 2>), blocks(threads), dim3(kThreads), 0, s, p, clear);
+  // Membranes that do not fit the 256 MiB of the last cache are read past it, one step in flight per thread: a backward call without input
+  // gradient of 2 -> 128 at 64 x 64, B = 16, 16 steps (512 MiB) 210 -> 187 us, B = 64 777 -> 738, 2 -> 64 at 128 x 128, B = 4 (256 MiB)
+  // 121 -> 113; below they may still be there: B = 16 at 32 x 32 (128 MiB) 57 -> 61.  Without a pool there is no difference (2062 / 2056).
+  const bool once = windows2 && n_out * (size_t)p.n_steps >= ((size_t)64 << 20);
+  if (once) hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 1, true>), blocks(threads), dim3(kThreads), 0, s, p, clear);
+  else if (windows2) hipLaunchKernelGGL((lif_backward_pooled_kernel<4, 2>), blocks(threads), dim3(kThreads), 0, s, p, clear);
   else if (windows1) hipLaunchKernelGGL((lif_backward_pooled_kernel<2, 4>), blocks(threads), dim3(kThreads), 0, s, p, clear);
   else if (neurons4) hipLaunchKernelGGL((lif_backward_kernel<4, 1>), blocks(threads), dim3(kThreads), 0, s, p, clear);
   else hipLaunchKernelGGL((lif_backward_kernel<1, 4>), blocks(threads), dim3(kThreads), 0, s, p, clear);
