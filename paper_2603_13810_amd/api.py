@@ -55,7 +55,7 @@ def lib() -> ctypes.CDLL:
                                "(there is no CPU fallback for the HIP path)")
         L = ctypes.CDLL(LIB_PATH)
         dp, vp, i32p = ctypes.POINTER(tac_layer_desc_t), ctypes.c_void_p, ctypes.POINTER(ctypes.c_int32)
-        L.tac_out_shape.argtypes = [dp, i32p, i32p, i32p]
+        L.tac_out_shape.argtypes = [dp, vp, vp, vp]
         L.tac_out_shape.restype = ctypes.c_int
         L.tac_packed_bytes.argtypes = [ctypes.c_int32] * 5
         L.tac_packed_bytes.restype = ctypes.c_size_t
@@ -133,10 +133,16 @@ def stored_out_shape(desc: tac_layer_desc_t) -> Tuple[int, int, int]:
     return (T_out, Ho // 2, Wo // 2) if desc.out_format == TAC_OUT_BITS_MAXPOOL2 else (T_out, Ho, Wo)
 
 
+_Shape3 = ctypes.c_int32 * 3
+
+
 def tac_out_shape(desc: tac_layer_desc_t) -> Tuple[int, int, int]:
-    t, h, w = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
-    _check(lib().tac_out_shape(ctypes.byref(desc), ctypes.byref(t), ctypes.byref(h), ctypes.byref(w)))
-    return t.value, h.value, w.value
+    out = _Shape3()
+    at = ctypes.addressof(out)
+    status = lib().tac_out_shape(ctypes.byref(desc), at, at + 4, at + 8)
+    if status != TAC_OK:
+        _check(status)
+    return tuple(out)
 
 
 def tac_packed_bytes(T, B, C, H, W) -> int:
@@ -154,22 +160,23 @@ def tac_prepared_weight_bytes(desc: tac_layer_desc_t) -> int:
     return int(lib().tac_prepared_weight_bytes(ctypes.byref(desc)))
 
 
+# The two below run up to seven times per call: plain integers for the void* arguments, and the current stream's handle without a
+# Stream object (1.0 us).
 def _stream(stream=None):
     if stream is not None:
-        return ctypes.c_void_p(int(stream))
+        return int(stream)
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _dev_ptr(t, dtype=None, name="tensor"):
     if t is None:
         return None
-    import torch
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("%s must be a contiguous device tensor" % name)
     if dtype is not None and t.dtype != dtype:
         raise ValueError("%s must have dtype %s" % (name, dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def tac_prepare_weights(desc, w_oihw, w_prepared=None, stream=None):
@@ -205,15 +212,14 @@ def tac_conv_lif(desc, spikes_packed, w_prepared, bias=None, v_inout=None, out_s
     else:
         f = 1 if fmt == TAC_IN_BITS else 2
         need_in = desc.T * B * desc.Cin * desc.H * f * ((desc.W * f + 31) // 32) * 4
-    have_in = spikes_packed.numel() * spikes_packed.element_size()
-    if have_in != need_in:
-        raise ValueError("spikes_packed has %d bytes, the description needs %d" % (have_in, need_in))
-    if w_prepared.numel() * w_prepared.element_size() < tac_prepared_weight_bytes(desc):
+    if spikes_packed.nbytes != need_in:
+        raise ValueError("spikes_packed has %d bytes, the description needs %d" % (spikes_packed.nbytes, need_in))
+    if w_prepared.nbytes < tac_prepared_weight_bytes(desc):
         raise ValueError("prepared-weight buffer too small for this description")
     Hs, Ws = (Ho // 2, Wo // 2) if desc.out_format == TAC_OUT_BITS_MAXPOOL2 else (Ho, Wo)
     if out_spikes_packed is None:
         out_spikes_packed = torch.empty((T_out, B, Cout, Hs, (Ws + 31) // 32), dtype=torch.int32, device=spikes_packed.device)
-    elif out_spikes_packed.numel() * out_spikes_packed.element_size() != T_out * B * Cout * Hs * ((Ws + 31) // 32) * 4:
+    elif out_spikes_packed.nbytes != T_out * B * Cout * Hs * ((Ws + 31) // 32) * 4:
         raise ValueError("out_spikes_packed has the wrong size")
     if bias is not None and tuple(bias.shape) != (Cout,):
         raise ValueError("bias must be [Cout]")
@@ -343,12 +349,11 @@ def make_stack(layers):
         if L.get("v_trace") is not None and tuple(L["v_trace"].shape) != (T_out, desc.B, desc.Cout, Ho, Wo):
             raise ValueError("layer %d: v_trace must be [T_out,B,Cout,Ho,Wo]" % i)
         arr[i].desc = desc
-        val = lambda p: None if p is None else p.value
-        arr[i].w_prepared = val(_dev_ptr(L["w_prepared"], None, "w_prepared"))
-        arr[i].bias = val(_dev_ptr(L.get("bias"), torch.float32, "bias"))
-        arr[i].v_inout = val(_dev_ptr(L.get("v_inout"), torch.float32, "v_inout"))
-        arr[i].out_spikes_packed = val(_dev_ptr(L["out_spikes_packed"], None, "out_spikes_packed"))
-        arr[i].v_trace = val(_dev_ptr(L.get("v_trace"), torch.float32, "v_trace"))
+        arr[i].w_prepared = _dev_ptr(L["w_prepared"], None, "w_prepared")
+        arr[i].bias = _dev_ptr(L.get("bias"), torch.float32, "bias")
+        arr[i].v_inout = _dev_ptr(L.get("v_inout"), torch.float32, "v_inout")
+        arr[i].out_spikes_packed = _dev_ptr(L["out_spikes_packed"], None, "out_spikes_packed")
+        arr[i].v_trace = _dev_ptr(L.get("v_trace"), torch.float32, "v_trace")
         outs.append(L["out_spikes_packed"])
     return arr, outs
 
@@ -400,10 +405,9 @@ def tac_stack_backward(stack, weights, input, grad_out_last, *, surrogate=TAC_SG
                  if (l > 0 or first_layer_input_grad) else None)
         if tuple(weights[l].shape) != (d.Cout, d.Cin, 3, 3):
             raise ValueError("layer %d: weights must be [Cout,Cin,3,3]" % l)
-        val = lambda p: None if p is None else p.value
-        arr[l].w_oihw = val(_dev_ptr(weights[l], torch.float32, "weights"))
+        arr[l].w_oihw = _dev_ptr(weights[l], torch.float32, "weights")
         for k in ("grad_y", "grad_w", "grad_bias", "grad_in"):
-            setattr(arr[l], k, val(_dev_ptr(g[k])))
+            setattr(arr[l], k, _dev_ptr(g[k]))
         out.append(g)
     bwd = tac_backward_desc_t(surrogate=surrogate, detach_reset=int(bool(detach_reset)), alpha=alpha,
                               grad_in_per_group=int(bool(grad_in_per_group)))
