@@ -292,29 +292,29 @@ static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, 
   const int max_nco = f32 && kp > 1 && p.Cin >= 16 && p.Cout > 32 ? 2 : 1;
   // as many rows per block as its lanes hold; fewer only where such a tile does not fit the LDS
   for (int pw = p.Wo > 16 ? 5 : p.Wo > 8 ? 4 : p.Wo > 4 ? 3 : p.Wo > 2 ? 2 : 1; pw <= 5 && !found; ++pw)
-   for (int nco = 1; nco <= max_nco; ++nco)
-    for (int c = 1; c <= (f32 || p.Cout <= 32 || nco > 1 ? 1 : 2); ++c)
-      for (int x = 2; x >= 1; --x)
-        for (int trg = 4 * x / wb; trg >= 1; trg >>= 1) {
-          // pooled output, one row per block: the wave's two blocks are the two rows of a pooled row
-          const bool pairs = p.out_pool && pw == 5;
-          if (pairs && (x == 1 || trg < 2)) continue;
-          if (f32 && x == 2 && (!pairs || nco > 1)) continue; // two blocks with four partial sums each: one wave per SIMD
-          for (int fl = may_flatten ? 1 : 0; fl >= 0; --fl) {
-            MidPlan q;
-            if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w, 0, nco)) continue;
-            const double cost = mid_cost(q, p, c, x) * (nco > 1 ? 1.05 : 1.0);     // (where the estimates are close it is not faster)
-            // of equals the one that does not straddle samples, and of tiles that all have a compute unit to themselves the
-            // smaller one, both of which are tried later
-            const long long wgs = (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
-            if (found && (cost > best || (cost == best && wgs > 256 && q.flatten))) continue;
-            found = true;
-            best = cost;
-            out.q = q;
-            nmc = c;
-            nnp = x;
+    for (int nco = 1; nco <= max_nco; ++nco)
+      for (int c = 1; c <= (f32 || p.Cout <= 32 || nco > 1 ? 1 : 2); ++c)
+        for (int x = 2; x >= 1; --x)
+          for (int trg = 4 * x / wb; trg >= 1; trg >>= 1) {
+            // pooled output, one row per block: the wave's two blocks are the two rows of a pooled row
+            const bool pairs = p.out_pool && pw == 5;
+            if (pairs && (x == 1 || trg < 2)) continue;
+            if (f32 && x == 2 && (!pairs || nco > 1)) continue; // two blocks with four partial sums each: one wave per SIMD
+            for (int fl = may_flatten ? 1 : 0; fl >= 0; --fl) {
+              MidPlan q;
+              if (!mid_plan(q, p, kp, c, x, pw, trg, fl != 0, nmc_w, 0, nco)) continue;
+              const double cost = mid_cost(q, p, c, x) * (nco > 1 ? 1.05 : 1.0);     // (where the estimates are close it is not faster)
+              // of equals the one that does not straddle samples, and of tiles that all have a compute unit to themselves the
+              // smaller one, both of which are tried later
+              const long long wgs = (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
+              if (found && (cost > best || (cost == best && wgs > 256 && q.flatten))) continue;
+              found = true;
+              best = cost;
+              out.q = q;
+              nmc = c;
+              nnp = x;
+            }
           }
-        }
   return found;
 }
 

@@ -806,120 +806,120 @@ __global__ __launch_bounds__(SPLIT ? 512 : kMidThreads * NCO,
       }
       continue;
     } else {
-    if (!wave_active) { step += n_lif; continue; }
-    // ---- 2. contraction
-    f32x16 acc[NMC][NNP];
+      if (!wave_active) { step += n_lif; continue; }
+      // ---- 2. contraction
+      f32x16 acc[NMC][NNP];
 #pragma unroll
-    for (int mc = 0; mc < NMC; ++mc)
-#pragma unroll
-      for (int np = 0; np < NNP; ++np)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[mc][np][r] = bias_lds[mc * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
-    const int32_t* const tabh = tab + h;
-    if constexpr (F32) {
-      // Four partial sums per output (k-steps ks % 4), added at the end: the rounding error of a long fp32 sum grows
-      // with its length, and a quarter of the length keeps the membrane within the fp32 bar where one chain of
-      // 9 Cin terms does not.
-      f32x16 part[3][NNP];
-#pragma unroll
-      for (int i = 0; i < 3; ++i)
+      for (int mc = 0; mc < NMC; ++mc)
 #pragma unroll
         for (int np = 0; np < NNP; ++np)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) part[i][np][r] = 0.f;
-      // nks is a multiple of 4 (9 Cin / 2, Cin a multiple of 8); operands of four steps are fetched ahead
-      float wf[2][4], af[2][4][NNP];
-      int32_t off[4];
-      auto fetch = [&](int ks, float (&w)[4], float (&a)[4][NNP]) {
+          for (int r = 0; r < 16; ++r) acc[mc][np][r] = bias_lds[mc * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
+      const int32_t* const tabh = tab + h;
+      if constexpr (F32) {
+        // Four partial sums per output (k-steps ks % 4), added at the end: the rounding error of a long fp32 sum grows
+        // with its length, and a quarter of the length keeps the membrane within the fp32 bar where one chain of
+        // 9 Cin terms does not.
+        f32x16 part[3][NNP];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          w[i] = *reinterpret_cast<const float*>(w_lds + ((ks + i) * 64 + lane) * 4);
-#pragma unroll
-          for (int np = 0; np < NNP; ++np) a[i][np] = *reinterpret_cast<const float*>(lds + pix_base[np] + (uint32_t)off[i]);
-        }
-      };
-      auto offsets = [&](int ks) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) off[i] = tabh[2 * (ks + i)];
-      };
-      auto multiply = [&](const float (&w)[4], const float (&a)[4][NNP]) {
-#pragma unroll
-        for (int np = 0; np < NNP; ++np) {
-          acc[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[0], a[0][np], acc[0][np], 0, 0, 0);
-          part[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[1], a[1][np], part[0][np], 0, 0, 0);
-          part[1][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[2], a[2][np], part[1][np], 0, 0, 0);
-          part[2][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[3], a[3][np], part[2][np], 0, 0, 0);
-        }
-      };
-      // eight steps a turn and no way out of its middle (the accumulators would change registers on every turn); behind the last
-      // step the last four are fetched again
-      offsets(0);
-      fetch(0, wf[0], af[0]);
-      offsets(min(4, q.nks - 4));
-      int ks = 0;
-      for (; ks + 8 <= q.nks; ks += 8) {
-        fetch(ks + 4, wf[1], af[1]);
-        offsets(min(ks + 8, q.nks - 4));
-        __builtin_amdgcn_sched_barrier(0);               // in front of the MFMAs: else they wait for reads just issued
-        multiply(wf[0], af[0]);
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(min(ks + 8, q.nks - 4), wf[0], af[0]);
-        offsets(min(ks + 12, q.nks - 4));
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(wf[1], af[1]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (ks < q.nks) multiply(wf[0], af[0]);
-#pragma unroll
-      for (int np = 0; np < NNP; ++np)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[0][np][r] = (acc[0][np][r] + part[0][np][r]) + (part[1][np][r] + part[2][np][r]);
-    } else {
-      // fragments are requested F - 1 steps ahead, table offsets F steps before that; beyond the last step the fetches read
-      // what lies behind the weights (inside the LDS) and nobody uses it
-      constexpr int F = mid_depth(NMC, NNP);
-      bf16x8 af[F][NNP], wf[F][NMC];
-      int32_t off[F];
-      const uint8_t* const w_lane = w_lds + lane * 16;
-      auto fetch = [&](int ks, int set) {
-#pragma unroll
-        for (int mc = 0; mc < NMC; ++mc) wf[set][mc] = *reinterpret_cast<const bf16x8*>(w_lane + (ks * NMC + mc) * 1024);
-#pragma unroll
-        for (int np = 0; np < NNP; ++np) af[set][np] = *reinterpret_cast<const bf16x8*>(lds + pix_base[np] + (uint32_t)off[set]);
-        off[set] = tabh[2 * (ks + F)];
-      };
-#pragma unroll
-      for (int d = 0; d < F; ++d) off[d] = tabh[2 * d];
-#pragma unroll
-      for (int d = 0; d < F - 1; ++d) fetch(d, d);
-      auto multiply = [&](int set) {
-#pragma unroll
-        for (int mc = 0; mc < NMC; ++mc)
+        for (int i = 0; i < 3; ++i)
 #pragma unroll
           for (int np = 0; np < NNP; ++np)
-            acc[mc][np] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][mc], af[set][np], acc[mc][np], 0, 0, 0);
-      };
-      int ks = 0;
-      for (; ks + F <= q.nks; ks += F) {
 #pragma unroll
-        for (int d = 0; d < F; ++d) {
-          fetch(ks + d + F - 1, (d + F - 1) % F);
-          multiply(d);
+            for (int r = 0; r < 16; ++r) part[i][np][r] = 0.f;
+        // nks is a multiple of 4 (9 Cin / 2, Cin a multiple of 8); operands of four steps are fetched ahead
+        float wf[2][4], af[2][4][NNP];
+        int32_t off[4];
+        auto fetch = [&](int ks, float (&w)[4], float (&a)[4][NNP]) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            w[i] = *reinterpret_cast<const float*>(w_lds + ((ks + i) * 64 + lane) * 4);
+#pragma unroll
+            for (int np = 0; np < NNP; ++np) a[i][np] = *reinterpret_cast<const float*>(lds + pix_base[np] + (uint32_t)off[i]);
+          }
+        };
+        auto offsets = [&](int ks) {
+#pragma unroll
+          for (int i = 0; i < 4; ++i) off[i] = tabh[2 * (ks + i)];
+        };
+        auto multiply = [&](const float (&w)[4], const float (&a)[4][NNP]) {
+#pragma unroll
+          for (int np = 0; np < NNP; ++np) {
+            acc[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[0], a[0][np], acc[0][np], 0, 0, 0);
+            part[0][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[1], a[1][np], part[0][np], 0, 0, 0);
+            part[1][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[2], a[2][np], part[1][np], 0, 0, 0);
+            part[2][np] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[3], a[3][np], part[2][np], 0, 0, 0);
+          }
+        };
+        // eight steps a turn and no way out of its middle (the accumulators would change registers on every turn); behind the last
+        // step the last four are fetched again
+        offsets(0);
+        fetch(0, wf[0], af[0]);
+        offsets(min(4, q.nks - 4));
+        int ks = 0;
+        for (; ks + 8 <= q.nks; ks += 8) {
+          fetch(ks + 4, wf[1], af[1]);
+          offsets(min(ks + 8, q.nks - 4));
+          __builtin_amdgcn_sched_barrier(0);               // in front of the MFMAs: else they wait for reads just issued
+          multiply(wf[0], af[0]);
+          __builtin_amdgcn_sched_barrier(0);
+          fetch(min(ks + 8, q.nks - 4), wf[0], af[0]);
+          offsets(min(ks + 12, q.nks - 4));
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(wf[1], af[1]);
+          __builtin_amdgcn_sched_barrier(0);
         }
+        if (ks < q.nks) multiply(wf[0], af[0]);
+#pragma unroll
+        for (int np = 0; np < NNP; ++np)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[0][np][r] = (acc[0][np][r] + part[0][np][r]) + (part[1][np][r] + part[2][np][r]);
+      } else {
+        // fragments are requested F - 1 steps ahead, table offsets F steps before that; beyond the last step the fetches read
+        // what lies behind the weights (inside the LDS) and nobody uses it
+        constexpr int F = mid_depth(NMC, NNP);
+        bf16x8 af[F][NNP], wf[F][NMC];
+        int32_t off[F];
+        const uint8_t* const w_lane = w_lds + lane * 16;
+        auto fetch = [&](int ks, int set) {
+#pragma unroll
+          for (int mc = 0; mc < NMC; ++mc) wf[set][mc] = *reinterpret_cast<const bf16x8*>(w_lane + (ks * NMC + mc) * 1024);
+#pragma unroll
+          for (int np = 0; np < NNP; ++np) af[set][np] = *reinterpret_cast<const bf16x8*>(lds + pix_base[np] + (uint32_t)off[set]);
+          off[set] = tabh[2 * (ks + F)];
+        };
+#pragma unroll
+        for (int d = 0; d < F; ++d) off[d] = tabh[2 * d];
+#pragma unroll
+        for (int d = 0; d < F - 1; ++d) fetch(d, d);
+        auto multiply = [&](int set) {
+#pragma unroll
+          for (int mc = 0; mc < NMC; ++mc)
+#pragma unroll
+            for (int np = 0; np < NNP; ++np)
+              acc[mc][np] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[set][mc], af[set][np], acc[mc][np], 0, 0, 0);
+        };
+        int ks = 0;
+        for (; ks + F <= q.nks; ks += F) {
+#pragma unroll
+          for (int d = 0; d < F; ++d) {
+            fetch(ks + d + F - 1, (d + F - 1) % F);
+            multiply(d);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < F - 1; ++d)
+          if (ks + d < q.nks) multiply(d);
       }
+      // ---- 3. LIF steps on Y_k = acc (bias included)
+      for (int j = 0; j < n_lif; ++j, ++step) {
+        uint32_t word[NMC][2];
 #pragma unroll
-      for (int d = 0; d < F - 1; ++d)
-        if (ks + d < q.nks) multiply(d);
-    }
-    // ---- 3. LIF steps on Y_k = acc (bias included)
-    for (int j = 0; j < n_lif; ++j, ++step) {
-      uint32_t word[NMC][2];
-#pragma unroll
-      for (int mc = 0; mc < NMC; ++mc) word[mc][0] = word[mc][1] = 0u;
-      float* tl = TRACE ? p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_wave : nullptr;
-      lif_step<NMC, 64, TRACE, NNP>(V, acc, decay, p.theta, lg, word, tl, plane);
-      store_words(step, word);
-    }
+        for (int mc = 0; mc < NMC; ++mc) word[mc][0] = word[mc][1] = 0u;
+        float* tl = TRACE ? p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_wave : nullptr;
+        lif_step<NMC, 64, TRACE, NNP>(V, acc, decay, p.theta, lg, word, tl, plane);
+        store_words(step, word);
+      }
     }
   }
 
