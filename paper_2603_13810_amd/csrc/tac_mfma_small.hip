@@ -539,6 +539,9 @@ hipError_t mfma_small_prepare(const tac_layer_desc_t& d, const float* w_oihw, vo
 hipError_t mfma_small_launch(const LayerParams& p, hipStream_t s) { return first_launch(p, s); }
 
 // fp32 layers of the same shapes, on the vector kernel's prepared weights ([cin][tap][cout padded to 32] fp32)
+// Times against the vector kernel's (us): 1 -> 32 at 28 x 28, B = 128, 18 / 50 (see above), 2 -> 8 at 60 x 40, B = 128, one group 15.6 / 17.7, B = 8,
+// four groups 10.7 / 17.1.  With recorded membranes few channels are slower, 2 -> 8 at 60 x 40, B = 128, one group 31.8 / 18.8, 2 -> 16 32.3 / 28.7,
+// 2 -> 32 33.0 / 57.8; they are taken all the same, since a layer gives the same bits with and without recording.
 bool first_f32_supported(const LayerParams& p) {
   return !p.bf16 && !p.pool2 && !p.out_pool && p.Cin <= 2 && p.W <= kFirstMaxW;
 }
