@@ -15,6 +15,7 @@
 //   3. LIF:     V <- decay V + Y_k, spike iff V >= theta, subtractive reset; once for TAC
 //               and per-step, K times with the same Y_k for TAC-TP; each step's spikes
 //               leave as one wave ballot = two packed words.
+#include "tac_first_plan.h"
 #include "tac_mfma_common.h"
 
 namespace tac {

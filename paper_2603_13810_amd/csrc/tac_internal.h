@@ -77,8 +77,7 @@ bool mfma_small_supported(const tac_layer_desc_t& d);
 size_t mfma_small_weight_bytes(const tac_layer_desc_t& d);
 hipError_t mfma_small_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);
 hipError_t mfma_small_launch(const LayerParams& p, hipStream_t s);   // takes a shorter last group along
-// the same kernel for fp32 layers, on the direct family's prepared weights
-bool first_f32_supported(const LayerParams& p);
+// the same kernel for fp32 layers, on the direct family's prepared weights (which: first_f32_supported, tac_first_plan.h)
 hipError_t first_f32_launch(const LayerParams& p, hipStream_t s);
 
 // The backward pass (surrogate-gradient BPTT of one layer), resolved on the host.

@@ -20,14 +20,12 @@
 // (fp32: of the vector kernel): 2 -> 64 at 128 x 128 stride 2, B = 32, TAC-TP K = 2, 16 frames 28 / 48 (B = 16: 19 / 39); real-valued
 // 2 -> 128 at 64 x 64, B = 16, TAC-TP K = 4 24 / 45; 1 -> 32 at 28 x 28, B = 128, two groups of 4 7.5 / 18; fp32, 25 frames in groups
 // of 8 18 / 50, with membranes in groups of 4 39 / 78.
+#include "tac_first_plan.h"
 #include "tac_mfma_common.h"
 
 namespace tac {
 
 namespace {
-
-constexpr int kFirstWaves = 8;                 // per workgroup at most
-constexpr int kFirstMaxW = 128;                // input width limit (4 words per row)
 
 // x / d by multiplication: the product is the quotient or one less
 struct Div {
@@ -537,14 +535,6 @@ hipError_t mfma_small_prepare(const tac_layer_desc_t& d, const float* w_oihw, vo
 }
 
 hipError_t mfma_small_launch(const LayerParams& p, hipStream_t s) { return first_launch(p, s); }
-
-// fp32 layers of the same shapes, on the vector kernel's prepared weights ([cin][tap][cout padded to 32] fp32)
-// Times against the vector kernel's (us): 1 -> 32 at 28 x 28, B = 128, 18 / 50 (see above), 2 -> 8 at 60 x 40, B = 128, one group 15.6 / 17.7, B = 8,
-// four groups 10.7 / 17.1.  With recorded membranes few channels are slower, 2 -> 8 at 60 x 40, B = 128, one group 31.8 / 18.8, 2 -> 16 32.3 / 28.7,
-// 2 -> 32 33.0 / 57.8; they are taken all the same, since a layer gives the same bits with and without recording.
-bool first_f32_supported(const LayerParams& p) {
-  return !p.bf16 && !p.pool2 && !p.out_pool && p.Cin <= 2 && p.W <= kFirstMaxW;
-}
 
 hipError_t first_f32_launch(const LayerParams& p, hipStream_t s) { return first_launch(p, s); }
 

@@ -1,0 +1,16 @@
+// The host rules of the first layers' kernel, for the tests that hold them to what they are there for.
+#include "tac_first_plan.h"
+
+static tac::LayerParams params_of(const tac_layer_desc_t* d) {
+  tac::LayerParams p{};
+  p.B = d->B; p.Cin = d->Cin; p.H = d->H; p.W = d->W; p.Cout = d->Cout; p.stride = d->stride;
+  p.Ho = (d->H - 1) / d->stride + 1;
+  p.Wo = (d->W - 1) / d->stride + 1;
+  p.Wwo = (p.Wo + 31) / 32;
+  p.pool2 = d->in_format == TAC_IN_BITS_POOL2 ? 1 : d->in_format == TAC_IN_BITS_MAXPOOL2 ? 2 : 0;
+  p.out_pool = d->out_format == TAC_OUT_BITS_MAXPOOL2;
+  p.bf16 = d->precision == TAC_BF16;
+  return p;
+}
+
+extern "C" int fp32_layer_on_matrix_cores(const tac_layer_desc_t* d) { return tac::first_f32_supported(params_of(d)); }

@@ -1,0 +1,39 @@
+"""Which layers the matrix-core kernel of the first layers takes: host rules, compiled into a small library of their own
+(first_plan_shim.cpp)."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_2603_13810_amd import api, build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def shim(tmp_path_factory):
+    lib = str(tmp_path_factory.mktemp("first") / "first_plan.so")
+    subprocess.check_call([build.hipcc(), "--offload-arch=gfx950", "-O1", "-std=c++20", "-fPIC", "-shared", "-x", "hip", "-I",
+                           build.INCLUDE, "-I", build.CSRC, os.path.join(HERE, "first_plan_shim.cpp"), "-o", lib])
+    return ctypes.CDLL(lib)
+
+
+def _desc(B, Cin, Cout, H, W, stride=1, precision=api.TAC_FP32, **kw):
+    return api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP, stride=stride, precision=precision, **kw)
+
+
+# (Cin, Cout, H, W, stride): planes of 2^28 neurons and more, and the last ones below
+@pytest.mark.parametrize("shape,taken", [((1, 5, 2 ** 21, 128, 1), False), ((2, 7, 2 ** 21 + 1, 128, 1), False), ((1, 6, 2 ** 23, 128, 2), False),
+                                         ((1, 5, 2 ** 28, 1, 1), False), ((1, 4, 2 ** 22 - 1, 128, 1), True), ((1, 1, 2 ** 23, 128, 1), True),
+                                         ((1, 5, 2 ** 21 - 16, 128, 1), True), ((2, 8, 28, 28, 1), True), ((3, 8, 28, 28, 1), False),
+                                         ((1, 8, 28, 129, 1), False)])
+def test_membranes_of_fp32_layers_are_within_reach(shim, shape, taken):
+    Cin, Cout, H, W, stride = shape
+    d = _desc(1, Cin, Cout, H, W, stride)
+    api.tac_out_shape(d)                                       # an accepted layer
+    assert bool(shim.fp32_layer_on_matrix_cores(ctypes.byref(d))) == taken
+    if taken and Cin <= 2:
+        # the kernel's largest 32-bit membrane offset: four planes for the upper lane half (where it has channels), the tile's 16 rows
+        Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+        assert 4 * (16 * Wo + (4 * Ho * Wo if Cout > 4 else 0)) < 2 ** 32

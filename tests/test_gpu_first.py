@@ -6,7 +6,8 @@ import pytest
 
 from paper_2603_13810_amd import api, synth
 
-from gpu_util import check_layer
+from gpu_util import check_layer, run_oracle
+from parity_util import TOL_FP32, compare, np_unpack
 
 pytestmark = pytest.mark.gpu
 B16, F32 = api.TAC_BF16, api.TAC_FP32
@@ -70,3 +71,27 @@ def test_values_beyond_a_window_do_not_reach_it(Cin, precision):
     assert np.array_equal(clean["v_trace"][..., clear], dirty["v_trace"][..., clear])
     assert np.array_equal(clean["spikes"][..., clear], dirty["spikes"][..., clear])
     assert not np.isfinite(dirty["v_trace"][..., ~clear]).all()
+
+
+def test_membranes_behind_four_gib_fp32():
+    """Six channels of a plane of 2^28 neurons: the first and the last rows against the oracle on those rows alone."""
+    import torch
+    Cin, Cout, H, W, rows = 1, 6, 2 ** 21 + 3, 128, 10
+    dev = torch.device("cuda:0")
+    d = api.make_desc(1, 1, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=STEP, precision=F32)
+    g = torch.Generator(device=dev)
+    g.manual_seed(93)
+    s = (torch.rand((1, 1, Cin, H, W), generator=g, device=dev) < 0.3).to(torch.uint8)
+    w = synth.kaiming_normal(65, Cout, Cin) * np.float32(1.5)
+    v0 = torch.randn((1, Cout, H, W), generator=g, device=dev) * 0.3
+    v, vt = v0.clone(), torch.full((1, 1, Cout, H, W), float("nan"), device=dev)
+    out = torch.full((1, 1, Cout, H, W // 32), -1, dtype=torch.int32, device=dev)
+    api.tac_conv_lif(d, api.tac_pack_spikes(s), api.tac_prepare_weights(d, torch.from_numpy(w).to(dev)), None, v, out, vt)
+    assert not torch.isnan(vt).any()
+    for part, inner in ((slice(0, rows), slice(0, rows - 1)), (slice(H - rows, H), slice(1, rows))):     # (a crop's cut row sees padding)
+        host = lambda t: np.ascontiguousarray(t[..., part, :].cpu().numpy())
+        ref = run_oracle(host(s), w, K=1, beta=0.9, theta=1.0, mode=STEP, v0=host(v0))
+        spikes, trace, final = (np.ascontiguousarray(a[..., inner, :]) for a in (np_unpack(host(out), W), host(vt), host(v)))
+        par = compare(ref[0][..., inner, :], ref[1][..., inner, :], spikes, trace, 1.0, TOL_FP32)
+        assert par.ok and par.flips == 0, par
+        assert np.abs(final - ref[2][..., inner, :]).max() <= 1e-5 * max(1.0, np.abs(ref[2]).max())
