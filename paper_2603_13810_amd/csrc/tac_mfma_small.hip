@@ -21,7 +21,6 @@
 // 2 -> 128 at 64 x 64, B = 16, TAC-TP K = 4 24 / 45; 1 -> 32 at 28 x 28, B = 128, two groups of 4 7.5 / 18; fp32, 25 frames in groups
 // of 8 18 / 50, with membranes in groups of 4 39 / 78.
 #include "tac_first_plan.h"
-#include "tac_mfma_common.h"
 
 namespace tac {
 
@@ -56,9 +55,6 @@ struct FirstParams {
   float wj[TAC_MAX_K + 8];                     // beta^(K-1-j)
   double wjd[TAC_MAX_K + 8];
 };
-
-// row of the aggregate tile: a padding column on either side, room for the last word's four pixels
-__host__ __device__ constexpr int first_row_words(int W) { return ((W + 3) & ~3) + 2; }
 
 // KB: frames a thread asks for together, K's next power of two, at most 8 / CIN (frames beyond the group repeat its last and have
 // the weight zero).  A larger group's further frames are waited for.
@@ -465,25 +461,7 @@ hipError_t first_launch_k(const FirstParams& p, size_t lds, hipStream_t s) {
 }
 
 template <int CIN, bool F32>
-hipError_t first_launch_c(const LayerParams& l, FirstParams& p, hipStream_t s) {
-  p.n_pairs = l.out_pool ? (p.Ho / 2) * p.Wwo : (p.Ho * p.Wwo + 1) / 2;
-  const int co_blocks = (p.Cout + 31) / 32;
-  p.co_tiles = (co_blocks + 3) / 4;
-  p.blocks = (co_blocks + p.co_tiles - 1) / p.co_tiles;
-  p.pair_tiles = (p.n_pairs + kFirstWaves / p.blocks - 1) / (kFirstWaves / p.blocks);
-  p.pairs = (p.n_pairs + p.pair_tiles - 1) / p.pair_tiles;
-  // small grids: smaller workgroups, until there are two per compute unit
-  while (p.pairs > 1 && (long long)p.pair_tiles * p.co_tiles * p.B < 512) {
-    p.pairs = (p.pairs + 1) / 2;
-    p.pair_tiles = (p.n_pairs + p.pairs - 1) / p.pairs;
-  }
-  p.n_tiles = p.pair_tiles * p.co_tiles * p.B;
-  p.by_wwo = Div(p.Wwo); p.by_blocks = Div(p.blocks); p.by_pair_tiles = Div(p.pair_tiles); p.by_tiles = Div(p.pair_tiles * p.co_tiles);
-  // most output rows that a tile touches
-  const int rows = l.out_pool ? 2 * ((p.pairs + p.Wwo - 2) / p.Wwo + 1) : (2 * p.pairs + p.Wwo - 2) / p.Wwo + 1;
-  p.tile_words = (F32 ? CIN : 1) * ((rows - 1) * p.S + 3) * first_row_words(p.W);
-  const size_t lds = (size_t)2 * p.tile_words * 4 +
-                     (size_t)p.pairs * p.blocks * 4 * (p.v_trace ? 32 : p.v_inout ? kTurnFloats : 0);
+hipError_t first_launch_c(const LayerParams& l, const FirstParams& p, size_t lds, hipStream_t s) {
   return l.dense ? first_launch_k<CIN, F32, true>(p, lds, s) : first_launch_k<CIN, F32, false>(p, lds, s);
 }
 
@@ -501,8 +479,12 @@ hipError_t first_launch(const LayerParams& l, hipStream_t s) {
     p.wj[j] = l.wj[j];
     p.wjd[j] = l.wjd[j];
   }
-  if (l.bf16) return l.Cin == 1 ? first_launch_c<1, false>(l, p, s) : first_launch_c<2, false>(l, p, s);
-  return l.Cin == 1 ? first_launch_c<1, true>(l, p, s) : first_launch_c<2, true>(l, p, s);
+  const FirstPlan plan = first_plan(l);
+  p.n_pairs = plan.n_pairs; p.pair_tiles = plan.pair_tiles; p.co_tiles = plan.co_tiles; p.n_tiles = (int)plan.workgroups;
+  p.pairs = plan.pairs; p.blocks = plan.blocks; p.tile_words = plan.tile_words;
+  p.by_wwo = Div(p.Wwo); p.by_blocks = Div(p.blocks); p.by_pair_tiles = Div(p.pair_tiles); p.by_tiles = Div(p.pair_tiles * p.co_tiles);
+  if (l.bf16) return l.Cin == 1 ? first_launch_c<1, false>(l, p, plan.lds, s) : first_launch_c<2, false>(l, p, plan.lds, s);
+  return l.Cin == 1 ? first_launch_c<1, true>(l, p, plan.lds, s) : first_launch_c<2, true>(l, p, plan.lds, s);
 }
 
 }  // namespace

@@ -37,3 +37,14 @@ def test_membranes_of_fp32_layers_are_within_reach(shim, shape, taken):
         # the kernel's largest 32-bit membrane offset: four planes for the upper lane half (where it has channels), the tile's 16 rows
         Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
         assert 4 * (16 * Wo + (4 * Ho * Wo if Cout > 4 else 0)) < 2 ** 32
+
+
+# (B, Cout, H, W): launches of 2^32 threads and more, which a grid in one dimension cannot have, and of fewer; more channels than the
+# vector kernel has ever taken (its refusal stays)
+@pytest.mark.parametrize("shape,taken", [((65535, 8, 2049, 1), False), ((65535, 1, 2049, 15), False), ((65535, 8, 2000, 2), True),
+                                         ((1, 32 * 65536, 8, 1), False), ((1, 32 * 65535, 8, 1), True)])
+def test_launches_of_fp32_layers_fit_a_grid(shim, shape, taken):
+    B, Cout, H, W = shape
+    d = _desc(B, 1, Cout, H, W)
+    api.tac_out_shape(d)                                       # an accepted layer
+    assert bool(shim.fp32_layer_on_matrix_cores(ctypes.byref(d))) == taken
