@@ -447,8 +447,12 @@ __global__ void small_prepare_kernel(const float* __restrict__ w, uint32_t* __re
 template <int CIN, int KB, bool F32, bool DENSE>
 hipError_t first_launch_t(const FirstParams& p, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)p.n_tiles), block((unsigned)(p.pairs * p.blocks * 64));
-  if (p.v_trace) hipLaunchKernelGGL((first_kernel<CIN, KB, F32, DENSE, true>), grid, block, lds, s, p);
-  else hipLaunchKernelGGL((first_kernel<CIN, KB, F32, DENSE, false>), grid, block, lds, s, p);
+  auto kern = p.v_trace ? &first_kernel<CIN, KB, F32, DENSE, true> : &first_kernel<CIN, KB, F32, DENSE, false>;
+  if (lds > 64 * 1024) {                       // (fp32, two channels, stride 2 on wide rows, with a membrane to turn)
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, grid, block, lds, s, p);
   return hipGetLastError();
 }
 

@@ -13,4 +13,15 @@ static tac::LayerParams params_of(const tac_layer_desc_t* d) {
   return p;
 }
 
+// out: pairs, blocks, pair tiles, channel tiles, workgroups, bytes of LDS
+extern "C" void first_plan_of(const tac_layer_desc_t* d, int with_trace, int with_state, long long* out) {
+  tac::LayerParams p = params_of(d);
+  float somewhere;
+  p.v_trace = with_trace ? &somewhere : nullptr;
+  p.v_inout = with_state ? &somewhere : nullptr;
+  const tac::FirstPlan q = tac::first_plan(p);
+  const long long v[] = {q.pairs, q.blocks, q.pair_tiles, q.co_tiles, q.workgroups, (long long)q.lds};
+  for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+
 extern "C" int fp32_layer_on_matrix_cores(const tac_layer_desc_t* d) { return tac::first_f32_supported(params_of(d)); }

@@ -19,6 +19,18 @@ def shim(tmp_path_factory):
     return ctypes.CDLL(lib)
 
 
+FIELDS = ("pairs", "blocks", "pair_tiles", "co_tiles", "workgroups", "lds")
+
+
+@pytest.fixture(scope="module")
+def plan(shim):
+    def of(desc, trace=False, state=False):
+        out = (ctypes.c_longlong * len(FIELDS))()
+        shim.first_plan_of(ctypes.byref(desc), int(trace), int(state), out)
+        return dict(zip(FIELDS, out))
+    return of
+
+
 def _desc(B, Cin, Cout, H, W, stride=1, precision=api.TAC_FP32, **kw):
     return api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP, stride=stride, precision=precision, **kw)
 
@@ -48,3 +60,21 @@ def test_launches_of_fp32_layers_fit_a_grid(shim, shape, taken):
     d = _desc(B, 1, Cout, H, W)
     api.tac_out_shape(d)                                       # an accepted layer
     assert bool(shim.fp32_layer_on_matrix_cores(ctypes.byref(d))) == taken
+
+
+def test_lds_of_a_workgroup(plan):
+    # more than 64 KiB only where the launch asks for it (up to 80 KiB, two workgroups per compute unit), and the largest case of
+    # test_gpu_first.py is there
+    largest = 0
+    for precision in (api.TAC_FP32, api.TAC_BF16):
+        for W in range(1, 129):
+            for stride in (1, 2):
+                for Cout in (8, 64, 96, 128):
+                    for pooled in (False, True):
+                        if pooled and (precision == api.TAC_FP32 or W % 2 or (W // stride) % 2):
+                            continue
+                        d = _desc(512, 2, Cout, 256, W, stride, precision, **(dict(out_format=api.TAC_OUT_BITS_MAXPOOL2) if pooled else {}))
+                        for trace in (False, True):
+                            largest = max(largest, plan(d, trace, True)["lds"])
+    assert largest <= 80 * 1024
+    assert plan(_desc(64, 2, 32, 128, 128, 2), state=True) == dict(pairs=8, blocks=1, pair_tiles=8, co_tiles=1, workgroups=512, lds=largest)

@@ -73,6 +73,17 @@ def test_values_beyond_a_window_do_not_reach_it(Cin, precision):
     assert not np.isfinite(dirty["v_trace"][..., ~clear]).all()
 
 
+def test_workgroups_of_more_than_64_kib_of_lds():
+    # fp32, two channels of two aggregate tiles of 19 rows of 128 pixels, eight waves that turn their membranes
+    r = np.random.Generator(np.random.PCG64(9300))
+    s = (r.random((5, 64, 2, 128, 128)) < 0.2).astype(np.uint8)
+    w = synth.kaiming_normal(66, 32, 2) * np.float32(1.5)
+    v0 = (r.standard_normal((64, 32, 64, 64)) * 0.3).astype(np.float32)
+    par, g, ref = check_layer(s, w, K=2, beta=0.9, theta=1.0, mode=TP, stride=2, precision=F32, v0=v0, oracle_samples=[0, 31, 63])
+    assert ref[0].any()
+    print("first layer", par)
+
+
 def test_membranes_behind_four_gib_fp32():
     """Six channels of a plane of 2^28 neurons: the first and the last rows against the oracle on those rows alone."""
     import torch
