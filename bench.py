@@ -107,6 +107,16 @@ def layer_bound(Cin, Cout, H, W, precision_bf16, kernel):
     return "mfma" if (precision_bf16 and kernel == "mfma") else "alu"
 
 
+def kernel_name(desc):
+    """What the automatic choice runs: the family tac_select_kernel names, or the first layers' fp32 matrix-core kernel, which
+    works on the direct family's weights."""
+    from paper_2603_13810_amd import api
+    if api.tac_select_kernel(desc) == api.TAC_KERNEL_MFMA:
+        return "mfma"
+    first = desc.precision == api.TAC_FP32 and desc.Cin <= 2 and desc.W <= 128 and desc.in_format in (api.TAC_IN_BITS, api.TAC_IN_F32)
+    return "first_layer_fp32_mfma" if first else "direct"
+
+
 def roofline_entry(bound, flops, bytes_, kern_ms, **extra):
     if bound == "hbm":
         ach = bytes_ / (kern_ms * 1e-3) / 1e9
@@ -245,7 +255,7 @@ def main():
         Kg = 1 if mode == api.TAC_PER_STEP else K
         flops = 2.0 * B * Ho * Wo * L.Cout * L.Cin * 9 * (T // Kg)
         return dict(mode=api.MODE_NAMES[mode], K=Kg, ms=wall_ms, kernel_ms=kern_ms, flops=flops,
-                    kernel=("mfma" if api.tac_select_kernel(d) == api.TAC_KERNEL_MFMA else "direct"),
+                    kernel=kernel_name(d),
                     frames_per_s=B * T / (wall_ms * 1e-3), tflops=flops / (kern_ms * 1e-3) / 1e12,
                     out_bytes=out.numel() * 4)
 
@@ -471,7 +481,7 @@ def bench_stack(args, wl, dev):
         out = torch.empty((T_out, B, L.Cout, Ho, (Wo + 31) // 32), dtype=torch.int32, device=dev)
         Kg = 1 if mode == api.TAC_PER_STEP else K
         fl = 2.0 * B * Ho * Wo * L.Cout * L.Cin * 9 * (T // Kg)
-        kern = "mfma" if api.tac_select_kernel(d) == api.TAC_KERNEL_MFMA else "direct"
+        kern = kernel_name(d)
         layers.append(dict(desc=d, wp=wp, out=out, w32=w32, K=K, flops=fl, stride=L.stride, pool2=L.pool2_in,
                            kernel=kern, bytes=in_bytes + out.numel() * 4,
                            bound=layer_bound(L.Cin, L.Cout, H, W, PREC == api.TAC_BF16, kern),

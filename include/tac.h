@@ -63,7 +63,7 @@ enum { TAC_IN_BITS = 0, TAC_IN_BITS_POOL2 = 1, TAC_IN_BITS_MAXPOOL2 = 2, TAC_IN_
 enum { TAC_OUT_BITS = 0, TAC_OUT_BITS_MAXPOOL2 = 1 };
 /* Kernel family.  AUTO picks MFMA when the shape qualifies (see
  * tac_select_kernel), else DIRECT.  Forcing MFMA on a shape it does not
- * support is TAC_ERR_UNSUPPORTED. */
+ * support is TAC_ERR_UNSUPPORTED.  Forcing DIRECT runs the vector kernel. */
 enum { TAC_KERNEL_AUTO = 0, TAC_KERNEL_DIRECT = 1, TAC_KERNEL_MFMA = 2 };
 
 enum {
@@ -118,7 +118,9 @@ size_t tac_packed_bytes(int32_t T, int32_t B, int32_t C, int32_t H, int32_t W);
  *     this member also takes precision = TAC_FP32 (float32 operands, v_mfma_f32_32x32x2_f32) while the
  *     float32 weights of a tile of output channels and the aggregate tile fit the LDS (up to about 64 input
  *     channels);
- * everything else runs on the DIRECT kernel (fp32 vector FMAs, any shape, every input format). */
+ * everything else is of the DIRECT family: fp32 vector FMAs, any shape, every input format.  TAC_FP32 layers with Cin = 1
+ * or 2, W <= 128 and no pool on load belong to it by name and by their prepared weights, which are the vector kernel's; with
+ * TAC_KERNEL_AUTO they run on the fp32 matrix cores (the first layers' kernel), with TAC_KERNEL_DIRECT on the vector kernel. */
 int tac_select_kernel(const tac_layer_desc_t* desc);
 
 /* Size of the prepared-weight buffer for this layer.  0 on an invalid desc. */

@@ -164,6 +164,7 @@ int tac_conv_lif(const tac_layer_desc_t* d, const void* input, const void* w_pre
   p.dense = desc->in_format == TAC_IN_F32;
   p.out_pool = desc->out_format == TAC_OUT_BITS_MAXPOOL2;
   p.mfma_kind = kern == TAC_KERNEL_MFMA ? tac::mfma_kind(*desc) : 0;
+  p.vector_only = desc->kernel == TAC_KERNEL_DIRECT;
   p.Hs = p.pool2 ? 2 * desc->H : desc->H;
   p.Wwi = ((p.pool2 ? 2 * desc->W : desc->W) + 31) / 32;
   p.Wwo = (p.Wo + 31) / 32;

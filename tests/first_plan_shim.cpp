@@ -9,6 +9,7 @@ static tac::LayerParams params_of(const tac_layer_desc_t* d) {
   p.Wwo = (p.Wo + 31) / 32;
   p.pool2 = d->in_format == TAC_IN_BITS_POOL2 ? 1 : d->in_format == TAC_IN_BITS_MAXPOOL2 ? 2 : 0;
   p.out_pool = d->out_format == TAC_OUT_BITS_MAXPOOL2;
+  p.vector_only = d->kernel == TAC_KERNEL_DIRECT;
   p.bf16 = d->precision == TAC_BF16;
   return p;
 }

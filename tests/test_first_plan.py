@@ -51,6 +51,13 @@ def test_membranes_of_fp32_layers_are_within_reach(shim, shape, taken):
         assert 4 * (16 * Wo + (4 * Ho * Wo if Cout > 4 else 0)) < 2 ** 32
 
 
+def test_a_caller_who_asks_for_the_vector_kernel_gets_it(shim):
+    for kernel, taken in ((api.TAC_KERNEL_AUTO, True), (api.TAC_KERNEL_DIRECT, False)):
+        d = _desc(4, 1, 8, 28, 28, kernel=kernel)
+        assert bool(shim.fp32_layer_on_matrix_cores(ctypes.byref(d))) == taken
+        assert api.tac_select_kernel(d) == api.TAC_KERNEL_DIRECT and api.tac_prepared_weight_bytes(d) == 9 * 32 * 4    # one layout
+
+
 # (B, Cout, H, W): launches of 2^32 threads and more, which a grid in one dimension cannot have, and of fewer; more channels than the
 # vector kernel has ever taken (its refusal stays)
 @pytest.mark.parametrize("shape,taken", [((65535, 8, 2049, 1), False), ((65535, 1, 2049, 15), False), ((65535, 8, 2000, 2), True),

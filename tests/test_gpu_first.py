@@ -73,6 +73,24 @@ def test_values_beyond_a_window_do_not_reach_it(Cin, precision):
     assert not np.isfinite(dirty["v_trace"][..., ~clear]).all()
 
 
+@pytest.mark.parametrize("case", [CASES[i] for i in (0, 2, 7, 10)], ids=[CASES[i][-1] for i in (0, 2, 7, 10)])
+def test_the_vector_kernel_takes_the_same_layers_and_weights(case):
+    """fp32 first layers on the kernel that TAC_KERNEL_DIRECT asks for; weights prepared for it serve the automatic choice too."""
+    import torch
+    Cin, Cout, H, W, stride, B, T, K, mode, _ = case
+    r = np.random.Generator(np.random.PCG64(9400 + Cin + Cout + H + W))
+    s = (r.random((T, B, Cin, H, W)) < 0.3).astype(np.uint8)
+    w = synth.kaiming_normal(67, Cout, Cin) * np.float32(1.5)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    kw = dict(K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, precision=F32, v0=(r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32))
+    for kernel in (api.TAC_KERNEL_DIRECT, api.TAC_KERNEL_AUTO):
+        par, g, ref = check_layer(s, w, kernel=kernel, expect_kernel=api.TAC_KERNEL_DIRECT, **kw)
+        print("first layer", par)
+    wp = [api.tac_prepare_weights(api.make_desc(T, B, Cin, H, W, Cout, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, kernel=kernel),
+                                  torch.from_numpy(w).cuda()) for kernel in (api.TAC_KERNEL_DIRECT, api.TAC_KERNEL_AUTO)]
+    assert torch.equal(*wp)
+
+
 def test_workgroups_of_more_than_64_kib_of_lds():
     # fp32, two channels of two aggregate tiles of 19 rows of 128 pixels, eight waves that turn their membranes
     r = np.random.Generator(np.random.PCG64(9300))
