@@ -43,8 +43,8 @@ inline FirstPlan first_plan(const LayerParams& l) {
 
 // fp32 layers of the same shapes, on the vector kernel's prepared weights ([cin][tap][cout padded to 32] fp32)
 // Times against the vector kernel's (us): 1 -> 32 at 28 x 28, B = 128, 18 / 50 (see there), 2 -> 8 at 60 x 40, B = 128, one group 15.6 / 17.7, B = 8,
-// four groups 10.7 / 17.1.  With recorded membranes few channels are slower, 2 -> 8 at 60 x 40, B = 128, one group 31.8 / 18.8, 2 -> 16 32.3 / 28.7,
-// 2 -> 32 33.0 / 57.8; they are taken all the same, since a layer gives the same bits with and without recording.
+// four groups 10.7 / 17.1; with recorded membranes at 60 x 40, B = 128, one group, 2 -> 8 17.2 / 19.4, 2 -> 16 20.4 / 28.6, 2 -> 32 33.1 / 57.8 (a
+// layer gives the same bits with and without recording: both take the same kernel).
 inline bool first_f32_supported(const LayerParams& p) {
   if (p.vector_only || p.bf16 || p.pool2 || p.out_pool || p.Cin > 2 || p.W > kFirstMaxW) return false;
   // The upper lane half's membranes are four planes behind the lower one's, in 32-bit byte offsets from the tile's first row: planes of 2^28

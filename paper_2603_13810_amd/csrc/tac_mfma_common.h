@@ -161,7 +161,8 @@ struct LaneGeom {
 //   output width 16:       a half is two rows of 16 pixels; lane
 //                          ((r & 7) << 3) | (h << 2) | (np << 1) | sub of word[mc][r >> 3] holds
 //                          row 2 np + sub.
-template <int NMC, int WO, bool TRACE, int NP = 2>
+// NQ: quads of registers that hold channels (fewer than four where a layer has at most 8 NQ of them; the others are left alone).
+template <int NMC, int WO, bool TRACE, int NP = 2, int NQ = 4>
 __device__ __forceinline__ void lif_step(float (&V)[NMC][NP][16], const f32x16 (&acc)[NMC][NP], float decay, float theta,
                                          const LaneGeom& lg, uint32_t (&word)[NMC][2], float* __restrict__ trace_wave,
                                          size_t plane) {
@@ -171,7 +172,7 @@ __device__ __forceinline__ void lif_step(float (&V)[NMC][NP][16], const f32x16 (
       constexpr int np = decltype(np_)::value;
       // four registers at a time: all four membranes and compares first, then the four ballot
       // hand-overs, then the four resets, so that no instruction waits on the one before it
-      static_for<0, 4>([&](auto r4_) {
+      static_for<0, NQ>([&](auto r4_) {
         constexpr int r0 = decltype(r4_)::value * 4;
         float v[4];
         uint64_t m[4];

@@ -58,8 +58,14 @@ struct FirstParams {
 
 // KB: frames a thread asks for together, K's next power of two, at most 8 / CIN (frames beyond the group repeat its last and have
 // the weight zero).  A larger group's further frames are waited for.
-template <int CIN, int KB, bool F32, bool DENSE, bool TRACE>
-__global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(const FirstParams p) {
+// NQ: quads of result registers with channels in them (4: all 32 channels of a block).  fp32 layers of up to 8 or 16 channels that record their
+// membranes step and store 1 or 2, and fit 128 registers, four waves on a SIMD in the place of two: what bounds calls of few steps is a
+// workgroup's chain from its parameters to its stores, about 8 us whatever it stores.  2 -> 8 at 60 x 40, B = 128, one group of two 31.3 -> 17.2 us,
+// 2 -> 16 32.3 -> 20.4, 2 -> 8 at 83 x 12 23.6 -> 13.1.
+template <int CIN, int KB, bool F32, bool DENSE, bool TRACE, int NQ = 4>
+__global__ __launch_bounds__(kFirstWaves * 64, TRACE && NQ == 4 ? 2 : 4) void first_kernel(const FirstParams p) {
+  static_assert(NQ == 4 || TRACE, "channels along the lanes: the registers are pixels");
+  constexpr int NR = 4 * NQ;                                           // registers that are stepped
   constexpr int NS = F32 ? (9 * CIN + 1) / 2 : CIN;                    // k-steps
   constexpr int PX = DENSE ? 1 : 4;                                    // pixels a thread forms at a time
   extern __shared__ __attribute__((aligned(16))) uint32_t tiles[];
@@ -216,7 +222,7 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
 #pragma unroll
     for (int np = 0; np < 2; ++np)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < NR; ++r) {
         // (lanes outside the image or the channels load a membrane that is inside; nobody stores theirs)
         const int c = min(8 * (r >> 2) + (r & 3), lg.co_lim - 1);
         V[0][np][r] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(v_wave) + (c >= 0 ? (size_t)c * plane * 4 + lg.v_off[np] : 0));
@@ -346,7 +352,7 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
         if (p.bias) {
           f32x16 c;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) c[r] = TRACE ? bias_lds[8 * (r >> 2) + 4 * h + (r & 3)] : bias;
+          for (int r = 0; r < 16; ++r) c[r] = r >= NR ? 0.f : TRACE ? bias_lds[8 * (r >> 2) + 4 * h + (r & 3)] : bias;
           multiply(c);
         } else {
           f32x16 c = {};
@@ -400,7 +406,7 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
         if constexpr (TRACE) {
           uint32_t word[1][2] = {{0u, 0u}};
           float* const tl = p.v_trace + step * ((size_t)p.B * p.Cout * plane) + ((size_t)b * p.Cout + co0) * plane + (size_t)row0 * p.Wo;
-          lif_step<1, 64, true>(V, acc, decay, p.theta, lg, word, tl, plane);
+          lif_step<1, 64, true, 2, NQ>(V, acc, decay, p.theta, lg, word, tl, plane);
           // pooled: the two rows of a window stand in neighbouring lanes
           store(p.out_pool ? pool_pairs(word[0][0] | (uint32_t)__shfl_xor((int)word[0][0], 1, 64)) : word[0][0]);
         } else {
@@ -418,7 +424,7 @@ __global__ __launch_bounds__(kFirstWaves * 64, TRACE ? 2 : 4) void first_kernel(
     for (int np = 0; np < 2; ++np) {
       if constexpr (!TRACE) turn_block(V[0][np], turn, n, h);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
+      for (int r = 0; r < NR; ++r) {
         const int c = 8 * (r >> 2) + (r & 3);
         if (lg.ok[np] && c < lg.co_lim)
           *reinterpret_cast<float*>(reinterpret_cast<char*>(v_wave) + (size_t)c * plane * 4 + lg.v_off[np]) = V[0][np][r];
@@ -448,6 +454,9 @@ template <int CIN, int KB, bool F32, bool DENSE>
 hipError_t first_launch_t(const FirstParams& p, size_t lds, hipStream_t s) {
   const dim3 grid((unsigned)p.n_tiles), block((unsigned)(p.pairs * p.blocks * 64));
   auto kern = p.v_trace ? &first_kernel<CIN, KB, F32, DENSE, true> : &first_kernel<CIN, KB, F32, DENSE, false>;
+  if constexpr (F32) {
+    if (p.v_trace && p.Cout <= 16) kern = p.Cout <= 8 ? &first_kernel<CIN, KB, F32, DENSE, true, 1> : &first_kernel<CIN, KB, F32, DENSE, true, 2>;
+  }
   if (lds > 64 * 1024) {                       // (fp32, two channels, stride 2 on wide rows, with a membrane to turn)
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
     if (e != hipSuccess) return e;

@@ -51,6 +51,20 @@ def test_tiles_of_first_layers(case, precision, dense):
     print("first layer", par)
 
 
+@pytest.mark.parametrize("Cout", [1, 7, 8, 9, 16, 17])
+@pytest.mark.parametrize("Cin,K,T,mode", [(1, 2, 5, TP), (2, 8, 17, TAC), (1, 16, 16, TAC), (2, 1, 3, STEP)])
+def test_recorded_membranes_of_few_channels_fp32(Cin, K, T, mode, Cout):
+    """Up to 8 and up to 16 channels have kernels that record a quarter and a half of the registers."""
+    r = np.random.Generator(np.random.PCG64(9150 + Cin + Cout + K))
+    s = (r.random((T, 3, Cin, 13, 37)) < 0.3).astype(np.uint8)
+    w = synth.kaiming_normal(68, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    v0 = (r.standard_normal((3, Cout, 13, 37)) * 0.3).astype(np.float32)
+    for x in (s, (s * r.random(s.shape)).astype(np.float32)):
+        par, g, ref = check_layer(x, w, K=K, beta=0.9, theta=1.0, mode=mode, precision=F32, bias=bias, v0=v0)
+        print("first layer", par)
+
+
 @pytest.mark.parametrize("precision", [B16, F32], ids=["bf16", "fp32"])
 @pytest.mark.parametrize("Cin", [1, 2])
 def test_values_beyond_a_window_do_not_reach_it(Cin, precision):
