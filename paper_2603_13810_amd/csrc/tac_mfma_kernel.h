@@ -109,7 +109,7 @@ struct Geo {
   // behind it, when the output spikes are pooled before they are stored: the exchange area of pooled_store
   // (output rows of 32 or 64 pixels only)
   static constexpr bool kCanPoolOut = S == 1 && kWo >= 32;
-  static constexpr int pool_bytes(int MC) { return kCanPoolOut ? pool_exchange_bytes(kTileRows, MC * 32, 1) : 0; }
+  static constexpr int pool_bytes(int MC) { return kCanPoolOut ? pool_exchange_bytes(kTileRows, MC * 32) : 0; }
   // LDS column (in 16-byte units) of padded pixel xp
   __host__ __device__ static constexpr int col(int xp) { return S == 1 ? xp : (xp & 1) * kXH + (xp >> 1); }
   // the loader pipeline has kSteps + 2 slots (slot i reads the words of step i, looks up step
@@ -875,9 +875,9 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         if constexpr (G::kCanPoolOut) {
           const uint32_t plane_p = (uint32_t)(Ho >> 1);                      // one word per pooled row
           uint32_t* ex = reinterpret_cast<uint32_t*>(lds + G::lds_bytes(K, MC)) + (step & 1) * (G::kTileRows * kCT);
-          pooled_store<MC, COLS>(word, ex, tid, kThreads, G::kTileRows, 1, G::kWaveRows == 2, wave * G::kWaveRows, 0,
-                           p.out + (step * p.B * p.Cout + (size_t)b * p.Cout + co_wave) * plane_p + (y0 >> 1), plane_p, 1,
-                           min(G::kTileRows >> 1, (Ho - y0) >> 1), kCT);
+          pooled_store<MC, COLS>(word, ex, tid, kThreads, G::kTileRows, G::kWaveRows == 2, wave * G::kWaveRows,
+                           p.out + (step * p.B * p.Cout + (size_t)b * p.Cout + co_wave) * plane_p + (y0 >> 1), plane_p,
+                           min(G::kTileRows >> 1, (Ho - y0) >> 1));
         }
       } else if (out_ok) {
         uint32_t* const o = out_wave + step * out_step;
@@ -1056,7 +1056,7 @@ inline void fill_params(MfmaParams& mp, const LayerParams& p) {
   mp.spikes = p.spikes; mp.w = static_cast<const uint8_t*>(p.w); mp.bias = p.bias; mp.v_inout = p.v_inout;
   mp.out = p.out; mp.v_trace = p.v_trace;
   mp.B = p.B; mp.Cin = p.Cin; mp.H = p.H; mp.W = p.W; mp.Ho = p.Ho; mp.Wo = p.Wo; mp.Cout = p.Cout; mp.stride = p.stride;
-  mp.K = p.K; mp.G = p.G; mp.n_lif = p.n_lif; mp.maxpool = p.pool2 == 2; mp.dense = 0; mp.out_pool = p.out_pool;
+  mp.K = p.K; mp.G = p.G; mp.n_lif = p.n_lif; mp.maxpool = p.pool2 == 2; mp.out_pool = p.out_pool;
   mp.row_tiles = 0;
   mp.decay = p.decay; mp.theta = p.theta;
   for (int j = 0; j < TAC_MAX_K; ++j) {

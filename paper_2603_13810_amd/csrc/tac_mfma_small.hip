@@ -505,14 +505,7 @@ hipError_t first_launch(const LayerParams& l, hipStream_t s) {
 bool mfma_small_supported(const tac_layer_desc_t& d) {
   if (d.precision != TAC_BF16 || (d.in_format != TAC_IN_BITS && d.in_format != TAC_IN_F32)) return false;
   if (d.Cin < 1 || d.Cin > 2) return false;
-  if (d.W > kFirstMaxW) return false;
-  if (d.in_format == TAC_IN_F32) return true;
-  // Groups of so many frames that their words are more than 2304 in four (two) output rows belong to the vector kernel: prepared
-  // weights are laid out for one or the other, and callers keep them.
-  const int K = d.mode == TAC_PER_STEP ? 1 : d.K;
-  const int Wo = (d.W + 2 - 3) / d.stride + 1;
-  const int rows = (Wo > 64 ? 1 : 3) * d.stride + 3;
-  return d.Cin * rows * ((d.W + 31) / 32) * K <= 2304;
+  return d.W <= kFirstMaxW;
 }
 
 size_t mfma_small_weight_bytes(const tac_layer_desc_t& d) {
