@@ -9,7 +9,7 @@ hipError_t mid_launch_f32(const MidParams&, int, int, hipStream_t) { return hipS
 hipError_t mid_launch_f32_trace(const MidParams&, int, int, hipStream_t) { return hipSuccess; }
 }  // namespace tac
 
-// out (mid_plan_of): kp, nmc, nnp, direct, jobs, loaders, batches, flatten, rows per block, workgroups, bytes of LDS.  0: the kernel does not
+// out (mid_plan_of): kp, nmc, nnp, direct, jobs, loaders, batches, flatten, rows per block, workgroups, bytes of LDS, split, nco.  0: the kernel does not
 // take the layer, -1: no tile fits.
 static tac::LayerParams params_of(const tac_layer_desc_t* d, float* trace) {
   tac::LayerParams p;
@@ -39,7 +39,7 @@ extern "C" int mid_plan_of(const tac_layer_desc_t* d, int with_trace, int* out) 
   if (!tac::mid_choose(p, a, kp, nmc, nnp)) return -1;
   const tac::MidPlan& q = a.q;
   const int v[] = {kp, nmc, nnp, q.direct, q.n_jobs, q.loaders, q.batches, q.flatten, q.rpb,
-                   q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B), q.total};
+                   q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B), q.total, q.split, q.nco};
   std::copy(std::begin(v), std::end(v), out);
   return 1;
 }

@@ -1,6 +1,6 @@
 """Small images on many channels in the in-between kernel: eight waves share a workgroup's pixel blocks, eight or four of them one,
 and add up their parts of the contraction; against the oracle, at the edges of the ranges of k-steps, of the blocks and of the four
-steps that are stored together."""
+steps that are stored together.  And fp32 layers of several tiles of 32 output channels, one or two tiles a workgroup."""
 import numpy as np
 import pytest
 
@@ -8,6 +8,7 @@ from paper_2603_13810_amd import api, synth
 from gpu_util import check_layer
 
 pytestmark = pytest.mark.gpu
+B16, F32 = api.TAC_BF16, api.TAC_FP32
 TAC, TP, STEP = api.TAC_COLLAPSE, api.TAC_PRESERVE, api.TAC_PER_STEP
 
 # (B, Cin, Cout, H, W, stride, pool in the writer, mode, K, T, what)
@@ -15,7 +16,7 @@ CASES = [
     (1, 64, 32, 1, 1, 1, False, TAC, 2, 3, "one pixel, ranges of four and five steps"),
     (2, 64, 33, 2, 2, 1, True, TP, 3, 7, "a second block of one channel, three steps together, a last group of one"),
     (3, 72, 40, 3, 16, 1, False, TP, 5, 11, "five steps in two goes, rows of 16"),
-    (5, 96, 64, 7, 7, 1, False, TAC, 4, 9, "blocks that straddle samples"),
+    (5, 96, 64, 7, 7, 1, False, TAC, 4, 9, "rows of seven pixels"),
     (16, 128, 128, 16, 16, 1, True, TP, 4, 8, "four waves a block"),
     (16, 128, 128, 4, 4, 1, True, TP, 8, 16, "eight waves a block, eight steps"),
     (1, 128, 70, 16, 9, 1, False, STEP, 1, 3, "single frames"),
@@ -41,10 +42,10 @@ def test_waves_that_share_a_pixel_block(case):
     print(case, par)
 
 
-# fp32 layers: two tiles of 32 output channels over one aggregate tile; a last workgroup with one of them, a tile of few channels
+# fp32 layers of so few rows that a workgroup takes one tile of 32 output channels; the last tile has few channels
 @pytest.mark.parametrize("case", [(2, 32, 96, 9, 14, 1, True, TAC, 4, 9), (1, 16, 33, 7, 20, 2, False, TP, 3, 7), (3, 40, 130, 5, 6, 1, False, TAC, 16, 17)],
                          ids=["three tiles", "a second tile of one channel", "five tiles, a last group of one"])
-def test_two_channel_tiles_over_one_aggregate_tile_fp32(case):
+def test_one_channel_tile_over_an_aggregate_tile_fp32(case):
     B, Cin, Cout, H, W, stride, pool, mode, K, T = case
     r = np.random.Generator(np.random.PCG64(6700 + Cin + Cout + K))
     f = 2 if pool else 1
@@ -57,3 +58,38 @@ def test_two_channel_tiles_over_one_aggregate_tile_fp32(case):
                               expect_kernel=api.TAC_KERNEL_MFMA)
     assert ref[0].any()
     print(case, par)
+
+
+# (B, Cin, Cout, H, W, stride, pool on load, pool in the writer, precision, mode, K, T), and what the launch's plan has in it, with and
+# without the membrane trace (test_mid_plan.py holds the choice to it on the CPU).  nco = 2: two tiles of 32 output channels over one
+# aggregate tile, the last workgroup of an odd number with one of them.
+VARIANTS = {
+    "fp32, two tiles a workgroup, three in all, stride 2": ((2, 24, 96, 10, 15, 2, True, False, F32, TAC, 16, 32), dict(nco=2)),
+    "fp32, a second tile of one channel, two words a row": ((20, 32, 33, 18, 47, 1, "max", False, F32, TAC, 2, 5), dict(nco=2, rpb=1)),
+    "fp32, five tiles, two words a row": ((12, 32, 130, 9, 35, 1, True, False, F32, TAC, 4, 9), dict(nco=2, rpb=1)),
+    "fp32, five tiles, blocks of two samples": ((32, 40, 160, 17, 9, 1, True, False, F32, TAC, 3, 7), dict(nco=2, flatten=1, rpb=2)),
+    "fp32, three tiles, two loaders": ((32, 48, 96, 6, 48, 1, "max", False, F32, TAC, 8, 9), dict(nco=2, loaders=2)),
+    "fp32, five tiles, pooled output": ((20, 40, 160, 24, 12, 1, False, True, F32, TAC, 2, 5), dict(nco=2)),
+    "fp32, three tiles, a last group of one": ((64, 32, 96, 14, 14, 1, True, False, F32, TP, 3, 7), dict(nco=2, rpb=2)),
+    "eight waves a block of two samples, two jobs a wave": ((2, 104, 33, 19, 2, 1, False, False, B16, TP, 4, 9), dict(split=8, flatten=1, rpb=16, jobs=13, batches=1)),
+    "eight waves a block, two batches, stride 2": ((2, 88, 130, 15, 1, 2, False, False, B16, TP, 5, 6), dict(split=8, batches=2)),
+    "four waves a block of two samples, direct": ((12, 72, 96, 15, 13, 1, False, False, B16, TP, 2, 5), dict(split=4, flatten=1, rpb=2, direct=1)),
+    "four waves a block, two jobs of two batches": ((64, 104, 130, 14, 1, 1, False, False, B16, TAC, 3, 4), dict(split=4, flatten=1, jobs=13, batches=2)),
+}
+
+
+@pytest.mark.parametrize("name", VARIANTS)
+def test_variant(name):
+    B, Cin, Cout, H, W, stride, pool, out_pool, precision, mode, K, T = VARIANTS[name][0]
+    r = np.random.Generator(np.random.PCG64(6800 + Cin + Cout + H + W + K))
+    f = 2 if pool else 1
+    s = (r.random((T, B, Cin, f * H, f * W)) < 0.12).astype(np.uint8)
+    w = synth.kaiming_normal(65, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    v0 = (r.standard_normal((B, Cout, Ho, Wo)) * 0.3).astype(np.float32)
+    par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, pool2=pool, precision=precision, bias=bias, v0=v0,
+                              expect_kernel=api.TAC_KERNEL_MFMA, oracle_samples=[0, 1, B // 2, B - 1] if B > 8 else None,
+                              **(dict(out_pool=True) if out_pool else {}))
+    assert ref[0].any()
+    print(name, par)

@@ -10,10 +10,11 @@ import time
 import pytest
 
 from paper_2603_13810_amd import api, build
+import test_gpu_mid_split
 from test_gpu_mid import VARIANTS
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-FIELDS = ("kp", "nmc", "nnp", "direct", "jobs", "loaders", "batches", "flatten", "rpb", "workgroups", "lds")
+FIELDS = ("kp", "nmc", "nnp", "direct", "jobs", "loaders", "batches", "flatten", "rpb", "workgroups", "lds", "split", "nco")
 
 
 @pytest.fixture(scope="module")
@@ -44,6 +45,24 @@ def test_case_takes_the_variant_it_is_there_for(plan, name):
         assert {k: got[k] for k in want} == want
     if "two pixels a thread" in name:
         assert case[1] // 8 * 4 * case[4] > 256                # at least four rows of aggregates
+
+
+@pytest.mark.parametrize("name", test_gpu_mid_split.VARIANTS)
+def test_case_of_shared_blocks_and_tiles_takes_its_variant(plan, name):
+    case, want = test_gpu_mid_split.VARIANTS[name]
+    for trace in (False, True):
+        got = plan(*case, trace=trace)
+        assert {k: got[k] for k in want} == want
+        if "two samples" in name:
+            assert ((case[3] - 1) // case[5] + 1) % got["rpb"] != 0
+
+
+@pytest.mark.parametrize("case", test_gpu_mid_split.CASES, ids=[c[-1] for c in test_gpu_mid_split.CASES])
+def test_cases_of_waves_that_share_a_block(plan, case):
+    B, Cin, Cout, H, W, stride, out_pool, mode, K, T, what = case
+    for trace in (False, True):
+        got = plan(B, Cin, Cout, H, W, stride, False, out_pool, api.TAC_BF16, mode, K, T, trace)
+        assert got["split"] == (4 if "four waves" in what else 8)
 
 
 def test_single_frames_of_few_channels_share_the_compute_units(plan):
