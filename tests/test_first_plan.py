@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 from paper_2603_13810_amd import api, build
+from test_gpu_first import TILES
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -67,6 +68,18 @@ def test_launches_of_fp32_layers_fit_a_grid(shim, shape, taken):
     d = _desc(B, 1, Cout, H, W)
     api.tac_out_shape(d)                                       # an accepted layer
     assert bool(shim.fp32_layer_on_matrix_cores(ctypes.byref(d))) == taken
+
+
+@pytest.mark.parametrize("name", TILES)
+def test_case_has_the_tiles_it_is_there_for(plan, name):
+    (Cin, Cout, H, W, stride, B, T, K, mode, pooled), (pairs, blocks, rest) = TILES[name]
+    for precision in (api.TAC_BF16,) if pooled else (api.TAC_BF16, api.TAC_FP32):
+        d = _desc(B, Cin, Cout, H, W, stride, precision, **(dict(out_format=api.TAC_OUT_BITS_MAXPOOL2) if pooled else {}))
+        got = plan(d)
+        Ho, words = (H - 1) // stride + 1, ((W - 1) // stride + 32) // 32
+        in_all = Ho // 2 * words if pooled else (Ho * words + 1) // 2
+        assert (got["pairs"], got["blocks"], in_all - got["pairs"] * (got["pair_tiles"] - 1)) == (pairs, blocks, rest)
+        assert got["workgroups"] >= 512
 
 
 def test_lds_of_a_workgroup(plan):

@@ -51,6 +51,39 @@ def test_tiles_of_first_layers(case, precision, dense):
     print("first layer", par)
 
 
+# Layers of so many samples that a tile has several block pairs: (Cin, Cout, H, W, stride, B, T, K, mode, pool in the writer), and
+# (pairs, blocks of 32 channels, pairs of the sample's last tile).  test_first_plan.py holds the choice to them on the CPU.
+TILES = {
+    "two pairs of four channel blocks, pooled": ((2, 128, 64, 64, 1, 16, 5, 4, TP, True), (2, 4, 2)),
+    "eight pairs, three words a row, pooled, a short last tile": ((1, 32, 10, 90, 1, 256, 3, 2, TAC, True), (8, 1, 7)),
+    "four pairs, two words a row, pooled, a short last tile": ((2, 64, 14, 34, 1, 128, 4, 3, TP, True), (4, 2, 2)),
+    "eight pairs, stride 2, four words a row": ((2, 32, 128, 128, 2, 64, 3, 2, TAC, False), (8, 1, 8)),
+    "six pairs, three words a row, a short last tile": ((1, 24, 11, 70, 1, 256, 4, 4, TAC, False), (6, 1, 5)),
+    "two pairs of three channel blocks, a last tile of one": ((2, 96, 7, 33, 1, 128, 5, 2, TP, False), (2, 3, 1)),
+    "three pairs of two channel blocks, stride 2": ((1, 40, 11, 40, 2, 512, 3, 1, STEP, False), (3, 2, 3)),
+    "eight pairs, one word a row": ((2, 9, 32, 17, 1, 400, 4, 3, TAC, False), (8, 1, 8)),
+}
+
+
+# (fp32 first layers have no pool in the writer)
+@pytest.mark.parametrize("dense", [False, True], ids=["bits", "values"])
+@pytest.mark.parametrize("name,precision", [(n, p) for n in TILES for p in (B16, F32) if p == B16 or not TILES[n][0][-1]])
+def test_tiles_of_several_pairs(name, precision, dense):
+    Cin, Cout, H, W, stride, B, T, K, mode, pooled = TILES[name][0]
+    r = np.random.Generator(np.random.PCG64(9500 + 7 * Cin + Cout + H + W + T + K))
+    s = (r.random((T, B, Cin, H, W), dtype=np.float32) < 0.3).astype(np.uint8)
+    if dense:
+        s = s * r.random(s.shape, dtype=np.float32)
+    w = synth.kaiming_normal(69, Cout, Cin) * np.float32(1.5)
+    bias = (r.standard_normal(Cout) * 0.1).astype(np.float32)
+    Ho, Wo = (H - 1) // stride + 1, (W - 1) // stride + 1
+    v0 = r.standard_normal((B, Cout, Ho, Wo), dtype=np.float32) * np.float32(0.3)
+    par, g, ref = check_layer(s, w, K=K, beta=0.9, theta=1.0, mode=mode, stride=stride, precision=precision, bias=bias, v0=v0,
+                              oracle_samples=[0, 1, B // 2, B - 1], **(dict(out_pool=True) if pooled else {}))
+    assert ref[0].any()
+    print(name, par)
+
+
 @pytest.mark.parametrize("Cout", [1, 7, 8, 9, 16, 17])
 @pytest.mark.parametrize("Cin,K,T,mode", [(1, 2, 5, TP), (2, 8, 17, TAC), (1, 16, 16, TAC), (2, 1, 3, STEP)])
 def test_recorded_membranes_of_few_channels_fp32(Cin, K, T, mode, Cout):
