@@ -161,12 +161,16 @@ def tac_prepared_weight_bytes(desc: tac_layer_desc_t) -> int:
 
 
 # The two below run up to seven times per call: plain integers for the void* arguments, and the current stream's handle without a
-# Stream object (1.0 us).
+# Stream object (1.0 us) where torch has the function that gives it.
 def _stream(stream=None):
     if stream is not None:
         return int(stream)
     import torch
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    try:
+        handle = torch._C._cuda_getCurrentRawStream
+    except AttributeError:
+        return torch.cuda.current_stream().cuda_stream
+    return handle(torch.cuda.current_device())
 
 
 def _dev_ptr(t, dtype=None, name="tensor"):

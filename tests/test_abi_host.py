@@ -259,3 +259,15 @@ def test_matrix_core_probe_rejects_bad_requests_before_any_launch():
     assert L.tac_mfma_probe(0, fake, None) == api.TAC_ERR_BAD_PARAM
     assert L.tac_mfma_probe(10, ctypes.c_void_p(0x1002), None) == api.TAC_ERR_ALIGN
     assert L.tac_mfma_probe_workgroups() % 4 == 0 and L.tac_mfma_probe_workgroups() > 0
+
+
+def test_current_stream_without_the_private_function(monkeypatch):
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 0)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x5678, raising=False)
+    assert api._stream() == 0x5678
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert api._stream() == 0x1234
+    assert api._stream(0) == 0
