@@ -158,6 +158,11 @@ int tac_prepare_weights(const tac_layer_desc_t* desc, const float* w_oihw, void*
  *                      ([T_out][B][Cout][Ho/2][ceil(Wo/2/32)] with TAC_OUT_BITS_MAXPOOL2)
  *   v_trace            DEVICE, optional debug output, float32 [T_out][B][Cout][Ho][Wo]:
  *                      membrane BEFORE the reset at every LIF step; NULL in timed runs
+ * Samples are independent, and a sample's outputs have the same bits whatever B is, with one exception: TAC_BF16 layers
+ * of the in-between member (see tac_select_kernel) with Cin >= 64, output rows of at most 16 pixels and no pool on load sum
+ * the products of a neuron in eight parts while B Ho Cout is small (at most 512 blocks of 32 pixels x 32 channels; 128
+ * channels at 16 x 16: up to 16 samples), in one chain beyond.  Both are fp32 sums of the same products; their last
+ * bits differ, and with them a spike where the membrane comes that close to theta.
  * Buffers must not overlap.  All pointers need 4-byte alignment (input 8-byte with
  * TAC_IN_BITS_MAXPOOL2 on the MFMA kernel; w_prepared 16-byte), else TAC_ERR_ALIGN. */
 int tac_conv_lif(const tac_layer_desc_t* desc, const void* input, const void* w_prepared,
@@ -293,7 +298,8 @@ typedef struct tac_backward_desc {
  *              gradient to each input of the mean pool; all of it to the first maximal input of the
  *              max pool's window in row-major order (the first set bit, else the first input)
  * Enqueued on `stream`; nothing is allocated or synchronised; sums over pixels use float atomics,
- * so the last bits of grad_w and grad_bias depend on the order of arrival.
+ * so the last bits of grad_w and grad_bias depend on the order of arrival.  Those of grad_in may depend on how many
+ * (group, sample) pairs there are (fp32 gradients of few pixels are summed in four parts).
  * Errors: as tac_conv_lif; TAC_ERR_UNSUPPORTED for W > 1024 or
  * more than 65535 (group, sample) pairs; TAC_ERR_BAD_PARAM for a bad surrogate or alpha <= 0. */
 int tac_conv_lif_backward(const tac_layer_desc_t* desc, const tac_backward_desc_t* bwd, const void* input,

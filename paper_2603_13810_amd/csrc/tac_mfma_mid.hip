@@ -246,6 +246,7 @@ hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void
 // Small images on many channels: eight waves share the pixel blocks of a workgroup (the kernel's SPLIT), as long as there are few of them:
 // 512 blocks of 32 pixels x 32 channels.  Beyond that the four-wave tiles fill their waves and the exchange of partial sums costs more
 // than it gives (us, split / not: 128 -> 128 at 16 x 16, K = 4, B = 16 (512) 23.5 / 33; B = 64 92 / 72; 64 -> 64 at 10 x 10, B = 128 (1280) 47 / 29).
+// The two sum the products in different orders, so that a sample's last bits differ between the two sides of this line, the batch included.
 static bool mid_split_rule(const LayerParams& p) {
   if (!p.bf16 || p.pool2 || p.Cin < 64 || p.Wo > 16) return false;
   const int rows = p.Wo > 8 ? 2 : p.Wo > 4 ? 4 : p.Wo > 2 ? 8 : 16;    // of a block

@@ -5,7 +5,8 @@ import numpy as np
 import pytest
 
 from paper_2603_13810_amd import api, synth
-from gpu_util import check_layer
+from gpu_util import check_layer, run_gpu
+from parity_util import TOL_FP32, compare
 
 pytestmark = pytest.mark.gpu
 B16, F32 = api.TAC_BF16, api.TAC_FP32
@@ -93,3 +94,24 @@ def test_variant(name):
                               **(dict(out_pool=True) if out_pool else {}))
     assert ref[0].any()
     print(name, par)
+
+
+# (samples of a call whose waves share blocks, samples of one whose waves do not), 128 -> 128 channels at 16 x 16
+SHARED, ALONE = (8, 16), (32, 64)
+
+
+def test_a_batch_and_its_parts_agree():
+    """The rule for sharing blocks looks at the batch, and the two sides of it sum in different orders: a batch agrees with its parts to the
+    precision of fp32 sums, and bit for bit where both are on one side."""
+    r = np.random.Generator(np.random.PCG64(6900))
+    s = (r.random((8, 64, 128, 16, 16)) < 0.12).astype(np.uint8)
+    w = synth.kaiming_normal(66, 128, 128) * np.float32(1.5)
+    bias = (r.standard_normal(128) * 0.1).astype(np.float32)
+    kw = dict(K=4, beta=0.9, theta=1.0, mode=TP, precision=B16, bias=bias)
+    runs = {B: [run_gpu(s[:, i:i + B], w, **kw) for i in range(0, 64, B)] for B in SHARED + ALONE}
+    spikes, traces = ({B: np.concatenate([g[k] for g in v], axis=1) for B, v in runs.items()} for k in ("spikes", "v_trace"))
+    for one, other in (SHARED, ALONE):
+        assert np.array_equal(spikes[one], spikes[other]) and np.array_equal(traces[one], traces[other])
+    par = compare(spikes[SHARED[1]], traces[SHARED[1]].astype(np.float64), spikes[ALONE[0]], traces[ALONE[0]], 1.0, TOL_FP32)
+    assert par.ok, par
+    print("a batch and its parts", par)

@@ -65,6 +65,13 @@ def test_cases_of_waves_that_share_a_block(plan, case):
         assert got["split"] == (4 if "four waves" in what else 8)
 
 
+def test_batches_on_either_side_of_the_rule(plan):
+    for batches, shared in ((test_gpu_mid_split.SHARED, True), (test_gpu_mid_split.ALONE, False)):
+        for B in batches:
+            got = plan(B, 128, 128, 16, 16, 1, False, False, api.TAC_BF16, api.TAC_PRESERVE, 4, 8, True)
+            assert bool(got["split"]) == shared
+
+
 def test_single_frames_of_few_channels_share_the_compute_units(plan):
     # one workgroup of two pixel blocks per compute unit, 251 of them, takes 52 us a call; twice as many smaller ones without
     # staging 33 us
