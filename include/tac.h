@@ -163,6 +163,8 @@ int tac_prepare_weights(const tac_layer_desc_t* desc, const float* w_oihw, void*
  * the products of a neuron in eight parts while B Ho Cout is small (at most 512 blocks of 32 pixels x 32 channels; 128
  * channels at 16 x 16: up to 16 samples), in one chain beyond.  Both are fp32 sums of the same products; their last
  * bits differ, and with them a spike where the membrane comes that close to theta.
+ * Images of 2^28 and more output neurons per channel with 5 to 7 channels (millions of rows): with v_inout or v_trace
+ * TAC_ERR_UNSUPPORTED on the MFMA kernel; the DIRECT kernel takes them.
  * Buffers must not overlap.  All pointers need 4-byte alignment (input 8-byte with
  * TAC_IN_BITS_MAXPOOL2 on the MFMA kernel; w_prepared 16-byte), else TAC_ERR_ALIGN. */
 int tac_conv_lif(const tac_layer_desc_t* desc, const void* input, const void* w_prepared,

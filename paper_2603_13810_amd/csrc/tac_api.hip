@@ -175,6 +175,7 @@ int tac_conv_lif(const tac_layer_desc_t* d, const void* input, const void* w_pre
   p.n_lif = desc->mode == TAC_PRESERVE ? p.K : 1;
   p.bf16 = desc->precision == TAC_BF16;
   p.theta = desc->theta;
+  if (kern == TAC_KERNEL_MFMA && (v_inout || v_trace) && !tac::membranes_in_reach(p)) return TAC_ERR_UNSUPPORTED;
   // powers of beta in double from the fp32 beta the caller passed, rounded once
   const double beta = (double)desc->beta;
   double pw = 1.0;

@@ -6,7 +6,6 @@ namespace tac {
 
 constexpr int kFirstWaves = 8;                 // per workgroup at most
 constexpr int kFirstMaxW = 128;                // input width limit (4 words per row)
-constexpr int kFirstTileRows = 16;             // output rows per workgroup at most
 
 // row of the aggregate tile: a padding column on either side, room for the last word's four pixels
 __host__ __device__ constexpr int first_row_words(int W) { return ((W + 3) & ~3) + 2; }
@@ -47,10 +46,7 @@ inline FirstPlan first_plan(const LayerParams& l) {
 // layer gives the same bits with and without recording: both take the same kernel).
 inline bool first_f32_supported(const LayerParams& p) {
   if (p.vector_only || p.bf16 || p.pool2 || p.out_pool || p.Cin > 2 || p.W > kFirstMaxW) return false;
-  // The upper lane half's membranes are four planes behind the lower one's, in 32-bit byte offsets from the tile's first row: planes of 2^28
-  // neurons with channels there (more than 2 million rows) belong to the vector kernel, which counts in 64 bits.
-  const long long plane = (long long)p.Ho * p.Wo;
-  if (p.Cout > 4 && (4 * plane + kFirstTileRows * p.Wo) * 4 >= (1ll << 32)) return false;
+  if (!membranes_in_reach(p)) return false;    // (the vector kernel counts in 64 bits)
   // A launch has fewer than 2^32 threads in one dimension, and all workgroups are in one; the vector kernel's are in three (65535 times its 32
   // channels at most).
   const FirstPlan plan = first_plan(p);

@@ -38,6 +38,11 @@ struct LayerParams {
   float decay_last;
 };
 
+// Whether the kernels of first layers and of the shapes in between reach a layer's membranes: the upper lane half's are four planes
+// behind the lower one's, in 32-bit byte offsets from the tile's first row (tiles of at most 2048 pixels).  From planes of 2^28 neurons on (5 to 7
+// channels; more do not fit the limit of 2^31 per step) they do not.
+inline bool membranes_in_reach(const LayerParams& p) { return p.Cout <= 4 || 4ll * p.Ho * p.Wo + 2048 < (1ll << 30); }
+
 // direct (vector-FMA) kernel family: any shape
 size_t direct_weight_bytes(const tac_layer_desc_t& d);
 hipError_t direct_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);

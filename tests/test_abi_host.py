@@ -271,3 +271,13 @@ def test_current_stream_without_the_private_function(monkeypatch):
     monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
     assert api._stream() == 0x1234
     assert api._stream(0) == 0
+
+
+# 2^28 neurons a channel: a first layer, one in between, one in between with the pool in the writer
+@pytest.mark.parametrize("shape", [(1, 5, {}), (8, 6, {}), (8, 5, dict(out_format=api.TAC_OUT_BITS_MAXPOOL2))], ids=["first", "in between", "pooled"])
+def test_membranes_out_of_reach_are_refused(shape):
+    Cin, Cout, kw = shape
+    d = api.make_desc(1, 1, Cin, 2 ** 22, 64, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP, precision=api.TAC_BF16, **kw)
+    assert api.tac_select_kernel(d) == api.TAC_KERNEL_MFMA
+    call = lambda v, trace: api.lib().tac_conv_lif(ctypes.byref(d), 4096, 4096, None, v, 4096, trace, None)
+    assert call(4096, None) == call(None, 4096) == call(4096, 4096) == api.TAC_ERR_UNSUPPORTED
