@@ -164,6 +164,7 @@ int tac_prepare_weights(const tac_layer_desc_t* desc, const float* w_oihw, void*
  * channels at 16 x 16: up to 16 samples), in one chain beyond.  Both are fp32 sums of the same products; their last
  * bits differ, and with them a spike where the membrane comes that close to theta.  (Also TAC_FP32 layers of one or two input
  * channels over so many samples and rows that the first layers' kernel would take 2^32 threads: they run on the vector kernel.)
+ * TAC_KERNEL_DIRECT sums in one order whatever B is.
  * Images of 2^28 and more output neurons per channel with 5 to 7 channels (millions of rows): with v_inout or v_trace
  * TAC_ERR_UNSUPPORTED on the MFMA kernel; the DIRECT kernel takes them.
  * Buffers must not overlap.  All pointers need 4-byte alignment (input 8-byte with
