@@ -333,18 +333,21 @@ __device__ __forceinline__ uint32_t pooled_of_cols(const uint32_t (&bits)[2]) {
 //   plane_p    words per channel of the pooled tensor
 //   rows_p     pooled rows of the tile inside the image
 // Called by all threads of the workgroup (it contains a barrier); consecutive steps alternate between two areas.
-// COLS: the words as words_of_cols leaves them (lane 32 np + n: channel n).
-template <int NMC, bool COLS>
+//   c_first    first channel of the wave within the tile
+// COLS: the words as words_of_cols leaves them (lane 32 np + n: channel n).  MC: 32-channel blocks of the tile (NMC of them the wave's).  GH = 2:
+// the wave's words are those of registers 0 .. 7, in lanes 0 .. 31.
+template <int NMC, bool COLS, int MC = NMC, int GH = 1>
 __device__ __forceinline__ void pooled_store(const uint32_t (&word)[NMC][2], uint32_t* ex, int tid, int nthreads, int rows,
-                                             bool two_rows, int row0, uint32_t* out_tile, size_t plane_p, int rows_p) {
-  constexpr int ctile = NMC * 32;
+                                             bool two_rows, int row0, int c_first, uint32_t* out_tile, size_t plane_p, int rows_p) {
+  constexpr int ctile = MC * 32;
   const int lane = tid & 63;
   const int r = lane >> 2, hi = (lane >> 1) & 1, np = COLS ? lane >> 5 : lane & 1;
   const int c_lane = COLS ? lane & 31 : 8 * (r >> 2) + 4 * hi + (r & 3);
 #pragma unroll
   for (int mc = 0; mc < NMC; ++mc) {
     const uint32_t hp = pool_pairs(word[mc][0]);
-    const int c = mc * 32 + c_lane;
+    const int c = c_first + mc * 32 + c_lane;
+    if (GH == 2 && lane >= 32) continue;
     if (two_rows)
       ex[(row0 + np) * ctile + c] = hp;
     else

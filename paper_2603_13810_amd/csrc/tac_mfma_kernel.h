@@ -72,15 +72,16 @@ __host__ __device__ constexpr int lut_bytes(int K, bool room) {
 
 // Compile-time geometry of a tile: input width WIN (32 or 64 pixels = 1 or 2 words), stride S,
 // NP blocks of 32 output pixels per wave (2; 1 gives half as high a tile, for layers whose grid
-// would otherwise leave compute units idle; output rows of at most 32 pixels only).
-template <int WIN, int S, int NP = 2>
+// would otherwise leave compute units idle; output rows of at most 32 pixels only).  CW: of the four waves, CW share a
+// pixel block (each with its part of the channels), so that the tile is 1 / CW as high.  GH: groups of frames in hand at a time (see the kernel).
+template <int WIN, int S, int NP = 2, int CW = 1, int GH = 1>
 struct Geo {
   static constexpr int kWo = WIN / S;                        // output width: 64, 32 or 16
   static constexpr int kS = S;
   static constexpr int kNP = NP;
   static_assert(NP == 2 || (NP == 1 && kWo <= 32), "half tiles: whole rows per wave");
   static constexpr int kWaveRows = NP * 32 / kWo;            // output rows per wave
-  static constexpr int kTileRows = kWaves * kWaveRows;       // output rows per workgroup
+  static constexpr int kTileRows = kWaves / CW * kWaveRows;  // output rows per workgroup
   static constexpr int kInRows = (kTileRows - 1) * S + 3;    // input rows with the 3x3 halo
   static constexpr int kWW = WIN / 32;                       // words per input row
   static constexpr int kRowWords = kInRows * kWW;            // staged words per channel and frame
@@ -97,15 +98,18 @@ struct Geo {
   __host__ __device__ static constexpr int words_bytes(int K) { return kRowWords * (K * kChunk + stage_pad(K)) * 4; }
   static constexpr int kOutWords = (kWo + 31) / 32;          // packed words per output row
   static constexpr int kLdsA = 0;
-  static constexpr int kLdsW = kLdsA + 2 * kABuf;
+  static constexpr int kLdsW = kLdsA + GH * 2 * kABuf;
   // two weight buffers of 9 taps x MC blocks of one KiB, bias, aggregate table, one staging buffer: a wave stages
   // the words of the four channels it aggregates itself, so its in-order LDS accesses are all the ordering the
   // buffer needs (the words of chunk s+2 are written behind the wave's last read of chunk s+1's)
   __host__ __device__ static constexpr int lds_bias(int MC) { return kLdsW + 2 * 9 * MC * 1024; }
   __host__ __device__ static constexpr int lds_lut(int MC) { return lds_bias(MC) + kCoutTile * 4; }
   // the pair table of K = 4 (1 KiB) where the largest tile of the geometry still fits with it
-  static constexpr bool kLutRoom = lds_lut(kMC) + 1024 + words_bytes(4) <= kLdsLimit;
-  static constexpr int lds_bytes(int K, int MC = kMC) { return lds_lut(MC) + lut_bytes(K, kLutRoom) + words_bytes(K); }
+  static constexpr bool kLutRoom = GH == 2 || lds_lut(kMC) + 1024 + words_bytes(4) <= kLdsLimit;
+  // GH = 2: the sums that the two halves of the workgroup exchange, half of every wave's
+  static constexpr int exchange_bytes(int MC) { return GH == 2 ? 2 * kWaves * (MC / CW) * NP * 8 * 256 : 0; }
+  static constexpr int lds_exchange(int K, int MC) { return lds_lut(MC) + lut_bytes(K, kLutRoom) + GH * words_bytes(K); }
+  static constexpr int lds_bytes(int K, int MC = kMC) { return lds_exchange(K, MC) + exchange_bytes(MC); }
   // behind it, when the output spikes are pooled before they are stored: the exchange area of pooled_store
   // (output rows of 32 or 64 pixels only)
   static constexpr bool kCanPoolOut = S == 1 && kWo >= 32;
@@ -422,9 +426,18 @@ __device__ __forceinline__ void lds_barrier() {
 // their LDS allows it two workgroups share a compute unit, and with the wave priorities below (high while a wave
 // feeds the matrix cores, low during its LIF steps) one workgroup's LIF steps run under the other's MFMAs.
 // COLS: the LIF steps run with a channel per lane (lif_step_cols); the MFMA operands are swapped and a register is a pixel.
-template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP, bool AGG = false, bool COLS = false>
-__global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_kernel(const MfmaParams p) {
-  using G = Geo<WIN, S, NP>;
+// GH = 2: see launch_pairs.  Eight waves; the two halves of the workgroup take consecutive groups of frames, each with A tiles and staged
+// words of its own, on the same weights.  The groups' LIF steps follow each other, so behind the chunks a wave hands half of its
+// sums to the wave of the other half with the same pixels and channels: half 0 steps registers 0 .. 7 of every block (16 of its 32 channels) through
+// both groups, half 1 registers 8 .. 15.  No sum is formed in another order.
+template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP, bool AGG = false, bool COLS = false, int GH = 1, int CW = 1>
+__global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 : 1) void mfma_kernel(const MfmaParams p) {
+  using G = Geo<WIN, S, NP, CW, GH>;
+  static_assert(GH == 1 || (MC == 2 && !MP && !AGG && !COLS), "pairs of groups: tiles of 64 channels, pixels along the lanes");
+  static_assert(CW == 1 || GH == 2, "waves that share a pixel block: pairs of groups");
+  constexpr int MCW = MC / CW;                 // 32-channel blocks per wave
+  constexpr int kRegs = 16 / GH;               // registers of a block that a wave steps
+  constexpr int kNT = kThreads * GH;
   // MC = 32-channel blocks per workgroup and wave: 4 (128 output channels), or 2 (64) for layers
   // whose grid would otherwise leave compute units idle.  The prepared weights are laid out
   // for 128-channel tiles either way; a 64-channel workgroup copies its half of each tap.
@@ -439,7 +452,9 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int q = wave;                          // the cin quad this wave aggregates in every chunk
+  const int half = GH == 2 ? wave >> 2 : 0;    // GH = 2: which group of a pair
+  const int q = wave & 3;                      // the cin quad this wave aggregates in every chunk
+  const int px_wave = q / CW, co_part = q % CW;
   // Workgroups are handed to the 8 XCDs round-robin.  Tiles are numbered row tile fastest,
   // then cout tile, then sample, and XCD x takes the x-th eighth of that list: row tiles
   // that are neighbours in the image then run at about the same time under the same L2, which
@@ -456,15 +471,16 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   const int NC = p.Cin / kChunk;
   const int n = lane & 31, h = lane >> 5;
   const int Ho = p.Ho;
-  const int co_wave = co_tile * kCT;
-  const int total = p.G * NC;
+  const int co_wave = co_tile * kCT + co_part * (MCW * 32);
+  const int total = (p.G + GH - 1) / GH * NC;
   uint8_t* const lut = lds + kLdsLut;
-  uint8_t* const words0 = lut + lut_bytes(KT, G::kLutRoom);
-  const int oy_wave = y0 + wave * G::kWaveRows;                // first output row of this wave
+  uint8_t* const words0 = lut + lut_bytes(KT, G::kLutRoom) + half * G::words_bytes(K);
+  uint8_t* const a_lds = lds + G::kLdsA + half * (2 * G::kABuf);
+  const int oy_wave = y0 + px_wave * G::kWaveRows;             // first output row of this wave
 
   // zero padding columns (left of pixel 0, right of the last pixel) of both A buffers; they
   // are never written again
-  for (int i = tid; i < 2 * 2 * G::kInRows * 2; i += kThreads) {
+  for (int i = tid; i < GH * 2 * 2 * G::kInRows * 2; i += kNT) {
     const int side = i & 1, rr = (i >> 1) % G::kInRows, hh = (i >> 1) / G::kInRows % 2, bb = (i >> 1) / (2 * G::kInRows);
     const int c = side ? G::col(WIN + 1) : G::col(0);
     *reinterpret_cast<u32x4*>(lds + G::kLdsA + bb * G::kABuf + hh * G::kAHalf + (rr * G::kXP + c) * 16) = u32x4{0, 0, 0, 0};
@@ -479,30 +495,31 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   for (int np = 0; np < NP; ++np) {
     const int pix = np * 32 + n;
     const int lr = pix / G::kWo, ox = pix % G::kWo;
-    a_frag_off[np] = h * G::kAHalf + (((wave * G::kWaveRows + lr) * S) * G::kXP + G::col(ox * S)) * 16;
+    a_frag_off[np] = h * G::kAHalf + (((px_wave * G::kWaveRows + lr) * S) * G::kXP + G::col(ox * S)) * 16;
   }
   // wave-uniform element offset of (sample, first channel of the tile, first row of the wave)
   const size_t v_wave = ((size_t)b * p.Cout + co_wave) * plane + (size_t)oy_wave * G::kWo;
 
   // membrane, MFMA result layout: register r of tile (mc, np), lane -> cout = 32 mc + 8 (r/4) + 4 h + r%4
   static_assert(!COLS || (!TRACE && !AGG), "recorded membranes are stored with pixels along the lanes");
-  float V[MC][NP][16];
-  f32x16 acc[MC][NP];
+  float V[MCW][NP][16];                        // (GH = 2: the first 8 of a block)
+  f32x16 acc[MCW][NP];
   uint64_t agg_sum = 0;
   uint64_t* const agg = AGG ? &agg_sum : nullptr;
 #pragma unroll
-  for (int mc = 0; mc < MC; ++mc)
+  for (int mc = 0; mc < MCW; ++mc)
 #pragma unroll
     for (int np = 0; np < NP; ++np)
 #pragma unroll
       for (int r = 0; r < 16; ++r) V[mc][np][r] = 0.f;
+  const size_t v_regs = v_wave + (size_t)(half * 16) * plane;           // the first channel that the wave steps
   if (!AGG && p.v_inout) {
     const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane, p.theta);
-    const char* vb = reinterpret_cast<const char*>(p.v_inout + v_wave);
+    const char* vb = reinterpret_cast<const char*>(p.v_inout + v_regs);
     static_for<0, NP>([&](auto np_) {
       constexpr int np = decltype(np_)::value;
       if (lg.ok[np]) {
-        static_for<0, MC>([&](auto mc_) { static_for<0, 16>([&](auto r_) {
+        static_for<0, MCW>([&](auto mc_) { static_for<0, kRegs>([&](auto r_) {
           constexpr int mc = decltype(mc_)::value, r = decltype(r_)::value;
           V[mc][np][r] = *reinterpret_cast<const float*>(vb + (size_t)(mc * 32 + 8 * (r >> 2) + (r & 3)) * plane * 4 + lg.v_off[np]);
         }); });
@@ -510,7 +527,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     });
     if constexpr (COLS) {
       float* const t = reinterpret_cast<float*>(lds + G::kLdsW) + wave * kTurnFloats;
-      static_for<0, MC>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
+      static_for<0, MCW>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
       __syncthreads();                         // before the first weights arrive there
     }
   }
@@ -523,10 +540,12 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     const uint32_t* spk;
     const uint8_t* w;
     int c, left;             // chunk within the group; chunks after this one
+    int g;                   // GH = 2: the group
   };
   const size_t in_plane = (size_t)p.H * G::kWW * (MP ? 4 : 1);                 // stored dwords per (frame, sample, cin)
   const size_t spk_chunk = (size_t)kChunk * in_plane;
-  const size_t spk_wrap = (size_t)K * p.B * p.Cin * in_plane - (size_t)NC * spk_chunk;
+  const size_t spk_group = (size_t)K * p.B * p.Cin * in_plane;
+  const size_t spk_wrap = spk_group - (size_t)NC * spk_chunk;
   auto advance = [&](Cursor& cu) {
     if (cu.left > 0) {
       --cu.left;
@@ -537,6 +556,11 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         cu.c = 0;
         cu.spk += spk_wrap;
         cu.w -= (size_t)NC * kWBuf;
+        if constexpr (GH == 2) {
+          // two groups on; behind an odd last one the second half of the workgroup repeats it, and nobody uses that
+          if (cu.g + 2 < p.G) cu.spk += spk_group;
+          cu.g += 2;
+        }
       }
     }
   };
@@ -568,8 +592,8 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
       static_for<i0, i1>([&](auto i_) {
         constexpr int i = decltype(i_)::value;
         if constexpr (i < 5) {
-          const int blk = wave + 4 * i;              // 0 .. 17 (the fifth round only for waves 0 and 1)
-          if (i < 4 || wave < 2)
+          const int blk = wave + 4 * GH * i;         // 0 .. 17 (the last round only for waves 0 and 1)
+          if (GH == 2 ? i < 2 || (i == 2 && wave < 2) : i < 4 || wave < 2)
             lds_dma16<1, 0>(src + (uint32_t)((blk >> 1) * 4096 + (blk & 1) * 1024) + w_half_off + w_lane_off, dst + blk * 1024);
         }
       });
@@ -585,10 +609,10 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   constexpr std::integral_constant<int, 9> c9;
 
   StagePlan<NG> plan;
-  stage_plan<G, NG, MP>(plan, p, K, tid, y0 * S - 1);
+  stage_plan<G, NG, MP>(plan, p, K, tid & (kThreads - 1), y0 * S - 1);
   uint32_t wd[NG][KMAX * (MP ? 4 : 1)];         // staged words in flight
   const uint32_t fstride = (uint32_t)((size_t)p.B * p.Cin * in_plane);         // dwords between frames
-  lut_fill<KT, lut_pairs(KT, G::kLutRoom)>(lut, p, tid);
+  if (half == 0) lut_fill<KT, lut_pairs(KT, G::kLutRoom)>(lut, p, tid);
 
   // ---- prologue: A tile of chunk 0, weights of chunks 0 and 1, staged words of chunk 1,
   //      words of chunk 2 in registers
@@ -597,7 +621,8 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   const uint8_t* w_n2;                          // weights and words of chunk s + 2
   const uint32_t* spk_n2;
   {
-    cur.spk = p.spikes + ((size_t)b * p.Cin) * in_plane;
+    cur.g = GH == 2 ? min(half, p.G - 1) : 0;
+    cur.spk = p.spikes + ((size_t)b * p.Cin) * in_plane + cur.g * spk_group;
     cur.w = p.w + (size_t)(MC == 4 ? co_tile : co_tile >> 1) * NC * kWBuf;     // the 128-channel tile's weights
     cur.c = 0;
     cur.left = total - 1;
@@ -609,7 +634,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     weights_to_lds(cur.w, lds + G::kLdsW + kWBufL, c0, c9);
     stage_load<KMAX, NG, MP, G::kWW>(wd, plan, cur.spk, fstride, K);
     __syncthreads();                            // the aggregate table
-    for (int st = 0; st < G::kSteps; ++st) expand_step<G, KT>(p, words0, lut, lds + G::kLdsA, K, lane, q, st, agg);
+    for (int st = 0; st < G::kSteps; ++st) expand_step<G, KT>(p, words0, lut, a_lds, K, lane, q, st, agg);
     stage_store<KT, KMAX, NG, MP>(wd, plan, words0, K);
     advance(cur);                               // chunk 2
     w_n2 = cur.w;
@@ -620,7 +645,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   lds_dma_wait();                               // the weights of chunks 0 and 1
   __syncthreads();
 
-  const int w_frag_off = lane * 16;                                  // + tap*kWTap + mc*1024
+  const int w_frag_off = lane * 16 + co_part * (MCW * 1024);         // + tap*kWTap + mc*1024
 
   // MFMA operand fragments are fetched kAhead taps before the tap that multiplies them.  One tap ahead (tiles with at
   // least four MFMAs per tap), two slots: tap t multiplies slot t & 1 while slot (t+1) & 1 is being fetched; tap 8
@@ -628,7 +653,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   // ahead (tiles with two MFMAs per tap, whose single tap is shorter than an LDS read takes), three slots: tap t
   // multiplies slot t % 3 while slot (t+2) % 3 is being fetched; nine taps are three rounds of the ring, so the next
   // chunk finds its taps 0 and 1 in slots 0 and 1.
-  constexpr int kAhead = (MC * NP <= 2 && !AGG) ? 2 : 1;
+  constexpr int kAhead = (MCW * NP <= 2 && !AGG) ? 2 : 1;
   constexpr int kBarTap = 8 - kAhead;            // the workgroup barrier follows this tap
   // Loader slots per tap and the distance, in slots, between the three stages of the loader's pipeline (read the
   // words of a step, look its table entries up, write its aggregates): one tap, so that no stage waits for an LDS
@@ -639,23 +664,23 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   }();
   constexpr int kLD = kSPT;                      // slots between the stages
   constexpr int kSets = 2 * kLD + 1;             // register sets in flight
-  bf16x8 wf[kAhead + 1][MC], af[kAhead + 1][NP];
+  bf16x8 wf[kAhead + 1][MCW], af[kAhead + 1][NP];
   auto fetch = [&](const uint8_t* a_buf, const uint8_t* w_buf, int tap, int slot) {
     if constexpr (AGG) return;
     const int ky = tap / 3, kx = tap % 3;
     const int tap_off = (ky * G::kXP + G::col(kx)) * 16;            // col(ox S + kx) = col(ox S) + col(kx)
 #pragma unroll
-    for (int mc = 0; mc < MC; ++mc)
+    for (int mc = 0; mc < MCW; ++mc)
       wf[slot][mc] = *reinterpret_cast<const bf16x8*>(w_buf + tap * kWTapL + mc * 1024 + w_frag_off);
 #pragma unroll
     for (int np = 0; np < NP; ++np)
       af[slot][np] = *reinterpret_cast<const bf16x8*>(a_buf + a_frag_off[np] + tap_off);
   };
   if constexpr (kAhead == 1) {
-    fetch(lds + G::kLdsA, lds + G::kLdsW, 0, 1);
+    fetch(a_lds, lds + G::kLdsW, 0, 1);
   } else {
-    fetch(lds + G::kLdsA, lds + G::kLdsW, 0, 0);
-    fetch(lds + G::kLdsA, lds + G::kLdsW, 1, 1);
+    fetch(a_lds, lds + G::kLdsW, 0, 0);
+    fetch(a_lds, lds + G::kLdsW, 1, 1);
   }
 
   // One chunk of 16 input channels: 9 taps of MFMAs on buffers PAR, while the A tile of the
@@ -666,16 +691,16 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   static_assert((kBarTap + 1) * kSPT >= G::kSteps + 2 * kLD, "the loader must be done before the barrier");
   auto chunk_iteration = [&](int s) {
     const int PAR = s & 1;
-    const uint8_t* a_cur = lds + G::kLdsA + PAR * G::kABuf;
+    const uint8_t* a_cur = a_lds + PAR * G::kABuf;
     const uint8_t* w_cur = lds + G::kLdsW + PAR * kWBufL;
-    uint8_t* a_next = lds + G::kLdsA + (PAR ^ 1) * G::kABuf;
+    uint8_t* a_next = a_lds + (PAR ^ 1) * G::kABuf;
     uint8_t* w_next = lds + G::kLdsW + (PAR ^ 1) * kWBufL;
     const uint8_t* words_next = words0;          // words of chunk s+1 (read now)
     uint8_t* words_nn = words0;                  // words of chunk s+2: written at tap kBarTap, behind this chunk's reads
     StepRegs<(KT > 0 ? KT : 1)> sr[kSets];  // loader step i uses set i % kSets
     if constexpr (kAhead == 1) {
 #pragma unroll
-      for (int mc = 0; mc < MC; ++mc) wf[0][mc] = wf[1][mc];
+      for (int mc = 0; mc < MCW; ++mc) wf[0][mc] = wf[1][mc];
 #pragma unroll
       for (int np = 0; np < NP; ++np) af[0][np] = af[1][np];
     }
@@ -745,7 +770,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
       }
       if constexpr (!AGG) {
 #pragma unroll
-        for (int mc = 0; mc < MC; ++mc)
+        for (int mc = 0; mc < MCW; ++mc)
 #pragma unroll
           for (int np = 0; np < NP; ++np)
             acc[mc][np] = COLS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[slot][np], wf[slot][mc], acc[mc][np], 0, 0, 0)
@@ -770,7 +795,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         constexpr int kValuPerMfma = (KT == 16 ? 4 : 2) * kSPT;
         constexpr int kDsPerMfma = (kSPT == 1 && KT != 16) ? 2 : 3;
 #pragma unroll
-        for (int i = 0; i < NP * MC; ++i) {
+        for (int i = 0; i < NP * MCW; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, kDsPerMfma, 0);
           __builtin_amdgcn_sched_group_barrier(0x002, kValuPerMfma, 0);
@@ -792,10 +817,10 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
   // Packed stores (lane order: see lif_step and words_of_cols).  The lane's word of 32-channel block mc sits at
   // out_wave + mc * 32 * out_plane + out_off, with out_wave wave-uniform and out_off a small
   // per-lane offset, the only part kept in a vector register across the time loop.
-  constexpr int kStoreRegs = G::kWo >= 32 ? 1 : 2;
+  constexpr int kStoreRegs = G::kWo >= 32 || GH == 2 ? 1 : 2;
   const uint32_t out_plane = (uint32_t)(Ho * G::kOutWords);           // words per (step, b, cout)
   const size_t out_step = (size_t)p.B * p.Cout * out_plane;
-  uint32_t* const out_wave = p.out + ((size_t)b * p.Cout + co_wave) * out_plane + (size_t)oy_wave * G::kOutWords;
+  uint32_t* const out_wave = p.out + ((size_t)b * p.Cout + co_wave + half * 16) * out_plane + (size_t)oy_wave * G::kOutWords;
   uint32_t out_off;                            // in words; store register 1: + 16 out_plane (a channel per lane: the next row)
   int out_row;                                                        // the lane's row within the wave
   if constexpr (COLS) {
@@ -811,10 +836,11 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     out_row = lane & 3;
     out_off = (uint32_t)(8 * (r >> 2) + 4 * hi + (r & 3)) * out_plane + out_row;
   }
-  const bool out_ok = oy_wave + out_row < Ho && out_row < G::kWaveRows;      // half tiles: the lanes of the absent block store nothing
+  // half tiles: the lanes of the absent block store nothing; GH = 2: nor those of the other half's registers
+  const bool out_ok = oy_wave + out_row < Ho && out_row < G::kWaveRows && (GH == 1 || G::kWo < 32 || lane < 32);
 
   int s = 0;
-  for (int g = 0; g < p.G; ++g) {
+  for (int g0 = 0; g0 < p.G; g0 += GH) {
     // Nothing may be in flight when the chunk loop is entered: a load still pending here (a
     // register reloaded after the epilogue, say) would otherwise be waited for inside the loop,
     // at its first use, in every iteration, and that wait would also cover the loads the loop
@@ -822,7 +848,7 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0), other counters untouched
     __builtin_amdgcn_s_setprio(3);              // MFMA phase: ahead of a co-resident workgroup's LIF steps
 #pragma unroll
-    for (int mc = 0; mc < MC; ++mc)
+    for (int mc = 0; mc < MCW; ++mc)
 #pragma unroll
       for (int np = 0; np < NP; ++np)
 #pragma unroll
@@ -832,34 +858,73 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     __builtin_amdgcn_s_setprio(0);
     if constexpr (AGG) continue;
 
+    // GH = 2: the sums of the second group, in registers 0 .. 7 of a block, those of the first one in acc's registers 0 .. 7
+    [[maybe_unused]] f32x16 y_next[MCW][NP];
+    if constexpr (GH == 2) {
+      uint8_t* const ex = lds + G::lds_exchange(K, MC) + lane * 16;    // [wave][block][4 registers][lane]
+      constexpr int kWaveEx = MCW * NP * 8 * 256;
+      auto send = [&](auto r0_) {
+        static_for<0, MCW * NP * 2>([&](auto i_) {
+          constexpr int i = decltype(i_)::value, r = decltype(r0_)::value + (i & 1) * 4;
+          const f32x16& a = acc[i / 2 / NP][i / 2 % NP];
+          *reinterpret_cast<f32x4v*>(ex + wave * kWaveEx + i * 1024) = f32x4v{a[r], a[r + 1], a[r + 2], a[r + 3]};
+        });
+      };
+      if (half == 0) send(std::integral_constant<int, 8>{});
+      else send(std::integral_constant<int, 0>{});
+      lds_barrier();
+      static_for<0, MCW * NP * 2>([&](auto i_) {
+        constexpr int i = decltype(i_)::value, mc = i / 2 / NP, np = i / 2 % NP, r = (i & 1) * 4;
+        const f32x4v in = *reinterpret_cast<const f32x4v*>(ex + (wave ^ 4) * kWaveEx + i * 1024);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          y_next[mc][np][r + k] = half == 0 ? in[k] : acc[mc][np][8 + r + k];
+          if (half) acc[mc][np][r + k] = in[k];
+        }
+      });
+    }
+
     // ---- LIF epilogue on Y_k = acc + bias
-    const float* bias_lds = reinterpret_cast<const float*>(lds + kLdsBias);
+    const float* bias_lds = reinterpret_cast<const float*>(lds + kLdsBias) + co_part * (MCW * 32) + half * 16;
     if (p.bias) {
 #pragma unroll
-      for (int mc = 0; mc < MC; ++mc)
+      for (int mc = 0; mc < MCW; ++mc)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < kRegs; ++r) {
           const float bv = bias_lds[mc * 32 + (COLS ? n : 8 * (r >> 2) + 4 * h + (r & 3))];
 #pragma unroll
-          for (int np = 0; np < NP; ++np) acc[mc][np][r] += bv;
+          for (int np = 0; np < NP; ++np) {
+            acc[mc][np][r] += bv;
+            if constexpr (GH == 2) y_next[mc][np][r] += bv;
+          }
         }
     }
     // epilogue geometry, recomputed per group: nothing of it lives across the MFMA loop
     [[maybe_unused]] const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane, p.theta);
-    for (int j = 0; j < p.n_lif; ++j) {
-      const size_t step = (size_t)g * p.n_lif + j;
-      uint32_t word[MC][2];
+    const int g_n = GH == 2 && g0 + 1 < p.G ? 2 : 1;
+    for (int gi = 0; gi < g_n; ++gi) {
+    if (GH == 2 && gi == 1) {
 #pragma unroll
-      for (int mc = 0; mc < MC; ++mc) word[mc][0] = word[mc][1] = 0u;
+      for (int mc = 0; mc < MCW; ++mc)
+#pragma unroll
+        for (int np = 0; np < NP; ++np)
+#pragma unroll
+          for (int r = 0; r < kRegs; ++r) acc[mc][np][r] = y_next[mc][np][r];
+    }
+    for (int j = 0; j < p.n_lif; ++j) {
+      const size_t step = (size_t)(g0 + gi) * p.n_lif + j;
+      uint32_t word[MCW][2];
+#pragma unroll
+      for (int mc = 0; mc < MCW; ++mc) word[mc][0] = word[mc][1] = 0u;
       if constexpr (TRACE) {
-        float* tl = p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_wave;
+        float* tl = p.v_trace + step * ((size_t)p.B * p.Cout * plane) + v_regs;
         size_t plane_l = plane;
         asm volatile("" : "+s"(plane_l));       // keep the trace addresses out of the loop preheader
-        lif_step<MC, G::kWo, true, NP>(V, acc, p.decay, p.theta, lg, word, tl, plane_l);
+        lif_step<MCW, G::kWo, true, NP, kRegs / 4>(V, acc, p.decay, p.theta, lg, word, tl, plane_l);
       } else if constexpr (!COLS) {
-        lif_step<MC, G::kWo, false, NP>(V, acc, p.decay, p.theta, lg, word, nullptr, plane);
+        lif_step<MCW, G::kWo, false, NP, kRegs / 4>(V, acc, p.decay, p.theta, lg, word, nullptr, plane);
       } else {
-        static_for<0, MC>([&](auto mc_) {
+        static_for<0, MCW>([&](auto mc_) {
           constexpr int mc = decltype(mc_)::value;
           uint32_t bits[2];
           lif_step_cols<NP, NP == 1>(V[mc], acc[mc], p.decay, p.theta, bits);
@@ -875,8 +940,9 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         if constexpr (G::kCanPoolOut) {
           const uint32_t plane_p = (uint32_t)(Ho >> 1);                      // one word per pooled row
           uint32_t* ex = reinterpret_cast<uint32_t*>(lds + G::lds_bytes(K, MC)) + (step & 1) * (G::kTileRows * kCT);
-          pooled_store<MC, COLS>(word, ex, tid, kThreads, G::kTileRows, G::kWaveRows == 2, wave * G::kWaveRows,
-                           p.out + (step * p.B * p.Cout + (size_t)b * p.Cout + co_wave) * plane_p + (y0 >> 1), plane_p,
+          pooled_store<MCW, COLS, MC, GH>(word, ex, tid, kNT, G::kTileRows, G::kWaveRows == 2, px_wave * G::kWaveRows,
+                           co_part * (MCW * 32) + half * 16,
+                           p.out + (step * p.B * p.Cout + (size_t)b * p.Cout + co_tile * kCT) * plane_p + (y0 >> 1), plane_p,
                            min(G::kTileRows >> 1, (Ho - y0) >> 1));
         }
       } else if (out_ok) {
@@ -885,10 +951,11 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
         for (int sr = 0; sr < kStoreRegs; ++sr) {
           if (COLS && sr == 1 && (NP == 1 || oy_wave + out_row + 1 >= Ho)) break;
 #pragma unroll
-          for (int mc = 0; mc < MC; ++mc)
+          for (int mc = 0; mc < MCW; ++mc)
             o[(uint32_t)(mc * 32 + (COLS ? 0 : sr * 16)) * out_plane + out_off + (COLS ? sr : 0)] = word[mc][sr];
         }
       }
+    }
     }
   }
   lds_dma_wait();
@@ -908,15 +975,15 @@ __global__ __launch_bounds__(kThreads, (MC == 2 && NP == 2) ? 2 : 1) void mfma_k
     size_t plane_l = plane;                   // opaque copy: the 128 addresses below are formed here,
     asm volatile("" : "+s"(plane_l));         // not before the time loop (they would not fit in registers)
     const LaneGeom lg = lane_geom<G>(lane, oy_wave, Ho, plane_l, p.theta);
-    char* vb = reinterpret_cast<char*>(p.v_inout + v_wave);
+    char* vb = reinterpret_cast<char*>(p.v_inout + v_regs);
     if constexpr (COLS) {
       float* const t = reinterpret_cast<float*>(lds + G::kLdsW) + wave * kTurnFloats;
-      static_for<0, MC>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
+      static_for<0, MCW>([&](auto mc_) { static_for<0, NP>([&](auto np_) { turn_block(V[decltype(mc_)::value][decltype(np_)::value], t, n, h); }); });
     }
     static_for<0, NP>([&](auto np_) {
       constexpr int np = decltype(np_)::value;
       if (lg.ok[np]) {
-        static_for<0, MC>([&](auto mc_) { static_for<0, 16>([&](auto r_) {
+        static_for<0, MCW>([&](auto mc_) { static_for<0, kRegs>([&](auto r_) {
           constexpr int mc = decltype(mc_)::value, r = decltype(r_)::value;
           *reinterpret_cast<float*>(vb + (size_t)(mc * 32 + 8 * (r >> 2) + (r & 3)) * plane_l * 4 + lg.v_off[np]) = V[mc][np][r];
         }); });
@@ -938,17 +1005,17 @@ inline int compute_units() {
   return n;
 }
 
-template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP = 2, bool COLS = false>
+template <int KT, int WIN, int S, bool TRACE, bool MP, int MC, int NP = 2, bool COLS = false, int GH = 1, int CW = 1>
 hipError_t launch_tile(const MfmaParams& mp, hipStream_t s) {
-  using G = Geo<WIN, S, NP>;
+  using G = Geo<WIN, S, NP, CW, GH>;
+  constexpr auto kern = &mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP, false, COLS, GH, CW>;
   constexpr int lds_layer = G::lds_bytes(KT > 0 ? KT : TAC_MAX_K, MC);
   constexpr int lds_max = lds_layer + G::pool_bytes(MC);
   static_assert(lds_max <= kLdsLimit, "tile does not fit the LDS");
   static std::once_flag once;               // one attribute call per kernel, also with several host threads
   static hipError_t attr = hipSuccess;
   std::call_once(once, [] {
-    attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP, false, COLS>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+    attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
   });
   if (attr != hipSuccess) return attr;
   if (mp.out_pool && !G::kCanPoolOut) return hipErrorInvalidValue;
@@ -956,7 +1023,7 @@ hipError_t launch_tile(const MfmaParams& mp, hipStream_t s) {
   MfmaParams q = mp;
   q.row_tiles = (mp.Ho + G::kTileRows - 1) / G::kTileRows;
   const dim3 grid(q.row_tiles * (mp.Cout / (MC * 32)) * mp.B);
-  hipLaunchKernelGGL((mfma_kernel<KT, WIN, S, TRACE, MP, MC, NP, false, COLS>), grid, dim3(kThreads), lds, s, q);
+  hipLaunchKernelGGL(kern, grid, dim3(kThreads * GH), lds, s, q);
   return hipGetLastError();
 }
 
@@ -983,9 +1050,40 @@ hipError_t launch_tile64(const MfmaParams& mp, hipStream_t s) {
   }
 }
 
+// Pairs of groups (the kernel's GH = 2), for grids that leave a compute unit one workgroup: eight waves then share its issue slots and its
+// trips to the LDS in the place of four, and the weights are copied once for two groups.  Tiles of 64 channels and 256, 128 or 64 pixels: the smallest one
+// whose grid the chip takes in one go.  us a call before and now, TAC-TP K = 2 at B = 16 unless stated: 256 -> 256 stride 2 at 32 x 32 (tiles of
+// 64 pixels) 126 / 71, single frames 218 / 127; 128 -> 128 stride 2 at 64 x 64 (128) 76 / 58; 128 -> 256 at 32 x 32 (256) 83 / 77; the pooled 128 -> 128
+// at 32 x 32, K = 4 (128) 39.7 / 35.0, with membranes 62 / 46.  With more tiles than compute units it loses: 64 -> 128 at 64 x 64 (512 of 256 pixels) 77 / 95, 128 -> 256 at
+// 32 x 32, B = 32 (512) 136 / 153; tiles of 64 pixels, two rounds: 128 -> 128 stride 2 at 64 x 64 58 -> 73.
+template <int KT, int WIN, int S, bool TRACE, int NP, int CW>
+bool launch_pairs_tile(const MfmaParams& mp, hipStream_t s, hipError_t& e) {
+  using G = Geo<WIN, S, NP, CW, 2>;
+  if constexpr (G::lds_bytes(KT > 0 ? KT : TAC_MAX_K, 2) + G::pool_bytes(2) > kLdsLimit) return false;
+  else {
+    if ((long long)((mp.Ho + G::kTileRows - 1) / G::kTileRows) * (mp.Cout / 64) * mp.B > compute_units()) return false;
+    e = launch_tile<KT, WIN, S, TRACE, false, 2, NP, false, 2, CW>(mp, s);
+    return true;
+  }
+}
+template <int KT, int WIN, int S, bool TRACE>
+bool launch_pairs(const MfmaParams& mp, hipStream_t s, hipError_t& e) {
+  if (mp.G < 2) return false;
+  if constexpr (Geo<WIN, S>::kWo <= 32) {
+    if (launch_pairs_tile<KT, WIN, S, TRACE, 1, 2>(mp, s, e) || launch_pairs_tile<KT, WIN, S, TRACE, 1, 1>(mp, s, e)) return true;
+  } else {
+    if (launch_pairs_tile<KT, WIN, S, TRACE, 2, 2>(mp, s, e)) return true;
+  }
+  return launch_pairs_tile<KT, WIN, S, TRACE, 2, 1>(mp, s, e);
+}
+
 template <int KT, int WIN, int S, bool TRACE, bool MP>
 hipError_t launch_traced(const MfmaParams& mp, hipStream_t s) {
   const int kComputeUnits = compute_units();
+  if constexpr (!MP) {
+    hipError_t e = hipSuccess;
+    if (launch_pairs<KT, WIN, S, TRACE>(mp, s, e)) return e;
+  }
   // The LIF steps of a group are pure vector work that follows the group's MFMAs.  Two workgroups of 64-channel tiles
   // per compute unit (where two of them fit the LDS) let one's LIF steps run under the other's MFMAs, at the price of
   // building every aggregate tile twice.  That pays where the steps weigh enough against the chunks of 16 input
