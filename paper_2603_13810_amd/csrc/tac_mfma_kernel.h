@@ -63,11 +63,12 @@ constexpr int kLdsLimit = 160 * 1024;          // LDS of one compute unit
 // Aggregate table: entry t = the aggregate (Eq. 2) of a pixel whose frames have the bits of t,
 // in the 2^23 fixed-point scale.  K <= 8: 2^K bf16 patterns.  K = 16: two tables of 256
 // integers (frames 0..7, frames 8..15) that are added before the one rounding to bf16.
-// Pair table (K = 2, and K = 4 where the tile leaves room): entry (t1 << K | t0) holds the bf16 patterns of two
+// Pair table (K = 4 where the tile leaves room): entry (t1 << K | t0) holds the bf16 patterns of two
 // neighbouring channels, t0 in the low half: one 32-bit read per channel pair instead of two 16-bit reads and a pack.
-__host__ __device__ constexpr bool lut_pairs(int K, bool room) { return K == 2 || (K == 4 && room); }
+// K = 2: the four entries are two registers, and a byte permutation is the look-up (see lookup).
+__host__ __device__ constexpr bool lut_pairs(int K, bool room) { return K == 4 && room; }
 __host__ __device__ constexpr int lut_bytes(int K, bool room) {
-  return lut_pairs(K, room) ? (4 << (2 * K)) : (K == 16 ? 2048 : (K >= 2 && K <= 8 ? ((2 << K) + 15) / 16 * 16 : 0));
+  return lut_pairs(K, room) ? (4 << (2 * K)) : (K == 16 ? 2048 : (K > 2 && K <= 8 ? ((2 << K) + 15) / 16 * 16 : 0));
 }
 
 // Compile-time geometry of a tile: input width WIN (32 or 64 pixels = 1 or 2 words), stride S,
@@ -259,7 +260,7 @@ __device__ __forceinline__ void lut_fill(uint8_t* lut, const MfmaParams& p, int 
       }
       reinterpret_cast<uint32_t*>(lut)[t] = pack_bf16((float)a0, (float)a1);
     }
-  } else if constexpr (KT >= 2 && KT <= 8) {
+  } else if constexpr (KT > 2 && KT <= 8) {
     for (int t = tid; t < (1 << KT); t += kThreads) {
       uint32_t acc = 0;
 #pragma unroll
@@ -318,9 +319,25 @@ __device__ __forceinline__ void read_words(StepRegs<KT>& sr, const uint8_t* word
   }
 }
 
+// The table of K = 2 in two registers: entries 0 and 1, entries 2 and 3.
+struct PairTable {
+  uint32_t lo, hi;
+};
+__device__ __forceinline__ PairTable pair_table(const MfmaParams& p) {
+  return {pack_bf16(0.f, (float)p.wq[0]), pack_bf16((float)p.wq[1], (float)(p.wq[0] + p.wq[1]))};
+}
+
 template <int KT, bool PAIRS>
-__device__ __forceinline__ void lookup(StepRegs<KT>& sr, const uint8_t* lut, int lane) {
-  if constexpr (PAIRS) {
+__device__ __forceinline__ void lookup(StepRegs<KT>& sr, const uint8_t* lut, const PairTable& two, int lane) {
+  if constexpr (KT == 2) {
+    // entry t is bytes 2 t and 2 t + 1 of the table; five vector operations in the place of four and a trip to the LDS
+    const uint32_t pos = lane & 30;
+#pragma unroll
+    for (int e2 = 0; e2 < 2; ++e2) {
+      const uint32_t t = __builtin_amdgcn_ubfe(sr.cw[2 * e2], pos, 2) | (__builtin_amdgcn_ubfe(sr.cw[2 * e2 + 1], pos, 2) << 16);
+      sr.lv[e2] = __builtin_amdgcn_perm(two.hi, two.lo, __umul24(t, 0x0202u) + 0x01000100u);
+    }
+  } else if constexpr (PAIRS) {
     const uint32_t pos = lane & 31 & ~(KT - 1);
 #pragma unroll
     for (int e2 = 0; e2 < 2; ++e2) {
@@ -359,7 +376,7 @@ __device__ __forceinline__ void a_write_packed(uint8_t* a_next, int lane, int q,
 template <class G, int KT>
 __device__ __forceinline__ void write_a(const StepRegs<KT>& sr, uint8_t* a_next, int lane, int q, int step, uint64_t* sum = nullptr) {
   u32x2 pk;
-  if constexpr (lut_pairs(KT, G::kLutRoom)) {
+  if constexpr (KT == 2 || lut_pairs(KT, G::kLutRoom)) {
     pk[0] = sr.lv[0];
     pk[1] = sr.lv[1];
   } else if constexpr (KT == 1) {
@@ -386,12 +403,12 @@ __device__ __forceinline__ void write_a(const StepRegs<KT>& sr, uint8_t* a_next,
 // Unpipelined form (prologue, and the run-time-K kernel, which reads the frames' words as
 // they are and adds the weights bit by bit).
 template <class G, int KT>
-__device__ __forceinline__ void expand_step(const MfmaParams& p, const uint8_t* words_buf, const uint8_t* lut,
+__device__ __forceinline__ void expand_step(const MfmaParams& p, const uint8_t* words_buf, const uint8_t* lut, const PairTable& two,
                                             uint8_t* a_next, int K, int lane, int q, int step, uint64_t* sum = nullptr) {
   if constexpr (KT > 0) {
     StepRegs<KT> sr;
     read_words<G, KT>(sr, words_buf, lane, q, step);
-    lookup<KT, lut_pairs(KT, G::kLutRoom)>(sr, lut, lane);
+    lookup<KT, lut_pairs(KT, G::kLutRoom)>(sr, lut, two, lane);
     write_a<G, KT>(sr, a_next, lane, q, step, sum);
   } else {
     const uint32_t* src = reinterpret_cast<const uint32_t*>(words_buf) + (lane_word<G>(lane, step) * (K * kChunk + G::stage_pad(K)) + q * 4);
@@ -612,6 +629,7 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
   stage_plan<G, NG, MP>(plan, p, K, tid & (kThreads - 1), y0 * S - 1);
   uint32_t wd[NG][KMAX * (MP ? 4 : 1)];         // staged words in flight
   const uint32_t fstride = (uint32_t)((size_t)p.B * p.Cin * in_plane);         // dwords between frames
+  const PairTable two = pair_table(p);
   if (half == 0) lut_fill<KT, lut_pairs(KT, G::kLutRoom)>(lut, p, tid);
 
   // ---- prologue: A tile of chunk 0, weights of chunks 0 and 1, staged words of chunk 1,
@@ -634,7 +652,7 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
     weights_to_lds(cur.w, lds + G::kLdsW + kWBufL, c0, c9);
     stage_load<KMAX, NG, MP, G::kWW>(wd, plan, cur.spk, fstride, K);
     __syncthreads();                            // the aggregate table
-    for (int st = 0; st < G::kSteps; ++st) expand_step<G, KT>(p, words0, lut, a_lds, K, lane, q, st, agg);
+    for (int st = 0; st < G::kSteps; ++st) expand_step<G, KT>(p, words0, lut, two, a_lds, K, lane, q, st, agg);
     stage_store<KT, KMAX, NG, MP>(wd, plan, words0, K);
     advance(cur);                               // chunk 2
     w_n2 = cur.w;
@@ -658,9 +676,10 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
   // Loader slots per tap and the distance, in slots, between the three stages of the loader's pipeline (read the
   // words of a step, look its table entries up, write its aggregates): one tap, so that no stage waits for an LDS
   // access issued in the same tap.  All writes are done by the barrier.
+  constexpr int kStages = KT == 1 || KT == 2 ? 1 : 2;     // distances from a step's read to its write
   constexpr int kSPT = [] {
     for (int n = 1;; ++n)
-      if ((kBarTap + 1) * n >= G::kSteps + (KT == 1 ? 1 : 2) * n) return n;
+      if ((kBarTap + 1) * n >= G::kSteps + kStages * n) return n;
   }();
   constexpr int kLD = kSPT;                      // slots between the stages
   constexpr int kSets = 2 * kLD + 1;             // register sets in flight
@@ -688,7 +707,7 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
   // look-ahead): by then every read of the PAR buffers has returned (the last taps' fragments have been fetched)
   // and every write to the PAR^1 buffers is done, so the taps behind it already fetch the first fragments of the
   // next chunk and start refilling the PAR weight buffer.
-  static_assert((kBarTap + 1) * kSPT >= G::kSteps + 2 * kLD, "the loader must be done before the barrier");
+  static_assert((kBarTap + 1) * kSPT >= G::kSteps + kStages * kLD, "the loader must be done before the barrier");
   auto chunk_iteration = [&](int s) {
     const int PAR = s & 1;
     const uint8_t* a_cur = a_lds + PAR * G::kABuf;
@@ -711,7 +730,7 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
     auto loader_reads = [&](int i) {
       if constexpr (KT > 0) {
         if (i < G::kSteps) read_words<G, KT>(sr[i % kSets], words_next, lane, q, i);
-        if (KT != 1 && i >= kLD && i - kLD < G::kSteps) lookup<KT, lut_pairs(KT, G::kLutRoom)>(sr[(i - kLD) % kSets], lut, lane);
+        if (kStages == 2 && i >= kLD && i - kLD < G::kSteps) lookup<KT, lut_pairs(KT, G::kLutRoom)>(sr[(i - kLD) % kSets], lut, two, lane);
       }
     };
 #pragma unroll
@@ -781,11 +800,12 @@ __global__ __launch_bounds__(kThreads * GH, (MC == 2 && NP == 2) || GH == 2 ? 2 
 #pragma unroll
       for (int i = tap * kSPT; i < (tap + 1) * kSPT; ++i) {
         if constexpr (KT > 0) {
-          constexpr int kD = (KT == 1 ? 1 : 2) * kLD;
+          constexpr int kD = kStages * kLD;
           if constexpr (kSPT > 1) loader_reads(i);
+          if (KT == 2 && i >= kD && i - kD < G::kSteps) lookup<KT, false>(sr[(i - kD) % kSets], lut, two, lane);
           if (i >= kD && i - kD < G::kSteps) write_a<G, KT>(sr[(i - kD) % kSets], a_next, lane, q, i - kD, agg_s);
         } else {
-          if (i < G::kSteps) expand_step<G, KT>(p, words_next, lut, a_next, K, lane, q, i, agg_s);
+          if (i < G::kSteps) expand_step<G, KT>(p, words_next, lut, two, a_next, K, lane, q, i, agg_s);
         }
       }
       if (tap == kBarTap) stage_store<KT, KMAX, NG, MP>(wd, plan, words_nn, K);
