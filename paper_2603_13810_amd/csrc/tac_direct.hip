@@ -16,6 +16,7 @@
 //   3. LIF:     V <- decay V + Y_k, spike iff V >= theta, subtractive reset; once for TAC
 //               and per-step, K times with the same Y_k for TAC-TP; each step's spikes
 //               leave as one wave ballot = two packed words.
+#include "tac_deep_plan.h"
 #include "tac_first_plan.h"
 #include "tac_mfma_common.h"
 
@@ -264,6 +265,8 @@ hipError_t direct_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* 
 
 hipError_t direct_launch(const LayerParams& p, hipStream_t s) {
   if (first_f32_supported(p)) return first_f32_launch(p, s);
+  DeepPlan deep;
+  if (!p.vector_only && deep_choose(p, deep)) return deep_launch(p, deep, s);
   const int nq = p.Ho * p.Wwo;
   // worst-case input rows behind 8 output words
   const int rows_out_max = (kWordsPerBlock + p.Wwo - 1) / p.Wwo + (p.Wwo > 1 && kWordsPerBlock % p.Wwo ? 1 : 0);
