@@ -397,7 +397,7 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
     e = backward_wgrad_mfma_launch(p, s);
     if (e != hipSuccess) return e;
   } else {
-    e = backward_wgrad_f32_launch(p, s);
+    if (!backward_wgrad_first_launch(p, s, e)) e = backward_wgrad_f32_launch(p, s);
     if (e != hipSuccess) return e;
   }
 

@@ -121,6 +121,7 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s);
 // 4 x 4, B = 4 (288) 47 / 43 us; 128 -> 128 at 4 x 4, B = 16 (18) 21.5 / 23.9 us.
 inline bool backward_clear_in_recurrence(size_t threads, size_t floats) { return floats <= 256 * threads; }
 hipError_t backward_wgrad_f32_launch(const BackwardParams& p, hipStream_t s);    // any layer, fp32 operands; adds to grad_w, grad_bias
+bool backward_wgrad_first_launch(const BackwardParams& p, hipStream_t s, hipError_t& e);     // first layers; false: not one that it takes
 bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_tile_supported(const BackwardParams& p);     // wide tiles (128 input channels), grad_w as scratch

@@ -108,3 +108,17 @@ def test_long_sums_of_one_sign(B, Cin, Cout, hw, T, rate):
     err = got["grad_w"].double().cpu().numpy().reshape(dW.shape) - dW
     assert np.linalg.norm(err) <= tol * np.linalg.norm(dW)
     assert np.abs(got["grad_bias"].double().cpu().numpy() - db).max() <= tol * db
+
+
+# first layers: quads with a remainder and at odd addresses, one and several groups of channels, strips, several pairs per item, a
+# shorter last group, both strides, bits and real values (those of 2 -> 96 stride 2 and 2 -> 300 outweigh dL/dY: the other kernel's)
+FIRST = [
+    (3, 1, 5, 9, 11, 1, BITS, 2, 5), (5, 1, 33, 28, 28, 1, BITS, 4, 9), (2, 2, 130, 13, 70, 1, BITS, 3, 7), (1, 2, 16, 100, 100, 2, BITS, 8, 9),
+    (2, 2, 64, 33, 31, 1, REAL, 2, 5), (1, 1, 128, 64, 64, 1, REAL, 4, 6), (3, 2, 96, 7, 9, 2, REAL, 1, 3), (70, 1, 8, 5, 4, 1, BITS, 1, 2),
+    (1, 1, 4, 1, 1, 1, BITS, 1, 1), (2, 2, 300, 6, 12, 1, REAL, 16, 17),
+]
+
+
+@pytest.mark.parametrize("case", FIRST, ids=["%d_to_%d_%dx%d_s%d_f%d" % c[1:7] for c in FIRST])
+def test_first_layers(case):
+    test_weight_and_bias_gradient(case)
