@@ -76,9 +76,13 @@ bool mfma_mid_supported(const tac_layer_desc_t& d);
 size_t mfma_mid_weight_bytes(const tac_layer_desc_t& d);
 hipError_t mfma_mid_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_prepared, hipStream_t s);
 hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s);      // takes a shorter last group along
+int mfma_mid_weight_blocks(const LayerParams& p);    // 32-channel blocks per tile of its prepared weights
 // bf16 layers that the members above leave to the vector kernel, on its prepared weights (which: deep_choose, tac_deep_plan.h); takes a shorter last group along
 struct DeepPlan;
 hipError_t deep_launch(const LayerParams& p, const DeepPlan& q, hipStream_t s);
+// bf16 layers of the kind in between with wide rows and no recorded membranes, on the same prepared weights (which: row_choose, tac_row_plan.h)
+struct RowPlan;
+hipError_t row_launch(const LayerParams& p, const RowPlan& q, hipStream_t s);
 // which member takes a layer: 0 none, 1 large, 2 short contraction, 3 in between
 int mfma_kind(const tac_layer_desc_t& d);
 // its member for short contractions (Cin * 9 <= 32)

@@ -218,6 +218,8 @@ bool mfma_mid_supported(const tac_layer_desc_t& d) {
   return mid_rule_bytes(d.Cin, d.stride, d.W, mid_nmc(d.Cin, d.stride, d.W, d.Cout, f32), f32) <= kMidLdsRule;
 }
 
+int mfma_mid_weight_blocks(const LayerParams& p) { return mid_nmc(p.Cin, p.stride, p.W, p.Cout, !p.bf16); }
+
 size_t mfma_mid_weight_bytes(const tac_layer_desc_t& d) {
   const bool f32 = d.precision == TAC_FP32;
   const int nmc = mid_nmc(d.Cin, d.stride, d.W, d.Cout, f32);
