@@ -1,20 +1,22 @@
-// Input gradient of the conv-LIF layer in fp32 on the matrix cores (v_mfma_f32_32x32x2_f32: operands, products and sums in
-// fp32) for the stride-1 layers that the bf16 kernels do not take:
+// Input gradient of the conv-LIF layer on the matrix cores, as accurate as in fp32, for the stride-1 layers that the bf16 kernels do not take:
 //   dA_k[ci][iy][ix] = sum over co, ky, kx of W[co][ci][ky][kx] * dY_k[co][iy + 1 - ky][ix + 1 - kx],
 // written per group, per frame of the group (times beta^(Kg-1-j)), or through the pool on load.
 //
-// D[32 ci x 32 px] += W^T[32 ci x 2 co] . dY[2 co x 32 px], one pair of output channels and one tap per MFMA.  Workgroup =
-// WI blocks of 32 input channels x a tile of pixels (rows of one or, in small images, of several (group, sample) pairs);
-// four waves = WI channel blocks x WX = 4 / WI parts of the pixels, NP blocks of 32 pixels each.  Eight output channels at a
-// time go through LDS: their weights as they lie in memory, [co][ci][9] (lanes nine floats apart: no bank conflict), and
-// their dY rows with the zero border; the next eight are requested before the MFMAs (NP x 36 of 64 cycles each).
-// Bound by the matrix cores on many channels, by the writes of the frames' gradients where those are per frame.
-// Against one pixel x 4 channels per thread (us): 128 -> 128, B = 16, 4 groups, gradient per group, at 16 x 16 / 8 x 8 /
-// 4 x 4 202 / 159 / 161 -> 68 / 45 / 46; 32 -> 64 at 14 x 14, B = 128, 7 groups, unpooled frames of the mean pool 98 -> 63.
+// dgrad_f32_kernel: D[32 ci x 32 px] += W^T[32 ci x 16 co] . dY[16 co x 32 px].  v_mfma_f32_32x32x2_f32 takes 512 cycles for the 16 channels; here each fp32
+// value is three bf16 values whose sum it is, and six products of v_mfma_f32_32x32x16_bf16 (192 cycles) are all that reach 2^-26 of the largest.
+// Fewer roundings of the sums make the result more accurate than the products of fp32 were: 96 <- 128 at 64 x 40, B = 16, three groups 4.8e-7 of the norm
+// instead of 6.0e-7, and on 34 other layers 0.81 to 0.88 of the error.  Infinities and NaN have no thirds: a round that holds one multiplies the values put
+// together again on v_mfma_f32_32x32x2_f32.
+// Workgroup = 32 input channels x a tile of pixels (rows of one or, in small images, of several (group, sample) pairs); four waves share the pixels,
+// NP blocks of 32 each.  Sixteen output channels at a time go through LDS as thirds, [third][tap][half of the channels][ci] and [third][half][position];
+// the next sixteen are requested before the MFMAs.  Two or three workgroups share a compute unit, so that one's splitting (400 vector instructions a round
+// and wave, which bound it together with the MFMAs' 1728 NP cycles) runs under another's products.
+// Before and after (us): 96 <- 128 at 64 x 40, B = 16, three groups 537 -> 192; 32 <- 64 at 14 x 14, B = 128, seven groups 91 -> 59; 160 <- 96 at 41 x 33,
+// 144 pairs 1290 -> 343; only 8 output channels on fewer tiles than compute units lose: 5.0 -> 6.2.
 //
-// Few pixels (small images, small batches) leave that kernel with a few dozen workgroups that go through Cout / 8 rounds of two barriers
-// each.  dgrad_f32_split_kernel shares a workgroup's 32 input channels x NP blocks of 32 pixels among four waves by output channel:
-// 32 of them a round, a quarter of the rounds, four times the workgroups, and the waves' sums meet in LDS at the end.
+// Few pixels (small images, small batches) leave that kernel with a few dozen workgroups that go through Cout / 16 rounds of two barriers
+// each.  dgrad_f32_split_kernel shares a workgroup's 32 input channels x NP blocks of 32 pixels among four waves by output channel, in products of fp32:
+// 32 of them a round, four times the workgroups, and the waves' sums meet in LDS at the end.
 #include <algorithm>
 #include "tac_mfma_common.h"
 
@@ -23,7 +25,7 @@ namespace tac {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kCo = 8;            // output channels per round
+constexpr int kCo = 16;           // output channels per round
 constexpr int kM = 2;             // dY values per thread and channel
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -32,26 +34,67 @@ struct DgradPlan {
   int n_strips, n_segs, pair_tiles, ci_groups;
   int px, pl, cw;                 // pixels of a tile, dwords per channel of dY in LDS (with border), per row
   int vec_w;                      // the weights can be read 16 bytes at a time
-  int off_dy, total;
+  int off_dy, off_bad, total;
 };
 
 __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
 }
 
-template <int WI, int NP>
-__global__ __launch_bounds__(kThreads, WI > 1 && NP == 4 ? 1 : 2) void dgrad_f32_kernel(const BackwardParams p, const DgradPlan q) {
-  constexpr int kRow = 288 * WI;                         // floats of weights per output channel
-  constexpr int NW = (kCo * kRow / 4 + kThreads - 1) / kThreads;
+// x = hi + mid + lo, three bf16 values (8 bits each and their signs: all 24 bits of x).  What does not round to a finite hi keeps its upper half as it is; the
+// others of an infinity or a NaN are zero.
+struct Thirds {
+  u32x4 hi, mid, lo;              // eight values
+};
+__device__ __forceinline__ Thirds thirds(const float (&x)[8], bool& not_finite) {
+  Thirds o;
+  uint32_t most = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) most = max(most, __float_as_uint(x[i]) & 0x7fffffffu);
+  if (__builtin_expect(most < 0x7f7f8000u, 1)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      o.hi[i] = pack_bf16(x[2 * i], x[2 * i + 1]);
+      const float r0 = x[2 * i] - __uint_as_float(o.hi[i] << 16), r1 = x[2 * i + 1] - __uint_as_float(o.hi[i] & 0xffff0000u);
+      o.mid[i] = pack_bf16(r0, r1);
+      o.lo[i] = pack_bf16(r0 - __uint_as_float(o.mid[i] << 16), r1 - __uint_as_float(o.mid[i] & 0xffff0000u));
+    }
+  } else {
+    not_finite |= most >= 0x7f800000u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      float r[2];
+      uint32_t up[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const float v = x[2 * i + e];
+        const uint32_t u = __float_as_uint(v), a = u & 0x7fffffffu;
+        up[e] = a > 0x7f800000u ? 0x7fc00000u : a >= 0x7f7f8000u ? u & 0xffff0000u : pack_bf16(v, 0.f) << 16;
+        r[e] = a >= 0x7f800000u ? 0.f : v - __uint_as_float(up[e]);
+      }
+      o.hi[i] = up[0] >> 16 | up[1];
+      o.mid[i] = pack_bf16(r[0], r[1]);
+      o.lo[i] = pack_bf16(r[0] - __uint_as_float(o.mid[i] << 16), r[1] - __uint_as_float(o.mid[i] & 0xffff0000u));
+    }
+  }
+  return o;
+}
+
+constexpr int kTapBytes = 1024 + 16;                     // a tap's 2 x 32 x 8 weights; 16 bytes spread the taps of an input channel over the banks
+constexpr int kWBytes = 9 * kTapBytes;
+
+// FAR: planes of 2^23 pixels and more, whose channels have a buffer descriptor each
+template <int NP, bool FAR>
+__global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(const BackwardParams p, const DgradPlan q) {
+  constexpr int NW = (2 * 288 + kThreads - 1) / kThreads;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-  float* const wl = reinterpret_cast<float*>(lds);
-  float* const dyl = reinterpret_cast<float*>(lds + q.off_dy);
+  uint8_t* const dyl = lds + q.off_dy;
+  const int d_term = q.pl * 32;                          // bytes of one third of dY, [half of the channels][position]
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wx = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
-  const int wi = wave % WI, wx = wave / WI;
   uint32_t t = blockIdx.x;
-  const int ci0 = (int)(t % (uint32_t)q.ci_groups) * (32 * WI); t /= (uint32_t)q.ci_groups;
+  const int ci0 = (int)(t % (uint32_t)q.ci_groups) * 32; t /= (uint32_t)q.ci_groups;
   const int x0 = (int)(t % (uint32_t)q.n_segs) * q.xw; t /= (uint32_t)q.n_segs;
   const int y0 = (int)(t % (uint32_t)q.n_strips) * q.rows; t /= (uint32_t)q.n_strips;
   const int pair0 = (int)t * q.n_pairs, pairs = min(q.n_pairs, p.G * p.B - pair0);
@@ -71,38 +114,48 @@ __global__ __launch_bounds__(kThreads, WI > 1 && NP == 4 ? 1 : 2) void dgrad_f32
     ok[b] = px_pair[b] < pairs && y0 + px_y[b] < p.H && x0 + px_x[b] < p.W;
     base[b] = ok[b] ? (px_pair[b] * (q.rows + 2) + px_y[b]) * q.cw + px_x[b] : 0;
   }
-  // what the thread stages of every output channel's dY
-  uint32_t off[kM];
-  bool inside[kM];
+  // What the thread stages, as byte offsets (below 2^30) from the row above the tile's first in a channel of dY, from a channel's first weight of the tile; a load
+  // at 2^30 or more gives zero
+  constexpr uint32_t kOutside = 1u << 30;
+  uint32_t off[kM], w_off[NW];
+  int w_dst[NW];
 #pragma unroll
   for (int m = 0; m < kM; ++m) {
     const int e = tid + m * kThreads;
     const int line = e / q.cw, c = e - line * q.cw, pr = line / (q.rows + 2), r = line - pr * (q.rows + 2);
     const int y = y0 + r - 1, x = x0 + c - 1;
-    inside[m] = e < q.pl && pr < pairs && y >= 0 && y < p.H && x >= 0 && x < p.W;
-    off[m] = inside[m] ? (uint32_t)((size_t)pr * p.Cout * plane + (size_t)y * p.W + x) : 0u;
+    const bool inside = e < q.pl && pr < pairs && y >= 0 && y < p.H && x >= 0 && x < p.W;
+    off[m] = inside ? (uint32_t)((size_t)pr * p.Cout * plane + (size_t)r * p.W + x) * 4u : kOutside;
   }
-  const float* const dy0 = p.grad_y + (size_t)pair0 * p.Cout * plane;
-  const int w_valid = min(32 * WI, p.Cin - ci0) * 9;     // floats of weights that exist per output channel
-  f32x4 wr[NW];
-  float dr[kCo][kM];
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const int e = tid + i * kThreads, half = e >= 288, f = e - 288 * half;
+    w_off[i] = e < 2 * 288 ? (uint32_t)(8 * half * p.Cin * 9 + f) * 4u : kOutside;
+    w_dst[i] = f % 9 * kTapBytes + half * 512 + f / 9 * 16;
+  }
+  const float* const dy0 = p.grad_y + (size_t)pair0 * p.Cout * plane + ((ptrdiff_t)y0 - 1) * p.W;      // (what lies in front of the array is never loaded)
+  const float* const w0 = p.w + (size_t)ci0 * 9;
+  auto source = [](const float* at, size_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(at), 0, (int)(bytes < kOutside ? bytes : kOutside), 0x00020000);
+  };
+  float wr[NW][8], dr[kM][kCo];
   auto request = [&](int co) {
+    // output channels beyond the last are beyond the end; input channels beyond the last find other weights, and are not stored
+    const size_t row = (size_t)co * p.Cin * 9, end = (size_t)p.Cout * p.Cin * 9 - (size_t)ci0 * 9;
+    const auto w_src = source(w0 + row, row < end ? (end - row) * 4 : 0);
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int e = tid + i * kThreads, c = e / (kRow / 4), f = 4 * (e - c * (kRow / 4));
-      const float* const src = p.w + ((size_t)min(co + c, p.Cout - 1) * p.Cin + ci0) * 9;
-      if (q.vec_w) {
-        wr[i] = *reinterpret_cast<const f32x4*>(src + min(f, w_valid - 4));
-      } else {
+    for (int i = 0; i < NW; ++i)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) wr[i][u] = src[min(f + u, w_valid - 1)];
-      }
-    }
+      for (int c = 0; c < 8; ++c)
+        wr[i][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(w_src, (int)(w_off[i] + (uint32_t)c * (uint32_t)p.Cin * 36u), 0, 0));
+    const auto d_src = source(dy0 + (size_t)co * plane, kOutside);
 #pragma unroll
     for (int c = 0; c < kCo; ++c) {
-      const float* const src = dy0 + (size_t)min(co + c, p.Cout - 1) * plane;
+      const bool there = co + c < p.Cout;
+      const auto own = FAR ? source(dy0 + (size_t)(co + c) * plane, there ? kOutside : 0) : d_src;
+      const uint32_t chan = FAR ? 0u : there ? (uint32_t)c * (uint32_t)plane * 4u : kOutside;
 #pragma unroll
-      for (int m = 0; m < kM; ++m) dr[c][m] = src[off[m]];
+      for (int m = 0; m < kM; ++m) dr[m][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(own, (int)(off[m] + chan), 0, 0));
     }
   };
   f32x16 acc[NP];
@@ -112,42 +165,85 @@ __global__ __launch_bounds__(kThreads, WI > 1 && NP == 4 ? 1 : 2) void dgrad_f32
     for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
   const bool active = wx * NP * 32 < pairs * per_pair;   // wave-uniform
 
+  int* const bad_round = reinterpret_cast<int*>(lds + q.off_bad);        // of this round and of the next
+  if (tid < 2) bad_round[tid] = 0;
   request(0);
-  for (int co = 0; co < p.Cout; co += kCo) {
+  for (int co = 0, round = 0; co < p.Cout; co += kCo, round ^= 1) {
     __syncthreads();                                     // the round before has been read
+    bool bad = false;
+    if (tid == 0) bad_round[round ^ 1] = 0;
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const int e = tid + i * kThreads;
-      // channels beyond Cout are zeros against zeros (the last channel's weights, read in their place, may be infinite); input
-      // channels beyond Cin are not stored
-      if (e < kCo * kRow / 4) *reinterpret_cast<f32x4*>(wl + 4 * e) = co + e / (kRow / 4) < p.Cout ? wr[i] : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int i = 0; i < NW; ++i)
+      if (tid + i * kThreads < 2 * 288) {
+        const Thirds v = thirds(wr[i], bad);
+        uint8_t* const dst = lds + w_dst[i];
+        *reinterpret_cast<u32x4*>(dst) = v.hi;
+        *reinterpret_cast<u32x4*>(dst + kWBytes) = v.mid;
+        *reinterpret_cast<u32x4*>(dst + 2 * kWBytes) = v.lo;
+      }
 #pragma unroll
     for (int m = 0; m < kM; ++m)
       if (tid + m * kThreads < q.pl) {
 #pragma unroll
-        for (int c = 0; c < kCo; ++c) dyl[c * q.pl + tid + m * kThreads] = inside[m] && co + c < p.Cout ? dr[c][m] : 0.f;
+        for (int half = 0; half < 2; ++half) {
+          float x[8];
+#pragma unroll
+          for (int c = 0; c < 8; ++c) x[c] = dr[m][8 * half + c];
+          const Thirds v = thirds(x, bad);
+          uint8_t* const dst = dyl + (half * q.pl + tid + m * kThreads) * 16;
+          *reinterpret_cast<u32x4*>(dst) = v.hi;
+          *reinterpret_cast<u32x4*>(dst + d_term) = v.mid;
+          *reinterpret_cast<u32x4*>(dst + 2 * d_term) = v.lo;
+        }
       }
     if (co + kCo < p.Cout) request(co + kCo);
+    if (bad) bad_round[round] = 1;
     __syncthreads();
+    const bool any_bad = __builtin_amdgcn_readfirstlane(bad_round[round]) != 0;
     if (!active) continue;
-    const float* const w_lane = wl + h * kRow + (wi * 32 + n) * 9;
-    const float* const d_half = dyl + h * q.pl;
+    const uint8_t* const w_lane = lds + lane * 16;
+    const uint8_t* const d_half = dyl + h * q.pl * 16;
+    auto load = [&](const uint8_t* at) { return *reinterpret_cast<const bf16x8*>(at); };
+    if (__builtin_expect(!any_bad, 1)) {
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+      for (int tap = 0; tap < 9; ++tap) {
+        const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+        bf16x8 w[3], d[NP][3];
 #pragma unroll
-      for (int i = 0; i < kCo / 2; ++i) {
-        const float wv = w_lane[2 * i * kRow + tap];
+        for (int e = 0; e < 3; ++e) w[e] = load(w_lane + tap * kTapBytes + e * kWBytes);
 #pragma unroll
         for (int b = 0; b < NP; ++b)
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, d_half[2 * i * q.pl + base[b] + shift], acc[b], 0, 0, 0);
+#pragma unroll
+          for (int e = 0; e < 3; ++e) d[b][e] = load(d_half + (base[b] + shift) * 16 + e * d_term);
+        // the products of 2^-18 and more of the largest; the three left out are below 2^-26 of it
+#pragma unroll
+        for (int e = 0; e < 6; ++e) {
+          constexpr int kW[6] = {0, 2, 1, 0, 1, 0}, kD[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], acc[b], 0, 0, 0);
+        }
+      }
+    } else {
+      // an infinity or a NaN: the values put together again (exactly), in products of fp32
+      auto whole = [&](const uint8_t* at, int term, int i) {
+        const float hi = (float)load(at)[i], mid = (float)load(at + term)[i], lo = (float)load(at + 2 * term)[i];
+        return hi + (mid + lo);
+      };
+#pragma clang loop unroll(disable)
+      for (int tap = 0; tap < 9; ++tap) {
+        const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float wv = whole(w_lane + tap * kTapBytes, kWBytes, i);
+#pragma unroll
+          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, whole(d_half + (base[b] + shift) * 16, d_term, i), acc[b], 0, 0, 0);
+        }
       }
     }
   }
   if (!active) return;
   // ---- register r of acc[b] on lane (n, h): input channel 8 (r / 4) + 4 h + r % 4 of the wave, pixel n of block b
-  const int ci_w = ci0 + wi * 32 + 4 * h;
+  const int ci_w = ci0 + 4 * h;
 #pragma unroll
   for (int b = 0; b < NP; ++b) {
     if (!ok[b]) continue;
@@ -347,9 +443,9 @@ __global__ __launch_bounds__(kThreads, 2) void dgrad_f32_split_kernel(const Back
   }
 }
 
-// split: dgrad_f32_split_kernel's tile
-bool dgrad_f32_tile(const BackwardParams& p, int wi, int np, DgradPlan& q, bool split = false) {
-  const int px_max = (split ? 1 : 4 / wi) * np * 32, pl_max = split ? kSplitPl : kM * kThreads, co = split ? kSplitCo : kCo;
+// Tiles of 32 * wi input channels and up to `blocks` blocks of 32 pixels with up to pl_max positions of dY
+bool dgrad_f32_tile(const BackwardParams& p, int wi, int blocks, int pl_max, DgradPlan& q) {
+  const int px_max = blocks * 32;
   q.xw = std::min(p.W, std::min(64, px_max));
   q.n_segs = (p.W + q.xw - 1) / q.xw;
   q.cw = q.xw + 2;
@@ -359,71 +455,72 @@ bool dgrad_f32_tile(const BackwardParams& p, int wi, int np, DgradPlan& q, bool 
   q.n_strips = (p.H + q.rows - 1) / q.rows;
   q.rows = (p.H + q.n_strips - 1) / q.n_strips;
   q.n_pairs = 1;
-  // several (group, sample) pairs while they fit the tile, with 32-bit offsets between them
+  // several (group, sample) pairs while they fit the tile, with byte offsets below 2^30 between them
   if (q.n_strips == 1 && q.n_segs == 1)
     while (q.n_pairs * 2 * q.rows * q.xw <= px_max && q.n_pairs * 2 * (q.rows + 2) * q.cw <= pl_max &&
-           (long long)q.n_pairs * 2 * p.Cout * p.H * p.W < (1ll << 31))
+           (long long)q.n_pairs * 2 * p.Cout * p.H * p.W < (1ll << 28))
       q.n_pairs *= 2;
   q.pair_tiles = (p.G * p.B + q.n_pairs - 1) / q.n_pairs;
   q.ci_groups = (p.Cin + 32 * wi - 1) / (32 * wi);
   q.px = q.n_pairs * q.rows * q.xw;
   q.pl = q.n_pairs * (q.rows + 2) * q.cw;
-  q.vec_w = p.Cin % 4 == 0 && ((uintptr_t)p.w & 15u) == 0;
-  q.off_dy = co * 288 * wi * 4;
-  q.total = std::max(q.off_dy + co * q.pl * 4, split ? np * 16384 : 0);
   return true;
+}
+long long dgrad_f32_tiles(const DgradPlan& q) { return (long long)q.pair_tiles * q.n_strips * q.n_segs * q.ci_groups; }
+
+// Whether four waves share the output channels of one block of pixels: on few tiles, whose four chains of sums are also the more accurate ones (128 -> 128 at 8 x 8:
+// 2.9e-7 of the norm against 4.4e-7).  The line is where that kernel met one of tiles of up to 512 pixels with chains of fp32 products.
+bool dgrad_f32_splits(const BackwardParams& p, DgradPlan& q) {
+  if (!dgrad_f32_tile(p, 1, 1, kSplitPl, q)) return false;
+  const long long tiles = dgrad_f32_tiles(q);
+  if (tiles > 512) return false;
+  const double cost = ((p.Cout + kSplitCo - 1) / kSplitCo) * (tiles > 256 ? 1.7 : 1.15) * (36 * 64 + 3000.0) + 4600.0;
+  const int wi = p.Cin > 64 ? 4 : p.Cin > 32 ? 2 : 1;
+  bool better = true;
+  for (int n : {4, 2, 1}) {
+    DgradPlan c{};
+    if (dgrad_f32_tile(p, wi, 4 / wi * n, kM * kThreads, c))
+      better &= cost < (double)((dgrad_f32_tiles(c) + 255) / 256) * ((p.Cout + 7) / 8) * (n * 36 * 64 + 1800.0);
+  }
+  q.vec_w = p.Cin % 4 == 0 && ((uintptr_t)p.w & 15u) == 0;
+  q.off_dy = kSplitCo * 288 * 4;
+  q.total = std::max(q.off_dy + kSplitCo * q.pl * 4, 16384);
+  return better;
 }
 
 }  // namespace
 
 hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
-  const int wi = p.Cin > 64 ? 4 : p.Cin > 32 ? 2 : 1;
   DgradPlan q{};
+  auto launch = [&](auto kern) -> hipError_t {
+    const long long grid = dgrad_f32_tiles(q);
+    if (grid >= (1ll << 31)) return hipErrorInvalidValue;
+    if (q.total > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), q.total, s, p, q);
+    return hipGetLastError();
+  };
+  if (dgrad_f32_splits(p, q)) return launch(&dgrad_f32_split_kernel<1>);
+  // Cycles of a round, fitted: a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several (7850, 4000)
   int np = 0;
   double best = 0.0;
-  long long grid = 0;
-  for (int n : {4, 2, 1}) {
+  for (int n : {2, 1}) {
     DgradPlan c{};
-    if (!dgrad_f32_tile(p, wi, n, c)) continue;
-    // two resident workgroups share a compute unit's matrix cores: rounds of one workgroup's MFMAs, plus its staging
-    const long long tiles = (long long)c.pair_tiles * c.n_strips * c.n_segs * c.ci_groups;
-    const double cost = (double)((tiles + 255) / 256) * ((p.Cout + kCo - 1) / kCo) * (n * 36 * 64 + 1800.0);
+    if (!dgrad_f32_tile(p, 1, 4 * n, kM * kThreads, c)) continue;
+    const double per_cu = (double)((dgrad_f32_tiles(c) + 255) / 256), cost = std::max(n == 2 ? 10700.0 : 7500.0, per_cu * (n == 2 ? 7850.0 : 4000.0));
     if (np && cost >= best) continue;
     np = n;
     best = cost;
     q = c;
-    grid = tiles;
   }
-  // Four waves that share the output channels, as long as two workgroups per compute unit hold all the tiles (us of the kernel, split / not:
-  // 128 -> 128, 64 pairs at 8 x 8 (512 tiles) 31 / 51, at 4 x 4 (128) 25 / 53; at 16 x 16 (2048) the matrix cores are the bound and the weights
-  // come four times as often: 115 / 72)
-  bool split = false;
-  DgradPlan c{};
-  if (dgrad_f32_tile(p, 1, 1, c, true)) {
-    const long long tiles = (long long)c.pair_tiles * c.n_strips * c.n_segs * c.ci_groups;
-    const double cost = ((p.Cout + kSplitCo - 1) / kSplitCo) * (tiles > 256 ? 1.7 : 1.15) * (36 * 64 + 3000.0) + 4600.0;
-    if (tiles <= 512 && (!np || cost < best)) {
-      split = true;
-      np = 1;
-      q = c;
-      grid = tiles;
-    }
-  }
-  if (!np || grid >= (1ll << 31)) return hipErrorInvalidValue;
-  auto launch = [&](auto kern) -> hipError_t {
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), q.total, s, p, q);
-    return hipGetLastError();
-  };
-  auto with_np = [&](auto wi_) -> hipError_t {
-    constexpr int WI = decltype(wi_)::value;
-    return np == 4 ? launch(&dgrad_f32_kernel<WI, 4>) : np == 2 ? launch(&dgrad_f32_kernel<WI, 2>) : launch(&dgrad_f32_kernel<WI, 1>);
-  };
-  if (split) return launch(&dgrad_f32_split_kernel<1>);
-  switch (wi) {
-    case 4: return with_np(std::integral_constant<int, 4>{});
-    case 2: return with_np(std::integral_constant<int, 2>{});
-    default: return with_np(std::integral_constant<int, 1>{});
-  }
+  if (!np) return hipErrorInvalidValue;
+  q.off_dy = 3 * kWBytes;
+  q.off_bad = q.off_dy + 3 * 32 * q.pl;
+  q.total = q.off_bad + 16;
+  if ((long long)p.H * p.W >= (1ll << 23) || p.Cin >= (1 << 20)) return np == 2 ? launch(&dgrad_f32_kernel<2, true>) : launch(&dgrad_f32_kernel<1, true>);
+  return np == 2 ? launch(&dgrad_f32_kernel<2, false>) : launch(&dgrad_f32_kernel<1, false>);
 }
 
 }  // namespace tac

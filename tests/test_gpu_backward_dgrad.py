@@ -83,3 +83,55 @@ def test_an_infinite_weight_of_the_last_channel_is_multiplied_once():
     assert (got[2] == float("inf")).all()             # the centre tap meets every pixel's own dL/dY, which is positive
     others = [0, 1, 3, 4, 5]
     assert torch.isfinite(got[others]).all() and (got[others] > 0).all()
+
+
+# Many tiles: products of bf16 thirds, (B, Cin, Cout, H, W, format, per group, K, T) as above
+MANY = [
+    (70, 33, 8, 9, 33, BITS, True, 2, 4),       # one round, half of it empty; two channel groups, the second of one channel
+    (60, 40, 17, 16, 16, BITS, True, 1, 2),     # a second round of one channel
+    (20, 64, 32, 21, 65, BITS, False, 2, 3),    # two row segments, the second of one pixel
+    (300, 96, 24, 6, 5, BITS, True, 2, 2),      # several samples a tile, the last tile partly filled
+    (90, 32, 64, 14, 14, MEAN, False, 4, 7),
+    (40, 24, 40, 11, 30, MAX, False, 2, 3),
+]
+
+
+@pytest.mark.parametrize("case", MANY, ids=["%d_to_%d_%dx%d_f%d" % c[1:6] for c in MANY])
+def test_input_gradient_on_many_tiles(case):
+    test_input_gradient(case)
+
+
+def test_values_that_have_no_thirds():
+    # infinities, NaN, a value that rounds beyond the largest bf16, subnormal ones
+    B, Cin, Cout, H, W = 60, 40, 24, 16, 16
+    r = np.random.Generator(np.random.PCG64(7600))
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    v = np.full((1, B, Cout, H, W), 1.0, np.float32)                # at the threshold: the surrogate's factor is 1
+    g = r.standard_normal(v.shape).astype(np.float32)
+    g[0, 1, 3, 5, 5] = np.inf
+    g[0, 2, 20, 0, 15] = -np.inf
+    g[0, 3, 0, 8, 8], g[0, 3, 1, 8, 9] = np.inf, -np.inf
+    g[0, 4, 23, 15, 0] = np.nan
+    g[0, 5, 7, 4, 4] = 3.4e38
+    g[0, 6] = 0.0
+    g[0, 6, 5, 5, 5] = 1e-40
+    w = (r.standard_normal((Cout, Cin, 3, 3)) * 0.1).astype(np.float32)
+    x = np_pack((r.random((1, B, Cin, H, W)) < 0.3).astype(np.uint8))
+    got = api.tac_conv_lif_backward(desc, torch.from_numpy(x).to(DEV), torch.from_numpy(w).to(DEV), torch.from_numpy(v).to(DEV), torch.from_numpy(g).to(DEV),
+                                    grad_in_per_group=True)
+    torch.cuda.synchronize()
+    gy = got["grad_y"].cpu().double()[0]
+    assert gy.isinf().sum() == 4 and gy.isnan().sum() == 1
+
+    def back(weights, grads):
+        return torch.nn.functional.conv_transpose2d(grads, weights, padding=1).numpy()
+    wd = torch.from_numpy(w).double()
+    have, want = got["grad_in"].cpu().numpy().reshape(B, Cin, H, W), back(wd, gy)
+    assert np.array_equal(np.isnan(have), np.isnan(want))
+    inf = np.isinf(want)
+    assert inf.any() and np.array_equal(have[inf], want[inf].astype(np.float32))
+    ok = np.isfinite(want)
+    size = back(wd.abs(), gy.nan_to_num(0.0, 0.0, 0.0).abs())
+    # the bound above, and 2^-126 per product of a subnormal part that the matrix cores may take as zero
+    tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
+    assert (np.abs(have[ok] - want[ok]) <= tol * size[ok] + 9 * Cout * 2.0 ** -126).all()
