@@ -311,6 +311,9 @@ bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
     while (q.n_pairs * q.rows * q.quads < 2 * lanes && bytes(q.rows, q.n_pairs + 1) <= limit && (long long)slices * (q.n_pairs + 1) <= all_pairs) ++q.n_pairs;
   q.pair_tiles = (all_pairs + q.n_pairs - 1) / q.n_pairs;
   q.split = (int)std::min<long long>(slices, (long long)q.pair_tiles * q.n_strips);
+  // few workgroups of real-valued frames have a long chain of loads each (2 -> 56 at 31 x 26, B = 2, three groups of 8 on 24 workgroups: 15.4 us, 9.4 on the other
+  // kernel; of 25 layers below this line 3 lost more than 5% by it)
+  if (p.dense && q.co_groups * q.split < 128) return false;
   q.rows_in = (q.rows - 1) * S + 3;
   q.off_w = std::max((int)bytes(q.rows, q.n_pairs), 8 * 72 * 4 + 8 * CPW * 8);
   q.total = q.off_w + 2 * TAC_MAX_K * 4;

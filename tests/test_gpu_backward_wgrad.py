@@ -116,6 +116,8 @@ FIRST = [
     (3, 1, 5, 9, 11, 1, BITS, 2, 5), (5, 1, 33, 28, 28, 1, BITS, 4, 9), (2, 2, 130, 13, 70, 1, BITS, 3, 7), (1, 2, 16, 100, 100, 2, BITS, 8, 9),
     (2, 2, 64, 33, 31, 1, REAL, 2, 5), (1, 1, 128, 64, 64, 1, REAL, 4, 6), (3, 2, 96, 7, 9, 2, REAL, 1, 3), (70, 1, 8, 5, 4, 1, BITS, 1, 2),
     (1, 1, 4, 1, 1, 1, BITS, 1, 1), (2, 2, 300, 6, 12, 1, REAL, 16, 17),
+    # real-valued frames on 128 workgroups and more
+    (24, 2, 64, 33, 31, 1, REAL, 2, 5), (40, 1, 128, 40, 24, 2, REAL, 4, 6), (60, 2, 96, 7, 9, 1, REAL, 1, 3),
 ]
 
 
