@@ -120,7 +120,9 @@ size_t tac_packed_bytes(int32_t T, int32_t B, int32_t C, int32_t H, int32_t W);
  *     channels);
  * everything else is of the DIRECT family: fp32 vector FMAs, any shape, every input format.  TAC_FP32 layers with Cin = 1
  * or 2, W <= 128 and no pool on load belong to it by name and by their prepared weights, which are the vector kernel's; with
- * TAC_KERNEL_AUTO they run on the fp32 matrix cores (the first layers' kernel), with TAC_KERNEL_DIRECT on the vector kernel. */
+ * TAC_KERNEL_AUTO they run on the fp32 matrix cores (the first layers' kernel), with TAC_KERNEL_DIRECT on the vector kernel.
+ * So do, on the bf16 matrix cores, its TAC_BF16 layers of packed input without a pool on either side whose Cin is a multiple of 8 from 16 to
+ * 256, whose output rows have at most 64 pixels and whose groups have at most 16 frames, while three rows of aggregates fit the LDS. */
 int tac_select_kernel(const tac_layer_desc_t* desc);
 
 /* Size of the prepared-weight buffer for this layer.  0 on an invalid desc. */
@@ -263,7 +265,8 @@ int tac_stack_forward(const tac_stack_layer_t* layers, int32_t n_layers, const v
  * 128 input channels); packed input, as it is or with the max pool on load; grad_y 16-byte aligned):
  * dY_k, A_k and W enter them rounded to bfloat16, sums are fp32.  Everything else, and TAC_FP32, is
  * fp32 arithmetic (on the fp32 matrix cores, but for dL/dS of stride 2 layers and of few input channels over
- * many pixels).  The rounding inside a bf16 forward pass is differentiated as if it were not there. */
+ * many pixels and dW of one or two input channels; dL/dS of larger grids multiplies three bf16 parts of every value, whose sum it is, and
+ * is nearer to the exact sum than products of fp32).  The rounding inside a bf16 forward pass is differentiated as if it were not there. */
 enum { TAC_SG_FAST_SIGMOID = 0, TAC_SG_ARCTAN = 1 };
 typedef struct tac_backward_desc {
   int32_t surrogate;      /* TAC_SG_FAST_SIGMOID / TAC_SG_ARCTAN                                */

@@ -1,7 +1,7 @@
 // DIRECT kernel family: the conv-LIF layer for any shape with fp32 vector FMAs.  Unless the caller asks for this family, fp32 layers with
 // one or two input channels go to the matrix-core kernel of the first layers on the same prepared weights (first_f32_supported: 1 -> 32
 // at 28 x 28, B = 128, 25 frames in groups of 8 18 us, 49 here, where the instructions around the FMAs and the loader's trips to memory are
-// the bound).
+// the bound), and bf16 layers of up to 256 channels to the deep kernel (deep_choose, tac_deep_plan.h).
 //
 // One workgroup (4 wavefronts) owns 8 consecutive packed output words of one sample
 // (32 output pixels each, so 1 to 8 output rows) for a block of CB output channels, and
