@@ -519,7 +519,7 @@ hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
   q.off_dy = 3 * kWBytes;
   q.off_bad = q.off_dy + 3 * 32 * q.pl;
   q.total = q.off_bad + 16;
-  if ((long long)p.H * p.W >= (1ll << 23) || p.Cin >= (1 << 20)) return np == 2 ? launch(&dgrad_f32_kernel<2, true>) : launch(&dgrad_f32_kernel<1, true>);
+  if ((long long)p.H * p.W >= (1ll << 23)) return np == 2 ? launch(&dgrad_f32_kernel<2, true>) : launch(&dgrad_f32_kernel<1, true>);
   return np == 2 ? launch(&dgrad_f32_kernel<2, false>) : launch(&dgrad_f32_kernel<1, false>);
 }
 

@@ -137,6 +137,7 @@ hipError_t backward_dgrad_tile_launch(const BackwardParams& p, hipStream_t s);
 // 16 -> 64 1040 / 737; 4 -> 64 at 28 x 28, B = 64, 2 groups 64 / 50).
 inline bool backward_dgrad_f32_supported(const BackwardParams& p) {
   if (p.stride != 1) return false;
+  if (p.Cin >= (1 << 20)) return false;                  // 30-bit byte offsets within the weights of 16 output channels
   const double pairs = (double)p.G * p.B, pixels = (double)p.H * p.W;
   const int fours = (p.Cin + 3) / 4;
   const double by_vectors = 0.35 + 0.07 * (p.Cin < 4 ? p.Cin : 4) + fours * pairs * (double)(((int64_t)p.H * p.W + 255) / 256 * 256) / 0.55e6;

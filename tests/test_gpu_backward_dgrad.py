@@ -135,3 +135,27 @@ def test_values_that_have_no_thirds():
     # the bound above, and 2^-126 per product of a subnormal part that the matrix cores may take as zero
     tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
     assert (np.abs(have[ok] - want[ok]) <= tol * size[ok] + 9 * Cout * 2.0 ** -126).all()
+
+
+def test_planes_beyond_one_descriptor():
+    # 2^23 pixels and more: every channel of a round has a descriptor of its own; corners and a middle part against double precision
+    Cin, Cout, H, W = 20, 18, 8397, 1000
+    desc = api.make_desc(1, 1, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(76)
+    g = torch.randn((1, 1, Cout, H, W), generator=gen, device=DEV)
+    w = torch.randn((Cout, Cin, 3, 3), generator=gen, device=DEV) * 0.1
+    x = torch.zeros((1, 1, Cin, H, (W + 31) // 32), dtype=torch.int32, device=DEV)
+    got = api.tac_conv_lif_backward(desc, x, w, torch.ones_like(g), g, grad_in_per_group=True)
+    torch.cuda.synchronize()
+    gy, have = got["grad_y"][0, 0], got["grad_in"].view(Cin, H, W)
+    wd, pad = w.cpu().double(), torch.nn.functional.pad
+    tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
+    for y0, x0 in ((0, 0), (0, W - 70), (H - 20, 0), (H - 20, W - 70), (4450, 500)):
+        y1, x1 = min(y0 + 20, H), min(x0 + 70, W)
+        part = pad(gy[:, max(y0 - 1, 0):y1 + 1, max(x0 - 1, 0):x1 + 1].cpu().double(), (int(x0 == 0), int(x1 == W), int(y0 == 0), int(y1 == H)))
+        # a part with a ring of one around it: the transposed convolution loses the ring on either side
+        want = torch.nn.functional.conv_transpose2d(part[None], wd, padding=2)[0]
+        size = torch.nn.functional.conv_transpose2d(part[None].abs(), wd.abs(), padding=2)[0]
+        assert want.shape[1:] == (y1 - y0, x1 - x0)
+        assert ((have[:, y0:y1, x0:x1].cpu().double() - want).abs() <= tol * size + 1e-12).all()
