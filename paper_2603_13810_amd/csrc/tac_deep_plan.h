@@ -34,6 +34,14 @@ __host__ __device__ constexpr int deep_unit_channels(int kp, int wave_steps) {
   return kp <= 2 ? 8 : kp == 4 ? (wave_steps == 9 ? 8 : 4) : kp == 8 ? (wave_steps == 9 ? 4 : 2) : 2;
 }
 
+// Scalar byte offset of the words of frame j, channel c of a unit, in a load from a round's first word.  The range check of a buffer load compares the
+// lane's offset with the descriptor's size less this one, which must not wrap below zero.
+__host__ __device__ constexpr uint32_t deep_scalar_offset(int j, int frames, uint32_t frame_words, int c, uint32_t channel_words) {
+  return ((uint32_t)(j < frames ? j : 0) * frame_words + (uint32_t)c * channel_words) * 4u;
+}
+// Frames of a round's first group, which no group of the round exceeds: a shorter last group alone in its round has only its own behind the descriptor's start.
+__host__ __device__ constexpr int deep_round_frames(int g0, int G, int K, int K_last) { return g0 < G ? K : K_last; }
+
 // False: the tile does not fit.
 inline bool deep_plan(DeepPlan& q, const LayerParams& p, int pb, bool flatten) {
   const int S = p.stride, C8 = p.Cin / 8, n_groups = p.G + (p.K_last ? 1 : 0);

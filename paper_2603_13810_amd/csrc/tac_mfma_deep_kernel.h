@@ -177,14 +177,14 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
     const size_t first = ((size_t)g0 * p.K * p.B + b0) * Cin * in_chan;
     const size_t bytes = ((size_t)(p.G * p.K + dp.K_last) * t_stride - first) * 4;
     const auto words = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.spikes + first), 0, (int)(bytes < 0x7fffffffu ? bytes : 0x7fffffffu), 0x00020000);
-    const int Kg = g0 + x.gb == p.G ? dp.K_last : p.K;
+    const int Kg = g0 + x.gb == p.G ? dp.K_last : p.K, frames = deep_round_frames(g0, p.G, p.K, dp.K_last);
     const uint32_t off = x.e[0] + ((uint32_t)x.gb * (uint32_t)p.K * (uint32_t)t_stride + (uint32_t)(x.cc * UC) * in_chan) * 4u;
 #pragma unroll
     for (int j = 0; j < KP; ++j) {
       const uint32_t voff = j < Kg ? off : kOutside;
 #pragma unroll
       for (int c = 0; c < UC; ++c)
-        wd[c][j] = __builtin_amdgcn_raw_buffer_load_b32(words, (int)voff, (int)(((uint32_t)(j < p.K ? j : 0) * (uint32_t)t_stride + (uint32_t)c * in_chan) * 4u), 0);
+        wd[c][j] = __builtin_amdgcn_raw_buffer_load_b32(words, (int)voff, (int)deep_scalar_offset(j, frames, (uint32_t)t_stride, c, in_chan), 0);
     }
   };
   const uint32_t two_lo = KP == 2 ? pack_bf16(0.f, (float)p.wq[0] * scale) : 0u;

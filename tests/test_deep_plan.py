@@ -24,6 +24,8 @@ def plan(tmp_path_factory):
     def of(desc):
         out = (ctypes.c_int * len(FIELDS))()
         return dict(zip(FIELDS, out)) if shim.deep_plan_of(ctypes.byref(desc), out) else None
+    shim.deep_loads_outside.restype = ctypes.c_longlong
+    of.loads_outside = lambda desc: shim.deep_loads_outside(ctypes.byref(desc))
     return of
 
 
@@ -62,6 +64,21 @@ def test_plans_cover_their_layers(plan):
         assert q["rpb"] * min(32, 1 << (Wo - 1).bit_length()) <= 32 or q["rpb"] == 1
         assert q["nseg"] * q["xs"] >= W > (q["nseg"] - 1) * q["xs"] and q["xs"] in (8, 16, 32)
         assert q["co_tiles"] * 32 >= Cout
+    assert taken > 500
+
+
+def test_frame_loads_stay_inside_the_descriptor(plan):
+    # a shorter last group that is alone in its round: its round has fewer frames than the others
+    assert plan.loads_outside(_desc(3, 192, 33, 5, 3, 1, api.TAC_COLLAPSE, 2, 9)) == 0
+    assert plan.loads_outside(_desc(2, 256, 48, 10, 8, 1, api.TAC_COLLAPSE, 16, 33)) == 0
+    r = random.Random(6)
+    taken = 0
+    for _ in range(2000):
+        K, B, Cin = r.randint(1, 16), r.choice([1, 2, 7]), 8 * r.randint(2, 32)
+        d = _desc(B, Cin, r.randint(1, 80), r.randint(1, 40), r.randint(1, 70), r.choice([1, 2]), api.TAC_COLLAPSE, K, r.randint(1, 40))
+        outside = plan.loads_outside(d)
+        taken += outside >= 0
+        assert outside <= 0
     assert taken > 500
 
 
