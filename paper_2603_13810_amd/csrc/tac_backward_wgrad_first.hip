@@ -18,9 +18,7 @@
 //   2 -> 64 stride 2, 8 groups at 128 x 128, B = 32     268 2.4e-7   254 1.9e-7
 //   1 -> 16, one group at 100 x 100, B = 128            148 3.9e-7    64 2.4e-7
 // Of 60 random first layers the median is 1.2 times as fast, the slowest 0.97; of 45 small ones (7 to 90 us) the slowest is 0.89 (26.4 us against 23.5: 2 -> 48 at 19 x 31, B = 16).
-#include <algorithm>
-#include <cmath>
-#include "tac_mfma_common.h"
+#include "tac_wgrad_first_plan.h"
 
 namespace tac {
 
@@ -28,16 +26,8 @@ namespace {
 
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int kThreads = 512;
-constexpr int CPW = 4;                   // output channels of a wave: up to 72 sums in registers, beside 16 values of dY
-constexpr int kLds = 72 * 1024;         // two workgroups per compute unit
-
-struct FirstWgradPlan {
-  int ncg, co_groups, split;
-  int n_pairs, rows, n_strips, pair_tiles;    // an item: (group, sample) pairs x output rows
-  int quads, rows_in, cw, cp;                 // quads per output row; aggregate rows per pair, floats per row and per (pair, channel)
-  int off_w, total;                           // LDS bytes
-};
+constexpr int kThreads = kFirstWgradThreads;
+constexpr int CPW = kFirstWgradChannels;
 
 __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
@@ -283,47 +273,9 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
   }
 }
 
-bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
-  const int S = p.stride, groups = (p.Cout + CPW - 1) / CPW;
-  q.quads = (p.Wo + 3) / 4;
-  q.cw = (q.quads * 4 * S + 3 + 7) & ~7;
-  q.ncg = 1;
-  // Workgroups of few channels need few slices to fill the chip (1 -> 32 at 28 x 28, B = 128: error 1.5e-7 with 64 slices, 1.9e-7 with 128, as fast), but
-  // rebuild the aggregates once more each, which weighs with real-valued frames (2 -> 128 at 64 x 64, B = 16: 122 us a call, 132 the other way).
-  const int most_groups = p.dense ? 4 : 8, most_slices = p.dense ? 128 : 64;
-  while (q.ncg < 8 && groups / q.ncg > most_groups) q.ncg *= 2;
-  q.co_groups = (groups + q.ncg - 1) / q.ncg;
-  // frames whose values outweigh dY stay with the other kernel: 2 -> 48 stride 2 at 64 x 67, B = 33, groups of 8 (4 times) 45 / 53 us a call, 2 -> 32 stride 2 at
-  // 32 x 32, B = 128, groups of 3 (3 times) 75 / 82; 1 -> 32 at 128 x 126, B = 64, groups of 16 (2 times) 174 / 168
-  if (p.dense && p.K * S * S * p.Cin * q.co_groups > 2 * p.Cout) return false;
-  const int lanes = 64 * 8 / q.ncg, all_pairs = p.G * p.B;
-  // rows of an item: two turns of the lanes, as far as the image and the LDS go; then pairs, while every slice gets an item
-  const int slices = std::max(1, std::min(most_slices, 512 / q.co_groups));
-  const int limit = kLds - 2 * TAC_MAX_K * 4;
-  auto bytes = [&](int rows, int pairs) { return (long long)pairs * p.Cin * ((rows - 1) * S + 3) * q.cw * 4; };
-  q.rows = std::min(p.Ho, std::max(1, 2 * lanes / q.quads));
-  while (q.rows > 1 && bytes(q.rows, 1) > limit) q.rows = (q.rows + 1) / 2;
-  if (bytes(q.rows, 1) > limit) return false;
-  q.n_strips = (p.Ho + q.rows - 1) / q.rows;
-  q.rows = (p.Ho + q.n_strips - 1) / q.n_strips;         // strips of the same height, as far as it goes
-  q.n_pairs = 1;
-  if (q.n_strips == 1)
-    while (q.n_pairs * q.rows * q.quads < 2 * lanes && bytes(q.rows, q.n_pairs + 1) <= limit && (long long)slices * (q.n_pairs + 1) <= all_pairs) ++q.n_pairs;
-  q.pair_tiles = (all_pairs + q.n_pairs - 1) / q.n_pairs;
-  q.split = (int)std::min<long long>(slices, (long long)q.pair_tiles * q.n_strips);
-  // few workgroups of real-valued frames have a long chain of loads each (2 -> 56 at 31 x 26, B = 2, three groups of 8 on 24 workgroups: 15.4 us, 9.4 on the other
-  // kernel; of 25 layers below this line 3 lost more than 5% by it)
-  if (p.dense && q.co_groups * q.split < 128) return false;
-  q.rows_in = (q.rows - 1) * S + 3;
-  q.off_w = std::max((int)bytes(q.rows, q.n_pairs), 8 * 72 * 4 + 8 * CPW * 8);
-  q.total = q.off_w + 2 * TAC_MAX_K * 4;
-  return (long long)q.pair_tiles * q.n_strips < (1ll << 31) && q.n_pairs * q.rows * q.quads < (1 << 20);
-}
-
 }  // namespace
 
 bool backward_wgrad_first_launch(const BackwardParams& p, hipStream_t s, hipError_t& e) {
-  if (p.Cin > 2 || p.pool2) return false;
   FirstWgradPlan q{};
   if (!first_wgrad_plan(p, q)) return false;
   const bool vec = p.Wo % 4 == 0 && ((uintptr_t)p.grad_y & 15) == 0;
@@ -332,7 +284,7 @@ bool backward_wgrad_first_launch(const BackwardParams& p, hipStream_t s, hipErro
     constexpr bool DENSE = decltype(dense_)::value;
     const auto kern = vec ? &wgrad_first_kernel<S, CIN, DENSE, true> : &wgrad_first_kernel<S, CIN, DENSE, false>;
     if (q.total > 64 * 1024) {
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+      e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kFirstWgradLds);
       if (e != hipSuccess) return;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)(q.co_groups * q.split)), dim3(kThreads), q.total, s, p, q);

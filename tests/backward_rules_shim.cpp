@@ -1,5 +1,5 @@
 // The host rules of the backward launch that choose between kernels, for the tests that hold them to what they are there for.
-#include "tac_internal.h"
+#include "tac_wgrad_first_plan.h"
 
 extern "C" int clear_in_recurrence(long long threads, long long floats) { return tac::backward_clear_in_recurrence((size_t)threads, (size_t)floats); }
 
@@ -7,4 +7,22 @@ extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int H, int 
   tac::BackwardParams p{};
   p.G = G; p.B = B; p.Cin = Cin; p.H = H; p.W = W; p.stride = stride;
   return tac::backward_dgrad_f32_supported(p);
+}
+
+// out: groups of channels per workgroup, channel groups, slices, pairs per item, rows per item, strips, pair tiles, bytes of LDS.  0: not that kernel's layer.
+extern "C" int first_weight_gradient(const tac_layer_desc_t* d, int* out) {
+  tac::BackwardParams p{};
+  p.B = d->B; p.Cin = d->Cin; p.H = d->H; p.W = d->W; p.Cout = d->Cout; p.stride = d->stride;
+  p.Ho = (d->H - 1) / d->stride + 1;
+  p.Wo = (d->W - 1) / d->stride + 1;
+  p.pool2 = d->in_format == TAC_IN_BITS_POOL2 ? 1 : d->in_format == TAC_IN_BITS_MAXPOOL2 ? 2 : 0;
+  p.dense = d->in_format == TAC_IN_F32;
+  p.K = d->mode == TAC_PER_STEP ? 1 : std::min(d->K, d->T);
+  p.K_last = d->T % p.K;
+  p.G = (d->T + p.K - 1) / p.K;
+  tac::FirstWgradPlan q{};
+  if (!tac::first_wgrad_plan(p, q)) return 0;
+  const int v[] = {q.ncg, q.co_groups, q.split, q.n_pairs, q.rows, q.n_strips, q.pair_tiles, q.total};
+  std::copy(std::begin(v), std::end(v), out);
+  return 1;
 }

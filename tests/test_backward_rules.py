@@ -5,7 +5,8 @@ import subprocess
 
 import pytest
 
-from paper_2603_13810_amd import build
+from paper_2603_13810_amd import api, build
+from test_gpu_backward_wgrad import FIRST, FIRST_TAKEN, INFINITE, REAL
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -34,3 +35,18 @@ def test_a_large_weight_gradient_is_not_cleared_by_a_handful_of_threads(rules, n
 def test_input_gradient_kernel(rules, case):
     G, B, Cin, hw, stride, matrix = case
     assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, hw, hw, stride)) == matrix
+
+
+PLAN = ("ncg", "co_groups", "split", "n_pairs", "rows", "n_strips", "pair_tiles", "lds")
+
+
+def _first(rules, B, Cin, Cout, H, W, stride, fmt, K, T):
+    d = api.make_desc(T, B, Cin, H, W, Cout, K=K, beta=0.9, theta=1.0, mode=api.TAC_COLLAPSE, stride=stride, in_format=fmt)
+    out = (ctypes.c_int * len(PLAN))()
+    return dict(zip(PLAN, out)) if rules.first_weight_gradient(ctypes.byref(d), out) else None
+
+
+def test_first_layers_take_the_kernel_they_are_there_for(rules):
+    assert [_first(rules, *case) is not None for case in FIRST] == FIRST_TAKEN
+    B, Cin, Cout, H, W = INFINITE
+    assert _first(rules, B, Cin, Cout, H, W, 1, REAL, 1, 1) and W % 4

@@ -120,7 +120,26 @@ FIRST = [
     (24, 2, 64, 33, 31, 1, REAL, 2, 5), (40, 1, 128, 40, 24, 2, REAL, 4, 6), (60, 2, 96, 7, 9, 1, REAL, 1, 3),
 ]
 
+# which of them run on the first layers' kernel (the choice is held to this on the CPU)
+FIRST_TAKEN = [True, True, True, True, False, False, False, True, True, False, True, True, True]
+
 
 @pytest.mark.parametrize("case", FIRST, ids=["%d_to_%d_%dx%d_s%d_f%d" % c[1:7] for c in FIRST])
 def test_first_layers(case):
     test_weight_and_bias_gradient(case)
+
+
+INFINITE = (24, 2, 64, 33, 31)      # B, Cin, Cout, H, W: enough workgroups for the first layers' kernel, 31 pixels a row
+
+
+def test_an_infinite_frame_value_stays_where_it_is_in_first_layers():
+    # the pixel that fills the row's last quad must not multiply the infinite value of the last column by zero
+    B, Cin, Cout, H, W = INFINITE
+    x = torch.rand((1, B, Cin, H, W), device=DEV)
+    x[0, 5, 1, 7, W - 1] = float("inf")
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP, in_format=REAL)
+    v = torch.zeros((1, B, Cout, H, W), device=DEV)
+    got = api.tac_conv_lif_backward(desc, x, torch.zeros((Cout, Cin, 3, 3), device=DEV), v, torch.ones_like(v), want_input_grad=False)
+    gw = got["grad_w"].cpu()
+    assert torch.isfinite(gw[:, 0]).all()
+    assert torch.isfinite(gw[:, 1, :, 0]).all() and torch.isinf(gw[:, 1, :, 1:]).all()
