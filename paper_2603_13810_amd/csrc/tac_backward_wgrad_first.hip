@@ -3,20 +3,23 @@
 // dW has 9 or 18 columns, which fill a third or half of a matrix-core tile, and its operands would have to be turned around in LDS; every dY value
 // is used 9 or 18 times only, so what bounds the layer is reading dY once.  Here a lane owns four neighbouring pixels: it reads its dY of a channel as 16
 // consecutive bytes (a wave's load is 1 KiB of consecutive addresses), the 3 x 6 aggregates around them from LDS once for four channels, and adds
-// the products to 36 Cin sums of its own.  Those meet across the lanes and waves of the workgroup at the end.
+// the products to 36 Cin sums of its own.
 //
 // Workgroup = eight waves = `ncg` groups of four output channels x 8 / ncg shares of the pixels, over a slice of the items (some (group, sample) pairs of a small
 // image, or a strip of rows of one).  The aggregates of an item are rebuilt from the frames into LDS.
 //
-// Error: a lane adds some hundred products in a chain, and the 64 lanes, the waves and the slices (64; 128 with real-valued frames) each add up sums of their own:
-// no larger than that of the matrix cores' kernel (norm against 64-bit sums, dY of both signs).
+// Error: a lane's chains of products end after 64 of them (kFirstWgradChain); the sums of the 64 lanes then meet in a tree and go on in 64 bits, in LDS, one set for
+// each wave.  What is rounded to fp32 again is a workgroup's sum, of which the slices (64; 128 with real-valued frames) add one each in memory.  Without the end of the
+// chains the error grew with the data: 1 -> 128, 2 steps of spikes everywhere at 64 x 64, B = 640, dY the same everywhere (chains of 640 equal products): 7.2e-7 of the norm, now
+// 1.0e-7, that kernel 1.2e-7.  Ending them costs less than a call's times differ.
 //
-// Backward calls without input gradient in us, that kernel (tac_backward_wgrad_f32.hip) and this one, with their errors:
-//   1 -> 32, 7 groups at 28 x 28, B = 128               102 3.0e-7    69 1.5e-7   (the kernel alone 63 / 30; dY is 90 MB)
-//   2 -> 128, real values, 4 groups at 64 x 64, B = 16  137 2.4e-7   122 2.4e-7
-//   2 -> 128, 4 groups at 64 x 64, B = 16               128 2.1e-7   106 1.9e-7
-//   2 -> 64 stride 2, 8 groups at 128 x 128, B = 32     268 2.4e-7   254 1.9e-7
-//   1 -> 16, one group at 100 x 100, B = 128            148 3.9e-7    64 2.4e-7
+// Backward calls without input gradient in us, that kernel (tac_backward_wgrad_f32.hip) and this one, with their errors (norm against 64-bit sums, dY of both signs):
+//   1 -> 32, 7 groups at 28 x 28, B = 128               102 2.9e-7    67 1.5e-7   (the kernel alone 63 / 30; dY is 90 MB)
+//   2 -> 128, real values, 4 groups at 64 x 64, B = 16  135 2.3e-7   115 2.3e-7
+//   2 -> 128, 4 groups at 64 x 64, B = 16               125 2.0e-7   101 1.8e-7
+//   2 -> 64 stride 2, 8 groups at 128 x 128, B = 32     255 2.5e-7   240 2.0e-7
+//   1 -> 16, one group at 100 x 100, B = 128            128 2.7e-7    64 1.6e-7
+//   1 -> 64, 32 steps at 128 x 128, B = 48             5830 3.0e-7  4830 1.6e-7
 // Of 60 random first layers the median is 1.2 times as fast, the slowest 0.97; of 45 small ones (7 to 90 us) the slowest is 0.89 (26.4 us against 23.5: 2 -> 48 at 19 x 31, B = 16).
 #include "tac_wgrad_first_plan.h"
 
@@ -80,6 +83,8 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
   float* const wl = reinterpret_cast<float*>(lds + q.off_w);           // frame weights: a whole group's, the last group's
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  double* const red = reinterpret_cast<double*>(lds + q.off_sum);      // [wave][channel][ci][tap]
+  double* const red_b = red + 8 * 72;                    // [wave][channel]
   const int slice = (int)(blockIdx.x % (uint32_t)q.split), co_group = (int)(blockIdx.x / (uint32_t)q.split);
   const int cg = wave % q.ncg, share = wave / q.ncg, shares = 8 / q.ncg;
   const int co0 = (co_group * q.ncg + cg) * CPW;
@@ -89,7 +94,8 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
     wl[tid] = tid < TAC_MAX_K ? (j < p.K ? p.wj[j] : 0.f) : (j < p.K_last ? p.wj_last[j] : 0.f);
   }
 
-  float acc[NS];                                         // [channel][ci][tap]
+  float acc[NS];                                         // [channel][ci][tap], of the last items
+  for (int i = lane; i < NS; i += 64) red[wave * NS + i] = 0.0;        // (the wave's own)
   double bias[CPW];
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
@@ -100,6 +106,7 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
 
   const int all_pairs = p.G * p.B, items = q.pair_tiles * q.n_strips;
   const float inv_quads = 1.0f / (float)q.quads, inv_b = 1.0f / (float)p.B;
+  int chain = 0;
   const int units_row = q.cw >> 3;                       // units of eight aggregates
   const float inv_units = 1.0f / (float)units_row, inv_cw = 1.0f / (float)q.cw, inv_cin_rows = 1.0f / (float)(CIN * q.rows_in);
   for (int it = slice; it < items; it += q.split) {
@@ -241,16 +248,21 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
             }
         }
     }
+    // ---- a chain of products ends: its 64 lanes' sums meet, and go on in 64 bits
+    if (++chain == q.flush || it + q.split >= items) {   // (uniform)
+      chain = 0;
+      int l = lane;
+      asm volatile("" : "+v"(l));                        // what depends on the lane is formed here: nothing of it is kept across items
+      lane_sums<NS, 0>(acc, l);
+      static_for<0, lane_sum_left(NS)>([&](auto j_) {
+        constexpr int j = decltype(j_)::value;
+        red[wave * NS + lane_sum_index<NS>(j, l)] += (double)acc[j];          // (lanes with the same value read, then write it, together)
+      });
+#pragma unroll
+      for (int i = 0; i < NS; ++i) acc[i] = 0.f;
+    }
   }
-  // ---- lanes, then the waves that share a group of channels, then the slices
-  float* const red = reinterpret_cast<float*>(lds);      // [wave][channel][ci][tap]
-  double* const red_b = reinterpret_cast<double*>(lds + 8 * 72 * 4);   // [wave][channel]
-  __syncthreads();
-  lane_sums<NS, 0>(acc, lane);
-  static_for<0, lane_sum_left(NS)>([&](auto j_) {
-    constexpr int j = decltype(j_)::value;
-    red[wave * NS + lane_sum_index<NS>(j, lane)] = acc[j];
-  });
+  // ---- the waves that share a group of channels, then the slices
 #pragma unroll
   for (int c = 0; c < CPW; ++c) {
     double v = bias[c];
@@ -261,9 +273,9 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
   __syncthreads();
   for (int e = tid; e < q.ncg * NS; e += kThreads) {
     const int g = e / NS, at = e - g * NS, co = (co_group * q.ncg + g) * CPW + at / (9 * CIN);
-    float v = 0.f;
+    double v = 0.0;
     for (int s = 0; s < shares; ++s) v += red[(s * q.ncg + g) * NS + at];
-    if (co < p.Cout) atomicAdd(p.grad_w + (size_t)co * (9 * CIN) + at % (9 * CIN), v);
+    if (co < p.Cout) atomicAdd(p.grad_w + (size_t)co * (9 * CIN) + at % (9 * CIN), (float)v);
   }
   if (p.grad_bias && tid < q.ncg * CPW) {
     const int g = tid / CPW, c = tid - g * CPW, co = (co_group * q.ncg + g) * CPW + c;

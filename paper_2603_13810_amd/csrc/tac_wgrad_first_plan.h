@@ -7,13 +7,17 @@ namespace tac {
 
 constexpr int kFirstWgradThreads = 512;
 constexpr int kFirstWgradChannels = 4;          // output channels of a wave: up to 72 sums in registers, beside 16 values of dY
-constexpr int kFirstWgradLds = 72 * 1024;       // two workgroups per compute unit
+constexpr int kFirstWgradSums = 8 * (72 + kFirstWgradChannels) * 8;     // LDS bytes of the waves' sums of dW and of the bias gradient
+constexpr int kFirstWgradLds = 72 * 1024 + kFirstWgradSums;             // two workgroups per compute unit
+// Products that a lane adds in a chain, as many as a chain of the other kernel's has MFMAs.  (More only where a strip of one row has more.)
+constexpr int kFirstWgradChain = 64;
 
 struct FirstWgradPlan {
   int ncg, co_groups, split;
   int n_pairs, rows, n_strips, pair_tiles;    // an item: (group, sample) pairs x output rows
   int quads, rows_in, cw;                     // quads per output row; aggregate rows per pair and channel, floats per row
-  int off_w, total;                           // LDS bytes
+  int flush;                                  // items after which a lane's chains of products end
+  int off_w, off_sum, total;                  // LDS bytes
 };
 
 // False: a layer of the other kernel's (wgrad_f32_kernel).
@@ -23,7 +27,7 @@ inline bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
   q.quads = (p.Wo + 3) / 4;
   q.cw = (q.quads * 4 * S + 3 + 7) & ~7;
   q.ncg = 1;
-  // Workgroups of few channels need few slices to fill the chip (1 -> 32 at 28 x 28, B = 128: error 1.5e-7 with 64 slices, 1.9e-7 with 128, as fast), but
+  // Workgroups of few channels need few slices to fill the chip (1 -> 32 at 28 x 28, B = 128: as fast with 64 slices as with 128, whose sums round twice as often), but
   // rebuild the aggregates once more each, which weighs with real-valued frames (2 -> 128 at 64 x 64, B = 16: 122 us a call, 132 the other way).
   const int most_groups = p.dense ? 4 : 8, most_slices = p.dense ? 128 : 64;
   while (q.ncg < 8 && groups / q.ncg > most_groups) q.ncg *= 2;
@@ -34,7 +38,7 @@ inline bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
   const int lanes = kFirstWgradThreads / q.ncg, all_pairs = p.G * p.B;
   // rows of an item: two turns of the lanes, as far as the image and the LDS go; then pairs, while every slice gets an item
   const int slices = std::max(1, std::min(most_slices, 512 / q.co_groups));
-  const int limit = kFirstWgradLds - 2 * TAC_MAX_K * 4;
+  const int limit = kFirstWgradLds - kFirstWgradSums - 2 * TAC_MAX_K * 4;
   auto bytes = [&](int rows, int pairs) { return (long long)pairs * p.Cin * ((rows - 1) * S + 3) * q.cw * 4; };
   q.rows = std::min(p.Ho, std::max(1, 2 * lanes / q.quads));
   while (q.rows > 1 && bytes(q.rows, 1) > limit) q.rows = (q.rows + 1) / 2;
@@ -49,9 +53,12 @@ inline bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
   // few workgroups of real-valued frames have a long chain of loads each (2 -> 56 at 31 x 26, B = 2, three groups of 8 on 24 workgroups: 15.4 us, 9.4 on the other
   // kernel; of 25 layers below this line 3 lost more than 5% by it)
   if (p.dense && q.co_groups * q.split < 128) return false;
+  // four products a quad and turn of the lanes
+  q.flush = std::max(1, kFirstWgradChain / (4 * ((q.n_pairs * q.rows * q.quads + lanes - 1) / lanes)));
   q.rows_in = (q.rows - 1) * S + 3;
-  q.off_w = std::max((int)bytes(q.rows, q.n_pairs), 8 * 72 * 4 + 8 * kFirstWgradChannels * 8);
-  q.total = q.off_w + 2 * TAC_MAX_K * 4;
+  q.off_w = (int)bytes(q.rows, q.n_pairs);
+  q.off_sum = q.off_w + 2 * TAC_MAX_K * 4;
+  q.total = q.off_sum + kFirstWgradSums;
   return (long long)q.pair_tiles * q.n_strips < (1ll << 31) && q.n_pairs * q.rows * q.quads < (1 << 20);
 }
 

@@ -85,7 +85,9 @@ def test_an_infinite_frame_value_stays_where_it_is():
     assert torch.isfinite(gw[:, 1, :, 0]).all() and torch.isinf(gw[:, 1, :, 1:]).all()
 
 
-@pytest.mark.parametrize("B,Cin,Cout,hw,T,rate", [(16, 256, 256, 40, 4, 0.12), (100, 256, 128, 32, 2, 1.0)])
+@pytest.mark.parametrize("B,Cin,Cout,hw,T,rate", [(16, 256, 256, 40, 4, 0.12), (100, 256, 128, 32, 2, 1.0),
+                                                    # first layers, 640 and 520 products a thread
+                                                    (640, 1, 128, 64, 2, 1.0), (520, 2, 64, 64, 4, 0.12)])
 def test_long_sums_of_one_sign(B, Cin, Cout, hw, T, rate):
     # 1e5 pixels and more per element, all terms positive: a sum that is one long chain of additions loses digits here.
     # dL/dY is the same everywhere within a step, so that dW is that value times the number of spikes under the tap.
@@ -102,7 +104,8 @@ def test_long_sums_of_one_sign(B, Cin, Cout, hw, T, rate):
     count = np.stack([padded[:, :, :, ky:ky + hw, kx:kx + hw].sum((1, 3, 4), dtype=np.int64) for ky in range(3) for kx in range(3)], -1)
     dW = np.broadcast_to((per_step[:, None, None] * count).sum(0), (Cout, Cin, 9))
     db = per_step.sum() * B * hw * hw
-    # Chains of at most some 64 MFMAs, 64 sums of chains, 8 waves and 48 slices follow one another; n additions, each
+    # Chains of at most some 64 MFMAs (first layers: products, whose sums meet in 64 bits), 64 sums of chains, 8 waves and 48 slices (first layers: 64) follow one
+    # another; n additions, each
     # rounded by up to 2^-24 of the sum so far, leave about 2^-24 sqrt(n) of it: n < 256
     tol = 16 * 2.0 ** -24
     err = got["grad_w"].double().cpu().numpy().reshape(dW.shape) - dW
