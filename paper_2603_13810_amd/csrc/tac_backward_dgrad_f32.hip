@@ -5,13 +5,13 @@
 // dgrad_f32_kernel: D[32 ci x 32 px] += W^T[32 ci x 16 co] . dY[16 co x 32 px].  v_mfma_f32_32x32x2_f32 takes 512 cycles for the 16 channels; here each fp32
 // value is three bf16 values whose sum it is, and six products of v_mfma_f32_32x32x16_bf16 (192 cycles) are all that reach 2^-26 of the largest.
 // Fewer roundings of the sums make the result more accurate than the products of fp32 were: 96 <- 128 at 64 x 40, B = 16, three groups 4.8e-7 of the norm
-// instead of 6.0e-7, and on 34 other layers 0.81 to 0.88 of the error.  Infinities and NaN have no thirds: a round that holds one multiplies the values put
-// together again on v_mfma_f32_32x32x2_f32.
+// instead of 6.0e-7, and on 34 other layers 0.81 to 0.88 of the error.  A round with an infinity, a NaN, or values that the subnormal numbers cut (below 2^-90)
+// multiplies the values put together again on v_mfma_f32_32x32x2_f32.
 // Workgroup = 32 input channels x a tile of pixels (rows of one or, in small images, of several (group, sample) pairs); four waves share the pixels,
 // NP blocks of 32 each.  Sixteen output channels at a time go through LDS as thirds, [third][tap][half of the channels][ci] and [third][half][position];
 // the next sixteen are requested before the MFMAs.  Two or three workgroups share a compute unit, so that one's splitting (400 vector instructions a round
 // and wave, which bound it together with the MFMAs' 1728 NP cycles) runs under another's products.
-// Before and after (us): 96 <- 128 at 64 x 40, B = 16, three groups 537 -> 192; 32 <- 64 at 14 x 14, B = 128, seven groups 91 -> 59; 160 <- 96 at 41 x 33,
+// Products of fp32 and these (us): 96 <- 128 at 64 x 40, B = 16, three groups 537 -> 192; 32 <- 64 at 14 x 14, B = 128, seven groups 91 -> 59; 160 <- 96 at 41 x 33,
 // 144 pairs 1290 -> 343; only 8 output channels on fewer tiles than compute units lose: 5.0 -> 6.2.
 //
 // Few pixels (small images, small batches) leave that kernel with a few dozen workgroups that go through Cout / 16 rounds of two barriers
@@ -41,17 +41,19 @@ __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
 }
 
-// x = hi + mid + lo, three bf16 values (8 bits each and their signs: all 24 bits of x).  What does not round to a finite hi keeps its upper half as it is; the
-// others of an infinity or a NaN are zero.
+// x = hi + mid + lo, three bf16 values (8 bits each and their signs: all 24 bits of x) of eight values.  A set has none where its largest value is infinite, a NaN or rounds
+// to an infinite hi, or lies (not being zero) below 2^-90, where the subnormal numbers begin to cut the lower parts off: then hi and mid are the two halves of
+// the fp32 value and lo is kHalves, which is no third of anything.
 struct Thirds {
-  u32x4 hi, mid, lo;              // eight values
+  u32x4 hi, mid, lo;
 };
-__device__ __forceinline__ Thirds thirds(const float (&x)[8], bool& not_finite) {
+constexpr uint32_t kThirdsFrom = (127u - 90u) << 23, kThirdsTo = 0x7f7f8000u, kHalves = 0x7fc1u;
+__device__ __forceinline__ Thirds thirds(const float (&x)[8], bool& none) {
   Thirds o;
   uint32_t most = 0;
 #pragma unroll
   for (int i = 0; i < 8; ++i) most = max(most, __float_as_uint(x[i]) & 0x7fffffffu);
-  if (__builtin_expect(most < 0x7f7f8000u, 1)) {
+  if (__builtin_expect(most - kThirdsFrom < kThirdsTo - kThirdsFrom || most == 0, 1)) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       o.hi[i] = pack_bf16(x[2 * i], x[2 * i + 1]);
@@ -60,24 +62,22 @@ __device__ __forceinline__ Thirds thirds(const float (&x)[8], bool& not_finite) 
       o.lo[i] = pack_bf16(r0 - __uint_as_float(o.mid[i] << 16), r1 - __uint_as_float(o.mid[i] & 0xffff0000u));
     }
   } else {
-    not_finite |= most >= 0x7f800000u;
+    none = true;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      float r[2];
-      uint32_t up[2];
-#pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float v = x[2 * i + e];
-        const uint32_t u = __float_as_uint(v), a = u & 0x7fffffffu;
-        up[e] = a > 0x7f800000u ? 0x7fc00000u : a >= 0x7f7f8000u ? u & 0xffff0000u : pack_bf16(v, 0.f) << 16;
-        r[e] = a >= 0x7f800000u ? 0.f : v - __uint_as_float(up[e]);
-      }
-      o.hi[i] = up[0] >> 16 | up[1];
-      o.mid[i] = pack_bf16(r[0], r[1]);
-      o.lo[i] = pack_bf16(r[0] - __uint_as_float(o.mid[i] << 16), r[1] - __uint_as_float(o.mid[i] & 0xffff0000u));
+      const uint32_t u0 = __float_as_uint(x[2 * i]), u1 = __float_as_uint(x[2 * i + 1]);
+      o.hi[i] = u0 >> 16 | (u1 & 0xffff0000u);
+      o.mid[i] = (u0 & 0xffffu) | u1 << 16;
+      o.lo[i] = kHalves | kHalves << 16;
     }
   }
   return o;
+}
+// The value again.  hi + (mid + lo) is exact.
+__device__ __forceinline__ float whole(const uint8_t* hi, int term) {
+  auto bits = [&](int part) { return (uint32_t)*reinterpret_cast<const uint16_t*>(hi + part * term) << 16; };
+  const uint32_t h = bits(0), m = bits(1), l = bits(2);
+  return l == kHalves << 16 ? __uint_as_float(h | m >> 16) : __uint_as_float(h) + (__uint_as_float(m) + __uint_as_float(l));
 }
 
 constexpr int kTapBytes = 1024 + 16;                     // a tap's 2 x 32 x 8 weights; 16 bytes spread the taps of an input channel over the banks
@@ -203,41 +203,37 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
     if (!active) continue;
     const uint8_t* const w_lane = lds + lane * 16;
     const uint8_t* const d_half = dyl + h * q.pl * 16;
-    auto load = [&](const uint8_t* at) { return *reinterpret_cast<const bf16x8*>(at); };
-    if (__builtin_expect(!any_bad, 1)) {
-#pragma unroll
-      for (int tap = 0; tap < 9; ++tap) {
-        const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
-        bf16x8 w[3], d[NP][3];
-#pragma unroll
-        for (int e = 0; e < 3; ++e) w[e] = load(w_lane + tap * kTapBytes + e * kWBytes);
-#pragma unroll
-        for (int b = 0; b < NP; ++b)
-#pragma unroll
-          for (int e = 0; e < 3; ++e) d[b][e] = load(d_half + (base[b] + shift) * 16 + e * d_term);
-        // the products of 2^-18 and more of the largest; the three left out are below 2^-26 of it
-#pragma unroll
-        for (int e = 0; e < 6; ++e) {
-          constexpr int kW[6] = {0, 2, 1, 0, 1, 0}, kD[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], acc[b], 0, 0, 0);
-        }
-      }
-    } else {
-      // an infinity or a NaN: the values put together again (exactly), in products of fp32
-      auto whole = [&](const uint8_t* at, int term, int i) {
-        const float hi = (float)load(at)[i], mid = (float)load(at + term)[i], lo = (float)load(at + 2 * term)[i];
-        return hi + (mid + lo);
-      };
+    if (__builtin_expect(any_bad, 0)) {
+      // the round in products of fp32
 #pragma clang loop unroll(disable)
       for (int tap = 0; tap < 9; ++tap) {
         const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
-#pragma unroll
+#pragma clang loop unroll(disable)
         for (int i = 0; i < 8; ++i) {
-          const float wv = whole(w_lane + tap * kTapBytes, kWBytes, i);
+          const float wv = whole(w_lane + tap * kTapBytes + 2 * i, kWBytes);
 #pragma unroll
-          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, whole(d_half + (base[b] + shift) * 16, d_term, i), acc[b], 0, 0, 0);
+          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, whole(d_half + (base[b] + shift) * 16 + 2 * i, d_term), acc[b], 0, 0, 0);
         }
+      }
+      continue;
+    }
+    auto load = [&](const uint8_t* at) { return *reinterpret_cast<const bf16x8*>(at); };
+#pragma unroll
+    for (int tap = 0; tap < 9; ++tap) {
+      const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+      bf16x8 w[3], d[NP][3];
+#pragma unroll
+      for (int e = 0; e < 3; ++e) w[e] = load(w_lane + tap * kTapBytes + e * kWBytes);
+#pragma unroll
+      for (int b = 0; b < NP; ++b)
+#pragma unroll
+        for (int e = 0; e < 3; ++e) d[b][e] = load(d_half + (base[b] + shift) * 16 + e * d_term);
+      // the products of 2^-18 and more of the largest; the three left out are below 2^-26 of it
+#pragma unroll
+      for (int e = 0; e < 6; ++e) {
+        constexpr int kW[6] = {0, 2, 1, 0, 1, 0}, kD[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], acc[b], 0, 0, 0);
       }
     }
   }

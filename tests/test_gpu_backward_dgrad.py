@@ -159,3 +159,22 @@ def test_planes_beyond_one_descriptor():
         size = torch.nn.functional.conv_transpose2d(part[None].abs(), wd.abs(), padding=2)[0]
         assert want.shape[1:] == (y1 - y0, x1 - x0)
         assert ((have[:, y0:y1, x0:x1].cpu().double() - want).abs() <= tol * size + 1e-12).all()
+
+
+@pytest.mark.parametrize("shift_g,shift_w", [(-118, 0), (-60, -62), (0, -118), (-95, 0)])
+def test_tiny_values_keep_their_digits(shift_g, shift_w):
+    # thirds of values below 2^-110 reach below the smallest subnormal bf16
+    B, Cin, Cout, H, W = 60, 40, 24, 16, 16
+    r = np.random.Generator(np.random.PCG64(7800))
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    g = np.ldexp(r.standard_normal((1, B, Cout, H, W)), shift_g).astype(np.float32)
+    g[0, B // 2:] *= np.float32(0.0)
+    w = np.ldexp(r.standard_normal((Cout, Cin, 3, 3)), shift_w).astype(np.float32)
+    x = torch.zeros((1, B, Cin, H, 1), dtype=torch.int32, device=DEV)
+    gd = torch.from_numpy(g).to(DEV)
+    got = api.tac_conv_lif_backward(desc, x, torch.from_numpy(w).to(DEV), torch.ones_like(gd), gd, grad_in_per_group=True)
+    gy, wd = got["grad_y"].cpu().double()[0], torch.from_numpy(w).double()
+    want, size = (torch.nn.functional.conv_transpose2d(a, b, padding=1) for a, b in ((gy, wd), (gy.abs(), wd.abs())))
+    # the bound of the other tests, and half of the smallest subnormal number for each rounding of a sum
+    tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
+    assert ((got["grad_in"].cpu().double().view_as(want) - want).abs() <= tol * size + 9 * Cout * 2.0 ** -150).all()
