@@ -265,9 +265,9 @@ int tac_stack_forward(const tac_stack_layer_t* layers, int32_t n_layers, const v
  * 128 input channels); packed input, as it is or with the max pool on load; grad_y 16-byte aligned):
  * dY_k, A_k and W enter them rounded to bfloat16, sums are fp32.  Everything else, and TAC_FP32, is
  * fp32 arithmetic (on the fp32 matrix cores, but for dL/dS of stride 2 layers and of few input channels over
- * many pixels and dW of one or two input channels; dL/dS of larger grids multiplies three bf16 parts of every value, whose sum it is, and
- * is nearer to the exact sum than products of fp32; 16 output channels among whose values are infinities, NaN or sets of eight
- * below 2^-90 are products of fp32).  The rounding inside a bf16 forward pass is differentiated as if it were not there. */
+ * many pixels and dW of one or two input channels; dL/dS of larger grids multiplies three bf16 parts of every value, whose sum it is,
+ * and is nearer to the exact sum than products of fp32 for any number of channels; 16 output channels among whose values are infinities,
+ * NaN or sets of eight below 2^-90 are products of fp32).  The rounding inside a bf16 forward pass is differentiated as if it were not there. */
 enum { TAC_SG_FAST_SIGMOID = 0, TAC_SG_ARCTAN = 1 };
 typedef struct tac_backward_desc {
   int32_t surrogate;      /* TAC_SG_FAST_SIGMOID / TAC_SG_ARCTAN                                */

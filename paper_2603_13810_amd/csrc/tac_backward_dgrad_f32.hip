@@ -4,9 +4,11 @@
 //
 // dgrad_f32_kernel: D[32 ci x 32 px] += W^T[32 ci x 16 co] . dY[16 co x 32 px].  v_mfma_f32_32x32x2_f32 takes 512 cycles for the 16 channels; here each fp32
 // value is three bf16 values whose sum it is, and six products of v_mfma_f32_32x32x16_bf16 (192 cycles) are all that reach 2^-26 of the largest.
-// Fewer roundings of the sums make the result more accurate than the products of fp32 were: 96 <- 128 at 64 x 40, B = 16, three groups 4.8e-7 of the norm
-// instead of 6.0e-7, and on 34 other layers 0.81 to 0.88 of the error.  A round with an infinity, a NaN, or values that the subnormal numbers cut (below 2^-90)
-// multiplies the values put together again on v_mfma_f32_32x32x2_f32.
+// The products of the first parts, once a tap and 16 channels, are one chain of sums; the five others, whose roundings are 2^-8 as large, are another, added at the end.
+// Few roundings at full size make the result more accurate than products of fp32 are, whatever the number of channels: 96 <- 128 at 64 x 40, B = 16, three
+// groups 2.2e-7 of the norm instead of 6.0e-7, 0.36 to 0.44 of the error on 30 layers of 8 to 128 output channels, 0.4 to 0.6 with 1 to 24 (in one chain
+// two output channels were off by twice as much as products of fp32).  A round with an infinity, a NaN, or values that the subnormal numbers cut (below 2^-90) multiplies the
+// values put together again on v_mfma_f32_32x32x2_f32.
 // Workgroup = 32 input channels x a tile of pixels (rows of one or, in small images, of several (group, sample) pairs); four waves share the pixels,
 // NP blocks of 32 each.  Sixteen output channels at a time go through LDS as thirds, [third][tap][half of the channels][ci] and [third][half][position];
 // the next sixteen are requested before the MFMAs.  Two or three workgroups share a compute unit, so that one's splitting (400 vector instructions a round
@@ -158,11 +160,11 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
       for (int m = 0; m < kM; ++m) dr[m][c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(own, (int)(off[m] + chan), 0, 0));
     }
   };
-  f32x16 acc[NP];
+  f32x16 acc[NP], small[NP];                             // the products of the first parts; the others, which start at 2^-8 of those
 #pragma unroll
   for (int b = 0; b < NP; ++b)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+    for (int r = 0; r < 16; ++r) acc[b][r] = small[b][r] = 0.f;
   const bool active = wx * NP * 32 < pairs * per_pair;   // wave-uniform
 
   int* const bad_round = reinterpret_cast<int*>(lds + q.off_bad);        // of this round and of the next
@@ -230,14 +232,20 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
         for (int e = 0; e < 3; ++e) d[b][e] = load(d_half + (base[b] + shift) * 16 + e * d_term);
       // the products of 2^-18 and more of the largest; the three left out are below 2^-26 of it
 #pragma unroll
-      for (int e = 0; e < 6; ++e) {
-        constexpr int kW[6] = {0, 2, 1, 0, 1, 0}, kD[6] = {2, 0, 1, 1, 0, 0};
+      for (int e = 0; e < 5; ++e) {
+        constexpr int kW[5] = {0, 2, 1, 0, 1}, kD[5] = {2, 0, 1, 1, 0};
 #pragma unroll
-        for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], acc[b], 0, 0, 0);
+        for (int b = 0; b < NP; ++b) small[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], small[b], 0, 0, 0);
       }
+#pragma unroll
+      for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], d[b][0], acc[b], 0, 0, 0);
     }
   }
   if (!active) return;
+#pragma unroll
+  for (int b = 0; b < NP; ++b)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[b][r] += small[b][r];
   // ---- register r of acc[b] on lane (n, h): input channel 8 (r / 4) + 4 h + r % 4 of the wave, pixel n of block b
   const int ci_w = ci0 + 4 * h;
 #pragma unroll

@@ -161,6 +161,33 @@ def test_planes_beyond_one_descriptor():
         assert ((have[:, y0:y1, x0:x1].cpu().double() - want).abs() <= tol * size + 1e-12).all()
 
 
+@pytest.mark.parametrize("Cout", [1, 2, 4, 8, 24])
+def test_few_output_channels_are_no_further_off_than_products_of_fp32(Cout):
+    # 400 tiles: products of bf16 thirds.  What products of fp32 leave is put together here, two output channels and a tap at a time, each sum rounded to fp32.
+    B, Cin, H, W = 100, 40, 28, 28
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(7700 + Cout)
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    g = torch.randn((1, B, Cout, H, W), generator=gen, device=DEV)
+    w = torch.randn((Cout, Cin, 3, 3), generator=gen, device=DEV) * 0.1
+    x = torch.zeros((1, B, Cin, H, 1), dtype=torch.int32, device=DEV)
+    got = api.tac_conv_lif_backward(desc, x, w, torch.ones_like(g), g, grad_in_per_group=True)
+    have = got["grad_in"].view(B, Cin, H * W)
+    gy, wd = torch.nn.functional.pad(got["grad_y"][0].double(), (1, 1, 1, 1)), w.double()
+    want = torch.zeros((B, Cin, H * W), dtype=torch.float64, device=DEV)
+    fp32 = torch.zeros((B, Cin, H * W), device=DEV)
+    for co in range(0, Cout, 2):
+        for tap in range(9):
+            ky, kx = 2 - tap // 3, 2 - tap % 3
+            seen = gy[:, co:co + 2, ky:ky + H, kx:kx + W]
+            add = (wd[co:co + 2, None, :, tap // 3, tap % 3, None] * seen.reshape(B, -1, 1, H * W).transpose(0, 1)).sum(0)
+            want += add
+            fp32 = (fp32.double() + add).float()
+    err, err32 = (have.double() - want).norm(), (fp32.double() - want).norm()
+    print("Cout", Cout, "error", float(err / want.norm()), "of products of fp32", float(err32 / want.norm()))
+    assert err <= err32
+
+
 @pytest.mark.parametrize("shift_g,shift_w", [(-118, 0), (-60, -62), (0, -118), (-95, 0)])
 def test_tiny_values_keep_their_digits(shift_g, shift_w):
     # thirds of values below 2^-110 reach below the smallest subnormal bf16
