@@ -20,7 +20,7 @@
 //   2 -> 64 stride 2, 8 groups at 128 x 128, B = 32     255 2.5e-7   240 2.0e-7
 //   1 -> 16, one group at 100 x 100, B = 128            128 2.7e-7    64 1.6e-7
 //   1 -> 64, 32 steps at 128 x 128, B = 48             5830 3.0e-7  4830 1.6e-7
-// Of 60 random first layers the median is 1.2 times as fast, the slowest 0.97; of 45 small ones (7 to 90 us) the slowest is 0.89 (26.4 us against 23.5: 2 -> 48 at 19 x 31, B = 16).
+// The kernel alone on 287 random first layers that it takes: 1.35 times as fast as that kernel at the median, twelve slower than 0.96 (from 0.80: 19.3 us against 15.5).
 #include "tac_wgrad_first_plan.h"
 
 namespace tac {
@@ -241,8 +241,8 @@ __global__ __launch_bounds__(kThreads, 4) void wgrad_first_kernel(const Backward
           for (int u = 0; u < 4; ++u)
 #pragma unroll
             for (int kx = 0; kx < 3; ++kx) {
-              // an infinite frame value is not multiplied by the zero of a pixel that is not there
-              const float v = DENSE && !VEC && u > 0 ? (u < real ? a[u * S + kx] : 0.f) : a[u * S + kx];
+              // An infinite frame value is not multiplied by the zero of a pixel that is not there: only the first such pixel's left column is in the image.
+              const float v = DENSE && !VEC && u > 0 && kx == 0 ? (u < real ? a[u * S] : 0.f) : a[u * S + kx];
 #pragma unroll
               for (int c = 0; c < CPW; ++c) acc[(c * CIN + i) * 9 + ky * 3 + kx] = fmaf(g[c][u], v, acc[(c * CIN + i) * 9 + ky * 3 + kx]);
             }
