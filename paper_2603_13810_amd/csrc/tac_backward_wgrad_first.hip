@@ -20,7 +20,7 @@
 //   2 -> 64 stride 2, 8 groups at 128 x 128, B = 32     255 2.5e-7   240 2.0e-7
 //   1 -> 16, one group at 100 x 100, B = 128            128 2.7e-7    64 1.6e-7
 //   1 -> 64, 32 steps at 128 x 128, B = 48             5830 3.0e-7  4830 1.6e-7
-// The kernel alone on 287 random first layers that it takes: 1.35 times as fast as that kernel at the median, twelve slower than 0.96 (from 0.80: 19.3 us against 15.5).
+// The kernel alone on 271 random first layers that it takes: 1.36 times as fast as that kernel at the median, eight slower (from 0.83: 10.5 us against 8.7).
 #include "tac_wgrad_first_plan.h"
 
 namespace tac {

@@ -53,6 +53,11 @@ inline bool first_wgrad_plan(const BackwardParams& p, FirstWgradPlan& q) {
   // few workgroups of real-valued frames have a long chain of loads each (2 -> 56 at 31 x 26, B = 2, three groups of 8 on 24 workgroups: 15.4 us, 9.4 on the other
   // kernel; of 25 layers below this line 3 lost more than 5% by it)
   if (p.dense && q.co_groups * q.split < 128) return false;
+  // Few workgroups of one item each wait for its aggregates, a trip to memory for every four frames and turn of the threads: 2 -> 117 stride 2 at 55 x 68, B = 3,
+  // groups of 16 on 48 workgroups of 12 trips 19.3 us, 15.5 on the other kernel; of 207 layers 16 are below this line, nine of them slower on this kernel (0.80 to 0.99 of the
+  // speed) and seven faster (1.03 to 1.28).
+  const int lines = q.n_pairs * p.Cin * ((q.rows - 1) * S + 3), trips = (lines * (q.cw / 8) + kFirstWgradThreads - 1) / kFirstWgradThreads * ((p.K + 3) / 4);
+  if (!p.dense && p.Cin == 2 && q.co_groups * q.split < 64 && (long long)q.pair_tiles * q.n_strips <= q.split && trips >= 3) return false;
   // four products a quad and turn of the lanes
   q.flush = std::max(1, kFirstWgradChain / (4 * ((q.n_pairs * q.rows * q.quads + lanes - 1) / lanes)));
   q.rows_in = (q.rows - 1) * S + 3;

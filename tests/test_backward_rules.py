@@ -6,7 +6,7 @@ import subprocess
 import pytest
 
 from paper_2603_13810_amd import api, build
-from test_gpu_backward_wgrad import FIRST, FIRST_TAKEN, INFINITE, REAL
+from test_gpu_backward_wgrad import BITS, FIRST, FIRST_TAKEN, INFINITE, REAL
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -50,3 +50,11 @@ def test_first_layers_take_the_kernel_they_are_there_for(rules):
     assert [_first(rules, *case) is not None for case in FIRST] == FIRST_TAKEN
     B, Cin, Cout, H, W = INFINITE
     assert _first(rules, B, Cin, Cout, H, W, 1, REAL, 1, 1) and W % 4
+
+
+# two input channels, bits, few workgroups of one item each: the frames of a group and the turns of the threads that build its aggregates
+@pytest.mark.parametrize("case,taken", [((3, 2, 117, 55, 68, 2, BITS, 16, 19), False), ((2, 2, 20, 67, 66, 2, BITS, 8, 15), False), ((2, 2, 118, 48, 66, 2, BITS, 8, 9), False),
+                                        ((2, 2, 101, 46, 50, 2, BITS, 4, 4), True), ((3, 1, 117, 55, 68, 2, BITS, 16, 19), True),
+                                        ((8, 2, 117, 55, 68, 2, BITS, 16, 19), True), ((16, 2, 52, 51, 57, 2, BITS, 16, 16), True)])
+def test_small_first_layers(rules, case, taken):
+    assert (_first(rules, *case) is not None) == taken

@@ -121,10 +121,12 @@ FIRST = [
     (1, 1, 4, 1, 1, 1, BITS, 1, 1), (2, 2, 300, 6, 12, 1, REAL, 16, 17),
     # real-valued frames on 128 workgroups and more
     (24, 2, 64, 33, 31, 1, REAL, 2, 5), (40, 1, 128, 40, 24, 2, REAL, 4, 6), (60, 2, 96, 7, 9, 1, REAL, 1, 3),
+    # bits of two input channels on 64 workgroups and more (those of 2 -> 16 stride 2 are fewer)
+    (16, 2, 52, 51, 57, 2, BITS, 16, 17),
 ]
 
 # which of them run on the first layers' kernel (the choice is held to this on the CPU)
-FIRST_TAKEN = [True, True, True, True, False, False, False, True, True, False, True, True, True]
+FIRST_TAKEN = [True, True, True, False, False, False, False, True, True, False, True, True, True, True]
 
 
 @pytest.mark.parametrize("case", FIRST, ids=["%d_to_%d_%dx%d_s%d_f%d" % c[1:7] for c in FIRST])
