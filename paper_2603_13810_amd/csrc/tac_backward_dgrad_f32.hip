@@ -19,25 +19,16 @@
 // Few pixels (small images, small batches) leave that kernel with a few dozen workgroups that go through Cout / 16 rounds of two barriers
 // each.  dgrad_f32_split_kernel shares a workgroup's 32 input channels x NP blocks of 32 pixels among four waves by output channel, in products of fp32:
 // 32 of them a round, four times the workgroups, and the waves' sums meet in LDS at the end.
-#include <algorithm>
-#include "tac_mfma_common.h"
+#include "tac_dgrad_plan.h"
 
 namespace tac {
 
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kCo = 16;           // output channels per round
-constexpr int kM = 2;             // dY values per thread and channel
+constexpr int kThreads = kDgradThreads;
+constexpr int kCo = kDgradCo;
+constexpr int kM = kDgradM;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-struct DgradPlan {
-  int rows, xw, n_pairs;          // a tile: rows x columns of n_pairs (group, sample) pairs
-  int n_strips, n_segs, pair_tiles, ci_groups;
-  int px, pl, cw;                 // pixels of a tile, dwords per channel of dY in LDS (with border), per row
-  int vec_w;                      // the weights can be read 16 bytes at a time
-  int off_dy, off_bad, total;
-};
 
 __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
@@ -293,8 +284,6 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
   }
 }
 
-constexpr int kSplitCo = 32;      // output channels per round, eight for each of the four waves
-constexpr int kSplitPl = 112;     // dwords of dY per channel at most
 template <int NP>
 __global__ __launch_bounds__(kThreads, 2) void dgrad_f32_split_kernel(const BackwardParams p, const DgradPlan q) {
   constexpr int kRow = 288, NW = kSplitCo * kRow / 4 / kThreads, ND = kSplitCo * kSplitPl / kThreads;
@@ -447,51 +436,6 @@ __global__ __launch_bounds__(kThreads, 2) void dgrad_f32_split_kernel(const Back
   }
 }
 
-// Tiles of 32 * wi input channels and up to `blocks` blocks of 32 pixels with up to pl_max positions of dY
-bool dgrad_f32_tile(const BackwardParams& p, int wi, int blocks, int pl_max, DgradPlan& q) {
-  const int px_max = blocks * 32;
-  q.xw = std::min(p.W, std::min(64, px_max));
-  q.n_segs = (p.W + q.xw - 1) / q.xw;
-  q.cw = q.xw + 2;
-  for (q.rows = std::min(p.H, px_max / q.xw); q.rows >= 1; --q.rows)
-    if ((q.rows + 2) * q.cw <= pl_max) break;
-  if (q.rows < 1) return false;
-  q.n_strips = (p.H + q.rows - 1) / q.rows;
-  q.rows = (p.H + q.n_strips - 1) / q.n_strips;
-  q.n_pairs = 1;
-  // several (group, sample) pairs while they fit the tile, with byte offsets below 2^30 between them
-  if (q.n_strips == 1 && q.n_segs == 1)
-    while (q.n_pairs * 2 * q.rows * q.xw <= px_max && q.n_pairs * 2 * (q.rows + 2) * q.cw <= pl_max &&
-           (long long)q.n_pairs * 2 * p.Cout * p.H * p.W < (1ll << 28))
-      q.n_pairs *= 2;
-  q.pair_tiles = (p.G * p.B + q.n_pairs - 1) / q.n_pairs;
-  q.ci_groups = (p.Cin + 32 * wi - 1) / (32 * wi);
-  q.px = q.n_pairs * q.rows * q.xw;
-  q.pl = q.n_pairs * (q.rows + 2) * q.cw;
-  return true;
-}
-long long dgrad_f32_tiles(const DgradPlan& q) { return (long long)q.pair_tiles * q.n_strips * q.n_segs * q.ci_groups; }
-
-// Whether four waves share the output channels of one block of pixels: on few tiles, whose four chains of sums are also the more accurate ones (128 -> 128 at 8 x 8:
-// 2.9e-7 of the norm against 4.4e-7).  The line is where that kernel met one of tiles of up to 512 pixels with chains of fp32 products.
-bool dgrad_f32_splits(const BackwardParams& p, DgradPlan& q) {
-  if (!dgrad_f32_tile(p, 1, 1, kSplitPl, q)) return false;
-  const long long tiles = dgrad_f32_tiles(q);
-  if (tiles > 512) return false;
-  const double cost = ((p.Cout + kSplitCo - 1) / kSplitCo) * (tiles > 256 ? 1.7 : 1.15) * (36 * 64 + 3000.0) + 4600.0;
-  const int wi = p.Cin > 64 ? 4 : p.Cin > 32 ? 2 : 1;
-  bool better = true;
-  for (int n : {4, 2, 1}) {
-    DgradPlan c{};
-    if (dgrad_f32_tile(p, wi, 4 / wi * n, kM * kThreads, c))
-      better &= cost < (double)((dgrad_f32_tiles(c) + 255) / 256) * ((p.Cout + 7) / 8) * (n * 36 * 64 + 1800.0);
-  }
-  q.vec_w = p.Cin % 4 == 0 && ((uintptr_t)p.w & 15u) == 0;
-  q.off_dy = kSplitCo * 288 * 4;
-  q.total = std::max(q.off_dy + kSplitCo * q.pl * 4, 16384);
-  return better;
-}
-
 }  // namespace
 
 hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
@@ -506,18 +450,12 @@ hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), q.total, s, p, q);
     return hipGetLastError();
   };
-  if (dgrad_f32_splits(p, q)) return launch(&dgrad_f32_split_kernel<1>);
-  // Cycles of a round, fitted: a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several (7850, 4000)
   int np = 0;
-  double best = 0.0;
-  for (int n : {2, 1}) {
-    DgradPlan c{};
-    if (!dgrad_f32_tile(p, 1, 4 * n, kM * kThreads, c)) continue;
-    const double per_cu = (double)((dgrad_f32_tiles(c) + 255) / 256), cost = std::max(n == 2 ? 10700.0 : 7500.0, per_cu * (n == 2 ? 7850.0 : 4000.0));
-    if (np && cost >= best) continue;
-    np = n;
-    best = cost;
-    q = c;
+  if (dgrad_f32_choose(p, q, np)) {
+    q.vec_w = p.Cin % 4 == 0 && ((uintptr_t)p.w & 15u) == 0;
+    q.off_dy = kSplitCo * 288 * 4;
+    q.total = std::max(q.off_dy + kSplitCo * q.pl * 4, 16384);
+    return launch(&dgrad_f32_split_kernel<1>);
   }
   if (!np) return hipErrorInvalidValue;
   q.off_dy = 3 * kWBytes;

@@ -1,0 +1,87 @@
+// Host rules of the input gradient's fp32 kernels (tac_backward_dgrad_f32.hip; dgrad_kernel in tac_backward.hip).
+#pragma once
+#include <algorithm>
+#include "tac_mfma_common.h"
+
+namespace tac {
+
+constexpr int kDgradThreads = 256;
+constexpr int kDgradCo = 16;      // output channels per round
+constexpr int kDgradM = 2;        // dY values per thread and channel
+constexpr int kSplitCo = 32;      // output channels per round of the kernel whose waves share them, eight for each of the four
+constexpr int kSplitPl = 112;     // dwords of dY per channel at most
+
+struct DgradPlan {
+  int rows, xw, n_pairs;          // a tile: rows x columns of n_pairs (group, sample) pairs
+  int n_strips, n_segs, pair_tiles, ci_groups;
+  int px, pl, cw;                 // pixels of a tile, dwords per channel of dY in LDS (with border), per row
+  int vec_w;                      // the weights can be read 16 bytes at a time
+  int off_dy, off_bad, total;
+};
+
+// Tiles of 32 input channels and up to `blocks` blocks of 32 pixels with up to pl_max positions of dY
+inline bool dgrad_f32_tile(const BackwardParams& p, int blocks, int pl_max, DgradPlan& q) {
+  const int px_max = blocks * 32;
+  q.xw = std::min(p.W, std::min(64, px_max));
+  q.n_segs = (p.W + q.xw - 1) / q.xw;
+  q.cw = q.xw + 2;
+  for (q.rows = std::min(p.H, px_max / q.xw); q.rows >= 1; --q.rows)
+    if ((q.rows + 2) * q.cw <= pl_max) break;
+  if (q.rows < 1) return false;
+  q.n_strips = (p.H + q.rows - 1) / q.rows;
+  q.rows = (p.H + q.n_strips - 1) / q.n_strips;
+  q.n_pairs = 1;
+  // several (group, sample) pairs while they fit the tile, with byte offsets below 2^30 between them
+  if (q.n_strips == 1 && q.n_segs == 1)
+    while (q.n_pairs * 2 * q.rows * q.xw <= px_max && q.n_pairs * 2 * (q.rows + 2) * q.cw <= pl_max &&
+           (long long)q.n_pairs * 2 * p.Cout * p.H * p.W < (1ll << 28))
+      q.n_pairs *= 2;
+  q.pair_tiles = (p.G * p.B + q.n_pairs - 1) / q.n_pairs;
+  q.ci_groups = (p.Cin + 31) / 32;
+  q.px = q.n_pairs * q.rows * q.xw;
+  q.pl = q.n_pairs * (q.rows + 2) * q.cw;
+  return true;
+}
+inline long long dgrad_f32_tiles(const DgradPlan& q) { return (long long)q.pair_tiles * q.n_strips * q.n_segs * q.ci_groups; }
+
+
+// Microseconds of the kernels, fitted to 450 random layers (1 to 128 channels on either side, 3 x 3 to 64 x 72 pixels, 1 to 768 pairs) to 6 or 7% rms, and 9% for
+// the vector kernel.
+// Rounds of 16 output channels (cycles at 2.5 GHz): a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several
+// (7850, 4000); the stores.
+inline double dgrad_thirds_us(const DgradPlan& q, int np, const BackwardParams& p) {
+  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256), cycles = std::max(np == 2 ? 10700.0 : 7500.0, per_cu * (np == 2 ? 7850.0 : 4000.0));
+  return 2.4 + (p.Cout + kDgradCo - 1) / kDgradCo * cycles / 2500.0 + 0.9 * per_cu * np;
+}
+// Rounds of 32 output channels in products of fp32
+inline double dgrad_split_us(const DgradPlan& q, const BackwardParams& p) {
+  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
+  return 2.6 + (p.Cout + kSplitCo - 1) / kSplitCo * 3.55 * std::max(1.0, 0.64 * per_cu) + 2.7 * per_cu;
+}
+// A thread's chain over the output channels, or the pixels at the rate they go through; the stores
+inline double dgrad_vector_us(const BackwardParams& p) {
+  const double pairs = (double)p.G * p.B, pixels = (double)p.H * p.W, blocks = (double)(((int64_t)p.H * p.W + 255) / 256 * 256);
+  return 3.4 + p.Cout * (0.34 + 0.054 * std::min(p.Cin, 4) + (p.Cin + 3) / 4 * pairs * blocks * 1.465e-6) + p.Cin * pairs * pixels * 3.4e-6;
+}
+
+// np: blocks of 32 pixels a wave (0: no tile).  True: dgrad_f32_split_kernel, whose four waves share the output channels of one block of pixels, for few tiles: of the 450
+// layers 46 (128 -> 128 at 8 x 8, B = 16, one group 17.4 us, 28.1 on the other kernel; 16 -> 48 at 31 x 32, 16 pairs on 496 tiles 17.5 / 12.0: that one's).
+inline bool dgrad_f32_choose(const BackwardParams& p, DgradPlan& q, int& np) {
+  np = 0;
+  double best = 0.0;
+  for (int n : {2, 1}) {
+    DgradPlan c{};
+    if (!dgrad_f32_tile(p, 4 * n, kDgradM * kDgradThreads, c)) continue;
+    const double us = dgrad_thirds_us(c, n, p);
+    if (np && us >= best) continue;
+    np = n;
+    best = us;
+    q = c;
+  }
+  DgradPlan c{};
+  if (!np || !dgrad_f32_tile(p, 1, kSplitPl, c) || dgrad_f32_tiles(c) > 512 || dgrad_split_us(c, p) >= best) return false;
+  q = c;
+  return true;
+}
+
+}  // namespace tac

@@ -1,4 +1,5 @@
 // The host rules of the backward launch that choose between kernels, for the tests that hold them to what they are there for.
+#include "tac_dgrad_plan.h"
 #include "tac_wgrad_first_plan.h"
 
 extern "C" int clear_in_recurrence(long long threads, long long floats) { return tac::backward_clear_in_recurrence((size_t)threads, (size_t)floats); }
@@ -7,6 +8,15 @@ extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int H, int 
   tac::BackwardParams p{};
   p.G = G; p.B = B; p.Cin = Cin; p.H = H; p.W = W; p.stride = stride;
   return tac::backward_dgrad_f32_supported(p);
+}
+
+// Whether the four waves of a workgroup share the output channels (where the input gradient is formed on the matrix cores)
+extern "C" int input_gradient_splits(int G, int B, int Cin, int Cout, int H, int W) {
+  tac::BackwardParams p{};
+  p.G = G; p.B = B; p.Cin = Cin; p.Cout = Cout; p.H = H; p.W = W; p.stride = 1;
+  tac::DgradPlan q{};
+  int np = 0;
+  return tac::dgrad_f32_choose(p, q, np);
 }
 
 // out: groups of channels per workgroup, channel groups, slices, pairs per item, rows per item, strips, pair tiles, bytes of LDS.  0: not that kernel's layer.

@@ -37,6 +37,14 @@ def test_input_gradient_kernel(rules, case):
     assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, hw, hw, stride)) == matrix
 
 
+# (pairs, Cin, Cout, H, W, whether four waves share the output channels): the faster side as measured, 1.2 times and more apart
+@pytest.mark.parametrize("case", [(16, 128, 128, 8, 8, True), (30, 64, 64, 8, 8, True), (24, 10, 32, 9, 44, False), (16, 16, 48, 31, 32, False),
+                                  (2, 40, 48, 63, 41, False), (6, 2, 48, 64, 27, False), (64, 128, 16, 8, 8, False), (8, 1, 16, 28, 28, False), (20, 12, 64, 12, 55, False)])
+def test_which_input_gradients_share_output_channels(rules, case):
+    pairs, Cin, Cout, H, W, splits = case
+    assert bool(rules.input_gradient_splits(1, pairs, Cin, Cout, H, W)) == splits
+
+
 PLAN = ("ncg", "co_groups", "split", "n_pairs", "rows", "n_strips", "pair_tiles", "lds")
 
 
