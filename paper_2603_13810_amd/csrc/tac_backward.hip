@@ -6,7 +6,7 @@
 //   lif_backward_kernel  dL/dY_k from dL/ds and the membranes the forward pass recorded
 //   dgrad_kernel         dL/dS_{kK+j} = beta^(Kg-1-j) * (dY_k convolved back through W): fp32 vector arithmetic, any shape (stride 2, few input channels)
 // and the choice among the matrix-core kernels of the other files.
-#include "tac_internal.h"
+#include "tac_dgrad_plan.h"
 
 namespace tac {
 

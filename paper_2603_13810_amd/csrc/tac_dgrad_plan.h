@@ -84,4 +84,21 @@ inline bool dgrad_f32_choose(const BackwardParams& p, DgradPlan& q, int& np) {
   return true;
 }
 
+// Which kernel forms an input gradient that is not the bf16 kernels': the matrix-core ones (true) take stride 1 and fill blocks of 32 input channels; the vector kernel takes
+// any layer, four input channels per thread, and is the faster one for few input channels over many pixels, by both estimates (us on the vector kernel and on the other:
+// 1 -> 64 at 64 x 64, B = 64, 8 groups 261 / 480, 4 -> 64 314 / 454, 8 -> 64 549 / 439; 1 -> 64 at 28 x 28, B = 64, 2 groups 34.6 / 28.1, 1 -> 8 7.6 / 10.0).  Its
+// chains of products are less accurate than thirds.  So it takes no layer for which it would not be the faster one even against 32 input channels in products of fp32 (per output
+// channel 0.23 us and the pixels at 0.184e6 a us, against 0.35 .. 0.63 and 0.55e6 for four), where thirds would be slower only with one to eight output channels (2 -> 1 at 35 x 31, 64
+// pairs 8.3 us, 4.4 there).
+inline bool backward_dgrad_f32_supported(const BackwardParams& p) {
+  if (p.stride != 1) return false;
+  if (p.Cin >= (1 << 20)) return false;                  // 30-bit byte offsets within the weights of 16 output channels
+  const double pairs = (double)p.G * p.B, pixels = (double)p.H * p.W;
+  const double by_vectors = 0.35 + 0.07 * std::min(p.Cin, 4) + (p.Cin + 3) / 4 * pairs * (double)(((int64_t)p.H * p.W + 255) / 256 * 256) / 0.55e6;
+  if (0.23 + (p.Cin + 31) / 32 * pairs * pixels / 0.184e6 <= by_vectors) return true;
+  DgradPlan q{};
+  int np = 0;
+  return dgrad_f32_choose(p, q, np) || !np || dgrad_thirds_us(q, np, p) <= dgrad_vector_us(p);
+}
+
 }  // namespace tac

@@ -130,20 +130,6 @@ bool backward_wgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_wgrad_mfma_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_tile_supported(const BackwardParams& p);     // wide tiles (128 input channels), grad_w as scratch
 hipError_t backward_dgrad_tile_launch(const BackwardParams& p, hipStream_t s);
-// Which fp32 kernel forms an input gradient.  The matrix-core kernel takes stride 1 and fills blocks of 32 input channels; the vector
-// kernel takes any layer, four input channels per thread, and is the faster one for few input channels over many pixels.  Estimated
-// us per output channel, of both: what a thread or a workgroup waits for, and the pixels at the rate they go through
-// (1 -> 64 at 64 x 64, B = 64, 8 groups: 240 us by the vector kernel, 726 on the matrix cores; 4 -> 64 303 / 719; 8 -> 64 542 / 716;
-// 16 -> 64 1040 / 737; 4 -> 64 at 28 x 28, B = 64, 2 groups 64 / 50).
-inline bool backward_dgrad_f32_supported(const BackwardParams& p) {
-  if (p.stride != 1) return false;
-  if (p.Cin >= (1 << 20)) return false;                  // 30-bit byte offsets within the weights of 16 output channels
-  const double pairs = (double)p.G * p.B, pixels = (double)p.H * p.W;
-  const int fours = (p.Cin + 3) / 4;
-  const double by_vectors = 0.35 + 0.07 * (p.Cin < 4 ? p.Cin : 4) + fours * pairs * (double)(((int64_t)p.H * p.W + 255) / 256 * 256) / 0.55e6;
-  const double by_matrices = 0.23 + (p.Cin + 31) / 32 * pairs * pixels / 0.184e6;
-  return by_matrices <= by_vectors;
-}
 hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s);
 bool backward_dgrad_mfma_supported(const BackwardParams& p);
 hipError_t backward_dgrad_mfma_launch(const BackwardParams& p, hipStream_t s);

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from paper_2603_13810_amd import api, build
+from test_gpu_backward_dgrad import CASES, VECTOR
 from test_gpu_backward_wgrad import BITS, FIRST, FIRST_TAKEN, INFINITE, REAL
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -27,14 +28,20 @@ def test_a_large_weight_gradient_is_not_cleared_by_a_handful_of_threads(rules, n
     assert bool(rules.clear_in_recurrence(threads, floats)) == aside
 
 
-# (groups, B, Cin, H = W, stride, on the matrix cores): the faster side as measured, 1.2 times and more apart
-@pytest.mark.parametrize("case", [(8, 64, 1, 64, 1, False), (8, 64, 4, 64, 1, False), (8, 64, 8, 64, 1, False), (8, 64, 16, 64, 1, True),
-                                  (12, 128, 1, 28, 1, False), (4, 4, 3, 200, 1, False), (2, 64, 1, 28, 1, False), (2, 64, 4, 28, 1, True),
-                                  (2, 64, 8, 28, 1, True), (2, 4, 1, 28, 1, True), (2, 64, 2, 7, 1, True), (7, 128, 32, 14, 1, True),
-                                  (4, 16, 128, 8, 1, True), (4, 16, 128, 8, 2, False)])
+# (groups, B, Cin, Cout, H = W, stride, on the matrix cores): the faster side as measured, 1.2 times and more apart
+@pytest.mark.parametrize("case", [(8, 64, 1, 64, 64, 1, False), (8, 64, 4, 64, 64, 1, False), (8, 64, 8, 64, 64, 1, True), (8, 64, 8, 8, 64, 1, False),
+                                  (8, 64, 16, 64, 64, 1, True), (12, 128, 1, 64, 28, 1, False), (12, 128, 1, 8, 28, 1, False), (4, 4, 3, 64, 200, 1, False),
+                                  (4, 4, 3, 16, 200, 1, False), (2, 64, 1, 64, 28, 1, True), (2, 64, 1, 8, 28, 1, False), (2, 64, 4, 64, 28, 1, True), (2, 64, 8, 64, 28, 1, True), (2, 4, 1, 64, 28, 1, True),
+                                  (2, 64, 2, 64, 7, 1, True), (7, 128, 32, 64, 14, 1, True), (4, 16, 128, 64, 8, 1, True), (4, 16, 128, 64, 8, 2, False)])
 def test_input_gradient_kernel(rules, case):
-    G, B, Cin, hw, stride, matrix = case
-    assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, hw, hw, stride)) == matrix
+    G, B, Cin, Cout, hw, stride, matrix = case
+    assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, Cout, hw, hw, stride)) == matrix
+
+
+def test_the_vector_kernel_has_its_cases(rules):
+    for case in CASES:
+        B, Cin, Cout, H, W, _, _, K, T = case
+        assert bool(rules.input_gradient_on_matrix_cores((T + K - 1) // K, B, Cin, Cout, H, W, 1)) == (case not in VECTOR)
 
 
 # (pairs, Cin, Cout, H, W, whether four waves share the output channels): the faster side as measured, 1.2 times and more apart

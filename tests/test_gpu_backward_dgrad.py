@@ -26,6 +26,7 @@ CASES = [
     (40, 3, 5, 30, 40, MAX, False, 2, 5),
     (30, 7, 3, 66, 80, MEAN, False, 1, 2),
 ]
+VECTOR = CASES[8:]        # (the choice is held to this on the CPU)
 
 
 @pytest.mark.parametrize("case", CASES, ids=["%d_to_%d_%dx%d_f%d" % c[1:6] for c in CASES])
