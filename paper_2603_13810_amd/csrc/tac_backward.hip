@@ -288,9 +288,16 @@ __global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const Bac
 // dY_k[co][y][x] W[co][ci][ky][kx] over the outputs (y, x) whose window covers the pixel, then
 // writes the gradient of each of the group's frames, dA scaled by the frame's weight.
 __global__ __launch_bounds__(kThreads) void dgrad_kernel(const BackwardParams p) {
-  const int ci0 = blockIdx.y * kCiTile;
+  // input channels in y, and beyond what a grid has there in x behind the pixels (one after the other in a loop, the stores would keep the weights out of scalar loads: 2.4 times the time)
+  uint32_t block = blockIdx.x, over = 0;
+  if (p.Cin > 65535 * kCiTile) {
+    const uint32_t blocks = ((uint32_t)(p.H * p.W) + kThreads - 1) / kThreads;
+    over = block / blocks;
+    block -= over * blocks;
+  }
+  const int ci0 = (int)((over * gridDim.y + blockIdx.y) * kCiTile);
   const int b = blockIdx.z % p.B, k = blockIdx.z / p.B;
-  const int px = blockIdx.x * kThreads + threadIdx.x;
+  const int px = (int)(block * kThreads + threadIdx.x);
   if (px >= p.H * p.W) return;
   const int iy = px / p.W, ix = px - iy * p.W;
   const size_t plane = (size_t)p.Ho * p.Wo;
@@ -408,7 +415,9 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
   } else if (p.grad_in && backward_dgrad_f32_supported(p)) {
     e = backward_dgrad_f32_launch(p, s);
   } else if (p.grad_in) {
-    const dim3 grid((p.H * p.W + kThreads - 1) / kThreads, (p.Cin + kCiTile - 1) / kCiTile, p.G * p.B);
+    unsigned across, over;
+    dgrad_vector_tiles(p.Cin, across, over);
+    const dim3 grid((p.H * p.W + kThreads - 1) / kThreads * over, across, p.G * p.B);
     hipLaunchKernelGGL(dgrad_kernel, grid, dim3(kThreads), 0, s, p);
     e = hipGetLastError();
   }

@@ -84,6 +84,13 @@ inline bool dgrad_f32_choose(const BackwardParams& p, DgradPlan& q, int& np) {
   return true;
 }
 
+// Tiles of four input channels of the vector kernel: `across` in y, where a grid has at most 65535 workgroups, `over` times.
+inline void dgrad_vector_tiles(int Cin, unsigned& across, unsigned& over) {
+  const long long tiles = ((long long)Cin + 3) / 4;
+  over = (unsigned)((tiles + 65534) / 65535);
+  across = (unsigned)((tiles + over - 1) / over);
+}
+
 // Which kernel forms an input gradient that is not the bf16 kernels': the matrix-core ones (true) take stride 1 and fill blocks of 32 input channels; the vector kernel takes
 // any layer, four input channels per thread, and is the faster one for few input channels over many pixels, by both estimates (us on the vector kernel and on the other:
 // 1 -> 64 at 64 x 64, B = 64, 8 groups 261 / 480, 4 -> 64 314 / 454, 8 -> 64 549 / 439; 1 -> 64 at 28 x 28, B = 64, 2 groups 34.6 / 28.1, 1 -> 8 7.6 / 10.0).  Its

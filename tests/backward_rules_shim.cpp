@@ -10,6 +10,8 @@ extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int Cout, i
   return tac::backward_dgrad_f32_supported(p);
 }
 
+extern "C" void vector_kernel_tiles(int Cin, unsigned* out) { tac::dgrad_vector_tiles(Cin, out[0], out[1]); }
+
 // Whether the four waves of a workgroup share the output channels (where the input gradient is formed on the matrix cores)
 extern "C" int input_gradient_splits(int G, int B, int Cin, int Cout, int H, int W) {
   tac::BackwardParams p{};

@@ -44,6 +44,13 @@ def test_the_vector_kernel_has_its_cases(rules):
         assert bool(rules.input_gradient_on_matrix_cores((T + K - 1) // K, B, Cin, Cout, H, W, 1)) == (case not in VECTOR)
 
 
+def test_the_vector_kernel_stays_within_a_grid(rules):
+    for Cin in (1, 4, 5, 262139, 262140, 262141, 1 << 20, 2 ** 31 - 1):
+        out = (ctypes.c_uint * 2)()
+        rules.vector_kernel_tiles(Cin, out)
+        assert out[0] <= 65535 and (out[1] - 1) * out[0] * 4 < Cin <= out[0] * out[1] * 4
+
+
 # (pairs, Cin, Cout, H, W, whether four waves share the output channels): the faster side as measured, 1.2 times and more apart
 @pytest.mark.parametrize("case", [(16, 128, 128, 8, 8, True), (30, 64, 64, 8, 8, True), (24, 10, 32, 9, 44, False), (16, 16, 48, 31, 32, False),
                                   (2, 40, 48, 63, 41, False), (6, 2, 48, 64, 27, False), (64, 128, 16, 8, 8, False), (8, 1, 16, 28, 28, False), (20, 12, 64, 12, 55, False)])

@@ -206,3 +206,23 @@ def test_tiny_values_keep_their_digits(shift_g, shift_w):
     # the bound of the other tests, and half of the smallest subnormal number for each rounding of a sum
     tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
     assert ((got["grad_in"].cpu().double().view_as(want) - want).abs() <= tol * size + 9 * Cout * 2.0 ** -150).all()
+
+
+@pytest.mark.parametrize("Cin,fmt,per_group", [((1 << 20) + 5, BITS, False), (1 << 20, BITS, True), ((1 << 20) + 2, MEAN, False)])
+def test_more_input_channels_than_a_grid_has_rows_for(Cin, fmt, per_group):
+    # the vector kernel's channels go on in x
+    B, Cout, H, W, T = 1, 2, 2, 2, 1
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(79)
+    desc = api.make_desc(T, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP, in_format=fmt)
+    f = 1 if fmt == BITS else 2
+    g = torch.randn((T, B, Cout, H, W), generator=gen, device=DEV)
+    w = torch.randn((Cout, Cin, 3, 3), generator=gen, device=DEV) * 0.1
+    x = torch.zeros((T, B, Cin, f * H, 1), dtype=torch.int32, device=DEV)
+    got = api.tac_conv_lif_backward(desc, x, w, torch.ones_like(g), g, grad_in_per_group=per_group)
+    gy, wd = got["grad_y"][0].cpu().double(), w.cpu().double()
+    want, size = (torch.nn.functional.conv_transpose2d(a, b, padding=1).view(Cin, H, W) for a, b in ((gy, wd), (gy.abs(), wd.abs())))
+    if fmt == MEAN:
+        want, size = (0.25 * a.repeat_interleave(2, 1).repeat_interleave(2, 2) for a in (want, size))
+    tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
+    assert ((got["grad_in"].cpu().double().view_as(want) - want).abs() <= tol * size + 1e-12).all()
