@@ -75,8 +75,8 @@ hipError_t mfma_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_
   return hipGetLastError();
 }
 
-// Whether the row kernel takes a layer, and how.  Choosing costs up to 40 us; the geometries a thread has asked for lately are remembered, in sets of four so that
-// the layers of a network do not turn each other out.
+// Whether the row kernel takes a layer, and how.  Choosing costs 17 us; the geometries a thread has asked for lately are remembered, in sets of four so that
+// the layers of a network do not turn each other out.  A plan is that of all lengths up to the next power of two groups: sequences of changing lengths choose a few times only.
 static bool row_remembered(const LayerParams& p, RowPlan& q) {
   struct Key {
     int v[12];
@@ -92,7 +92,7 @@ static bool row_remembered(const LayerParams& p, RowPlan& q) {
   };
   static thread_local Set known[16];
   if (!row_reaches(p)) return false;
-  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.K_last, p.n_lif, p.Wwi, mfma_mid_weight_blocks(p)}};
+  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, row_groups(p), p.K_last != 0, p.n_lif, p.Wwi, mfma_mid_weight_blocks(p)}};
   uint32_t hash = 2166136261u;
   for (int v : key.v) hash = (hash ^ (uint32_t)v) * 16777619u;
   Set& set = known[(hash >> 16) & 15];

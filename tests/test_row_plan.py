@@ -82,3 +82,14 @@ def test_forms_that_stay_on_the_older_kernels(plan):
     assert plan(_desc(24, 48, 80, 45, 16, *ok[5:])) is None and plan(_desc(24, 48, 80, 45, 65, *ok[5:])) is None     # pixels of a row
     assert plan(_desc(8, 8, 120, 16, 24, 1, api.TAC_PRESERVE, 2, 10)) is None                            # too little to do
     assert plan(_desc(4096, 128, 8, 512, 64, 1, api.TAC_COLLAPSE, 16, 16)) is None                       # a group's words: 2^31 bytes and more
+
+
+def test_lengths_up_to_the_next_power_of_two_groups_share_a_plan(plan):
+    # (with a shorter last group a second table takes its place in the LDS)
+    r = random.Random(8)
+    for _ in range(300):
+        K, B, Cin = r.randint(2, 16), r.choice([1, 2, 7, 60]), 8 * r.randint(3, 16)
+        rest = (B, Cin, r.randint(8, 200), r.randint(4, 60), r.randint(17, 64), r.choice([1, 2]), api.TAC_COLLAPSE, K)
+        plans = [[plan(_desc(*rest, g * K - K + last)) for g in range(17, 33)] for last in (K, 1, K - 1)]
+        assert all(p == plans[0][0] for p in plans[0])
+        assert all(p == plans[1][0] for p in plans[1] + plans[2])
