@@ -14,7 +14,7 @@
 // the next sixteen are requested before the MFMAs.  Two or three workgroups share a compute unit, so that one's splitting (400 vector instructions a round
 // and wave, which bound it together with the MFMAs' 1728 NP cycles) runs under another's products.
 // Products of fp32 and these (us): 96 <- 128 at 64 x 40, B = 16, three groups 537 -> 192; 32 <- 64 at 14 x 14, B = 128, seven groups 91 -> 59; 160 <- 96 at 41 x 33,
-// 144 pairs 1290 -> 343; only 8 output channels on fewer tiles than compute units lose: 5.0 -> 6.2.
+// 144 pairs 1290 -> 343.  Up to eight output channels (HALVES = 1): 64 <- 8 at 54 x 57, 144 pairs 91 -> 58, on fewer tiles than compute units 4.8 -> 5.0 (in full rounds 6.2).
 //
 // Few pixels (small images, small batches) leave that kernel with a few dozen workgroups that go through Cout / 16 rounds of two barriers
 // each.  dgrad_f32_split_kernel shares a workgroup's 32 input channels x NP blocks of 32 pixels among four waves by output channel, in products of fp32:
@@ -26,7 +26,6 @@ namespace tac {
 namespace {
 
 constexpr int kThreads = kDgradThreads;
-constexpr int kCo = kDgradCo;
 constexpr int kM = kDgradM;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
@@ -73,16 +72,20 @@ __device__ __forceinline__ float whole(const uint8_t* hi, int term) {
   return l == kHalves << 16 ? __uint_as_float(h | m >> 16) : __uint_as_float(h) + (__uint_as_float(m) + __uint_as_float(l));
 }
 
-constexpr int kTapBytes = 1024 + 16;                     // a tap's 2 x 32 x 8 weights; 16 bytes spread the taps of an input channel over the banks
-constexpr int kWBytes = 9 * kTapBytes;
+// LDS of a third of the weights: a tap's HALVES x 32 x 8 weights (16 bytes more spread the taps of an input channel over the banks), and with one half a tap of zeros
+__host__ __device__ constexpr int tap_bytes(int halves) { return halves * 512 + 16; }
+__host__ __device__ constexpr int w_bytes(int halves) { return (halves == 2 ? 9 : 10) * tap_bytes(halves); }
 
-// FAR: planes of 2^23 pixels and more, whose channels have a buffer descriptor each
-template <int NP, bool FAR>
+// FAR: planes of 2^23 pixels and more, whose channels have a buffer descriptor each.
+// HALVES = 1: at most eight output channels, one round.  The 16 places of a product are eight channels of two taps: five products of two taps instead of nine of which half is
+// zeros, and half of the splitting.
+template <int NP, bool FAR, int HALVES>
 __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(const BackwardParams p, const DgradPlan q) {
-  constexpr int NW = (2 * 288 + kThreads - 1) / kThreads;
+  constexpr int kCo = 8 * HALVES, kTapBytes = tap_bytes(HALVES), kWBytes = w_bytes(HALVES), kW = HALVES * 288;
+  constexpr int NW = (kW + kThreads - 1) / kThreads;
   extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
   uint8_t* const dyl = lds + q.off_dy;
-  const int d_term = q.pl * 32;                          // bytes of one third of dY, [half of the channels][position]
+  const int d_term = q.pl * 16 * HALVES;                 // bytes of one third of dY, [half of the channels][position]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wx = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n = lane & 31, h = lane >> 5;
@@ -123,8 +126,8 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
 #pragma unroll
   for (int i = 0; i < NW; ++i) {
     const int e = tid + i * kThreads, half = e >= 288, f = e - 288 * half;
-    w_off[i] = e < 2 * 288 ? (uint32_t)(8 * half * p.Cin * 9 + f) * 4u : kOutside;
-    w_dst[i] = f % 9 * kTapBytes + half * 512 + f / 9 * 16;
+    w_off[i] = e < kW ? (uint32_t)(8 * half * p.Cin * 9 + f) * 4u : kOutside;
+    w_dst[i] = f % 9 * kTapBytes + half * 512 + f / 9 * 16;          // (half 0 only with HALVES = 1)
   }
   const float* const dy0 = p.grad_y + (size_t)pair0 * p.Cout * plane + ((ptrdiff_t)y0 - 1) * p.W;      // (what lies in front of the array is never loaded)
   const float* const w0 = p.w + (size_t)ci0 * 9;
@@ -160,6 +163,7 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
 
   int* const bad_round = reinterpret_cast<int*>(lds + q.off_bad);        // of this round and of the next
   if (tid < 2) bad_round[tid] = 0;
+  if (HALVES == 1 && tid < 96) *reinterpret_cast<u32x4*>(lds + (tid >> 5) * kWBytes + 9 * kTapBytes + (tid & 31) * 16) = u32x4{0, 0, 0, 0};
   request(0);
   for (int co = 0, round = 0; co < p.Cout; co += kCo, round ^= 1) {
     __syncthreads();                                     // the round before has been read
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
     if (tid == 0) bad_round[round ^ 1] = 0;
 #pragma unroll
     for (int i = 0; i < NW; ++i)
-      if (tid + i * kThreads < 2 * 288) {
+      if (tid + i * kThreads < kW) {
         const Thirds v = thirds(wr[i], bad);
         uint8_t* const dst = lds + w_dst[i];
         *reinterpret_cast<u32x4*>(dst) = v.hi;
@@ -178,7 +182,7 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
     for (int m = 0; m < kM; ++m)
       if (tid + m * kThreads < q.pl) {
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
+        for (int half = 0; half < HALVES; ++half) {
           float x[8];
 #pragma unroll
           for (int c = 0; c < 8; ++c) x[c] = dr[m][8 * half + c];
@@ -194,39 +198,51 @@ __global__ __launch_bounds__(kThreads, NP == 1 ? 3 : 2) void dgrad_f32_kernel(co
     __syncthreads();
     const bool any_bad = __builtin_amdgcn_readfirstlane(bad_round[round]) != 0;
     if (!active) continue;
-    const uint8_t* const w_lane = lds + lane * 16;
-    const uint8_t* const d_half = dyl + h * q.pl * 16;
+    // a step: a tap of both halves of the channels, or two taps, one on either lane half (the tenth is zeros)
+    constexpr int kSteps = HALVES == 2 ? 9 : 5;
+    const uint8_t* const w_lane = HALVES == 2 ? lds + lane * 16 : lds + h * kTapBytes + n * 16;
+    const uint8_t* const d_lane = HALVES == 2 ? dyl + h * q.pl * 16 : dyl;
+    auto shift = [&](int step) {
+      auto of = [&](int tap) { return (2 - tap / 3) * q.cw + 2 - tap % 3; };
+      if constexpr (HALVES == 2) return of(step);
+      else return h ? of(min(2 * step + 1, 8)) : of(2 * step);
+    };
+    constexpr int kStepBytes = HALVES == 2 ? kTapBytes : 2 * kTapBytes;
     if (__builtin_expect(any_bad, 0)) {
       // the round in products of fp32
 #pragma clang loop unroll(disable)
-      for (int tap = 0; tap < 9; ++tap) {
-        const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+      for (int step = 0; step < kSteps; ++step) {
+        const int sh = shift(step);
 #pragma clang loop unroll(disable)
         for (int i = 0; i < 8; ++i) {
-          const float wv = whole(w_lane + tap * kTapBytes + 2 * i, kWBytes);
+          const float wv = whole(w_lane + step * kStepBytes + 2 * i, kWBytes);
 #pragma unroll
-          for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, whole(d_half + (base[b] + shift) * 16 + 2 * i, d_term), acc[b], 0, 0, 0);
+          for (int b = 0; b < NP; ++b) {
+            float dv = whole(d_lane + (base[b] + sh) * 16 + 2 * i, d_term);
+            if (HALVES == 1 && step == 4 && h) dv = 0.f;             // (no infinity times the zeros of the tenth tap)
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x2f32(wv, dv, acc[b], 0, 0, 0);
+          }
         }
       }
       continue;
     }
     auto load = [&](const uint8_t* at) { return *reinterpret_cast<const bf16x8*>(at); };
 #pragma unroll
-    for (int tap = 0; tap < 9; ++tap) {
-      const int shift = (2 - tap / 3) * q.cw + 2 - tap % 3;
+    for (int step = 0; step < kSteps; ++step) {
+      const int sh = shift(step);
       bf16x8 w[3], d[NP][3];
 #pragma unroll
-      for (int e = 0; e < 3; ++e) w[e] = load(w_lane + tap * kTapBytes + e * kWBytes);
+      for (int e = 0; e < 3; ++e) w[e] = load(w_lane + step * kStepBytes + e * kWBytes);
 #pragma unroll
       for (int b = 0; b < NP; ++b)
 #pragma unroll
-        for (int e = 0; e < 3; ++e) d[b][e] = load(d_half + (base[b] + shift) * 16 + e * d_term);
+        for (int e = 0; e < 3; ++e) d[b][e] = load(d_lane + (base[b] + sh) * 16 + e * d_term);
       // the products of 2^-18 and more of the largest; the three left out are below 2^-26 of it
 #pragma unroll
       for (int e = 0; e < 5; ++e) {
-        constexpr int kW[5] = {0, 2, 1, 0, 1}, kD[5] = {2, 0, 1, 1, 0};
+        constexpr int kFromW[5] = {0, 2, 1, 0, 1}, kFromD[5] = {2, 0, 1, 1, 0};
 #pragma unroll
-        for (int b = 0; b < NP; ++b) small[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kW[e]], d[b][kD[e]], small[b], 0, 0, 0);
+        for (int b = 0; b < NP; ++b) small[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[kFromW[e]], d[b][kFromD[e]], small[b], 0, 0, 0);
       }
 #pragma unroll
       for (int b = 0; b < NP; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[0], d[b][0], acc[b], 0, 0, 0);
@@ -458,11 +474,19 @@ hipError_t backward_dgrad_f32_launch(const BackwardParams& p, hipStream_t s) {
     return launch(&dgrad_f32_split_kernel<1>);
   }
   if (!np) return hipErrorInvalidValue;
-  q.off_dy = 3 * kWBytes;
-  q.off_bad = q.off_dy + 3 * 32 * q.pl;
+  const int halves = p.Cout <= 8 ? 1 : 2;
+  q.off_dy = 3 * w_bytes(halves);
+  q.off_bad = q.off_dy + 3 * 16 * halves * q.pl;
   q.total = q.off_bad + 16;
-  if ((long long)p.H * p.W >= (1ll << 23)) return np == 2 ? launch(&dgrad_f32_kernel<2, true>) : launch(&dgrad_f32_kernel<1, true>);
-  return np == 2 ? launch(&dgrad_f32_kernel<2, false>) : launch(&dgrad_f32_kernel<1, false>);
+  const bool far = (long long)p.H * p.W >= (1ll << 23);
+  auto with = [&](auto np_, auto halves_) {
+    constexpr int NP = decltype(np_)::value, HALVES = decltype(halves_)::value;
+    return far ? launch(&dgrad_f32_kernel<NP, true, HALVES>) : launch(&dgrad_f32_kernel<NP, false, HALVES>);
+  };
+  constexpr std::integral_constant<int, 1> one;
+  constexpr std::integral_constant<int, 2> two;
+  if (halves == 1) return np == 2 ? with(two, one) : with(one, one);
+  return np == 2 ? with(two, two) : with(one, two);
 }
 
 }  // namespace tac

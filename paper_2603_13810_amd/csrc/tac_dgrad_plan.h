@@ -48,9 +48,11 @@ inline long long dgrad_f32_tiles(const DgradPlan& q) { return (long long)q.pair_
 // Microseconds of the kernels, fitted to 450 random layers (1 to 128 channels on either side, 3 x 3 to 64 x 72 pixels, 1 to 768 pairs) to 6 or 7% rms, and 9% for
 // the vector kernel.
 // Rounds of 16 output channels (cycles at 2.5 GHz): a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several
-// (7850, 4000); the stores.
+// (7850, 4000); the stores.  Up to eight output channels take one shorter round (fitted to 174 layers, 7% rms).
 inline double dgrad_thirds_us(const DgradPlan& q, int np, const BackwardParams& p) {
-  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256), cycles = std::max(np == 2 ? 10700.0 : 7500.0, per_cu * (np == 2 ? 7850.0 : 4000.0));
+  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
+  const double cycles = p.Cout <= 8 ? std::max(np == 2 ? 6000.0 : 4300.0, per_cu * (np == 2 ? 5000.0 : 2300.0))
+                                    : std::max(np == 2 ? 10700.0 : 7500.0, per_cu * (np == 2 ? 7850.0 : 4000.0));
   return 2.4 + (p.Cout + kDgradCo - 1) / kDgradCo * cycles / 2500.0 + 0.9 * per_cu * np;
 }
 // Rounds of 32 output channels in products of fp32
@@ -93,10 +95,10 @@ inline void dgrad_vector_tiles(int Cin, unsigned& across, unsigned& over) {
 
 // Which kernel forms an input gradient that is not the bf16 kernels': the matrix-core ones (true) take stride 1 and fill blocks of 32 input channels; the vector kernel takes
 // any layer, four input channels per thread, and is the faster one for few input channels over many pixels, by both estimates (us on the vector kernel and on the other:
-// 1 -> 64 at 64 x 64, B = 64, 8 groups 261 / 480, 4 -> 64 314 / 454, 8 -> 64 549 / 439; 1 -> 64 at 28 x 28, B = 64, 2 groups 34.6 / 28.1, 1 -> 8 7.6 / 10.0).  Its
+// 1 -> 64 at 64 x 64, B = 64, 8 groups 261 / 480, 4 -> 64 314 / 454, 8 -> 64 549 / 439; 1 -> 64 at 28 x 28, B = 64, 2 groups 34.6 / 28.1, 1 -> 8 8.8 / 9.2).  Its
 // chains of products are less accurate than thirds.  So it takes no layer for which it would not be the faster one even against 32 input channels in products of fp32 (per output
-// channel 0.23 us and the pixels at 0.184e6 a us, against 0.35 .. 0.63 and 0.55e6 for four), where thirds would be slower only with one to eight output channels (2 -> 1 at 35 x 31, 64
-// pairs 8.3 us, 4.4 there).
+// channel 0.23 us and the pixels at 0.184e6 a us, against 0.35 .. 0.63 and 0.55e6 for four), where thirds would be slower only with one to four output channels (2 -> 1 at 35 x 31, 64
+// pairs 6.1 us, 5.0 there).
 inline bool backward_dgrad_f32_supported(const BackwardParams& p) {
   if (p.stride != 1) return false;
   if (p.Cin >= (1 << 20)) return false;                  // 30-bit byte offsets within the weights of 16 output channels

@@ -88,12 +88,15 @@ def test_an_infinite_weight_of_the_last_channel_is_multiplied_once():
 
 # Many tiles: products of bf16 thirds, (B, Cin, Cout, H, W, format, per group, K, T) as above
 MANY = [
-    (70, 33, 8, 9, 33, BITS, True, 2, 4),       # one round, half of it empty; two channel groups, the second of one channel
+    (70, 33, 8, 9, 33, BITS, True, 2, 4),       # one round; two channel groups, the second of one channel
+    (70, 33, 9, 9, 33, BITS, True, 2, 4),       # one round, half of it but for one channel empty
     (60, 40, 17, 16, 16, BITS, True, 1, 2),     # a second round of one channel
     (20, 64, 32, 21, 65, BITS, False, 2, 3),    # two row segments, the second of one pixel
     (300, 96, 24, 6, 5, BITS, True, 2, 2),      # several samples a tile, the last tile partly filled
     (90, 32, 64, 14, 14, MEAN, False, 4, 7),
     (40, 24, 40, 11, 30, MAX, False, 2, 3),
+    (70, 33, 1, 9, 33, BITS, False, 2, 4),      # up to eight output channels: two taps a product
+    (50, 70, 7, 20, 45, BITS, True, 2, 3), (3, 40, 8, 5, 5, BITS, True, 2, 3), (90, 24, 5, 14, 14, MEAN, False, 4, 7), (40, 24, 3, 11, 30, MAX, False, 2, 3),
 ]
 
 
@@ -136,6 +139,28 @@ def test_values_that_have_no_thirds():
     # the bound above, and 2^-126 per product of a subnormal part that the matrix cores may take as zero
     tol = 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3)
     assert (np.abs(have[ok] - want[ok]) <= tol * size[ok] + 9 * Cout * 2.0 ** -126).all()
+
+
+@pytest.mark.parametrize("Cout", [1, 7, 8])
+def test_values_that_have_no_thirds_in_one_round(Cout):
+    # up to eight output channels: a product takes two taps, the last one with zeros in the place of a tenth
+    B, Cin, H, W = 60, 40, 16, 16
+    r = np.random.Generator(np.random.PCG64(7650 + Cout))
+    desc = api.make_desc(1, B, Cin, H, W, Cout, K=1, beta=0.9, theta=1.0, mode=api.TAC_PER_STEP)
+    g = r.standard_normal((1, B, Cout, H, W)).astype(np.float32)
+    last = Cout - 1
+    g[0, 1, last, 5, 5], g[0, 2, 0, 0, 15], g[0, 3, last, 15, 0], g[0, 4, last, 7, 7] = np.inf, -np.inf, np.inf, np.nan
+    w = (r.standard_normal((Cout, Cin, 3, 3)) * 0.1).astype(np.float32)
+    x = torch.zeros((1, B, Cin, H, 1), dtype=torch.int32, device=DEV)
+    gd = torch.from_numpy(g).to(DEV)
+    got = api.tac_conv_lif_backward(desc, x, torch.from_numpy(w).to(DEV), torch.ones_like(gd), gd, grad_in_per_group=True)
+    gy, wd = got["grad_y"].cpu().double()[0], torch.from_numpy(w).double()
+    have, want = got["grad_in"].cpu().numpy().reshape(B, Cin, H, W), torch.nn.functional.conv_transpose2d(gy, wd, padding=1).numpy()
+    assert np.array_equal(np.isnan(have), np.isnan(want)) and np.isinf(want).any()
+    assert np.array_equal(have[np.isinf(want)], want[np.isinf(want)].astype(np.float32))
+    ok = np.isfinite(want)
+    size = torch.nn.functional.conv_transpose2d(gy.nan_to_num(0.0, 0.0, 0.0).abs(), wd.abs(), padding=1).numpy()
+    assert (np.abs(have[ok] - want[ok]) <= 4 * 2.0 ** -24 * ((9 * Cout) ** 0.5 + 3) * size[ok]).all()
 
 
 def test_planes_beyond_one_descriptor():
