@@ -48,9 +48,6 @@ __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
 }
 
-// i / d for a wave-uniform divisor and i below 2^20 (the quotient (i + 1/2) / d stays clear of integers by 1 / (2 d))
-__device__ __forceinline__ int small_div(int i, float r) { return (int)(((float)i + 0.5f) * r); }
-
 // Real-valued frames with one column tile: two workgroups per compute unit fill each other's waits for the frames (2 -> 128 at
 // 64 x 64, B = 16, 4 groups of 4: 132 us a backward call, 149 with one); frames of bits ask for their words one item ahead.
 __host__ __device__ constexpr bool wgrad_two_per_cu(int nt, bool dense) { return dense && nt == 1; }

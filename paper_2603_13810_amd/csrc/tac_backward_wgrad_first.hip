@@ -36,9 +36,6 @@ __device__ __forceinline__ int group_frames(const BackwardParams& p, int k) {
   return (k == p.G - 1 && p.K_last) ? p.K_last : p.K;
 }
 
-// i / d for a wave-uniform divisor and i below 2^20 (the quotient (i + 1/2) / d stays clear of integers by 1 / (2 d))
-__device__ __forceinline__ int small_div(int i, float r) { return (int)(((float)i + 0.5f) * r); }
-
 // Value of lane ^ (1 << STEP).
 template <int STEP>
 __device__ __forceinline__ float across(float v) {

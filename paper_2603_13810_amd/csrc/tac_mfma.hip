@@ -1,7 +1,7 @@
 // Host side of the matrix-core kernel family: which member takes a layer, prepared weights, dispatch to the
 // translation unit that holds the kernels of the layer's geometry (tac_mfma_kernel.h has the kernel itself).
-#include <cstring>
 #include <mutex>
+#include "tac_plan_memo.h"
 #include "tac_row_plan.h"
 
 namespace tac {
@@ -75,45 +75,28 @@ hipError_t mfma_prepare(const tac_layer_desc_t& d, const float* w_oihw, void* w_
   return hipGetLastError();
 }
 
-// Whether the row kernel takes a layer, and how.  Choosing costs 17 us; the geometries a thread has asked for lately are remembered, in sets of four so that
-// the layers of a network do not turn each other out.  A plan is that of all lengths up to the next power of two groups: sequences of changing lengths choose a few times only.
-static bool row_remembered(const LayerParams& p, RowPlan& q) {
-  struct Key {
-    int v[12];
-  };
-  struct Entry {
-    Key key;
+// Whether the row kernel takes a layer, and how.  Choosing costs 17 us; the geometries a thread has asked for lately are remembered.  A plan is that of all lengths up to the next power of two groups: sequences of changing lengths choose a few times only.
+static const RowPlan* row_remembered(const LayerParams& p) {
+  struct Choice {
     RowPlan q;
-    bool used, takes;
+    bool takes;
   };
-  struct Set {
-    Entry entry[4];
-    unsigned oldest;
-  };
-  static thread_local Set known[16];
-  if (!row_reaches(p)) return false;
-  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, row_groups(p), p.K_last != 0, p.n_lif, p.Wwi, mfma_mid_weight_blocks(p)}};
-  uint32_t hash = 2166136261u;
-  for (int v : key.v) hash = (hash ^ (uint32_t)v) * 16777619u;
-  Set& set = known[(hash >> 16) & 15];
-  Entry* e = nullptr;
-  for (Entry& x : set.entry)
-    if (x.used && !std::memcmp(&x.key, &key, sizeof(key))) e = &x;
-  if (!e) {
-    e = &set.entry[set.oldest++ & 3];
-    e->key = key;
-    e->takes = row_choose(p, e->q, key.v[11]);
-    e->used = true;
-  }
-  q = e->q;
-  return e->takes;
+  static thread_local PlanMemo<12, Choice> known;
+  if (!row_reaches(p)) return nullptr;
+  const int blocks = mfma_mid_weight_blocks(p);
+  const int key[12] = {p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, row_groups(p), p.K_last != 0, p.n_lif, p.Wwi, blocks};
+  const Choice* const c = known.of(key, [&](Choice& n) {
+    n.takes = row_choose(p, n.q, blocks);
+    return true;
+  });
+  return c->takes ? &c->q : nullptr;
 }
 
 hipError_t mfma_launch(const LayerParams& p, hipStream_t s) {
   if (p.mfma_kind == 2) return mfma_small_launch(p, s);
   if (p.mfma_kind == 3) {
-    RowPlan q;
-    return row_remembered(p, q) ? row_launch(p, q, s) : mfma_mid_launch(p, s);
+    const RowPlan* const q = row_remembered(p);
+    return q ? row_launch(p, *q, s) : mfma_mid_launch(p, s);
   }
   const bool t = p.v_trace != nullptr;
   if (p.W == 64 && p.stride == 1) return t ? mfma_large_w64s1_trace(p, s) : mfma_large_w64s1(p, s);

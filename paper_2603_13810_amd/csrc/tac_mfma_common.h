@@ -35,9 +35,42 @@ struct MfmaParams {
   int pool;                            // mid kernel: 2 x 2 pool on load, 1 mean, 2 max
 };
 
+// The parameters of a layer; the tiles are the launcher's.
+inline void fill_params(MfmaParams& mp, const LayerParams& p) {
+  mp.spikes = p.spikes; mp.w = static_cast<const uint8_t*>(p.w); mp.bias = p.bias; mp.v_inout = p.v_inout;
+  mp.out = p.out; mp.v_trace = p.v_trace;
+  mp.B = p.B; mp.Cin = p.Cin; mp.H = p.H; mp.W = p.W; mp.Ho = p.Ho; mp.Wo = p.Wo; mp.Cout = p.Cout; mp.stride = p.stride;
+  mp.K = p.K; mp.G = p.G; mp.n_lif = p.n_lif; mp.maxpool = p.pool2 == 2; mp.pool = p.pool2; mp.out_pool = p.out_pool;
+  mp.row_tiles = 0;
+  mp.decay = p.decay; mp.theta = p.theta;
+  for (int j = 0; j < TAC_MAX_K; ++j) {
+    // beta^(K-1-j) in 24-bit fixed point, from the fp32 table the host already rounded
+    const double q = (double)p.wj[j] * (double)(1u << kFixShift);
+    mp.wq[j] = j < p.K ? (uint32_t)(q + 0.5) : 0u;
+  }
+}
+
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   f32x2 f = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));   // v_cvt_pk_bf16_f32, nearest even
+}
+
+// i / d for a wave-uniform divisor of reciprocal r and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
+// the rounding of the reciprocal and the product moves it
+__device__ __forceinline__ int small_div(int i, float r) { return (int)(((float)i + 0.5f) * r); }
+struct SmallDiv {
+  int d;
+  float r;
+  __device__ __forceinline__ explicit SmallDiv(int divisor) : d(divisor), r(1.0f / (float)divisor) {}
+  __device__ __forceinline__ int quot(int i) const { return small_div(i, r); }
+};
+
+// Workgroup barrier that orders LDS traffic only: the compiler waits for this wave's LDS
+// accesses and for its direct-to-LDS loads, but leaves ordinary global loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // vdst[lane L0 + i * STEP + (j ? HALF : 0)] = x[i][j] for the wave-uniform values x[4][2]; other
@@ -92,6 +125,31 @@ __device__ __forceinline__ void frames_to_fields(uint32_t* w) {
       w[c] = bfi(m, lo, hi << (K / 2));
       w[c + K / 2] = bfi(m, lo >> (K / 2), hi);
     }
+  }
+}
+
+// The aggregates (Eq. 2) of a group of two frames, two channels at once: t, their frame bits at bits 0 and 16; the four bf16 entries in the halves of lo and hi.
+__device__ __forceinline__ uint32_t two_frame_pair(uint32_t hi, uint32_t lo, uint32_t t) {
+  return __builtin_amdgcn_perm(hi, lo, __umul24(t, 0x0202u) + 0x01000100u);
+}
+
+// Aggregates by frame bits: KP = 4, pairs of channels as two bf16; KP = 8, one bf16; KP = 16, 2^-23 fixed-point sums of frames 0 .. 7 and 8 .. 15.  `sets` tables of `words`
+// entries, the second one with the weights from first_last on.
+template <int KP>
+__device__ __forceinline__ void frame_tables(uint32_t* lut, int words, int sets, int first_last, const MfmaParams& p, int tid, int threads) {
+  const float scale = 1.0f / (float)(1u << kFixShift);
+#pragma clang loop unroll(disable)
+  for (int i = tid; i < words * sets; i += threads) {
+    const int set = i >= words, t = i - (set ? words : 0), f0 = set ? first_last : 0;
+    uint32_t a[2] = {0, 0};
+#pragma unroll
+    for (int j = 0; j < (KP == 4 ? 4 : 8); ++j) {
+      const int jj = f0 + j + (KP == 16 ? (t >> 8) * 8 : 0);
+      const uint32_t w = p.wq[min(jj, TAC_MAX_K - 1)];
+      a[0] += (t >> j) & 1 ? w : 0u;
+      if constexpr (KP == 4) a[1] += (t >> (4 + j)) & 1 ? w : 0u;
+    }
+    lut[i] = KP == 16 ? a[0] : pack_bf16((float)a[0] * scale, (float)a[1] * scale);
   }
 }
 

@@ -36,22 +36,6 @@ hipError_t deep_launch_trace(const DeepParams& p, hipStream_t s);
 
 namespace {
 
-// i / d for a wave-uniform divisor and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
-// the rounding of the reciprocal and the product moves it
-struct DeepDiv {
-  int d;
-  float r;
-  __device__ __forceinline__ explicit DeepDiv(int divisor) : d(divisor), r(1.0f / (float)divisor) {}
-  __device__ __forceinline__ int quot(int i) const { return (int)(((float)i + 0.5f) * r); }
-};
-
-// Orders LDS accesses only: loads of weights and words stay in flight.
-__device__ __forceinline__ void deep_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // KP: frames per table index (16: two indices of eight).  KS: k-steps of a wave at most.  GB groups x PB pixel blocks.
 template <int KP, bool TRACE, int KS, int GB, int PB>
 __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams dp) {
@@ -69,7 +53,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
   const int co_tile = (int)(blockIdx.x - row_tile * (uint32_t)q.co_tiles);
   const int co0 = co_tile * 32;
   // output rows are counted through all samples (fewer than 2^20), or the grid's z is the sample
-  const DeepDiv by_ho(p.Ho);
+  const SmallDiv by_ho(p.Ho);
   const int first_row = (int)row_tile * q.tr;
   const int b0 = q.flatten ? by_ho.quot(first_row) : (int)blockIdx.z;
   const int oy0 = q.flatten ? first_row - b0 * p.Ho : first_row;
@@ -91,7 +75,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
   bf16x8 w_own[KS];
   {
     // the vector kernel's layout: [cin][tap][cout padded to 32] fp32, rounded to bf16; slots beyond 9 Cin are zero
-    const DeepDiv by_cin(Cin);
+    const SmallDiv by_cin(Cin);
     const int cp = q.co_tiles * 32;
 #pragma unroll
     for (int k = 0; k < KS; ++k) {
@@ -115,10 +99,10 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
     const int n0 = min(p.Ho - oy0, q.tr) * S + (3 - S);                // LDS rows of the tile's first sample
     const int per_sample = p.Ho * S + (3 - S);
     const int lr_used = (rows_valid - 1) * S + sample_of(rows_valid - 1) * (3 - S) + 3;
-    const int row = DeepDiv(q.nseg).quot(i), seg = i - row * q.nseg;
+    const int row = SmallDiv(q.nseg).quot(i), seg = i - row * q.nseg;
     int bsel = 0, iy = oy0 * S - 1 + row;
     if (row >= n0) {
-      const int over = DeepDiv(per_sample).quot(row - n0);
+      const int over = SmallDiv(per_sample).quot(row - n0);
       bsel = 1 + over;
       iy = row - n0 - over * per_sample - 1;
     }
@@ -130,33 +114,19 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
   }
   // where a k-step's lane half finds its channels and tap
   if (tid < 2 * q.nks) {
-    const int kk = 8 * tid, tap = DeepDiv(Cin).quot(kk), cin = kk - tap * Cin;
+    const int kk = 8 * tid, tap = SmallDiv(Cin).quot(kk), cin = kk - tap * Cin;
     const int ky = (tap * 11) >> 5, kx = tap - ky * 3;                 // tap / 3 for the nine taps
     tab[tid] = tap < 9 ? (cin >> 3) * q.plane + (ky * q.wpx + col(kx)) * 16 : 0;
   }
   const float scale = 1.0f / (float)(1u << kFixShift);
-  const int first_last = p.K - dp.K_last;      // a shorter last group's weights are the last of a whole group's
-  if constexpr (KP >= 4) {
-#pragma clang loop unroll(disable)
-    for (int i = tid; i < q.lut_set / 4 * (dp.K_last ? 2 : 1); i += kDeepThreads) {
-      const int set = i >= q.lut_set / 4, t = i - (set ? q.lut_set / 4 : 0), f0 = set ? first_last : 0;
-      uint32_t a[2] = {0, 0};
-#pragma unroll
-      for (int j = 0; j < (KP == 4 ? 4 : 8); ++j) {
-        const int jj = f0 + j + (KP == 16 ? (t >> 8) * 8 : 0);
-        const uint32_t w = p.wq[min(jj, TAC_MAX_K - 1)];
-        a[0] += (t >> j) & 1 ? w : 0u;
-        if constexpr (KP == 4) a[1] += (t >> (4 + j)) & 1 ? w : 0u;
-      }
-      lut[i] = KP == 16 ? a[0] : pack_bf16((float)a[0] * scale, (float)a[1] * scale);
-    }
-  }
+  // (a shorter last group's weights are the last of a whole group's)
+  if constexpr (KP >= 4) frame_tables<KP>(lut, q.lut_set / 4, dp.K_last ? 2 : 1, p.K - dp.K_last, p, tid, kDeepThreads);
   if (tid < 32) bias_lds[tid] = (p.bias && co0 + tid < p.Cout) ? p.bias[co0 + tid] : 0.f;
-  deep_barrier();
+  lds_barrier();
 
   // ---- the units of a round: (row and segment, channels, group), the first fastest; a thread has one of them a turn
   const int CC = Cin / UC, units = n_pairs * CC;
-  const DeepDiv by_pairs(n_pairs), by_cc(CC);
+  const SmallDiv by_pairs(n_pairs), by_cc(CC);
   const int turns = (q.gb * units + kDeepThreads - 1) / kDeepThreads;
   struct Unit {
     int gb, cc;
@@ -228,7 +198,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
         for (int c2 = 0; c2 < UC / 2; ++c2) {
           const uint32_t t0 = __builtin_amdgcn_ubfe(wd[2 * c2][cl], sh, KP), t1 = __builtin_amdgcn_ubfe(wd[2 * c2 + 1][cl], sh, KP);
           if constexpr (KP == 1) v[c2] = one & __umul24(t0 | t1 << 16, 0xffffu);
-          else if constexpr (KP == 2) v[c2] = __builtin_amdgcn_perm(two_hi, lo, __umul24(t0 | t1 << 16, 0x0202u) + 0x01000100u);
+          else if constexpr (KP == 2) v[c2] = two_frame_pair(two_hi, lo, t0 | t1 << 16);
           else if constexpr (KP == 4) v[c2] = tb[t0 | t1 << 4];
           else v[c2] = tb[t0] | tb[t1] << 16;
         }
@@ -333,7 +303,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
         form_unit(g0, t + s, wd[s]);
         load_unit(t + s + 2 < turns ? g0 : g_next, t + s + 2 < turns ? t + s + 2 : s, wd[s]);
       });
-    deep_barrier();
+    lds_barrier();
     // ---- 2. the wave's k-steps, nine blocks' fragments at a time
     f32x16 acc[kDeepSets];
 #pragma unroll
@@ -352,7 +322,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
           if (kb + k < 1 || kb + k < n_k) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w_own[kb + k], af[k], acc[i], 0, 0, 0);
       }
     }
-    deep_barrier();                            // the aggregates have been read
+    lds_barrier();                            // the aggregates have been read
     {
       f32x2* const part = reinterpret_cast<f32x2*>(lds) + lane;        // [set][wave][register pair][lane]
 #pragma unroll
@@ -361,7 +331,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
 #pragma unroll
           for (int r2 = 0; r2 < 8; ++r2) part[((i * 8 + wave) * 8 + r2) * 64] = f32x2{acc[i][2 * r2], acc[i][2 * r2 + 1]};
     }
-    deep_barrier();
+    lds_barrier();
     float y[kDeepSets][2];
 #pragma unroll
     for (int i = 0; i < kDeepSets; ++i) {
@@ -380,7 +350,7 @@ __global__ __launch_bounds__(kDeepThreads, 2) void deep_kernel(const DeepParams 
 #pragma unroll
       for (int r = 0; r < 2; ++r) y[i][r] = in[0][r] + bias_lds[chan(r) + 4 * h];
     }
-    deep_barrier();                            // the next aggregates may take the place of the partial sums
+    lds_barrier();                            // the next aggregates may take the place of the partial sums
     // ---- 3. LIF steps
 #pragma clang loop unroll(disable)
     for (int i = 0; i < gn; ++i) {

@@ -335,7 +335,7 @@ __device__ __forceinline__ void lookup(StepRegs<KT>& sr, const uint8_t* lut, con
 #pragma unroll
     for (int e2 = 0; e2 < 2; ++e2) {
       const uint32_t t = __builtin_amdgcn_ubfe(sr.cw[2 * e2], pos, 2) | (__builtin_amdgcn_ubfe(sr.cw[2 * e2 + 1], pos, 2) << 16);
-      sr.lv[e2] = __builtin_amdgcn_perm(two.hi, two.lo, __umul24(t, 0x0202u) + 0x01000100u);
+      sr.lv[e2] = two_frame_pair(two.hi, two.lo, t);
     }
   } else if constexpr (PAIRS) {
     const uint32_t pos = lane & 31 & ~(KT - 1);
@@ -422,14 +422,6 @@ __device__ __forceinline__ void expand_step(const MfmaParams& p, const uint8_t* 
     a_write_packed<G>(a_next, lane, q, step,
                       u32x2{pack_bf16((float)acc[0], (float)acc[1]), pack_bf16((float)acc[2], (float)acc[3])});
   }
-}
-
-// Workgroup barrier that orders LDS traffic only: the compiler waits for this wave's LDS
-// accesses and for its direct-to-LDS loads, but leaves ordinary global loads in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // TRACE: also write the pre-reset membrane of every LIF step (a kernel of its own, so that the
@@ -1109,7 +1101,7 @@ hipError_t launch_traced(const MfmaParams& mp, hipStream_t s) {
   // building every aggregate tile twice.  That pays where the steps weigh enough against the chunks of 16 input
   // channels and the loader is cheap enough: measured on 64 x 64 layers, from one LIF step per eight chunks with
   // single frames (the per-step layer on 128 channels) and with groups of two frames and one step per group (TAC K = 2,
-  // whose pair table makes the loader cheap: 3 % faster on 128 channels), per four chunks with two steps per group of
+  // whose look-ups are cheap: 3 % faster on 128 channels when they read a table of pairs in the LDS), per four chunks with two steps per group of
   // two frames, per two chunks with larger groups (TAC-TP with groups of 4, 8 or 16 on 128 channels).
   if constexpr (!MP && KT >= 1 && 2 * Geo<WIN, S>::lds_bytes(KT, 2) <= kLdsLimit) {
     const int kChannelsPerStep = KT == 1 ? 128 : (KT == 2 ? (mp.n_lif == 1 ? 128 : 64) : 32);
@@ -1169,21 +1161,6 @@ hipError_t launch_geo(const MfmaParams& mp, hipStream_t s) {
 
 static_assert(max_k<64, 1>() == TAC_MAX_K && max_k<32, 1>() == TAC_MAX_K, "stride 1 takes every K");
 static_assert(max_k<64, 2>() >= 4 && max_k<32, 2>() >= 4, "stride 2 takes K up to 4");
-
-inline void fill_params(MfmaParams& mp, const LayerParams& p) {
-  mp.spikes = p.spikes; mp.w = static_cast<const uint8_t*>(p.w); mp.bias = p.bias; mp.v_inout = p.v_inout;
-  mp.out = p.out; mp.v_trace = p.v_trace;
-  mp.B = p.B; mp.Cin = p.Cin; mp.H = p.H; mp.W = p.W; mp.Ho = p.Ho; mp.Wo = p.Wo; mp.Cout = p.Cout; mp.stride = p.stride;
-  mp.K = p.K; mp.G = p.G; mp.n_lif = p.n_lif; mp.maxpool = p.pool2 == 2; mp.out_pool = p.out_pool;
-  mp.row_tiles = 0;
-  mp.decay = p.decay; mp.theta = p.theta;
-  for (int j = 0; j < TAC_MAX_K; ++j) {
-    // beta^(K-1-j) in 24-bit fixed point, from the fp32 table the host already rounded
-    const double q = (double)p.wj[j] * (double)(1u << kFixShift);
-    mp.wq[j] = j < p.K ? (uint32_t)(q + 0.5) : 0u;
-  }
-}
-
 
 template <int KT, int WIN>
 hipError_t launch_agg(const MfmaParams& mp, hipStream_t s) {

@@ -2,8 +2,8 @@
 // their prepared weights, and the tile a launch uses.
 #include <algorithm>
 #include <cmath>
-#include <cstring>
 #include "tac_mfma_mid_kernel.h"
+#include "tac_plan_memo.h"
 
 namespace tac {
 
@@ -323,49 +323,21 @@ static bool mid_choose(const LayerParams& p, MidParams& out, int& kp, int& nmc, 
 
 hipError_t mfma_mid_launch(const LayerParams& p, hipStream_t s) {
   MidParams a;
-  MfmaParams& mp = a.m;
-  mp.spikes = p.spikes; mp.w = static_cast<const uint8_t*>(p.w); mp.bias = p.bias; mp.v_inout = p.v_inout;
-  mp.out = p.out; mp.v_trace = p.v_trace;
-  mp.B = p.B; mp.Cin = p.Cin; mp.H = p.H; mp.W = p.W; mp.Ho = p.Ho; mp.Wo = p.Wo; mp.Cout = p.Cout; mp.stride = p.stride;
-  mp.K = p.K; mp.G = p.G; mp.n_lif = p.n_lif; mp.row_tiles = 0; mp.maxpool = 0; mp.pool = p.pool2; mp.out_pool = p.out_pool;
-  mp.decay = p.decay; mp.theta = p.theta;
-  for (int j = 0; j < TAC_MAX_K; ++j) {
-    const double q = (double)p.wj[j] * (double)(1u << kFixShift);
-    mp.wq[j] = j < p.K ? (uint32_t)(q + 0.5) : 0u;
-  }
+  fill_params(a.m, p);
   a.K_last = p.K_last; a.n_lif_last = p.n_lif_last; a.decay_last = p.decay_last;
-  // The choice looks at some hundred tiles (up to 18 us); the geometries a thread has asked for lately are remembered, in sets of
-  // four so that the layers of a network do not turn each other out (two of them in one place: 18 us each, every pass).
-  struct Key {
-    int v[14];
-    bool operator==(const Key& o) const { return std::memcmp(v, o.v, sizeof(v)) == 0; }
-  };
-  struct Entry {
-    Key key;
+  // The choice looks at some hundred tiles (up to 18 us); the geometries a thread has asked for lately are remembered.
+  struct Choice {
     MidPlan q;
     int kp, nmc, nnp;
-    bool used;
   };
-  struct Set {
-    Entry entry[4];
-    unsigned oldest;
-  };
-  static thread_local Set known[16];
-  const Key key{{p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.n_lif, p.pool2, p.out_pool, p.bf16, p.Wwi, p.v_trace != nullptr}};
-  uint32_t hash = 2166136261u;
-  for (int v : key.v) hash = (hash ^ (uint32_t)v) * 16777619u;
-  Set& set = known[(hash >> 16) & 15];
-  Entry* e = nullptr;
-  for (Entry& x : set.entry)
-    if (x.used && x.key == key) e = &x;
-  if (!e) {
-    e = &set.entry[set.oldest++ & 3];
-    e->used = false;
-    if (!mid_choose(p, a, e->kp, e->nmc, e->nnp)) return hipErrorInvalidValue;
-    e->key = key;
-    e->q = a.q;
-    e->used = true;
-  }
+  static thread_local PlanMemo<14, Choice> known;
+  const int key[14] = {p.B, p.Cin, p.H, p.W, p.Cout, p.stride, p.K, p.G, p.n_lif, p.pool2, p.out_pool, p.bf16, p.Wwi, p.v_trace != nullptr};
+  const Choice* const e = known.of(key, [&](Choice& n) {
+    if (!mid_choose(p, a, n.kp, n.nmc, n.nnp)) return false;
+    n.q = a.q;
+    return true;
+  });
+  if (!e) return hipErrorInvalidValue;
   a.q = e->q;
   const int kp = e->kp, nmc = e->nmc, nnp = e->nnp;
   if (!p.bf16) return p.v_trace ? mid_launch_f32_trace(a, kp, nnp, s) : mid_launch_f32(a, kp, nnp, s);

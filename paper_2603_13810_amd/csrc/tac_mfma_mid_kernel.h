@@ -86,15 +86,6 @@ constexpr int kMidDirect = 2;   // pixels of 8 channels per thread that go witho
 // units a lane takes per chunk
 __host__ __device__ constexpr int mid_units(int kp) { return kp <= 2 ? 2 : 1; }
 
-// i / d for a wave-uniform divisor and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
-// the rounding of the reciprocal and the product moves it
-struct SmallDiv {
-  int d;
-  float r;
-  __device__ __forceinline__ explicit SmallDiv(int divisor) : d(divisor), r(1.0f / (float)divisor) {}
-  __device__ __forceinline__ int quot(int i) const { return (int)(((float)i + 0.5f) * r); }
-};
-
 // KP: frames per table index (1, 2, 4 or 8; missing frames are zero words).  NMC x NNP: blocks of 32 channels x 32 pixels
 // per wave.  DIRECT: the plan's direct.  SPLIT: the plan's split, see below.
 //

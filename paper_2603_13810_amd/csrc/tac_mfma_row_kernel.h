@@ -28,22 +28,6 @@ struct RowParams {
 
 namespace {
 
-// i / d for a wave-uniform divisor and i below 2^20: (i + 1/2) / d is at least 1 / (2 d) from every integer, more than
-// the rounding of the reciprocal and the product moves it
-struct RowDiv {
-  int d;
-  float r;
-  __device__ __forceinline__ explicit RowDiv(int divisor) : d(divisor), r(1.0f / (float)divisor) {}
-  __device__ __forceinline__ int quot(int i) const { return (int)(((float)i + 0.5f) * r); }
-};
-
-// Orders LDS accesses only: words on their way stay in flight.
-__device__ __forceinline__ void row_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // KP: frames per table index (16: two indices of eight).  NNP: blocks of 32 pixels per wave.
 template <int KP, int NNP>
 __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) void row_kernel(const RowParams dp) {
@@ -62,7 +46,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
   const int co_grp = wave / q.pw, px_wave = wave - co_grp * q.pw;
   const int co0 = (co_tile * q.nco + co_grp) * 32;
   // output rows are counted through all samples (fewer than 2^20), or the grid's z is the sample
-  const RowDiv by_ho(p.Ho);
+  const SmallDiv by_ho(p.Ho);
   const int first_row = (int)row_tile * q.tr;
   const int b0 = q.flatten ? by_ho.quot(first_row) : (int)blockIdx.z;
   const int oy0 = q.flatten ? first_row - b0 * p.Ho : first_row;
@@ -93,7 +77,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
   // words of the tile's rows: byte offset from (frame, first sample, channel), top bit: outside the image
   const int n_pairs = q.lr * wws, n_px = q.lr * p.W;
   const int n0 = min(p.Ho - oy0, q.tr) * S + (3 - S);                  // LDS rows of the tile's first sample
-  const RowDiv by_sample(p.Ho * S + (3 - S)), by_wws(wws), by_w(p.W);
+  const SmallDiv by_sample(p.Ho * S + (3 - S)), by_wws(wws), by_w(p.W);
   const int lr_used = (rows_valid - 1) * S + sample_of(rows_valid - 1) * (3 - S) + 3;
   for (int i = tid; i < n_pairs; i += threads) {
     const int row = by_wws.quot(i), word = i - row * wws;
@@ -122,34 +106,20 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
   }
   // where a k-step's lane half finds its channels and tap; entries behind the last step are only ever fetched ahead
   for (int i = tid; i < 2 * q.nks + kRowTabPad; i += threads) {
-    const int kk = 8 * i, tap = RowDiv(Cin).quot(kk), cin = kk - tap * Cin;
+    const int kk = 8 * i, tap = SmallDiv(Cin).quot(kk), cin = kk - tap * Cin;
     const int ky = (tap * 11) >> 5, kx = tap - ky * 3;                 // tap / 3 for the nine taps
     tab[i] = tap < 9 ? (cin >> 3) * q.plane + (ky * q.wpx + col(kx)) * 16 : 0;
   }
   const float scale = 1.0f / (float)(1u << kFixShift);
-  const int first_last = p.K - dp.K_last;      // a shorter last group's weights are the last of a whole group's
-  if constexpr (KP >= 4) {
-#pragma clang loop unroll(disable)
-    for (int i = tid; i < q.lut_set / 4 * (dp.K_last ? 2 : 1); i += threads) {
-      const int set = i >= q.lut_set / 4, t = i - (set ? q.lut_set / 4 : 0), f0 = set ? first_last : 0;
-      uint32_t a[2] = {0, 0};
-#pragma unroll
-      for (int j = 0; j < (KP == 4 ? 4 : 8); ++j) {
-        const int jj = f0 + j + (KP == 16 ? (t >> 8) * 8 : 0);
-        const uint32_t w = p.wq[min(jj, TAC_MAX_K - 1)];
-        a[0] += (t >> j) & 1 ? w : 0u;
-        if constexpr (KP == 4) a[1] += (t >> (4 + j)) & 1 ? w : 0u;
-      }
-      lut[i] = KP == 16 ? a[0] : pack_bf16((float)a[0] * scale, (float)a[1] * scale);
-    }
-  }
+  // (a shorter last group's weights are the last of a whole group's)
+  if constexpr (KP >= 4) frame_tables<KP>(lut, q.lut_set / 4, dp.K_last ? 2 : 1, p.K - dp.K_last, p, tid, threads);
   if (tid < q.nco * 32) bias_lds[tid] = (p.bias && co_tile * q.nco * 32 + tid < p.Cout) ? p.bias[co_tile * q.nco * 32 + tid] : 0.f;
-  row_barrier();
+  lds_barrier();
 
   // ---- the loader.  A job is some blocks of 8 channels on some rows; a wave's jobs are wave, wave + waves, ..  Words to the wave's own corner of the LDS
   // as K-bit fields, [block][word][class][channel], then a pixel per lane.  Consecutive lanes load consecutive words of a channel.
   const int part_pairs = q.lrp * wws;
-  const RowDiv by_pairs(part_pairs);
+  const SmallDiv by_pairs(part_pairs);
   uint32_t wd[NCH][KP];
   auto job_units = [&](int job) { return 8 * min(q.cb, C8 - job / q.parts * q.cb) * part_pairs; };
   // Words are loaded through a buffer descriptor, which gives zeros for rows outside the image and frames that a group does not have.
@@ -202,7 +172,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
       if constexpr (KP == 1) {
         v[c2] = __umul24(t0 | t1 << 16, 0x3f80u);                      // one frame: its weight is 1, bf16 0x3f80
       } else if constexpr (KP == 2) {
-        v[c2] = __builtin_amdgcn_perm(two_hi, lo, __umul24(t0 | t1 << 16, 0x0202u) + 0x01000100u);
+        v[c2] = two_frame_pair(two_hi, lo, t0 | t1 << 16);
       } else if constexpr (KP == 4) {
         v[c2] = tb[t0 | t1 << 4];
       } else if constexpr (KP == 8) {
@@ -258,7 +228,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
 
   // ---- the lane's pixels: segment 2 block + n / 16 of the tile's rows; membranes are 32-bit byte offsets from the tile's (without a second sample
   // in the tile from its first row)
-  const RowDiv by_spr(q.spr);
+  const SmallDiv by_spr(q.spr);
   const int v_row = q.flatten ? 0 : oy0;
   LaneGeom lg;
   uint32_t pix[NNP];
@@ -326,7 +296,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
       asm volatile("" ::: "memory");
     }
     if (g == 0) lds_dma_wait();                // the weights
-    row_barrier();
+    lds_barrier();
     if (loader && g + 1 < n_groups) load_job(g + 1, wave);
     if (active) {
       // ---- 2. contraction: fragments are requested F - 1 steps ahead, table offsets F steps before that
@@ -385,7 +355,7 @@ __global__ __launch_bounds__(64 * row_max_waves(NNP), row_max_waves(NNP) / 4) vo
       }
     }
     step += n_lif;
-    row_barrier();                             // the group's fragments have been read
+    lds_barrier();                             // the group's fragments have been read
   }
   if (p.v_inout) {
 #pragma unroll
