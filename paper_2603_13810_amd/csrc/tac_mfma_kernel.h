@@ -1067,7 +1067,8 @@ hipError_t launch_tile64(const MfmaParams& mp, hipStream_t s) {
 // whose grid the chip takes in one go.  us a call before and now, TAC-TP K = 2 at B = 16 unless stated: 256 -> 256 stride 2 at 32 x 32 (tiles of
 // 64 pixels) 126 / 71, single frames 218 / 127; 128 -> 128 stride 2 at 64 x 64 (128) 76 / 58; 128 -> 256 at 32 x 32 (256) 83 / 77; the pooled 128 -> 128
 // at 32 x 32, K = 4 (128) 39.7 / 35.0, with membranes 62 / 46.  With more tiles than compute units it loses: 64 -> 128 at 64 x 64 (512 of 256 pixels) 77 / 95, 128 -> 256 at
-// 32 x 32, B = 32 (512) 136 / 153; tiles of 64 pixels, two rounds: 128 -> 128 stride 2 at 64 x 64 58 -> 73.
+// 32 x 32, B = 32 (512) 136 / 153; tiles of 64 pixels, two rounds: 128 -> 128 stride 2 at 64 x 64 58 -> 73.  Of 259 random layers that it takes
+// 1.66 times as fast on average, two slower (0.92 of the speed: three groups on tiles of 128 pixels).
 template <int KT, int WIN, int S, bool TRACE, int NP, int CW>
 bool launch_pairs_tile(const MfmaParams& mp, hipStream_t s, hipError_t& e) {
   using G = Geo<WIN, S, NP, CW, 2>;
@@ -1086,6 +1087,9 @@ bool launch_pairs(const MfmaParams& mp, hipStream_t s, hipError_t& e) {
   } else {
     if (launch_pairs_tile<KT, WIN, S, TRACE, 2, 2>(mp, s, e)) return true;
   }
+  // Three groups are two pairs, the second one half empty: on tiles no smaller than a group at a time has, that is the slower way (64 -> 256 at 32 x 32, B = 16, groups of eight 24.4 us
+  // with a group at a time, 27.5 in pairs; 96 -> 128 at 28 x 64, B = 16, TAC-TP K = 4 34.8 / 38.3; six such layers 0.89 to 1.03 of the speed; of five groups on 1.035 and more).
+  if (!TRACE && mp.G == 3) return false;
   return launch_pairs_tile<KT, WIN, S, TRACE, 2, 1>(mp, s, e);
 }
 

@@ -22,7 +22,8 @@ def _batch(Ho, Wo, Cout, pixels):
 # (input width, stride, input rows, pixels per tile)
 TILES = [(32, 1, 11, 64), (32, 1, 11, 128), (32, 1, 19, 256), (32, 2, 13, 64), (32, 2, 35, 128), (32, 2, 67, 256),
          (64, 2, 9, 64), (64, 2, 21, 128), (64, 2, 37, 256), (64, 1, 5, 128), (64, 1, 10, 256)]
-GROUPS = [(api.TAC_PER_STEP, 1, 3), (api.TAC_COLLAPSE, 2, 4), (api.TAC_PRESERVE, 2, 6), (api.TAC_PRESERVE, 4, 12)]
+# (three groups on tiles of 256 pixels go one at a time, but with recorded membranes)
+GROUPS = [(api.TAC_PER_STEP, 1, 3), (api.TAC_COLLAPSE, 2, 4), (api.TAC_PRESERVE, 2, 6), (api.TAC_PRESERVE, 4, 12), (api.TAC_PRESERVE, 2, 10)]
 
 
 @pytest.mark.parametrize("W,stride,H,pixels", TILES)
