@@ -287,17 +287,14 @@ __global__ __launch_bounds__(kThreads) void lif_backward_pooled_kernel(const Bac
 // Thread = one input pixel (iy, ix) of (group k, sample b), kCiTile input channels: sums
 // dY_k[co][y][x] W[co][ci][ky][kx] over the outputs (y, x) whose window covers the pixel, then
 // writes the gradient of each of the group's frames, dA scaled by the frame's weight.
+// OVER: more tiles of input channels than a grid has in y; the rest follows in x behind the pixels (dgrad_vector_tiles).  One after the other in a loop, the stores would keep the
+// weights out of scalar loads: 2.4 times the time.
+template <bool OVER>
 __global__ __launch_bounds__(kThreads) void dgrad_kernel(const BackwardParams p) {
-  // input channels in y, and beyond what a grid has there in x behind the pixels (one after the other in a loop, the stores would keep the weights out of scalar loads: 2.4 times the time)
-  uint32_t block = blockIdx.x, over = 0;
-  if (p.Cin > 65535 * kCiTile) {
-    const uint32_t blocks = ((uint32_t)(p.H * p.W) + kThreads - 1) / kThreads;
-    over = block / blocks;
-    block -= over * blocks;
-  }
+  const uint32_t blocks = OVER ? ((uint32_t)(p.H * p.W) + kThreads - 1) / kThreads : 0, over = OVER ? blockIdx.x / blocks : 0;
   const int ci0 = (int)((over * gridDim.y + blockIdx.y) * kCiTile);
   const int b = blockIdx.z % p.B, k = blockIdx.z / p.B;
-  const int px = (int)(block * kThreads + threadIdx.x);
+  const int px = (int)((blockIdx.x - over * blocks) * kThreads + threadIdx.x);
   if (px >= p.H * p.W) return;
   const int iy = px / p.W, ix = px - iy * p.W;
   const size_t plane = (size_t)p.Ho * p.Wo;
@@ -418,7 +415,8 @@ hipError_t backward_launch(const BackwardParams& p, hipStream_t s) {
     unsigned across, over;
     dgrad_vector_tiles(p.Cin, across, over);
     const dim3 grid((p.H * p.W + kThreads - 1) / kThreads * over, across, p.G * p.B);
-    hipLaunchKernelGGL(dgrad_kernel, grid, dim3(kThreads), 0, s, p);
+    if (over == 1) hipLaunchKernelGGL(dgrad_kernel<false>, grid, dim3(kThreads), 0, s, p);
+    else hipLaunchKernelGGL(dgrad_kernel<true>, grid, dim3(kThreads), 0, s, p);
     e = hipGetLastError();
   }
   return e;
