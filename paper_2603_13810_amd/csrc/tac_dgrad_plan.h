@@ -44,8 +44,20 @@ inline bool dgrad_f32_tile(const BackwardParams& p, int blocks, int pl_max, Dgra
 }
 inline long long dgrad_f32_tiles(const DgradPlan& q) { return (long long)q.pair_tiles * q.n_strips * q.n_segs * q.ci_groups; }
 
+// What follows the products: a value per group, or one for each frame of it, or four through a pool (to_max: to one of four that is looked up).  A workgroup's stores are a
+// chain, frame after frame, which outweighs the products of small layers: 64 <- 16 at 6 x 6, B = 3, one group of 8 through a max pool 18.4 us where the four waves share the
+// output channels (and an eighth of the values each), 48.3 on the other kernel, which its products favour.  us: of a frame's values, of those of each workgroup
+// of a compute unit in units of that; fitted to 570 random layers (10% rms).
+struct DgradStores {
+  double frame, pooled, to_max, per_workgroup;
+};
+inline double dgrad_store_us(const DgradStores& s, const BackwardParams& p, double per_cu) {
+  if (p.grad_in_group && !p.pool2) return 0.0;
+  const int K = std::max(1, (int)p.K);
+  return (p.pool2 == 2 ? s.to_max * K : p.pool2 ? s.pooled * K : s.frame * (K - 0.5)) * std::max(1.0, s.per_workgroup * per_cu);
+}
 
-// Microseconds of the kernels, fitted to 450 random layers (1 to 128 channels on either side, 3 x 3 to 64 x 72 pixels, 1 to 768 pairs) to 6 or 7% rms, and 9% for
+// Microseconds of the kernels without the frames' stores, fitted to 450 random layers with one value per group (1 to 128 channels on either side, 3 x 3 to 64 x 72 pixels, 1 to 768 pairs) to 6 or 7% rms, and 9% for
 // the vector kernel.
 // Rounds of 16 output channels (cycles at 2.5 GHz): a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several
 // (7850, 4000); the stores.  Up to eight output channels take one shorter round (fitted to 174 layers, 7% rms).
@@ -53,21 +65,26 @@ inline double dgrad_thirds_us(const DgradPlan& q, int np, const BackwardParams& 
   const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
   const double cycles = p.Cout <= 8 ? std::max(np == 2 ? 6000.0 : 4300.0, per_cu * (np == 2 ? 5000.0 : 2300.0))
                                     : std::max(np == 2 ? 10700.0 : 7500.0, per_cu * (np == 2 ? 7850.0 : 4000.0));
-  return 2.4 + (p.Cout + kDgradCo - 1) / kDgradCo * cycles / 2500.0 + 0.9 * per_cu * np;
+  // (a lane stores 16 channels of 32, of fewer input channels at most four of eight)
+  const int n = std::min(32, (int)p.Cin), stored = n / 8 * 4 + std::min(n % 8, 4);
+  const double stores = dgrad_store_us(np == 2 ? DgradStores{5.46, 6.83, 11.97, 0.66} : DgradStores{2.75, 3.64, 6.38, 0.57}, p, per_cu);
+  return 2.4 + (p.Cout + kDgradCo - 1) / kDgradCo * cycles / 2500.0 + 0.9 * per_cu * np + stores * stored / 16;
 }
 // Rounds of 32 output channels in products of fp32
 inline double dgrad_split_us(const DgradPlan& q, const BackwardParams& p) {
   const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
-  return 2.6 + (p.Cout + kSplitCo - 1) / kSplitCo * 3.55 * std::max(1.0, 0.64 * per_cu) + 2.7 * per_cu;
+  return 2.6 + (p.Cout + kSplitCo - 1) / kSplitCo * 3.55 * std::max(1.0, 0.64 * per_cu) + 2.7 * per_cu + dgrad_store_us({0.58, 0.72, 1.22, 0.67}, p, per_cu);
 }
 // A thread's chain over the output channels, or the pixels at the rate they go through; the stores
 inline double dgrad_vector_us(const BackwardParams& p) {
   const double pairs = (double)p.G * p.B, pixels = (double)p.H * p.W, blocks = (double)(((int64_t)p.H * p.W + 255) / 256 * 256);
-  return 3.4 + p.Cout * (0.34 + 0.054 * std::min(p.Cin, 4) + (p.Cin + 3) / 4 * pairs * blocks * 1.465e-6) + p.Cin * pairs * pixels * 3.4e-6;
+  return 3.4 + p.Cout * (0.34 + 0.054 * std::min(p.Cin, 4) + (p.Cin + 3) / 4 * pairs * blocks * 1.465e-6) + p.Cin * pairs * pixels * 3.4e-6 +
+         dgrad_store_us({0.17, 0.32, 0.95, 0.0}, p, 0.0) * std::min(p.Cin, 4) / 4 + dgrad_store_us({0.51e-6, 1.72e-6, 2.04e-6, 0.0}, p, 0.0) * p.Cin * pairs * pixels;
 }
 
 // np: blocks of 32 pixels a wave (0: no tile).  True: dgrad_f32_split_kernel, whose four waves share the output channels of one block of pixels, for few tiles: of the 450
-// layers 46 (128 -> 128 at 8 x 8, B = 16, one group 17.4 us, 28.1 on the other kernel; 16 -> 48 at 31 x 32, 16 pairs on 496 tiles 17.5 / 12.0: that one's).
+// layers 46 (128 -> 128 at 8 x 8, B = 16, one group 17.4 us, 28.1 on the other kernel; 16 -> 48 at 31 x 32, 16 pairs on 496 tiles 17.5 / 12.0: that one's); of 420 small layers, most
+// of which store frames or pooled frames, 185: the chosen kernels take 0.4% longer than the best, 9% by estimates without the stores.
 inline bool dgrad_f32_choose(const BackwardParams& p, DgradPlan& q, int& np) {
   np = 0;
   double best = 0.0;
@@ -80,8 +97,10 @@ inline bool dgrad_f32_choose(const BackwardParams& p, DgradPlan& q, int& np) {
     best = us;
     q = c;
   }
+  // Up to eight output channels are one short round of the other kernel, and less accurate here (8 channels 1.42e-7 of the norm, 1.10e-7 there); from nine on, on 22 layers that
+  // this rule gives back to products of fp32, the error is 0.7 to 1.0 of that of thirds in one chain
   DgradPlan c{};
-  if (!np || !dgrad_f32_tile(p, 1, kSplitPl, c) || dgrad_f32_tiles(c) > 512 || dgrad_split_us(c, p) >= best) return false;
+  if (!np || p.Cout <= 8 || !dgrad_f32_tile(p, 1, kSplitPl, c) || dgrad_f32_tiles(c) > 512 || dgrad_split_us(c, p) >= best) return false;
   q = c;
   return true;
 }

@@ -4,8 +4,16 @@
 
 extern "C" int clear_in_recurrence(long long threads, long long floats) { return tac::backward_clear_in_recurrence((size_t)threads, (size_t)floats); }
 
-extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int Cout, int H, int W, int stride) {
+// Its values per group (K = 0) or per frame of K (pool2: through that pool on load)
+static void written_as(tac::BackwardParams& p, int K, int pool2) {
+  p.grad_in_group = K == 0;
+  p.K = std::max(1, K);
+  p.pool2 = pool2;
+}
+
+extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int Cout, int H, int W, int stride, int K, int pool2) {
   tac::BackwardParams p{};
+  written_as(p, K, pool2);
   p.G = G; p.B = B; p.Cin = Cin; p.Cout = Cout; p.H = H; p.W = W; p.stride = stride;
   return tac::backward_dgrad_f32_supported(p);
 }
@@ -13,8 +21,9 @@ extern "C" int input_gradient_on_matrix_cores(int G, int B, int Cin, int Cout, i
 extern "C" void vector_kernel_tiles(int Cin, unsigned* out) { tac::dgrad_vector_tiles(Cin, out[0], out[1]); }
 
 // Whether the four waves of a workgroup share the output channels (where the input gradient is formed on the matrix cores)
-extern "C" int input_gradient_splits(int G, int B, int Cin, int Cout, int H, int W) {
+extern "C" int input_gradient_splits(int G, int B, int Cin, int Cout, int H, int W, int K, int pool2) {
   tac::BackwardParams p{};
+  written_as(p, K, pool2);
   p.G = G; p.B = B; p.Cin = Cin; p.Cout = Cout; p.H = H; p.W = W; p.stride = 1;
   tac::DgradPlan q{};
   int np = 0;

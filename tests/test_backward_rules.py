@@ -9,6 +9,7 @@ from paper_2603_13810_amd import api, build
 from test_gpu_backward_dgrad import CASES, VECTOR
 from test_gpu_backward_wgrad import BITS, FIRST, FIRST_TAKEN, INFINITE, REAL
 
+POOLS = {api.TAC_IN_BITS_POOL2: 1, api.TAC_IN_BITS_MAXPOOL2: 2}
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 
@@ -35,13 +36,14 @@ def test_a_large_weight_gradient_is_not_cleared_by_a_handful_of_threads(rules, n
                                   (2, 64, 2, 64, 7, 1, True), (7, 128, 32, 64, 14, 1, True), (4, 16, 128, 64, 8, 1, True), (4, 16, 128, 64, 8, 2, False)])
 def test_input_gradient_kernel(rules, case):
     G, B, Cin, Cout, hw, stride, matrix = case
-    assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, Cout, hw, hw, stride)) == matrix
+    assert bool(rules.input_gradient_on_matrix_cores(G, B, Cin, Cout, hw, hw, stride, 0, 0)) == matrix
 
 
 def test_the_vector_kernel_has_its_cases(rules):
     for case in CASES:
-        B, Cin, Cout, H, W, _, _, K, T = case
-        assert bool(rules.input_gradient_on_matrix_cores((T + K - 1) // K, B, Cin, Cout, H, W, 1)) == (case not in VECTOR)
+        B, Cin, Cout, H, W, fmt, per_group, K, T = case
+        frames, pool2 = (0 if per_group else K), (0 if fmt == BITS else POOLS[fmt])
+        assert bool(rules.input_gradient_on_matrix_cores((T + K - 1) // K, B, Cin, Cout, H, W, 1, frames, pool2)) == (case not in VECTOR)
 
 
 def test_the_vector_kernel_stays_within_a_grid(rules):
@@ -56,7 +58,16 @@ def test_the_vector_kernel_stays_within_a_grid(rules):
                                   (2, 40, 48, 63, 41, False), (6, 2, 48, 64, 27, False), (64, 128, 16, 8, 8, False), (8, 1, 16, 28, 28, False), (20, 12, 64, 12, 55, False)])
 def test_which_input_gradients_share_output_channels(rules, case):
     pairs, Cin, Cout, H, W, splits = case
-    assert bool(rules.input_gradient_splits(1, pairs, Cin, Cout, H, W)) == splits
+    assert bool(rules.input_gradient_splits(1, pairs, Cin, Cout, H, W, 0, 0)) == splits
+
+
+# Values for each frame of a group: (groups, B, Cin, Cout, H, W, K, pool on load (0 none, 1 mean, 2 max), shared): the faster side as measured, 1.1 times and more apart
+@pytest.mark.parametrize("case", [(1, 3, 64, 16, 6, 6, 8, 2, True), (2, 74, 32, 9, 5, 8, 16, 1, True), (1, 4, 40, 40, 34, 10, 8, 1, True), (1, 46, 24, 48, 13, 13, 3, 1, True),
+                                  (4, 17, 40, 15, 9, 9, 16, 0, True), (7, 100, 7, 13, 4, 4, 2, 1, False), (1, 3, 35, 2, 36, 36, 3, 0, False),
+                                  (1, 112, 1, 6, 27, 3, 4, 2, False), (4, 27, 16, 8, 8, 4, 1, 0, False)])
+def test_values_of_every_frame_are_stored_by_more_workgroups(rules, case):
+    G, B, Cin, Cout, H, W, K, pool2, splits = case
+    assert bool(rules.input_gradient_splits(G, B, Cin, Cout, H, W, K, pool2)) == splits
 
 
 PLAN = ("ncg", "co_groups", "split", "n_pairs", "rows", "n_strips", "pair_tiles", "lds")
