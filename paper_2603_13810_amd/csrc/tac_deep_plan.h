@@ -113,7 +113,7 @@ inline bool deep_choose(const LayerParams& p, DeepPlan& q) {
       if (wgs * kDeepThreads >= (1ll << 32)) continue;                 // threads of a launch in one dimension
       // two blocks a workgroup where one block each is more than the chip takes in one go
       const long long old = found ? (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B) : 0;
-      if (found && (c.flatten != q.flatten ? wgs >= old : old <= 256)) continue;
+      if (found && (c.flatten != q.flatten ? wgs >= old : old <= kFittedUnits)) continue;
       q = c;
       found = true;
     }

@@ -62,7 +62,7 @@ inline double dgrad_store_us(const DgradStores& s, const BackwardParams& p, doub
 // Rounds of 16 output channels (cycles at 2.5 GHz): a workgroup that has its compute unit to itself (two blocks a wave 10700, one 7500), or its part of several
 // (7850, 4000); the stores.  Up to eight output channels take one shorter round (fitted to 174 layers, 7% rms).
 inline double dgrad_thirds_us(const DgradPlan& q, int np, const BackwardParams& p) {
-  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
+  const double per_cu = (double)((dgrad_f32_tiles(q) + kFittedUnits - 1) / kFittedUnits);
   const double cycles = p.Cout <= 8 ? std::max(np == 2 ? 6000.0 : 4300.0, per_cu * (np == 2 ? 5000.0 : 2300.0))
                                     : std::max(np == 2 ? 10700.0 : 7500.0, per_cu * (np == 2 ? 7850.0 : 4000.0));
   // (a lane stores 16 channels of 32, of fewer input channels at most four of eight)
@@ -72,7 +72,7 @@ inline double dgrad_thirds_us(const DgradPlan& q, int np, const BackwardParams& 
 }
 // Rounds of 32 output channels in products of fp32
 inline double dgrad_split_us(const DgradPlan& q, const BackwardParams& p) {
-  const double per_cu = (double)((dgrad_f32_tiles(q) + 255) / 256);
+  const double per_cu = (double)((dgrad_f32_tiles(q) + kFittedUnits - 1) / kFittedUnits);
   return 2.6 + (p.Cout + kSplitCo - 1) / kSplitCo * 3.55 * std::max(1.0, 0.64 * per_cu) + 2.7 * per_cu + dgrad_store_us({0.58, 0.72, 1.22, 0.67}, p, per_cu);
 }
 // A thread's chain over the output channels, or the pixels at the rate they go through; the stores

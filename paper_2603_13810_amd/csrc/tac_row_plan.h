@@ -10,6 +10,7 @@ namespace tac {
 // Waves of a workgroup at most: one block of pixels leaves room for four waves on a SIMD (128 registers), two for three
 __host__ __device__ constexpr int row_max_waves(int nnp) { return nnp == 1 ? 16 : 12; }
 constexpr int kRowLds = 160 * 1024;
+constexpr int kRowMHz = 2350;                  // of the launches that row_cost is fitted to
 constexpr int kRowMaxK = 16;
 constexpr int kRowTabPad = 16;                 // entries of the slot table behind the last k-step (fetched ahead)
 constexpr int kRowDepth = 3;                   // sets of operand fragments in flight
@@ -103,33 +104,33 @@ inline int row_groups(const LayerParams& p) { return (int)std::bit_ceil((unsigne
 
 // Microseconds of a launch: the sum, over the turns that the chip takes, of what a compute unit spends on a group's aggregates (its instructions, or a
 // wave's own chain of loads and LDS trips), on its contraction (the matrix cores, or the waits for fragments) and on its LIF steps.  The
-// coefficients (cycles at 2.35 GHz) are a fit to 4600 timed launches of 127 random layers: 10% rms, and the plan chosen by it takes 1.6% longer than the best
+// coefficients (cycles at kRowMHz) are a fit to 4600 timed launches of 127 random layers: 10% rms, and the plan chosen by it takes 1.6% longer than the best
 // one on average.
 inline double row_cost(const RowPlan& q, const LayerParams& p) {
   const long long wgs = (long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B);
   const int mw = q.pw * q.nco, groups = row_groups(p);
   const int resident = std::max(1, std::min(kRowLds / q.total, row_max_waves(q.nnp) / q.waves));
-  const long long per_cu = (wgs + 255) / 256;
+  const long long per_cu = (wgs + kFittedUnits - 1) / kFittedUnits;
   const double together = (double)std::min<long long>(resident, per_cu), per_simd = together * q.waves / 4, multiply = together * mw / 4;
   const int turns = (q.n_jobs + q.waves - 1) / q.waves, chunks = (8 * q.cb * q.lrp * p.Wwi + 63) / 64, passes = (q.lrp * p.W + 63) / 64;
   const double issue = turns * (6.4 + chunks * (1.6 + 31 * q.kp) + passes * (12 + 35 * q.cb));
   const double form = std::max(3.4 * issue * std::max(per_simd, 1.0), 290.0 + turns * (430 + 180 * passes + 43 * chunks));
   const double contract = q.nks * std::max(45 * q.nnp * multiply, 38.0 + 51 * q.nnp);
   const double lif = p.n_lif * (27 + 613 * q.nnp * std::max(1.0, 0.5 * multiply));
-  return (double)((per_cu + resident - 1) / resident) * (15300 + groups * (form + contract + lif + 870)) / 2350 + 2.6;
+  return (double)((per_cu + resident - 1) / resident) * (15300 + groups * (form + contract + lif + 870)) / kRowMHz + 2.6;
 }
 
 // What row_cost is not below for any plan of some tiles: each of its terms with as many workgroups side by side as the waves allow, times the turns.  Most plans
 // are not worth working out after the first few: choosing takes 17 us on average instead of 32.
 inline double row_cost_least(const RowPlan& q, const LayerParams& p, int waves) {
   const int mw = q.pw * q.nco, groups = row_groups(p), nks = (9 * p.Cin + 15) / 16, at_once = std::max(1, row_max_waves(q.nnp) / waves);
-  const double per_cu = (double)(((long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B) + 255) / 256);
+  const double per_cu = (double)(((long long)q.row_tiles * q.co_tiles * (q.flatten ? 1 : p.B) + kFittedUnits - 1) / kFittedUnits);
   const double turns = std::ceil(per_cu / at_once), multiply = per_cu * mw / 4;
   // (a pass over 64 pixels of 8 channels is 38 instructions at least)
   const double form = std::max(3.4 * 38 / 4 * per_cu * (p.Cin / 8) * (q.lr * p.W) / 64, 290.0 * turns);
   const double contract = nks * std::max(45 * q.nnp * multiply, turns * (38.0 + 51 * q.nnp));
   const double lif = p.n_lif * (27 * turns + 613 * q.nnp * std::max(turns, 0.5 * multiply));
-  return 0.999999 * (turns * 15300 + groups * (form + contract + lif + 870 * turns)) / 2350 + 2.6;
+  return 0.999999 * (turns * 15300 + groups * (form + contract + lif + 870 * turns)) / kRowMHz + 2.6;
 }
 
 // The shapes the kernel reaches at all.  Layers that record their membranes stay on the older kernel: writing those takes most of their time, and with
