@@ -6,6 +6,10 @@
 
 namespace tac {
 
+// Compute units of the chip that the host rules' time estimates are fitted to, with everything else in them (an MI355X; on the CPU, where tests ask these rules, there is
+// none to ask).  Launchers that only count workgroups ask the device.
+constexpr int kFittedUnits = 256;
+
 // Everything a conv-LIF kernel needs, resolved on the host from tac_layer_desc_t.
 struct LayerParams {
   const uint32_t* spikes;   // packed input

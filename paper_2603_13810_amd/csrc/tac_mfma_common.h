@@ -21,10 +21,6 @@ typedef const __attribute__((address_space(1))) void* global_void_ptr;
 
 constexpr int kFixShift = 23;                  // fixed-point scale of the aggregation weights
 
-// Compute units of the chip that the host rules' time estimates are fitted to, with everything else in them (an MI355X; on the CPU, where tests ask these rules, there is
-// none to ask).  Launchers that only count workgroups ask the device.
-constexpr int kFittedUnits = 256;
-
 struct MfmaParams {
   const uint32_t* __restrict__ spikes;
   const uint8_t* __restrict__ w;       // prepared: [cout_tile][chunk][tap][mc][lane][8] bf16, scaled 2^-23
